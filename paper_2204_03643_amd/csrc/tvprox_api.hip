@@ -11,6 +11,7 @@
 #include "tv_common.hpp"
 #include "tv_dispatch.hpp"
 #include "tv_long.hpp"
+#include "tv_long_tri.hpp"
 #include "tv_small2d.hpp"
 #include "tv_plane2d.hpp"
 #include "tv_short.hpp"
@@ -577,7 +578,7 @@ __global__ __launch_bounds__(256) void seg_from_x_kernel(const float *__restrict
 int run_fwd(const float *y, const float *addend, float *x, float *resid, int32_t *info,
             uint2 *seg, uint32_t *order_ws, const tv_rows &r, const tv_lambda &l, int64_t n_rows,
             hipStream_t s, float *x2 = nullptr, bool warm = false, char *ml_ws = nullptr, bool io16 = false,
-            bool thread_per_sample = false, bool order_ready = false, bool psearch = false)
+            bool thread_per_sample = false, bool order_ready = false, bool psearch = false, bool tri = false)
 {
     FwdParams p;
     p.y = y; p.addend = addend; p.x = x; p.x2 = x2; p.resid = resid; p.lam = l.lam; p.info = info;
@@ -632,6 +633,7 @@ int run_fwd(const float *y, const float *addend, float *x, float *resid, int32_t
                             (!x2 || aligned16(x2));
         return launch_fwd_short<32>(p, packed, s, planes, ragged);
     }
+    if (tri) return tvk::launch_fwd_tri(p, s) == hipSuccess ? TV_OK : TV_ERR_HIP;      // (up to 768 samples)
     MlPlan pl;
     if (!p.warm && !addend && ml_plan(r, n_rows, &pl)) {
         if (ml_ws) return run_fwd_multilevel(p, l, n_rows, pl, ml_ws, s);
@@ -1286,6 +1288,8 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
         TV_SMALL2D_LAUNCH(tvk::tv2d_fwd_small_kernel, q, planes, H, W, stream);
         return launch_status();
     }
+    // one lambda for all planes: its gradient hinges on the last bits of x (see tv_long_tri.hpp)
+    const bool tri = lam.count == 1 && sweeps >= 3 && H <= 768 && W <= 768;
     for (int k = 0; k < sweeps; ++k) {
         const bool last = (k == sweeps - 1);
         const float *Yk = (k == 0) ? y : saved(2 * k - 1);
@@ -1294,12 +1298,12 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
         // From the second sweep on, P = D^T u of the row pass one sweep earlier (x = y - D^T u),
         // and likewise Q for the columns: each pass starts from that dual.
         st = run_fwd(Yk, k == 0 ? nullptr : P, Z, last ? nullptr : P, nullptr, codes(2 * k), nullptr,
-                     rrow, lrow, planes * H, stream, nullptr, true);
+                     rrow, lrow, planes * H, stream, nullptr, true, nullptr, false, false, false, false, tri);
         if (st != TV_OK) return st;
         // Y' = proxCols(Z + Q);  Q <- (Z + Q) - Y'
         // the last pass writes its output twice: where the reverse sweep will look for it, and to x
         st = run_fwd(Z, k == 0 ? nullptr : Q, Yn, last ? nullptr : Q, nullptr, codes(2 * k + 1), nullptr,
-                     rcol, lcol, planes * W, stream, last ? x : nullptr, true);
+                     rcol, lcol, planes * W, stream, last ? x : nullptr, true, nullptr, false, false, false, false, tri);
         if (st != TV_OK) return st;
     }
     return TV_OK;
