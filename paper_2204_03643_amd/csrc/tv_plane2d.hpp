@@ -20,18 +20,6 @@
 
 namespace tvk {
 
-// OR over the T <= 16 lanes of a row (rows are aligned groups of T lanes), the result in all of them.
-template <int T>
-__device__ __forceinline__ uint32_t row_or_all(uint32_t v)
-{
-    static_assert(T == 8 || T == 16, "butterflies inside a 16-lane DPP row");
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true);     // quad_perm [1,0,3,2]
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true);     // quad_perm [2,3,0,1]
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true);    // mirror within 8
-    if (T > 8) v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true);   // within 16
-    return v;
-}
-
 // T threads per row, C samples per thread: planes of at most S x S, S = T * C (16 x 2: up to
 // 32 x 32, with segment codes for the reverse sweep; 8 x 8: up to 64 x 64, whose reverse sweep
 // reads the saved pass outputs).  One plane per workgroup of S * T = 512 threads.
@@ -111,21 +99,9 @@ __global__ __launch_bounds__(T * T * C, C <= 4 ? 8 : 4) void tv2d_fwd_plane_kern
             if (valid && k0 + c < n) X[base + (k0 + c) * step] = xs[c];
 
         if constexpr (S <= 32) {
-            // segment code of the row: bit k = x jumps behind sample k / rises there
-            const float xnext0 = from_right<T, 1>(xs[0], t);
-            uint32_t jm = 0, up = 0;
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                const float d = xs[c] - ((c + 1 < C) ? xs[c + 1] : xnext0);
-                if (k0 + c < n - 1) {
-                    if (d != 0.f) jm |= 1u << (k0 + c);
-                    if (d < 0.f) up |= 1u << (k0 + c);
-                }
-            }
-            jm = row_or_all<T>(jm);
-            up = row_or_all<T>(up);
+            const uint2 code = row_segment_code<T, C>(xs, n, t);
             if (valid && t == 0)
-                p.codes[(size_t)i * p.code_stride + (size_t)plane * rows + j] = make_uint2(jm, up);
+                p.codes[(size_t)i * p.code_stride + (size_t)plane * rows + j] = code;
         }
         __syncthreads();
         // (planes of at most 32 x 32: the reverse sweep reads the codes written above)

@@ -72,6 +72,38 @@ __device__ __forceinline__ float from_right(float v, int t)
 // (wave_shr:1); measured, that changes nothing for them: their time goes into the PCR steps at
 // distances that no single shift covers.)
 
+// OR over the T <= 16 lanes of a row (rows are aligned groups of T lanes), the result in all of them.
+template <int T>
+__device__ __forceinline__ uint32_t row_or_all(uint32_t v)
+{
+    static_assert(T == 8 || T == 16, "butterflies inside a 16-lane DPP row");
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true);     // quad_perm [1,0,3,2]
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true);     // quad_perm [2,3,0,1]
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true);    // mirror within 8
+    if (T > 8) v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true);   // within 16
+    return v;
+}
+
+// Segment code of a row of at most 32 samples (FwdParams::seg) from its output, which is bit-constant
+// inside a segment: bit k of .x = x jumps behind sample k, of .y = it rises there.  xs: the thread's
+// chunk; every lane of the wave calls, all lanes of the row get the code.
+template <int T, int C>
+__device__ __forceinline__ uint2 row_segment_code(const float (&xs)[C], int n, int t)
+{
+    const float xnext0 = from_right<T, 1>(xs[0], t);
+    uint32_t jm = 0, up = 0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int k = t * C + c;
+        const float xn = (c + 1 < C) ? xs[c + 1] : xnext0;
+        if (k < n - 1) {
+            if (xn != xs[c]) jm |= 1u << k;
+            if (xn > xs[c]) up |= 1u << k;
+        }
+    }
+    return make_uint2(row_or_all<T>(jm), row_or_all<T>(up));
+}
+
 // Sum over the 64 lanes of a wave, the same total in every lane, in a fixed order: four
 // exchanges inside the 16-lane rows ride on the adds themselves (DPP), two swaps cross the rows.
 template <int LANES = 64>
