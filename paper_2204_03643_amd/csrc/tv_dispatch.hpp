@@ -83,11 +83,10 @@ inline Threshold table[kCount] = {
     // the one-launch kernel (fused16_dense_planes below): 49 152 planes 110 / 113, 61 440: 132 / 134.
     {"fused16_one_sweep_planes", 49152, "2D planes of at most 16 x 16, one sweep: one launch up to this many planes"},
     // ... and from this many planes on the one-launch kernel for planes of 9-16 a side is the
-    // variant held to 128 VGPRs (four waves per SIMD, 16-54 registers spilled): 8192 planes do not
-    // fill the three waves that the other variant allows (K = 2: 43 us against 45), 65 536 do
-    // (K = 4: 334 against 302).  The crossover is where the waves outnumber three per SIMD: 4
-    // planes per wave x 3 x 1024 SIMDs.
-    {"fused16_dense_planes", 24576, "2D planes of 9-16 a side in one launch: the four-waves-per-SIMD variant from this many planes on"},
+    // variant held to 128 VGPRs, four waves per SIMD (planes that do not fill their square take 129
+    // left alone; 16 384 planes of 14 x 14, K = 4: 101 us against 78).  The crossover is where the
+    // waves, 4 planes each, outnumber three per SIMD.
+    {"fused16_dense_planes", 12288, "2D planes of 9-16 a side in one launch: the four-waves-per-SIMD variant from this many planes on"},
     // 2D, small batches: one plane per workgroup of 512 threads, resident in LDS for all passes,
     // 16 threads x 2 samples per row (sides of 17-32) or 8 x 8 (sides of 33-64); tv_plane2d.hpp.
     // A lone row-per-lane wave per SIMD issues an instruction every 9 cycles, and pass by pass a

@@ -351,11 +351,15 @@ struct Small2dFwdParams {
 // IO16: y and x are bf16 in memory; the saved pass outputs stay fp32.
 // (Planes of 33-64 samples a side: tv_plane2d.hpp.  A row of 64 samples per lane would take four
 // arrays of 64 registers, the whole register file of a SIMD lane, for one wave per SIMD.)
-// Waves per SIMD asked of the register allocator: two at least; six for planes of 8 x 8 (80 VGPRs
-// instead of 87-96 at the price of 3-5 spilled registers: 65 536 planes, K = 4: 98 -> 95 us).
-// Four for planes of 16 x 16 (128 VGPRs instead of 145-168, 16-54 spilled) take 65 536 planes
-// with K = 4 from 334 to 302 us but 8192 planes with K = 2, which do not fill three waves per SIMD
-// anyway, from 43 to 45: that is the variant DENSE, which the dispatch takes for large batches.
+// Waves per SIMD asked of the register allocator: two at least; six for planes of 8 x 8, which fit
+// 64-73 registers.  Planes of 16 x 16 take 104 registers, four waves; planes of 9-15 a side 129, one
+// too many: the variant DENSE asks for 128 (16 384 planes of 14 x 14, K = 4: 101 -> 78 us), and the
+// dispatch takes it wherever a fourth wave has something to do.
+// What set these counts: every pass solves inside the loop over passes, and whatever the loop or the
+// solver's own loop could leave early kept arrays alive through the half it skips (see
+// RowSolver::solve, and below).  Without that, and with predicates that are formed where they are
+// used, planes of 28 x 28 (5355, K = 4) went from 259 to 186 us (215 spilled scalar registers), 16 x 16
+// (16 384, K = 4) from 95 to 71, 14 x 14 (65 536, K = 2) from 258 to 147, 32 x 32 (16 384, K = 4) from 373 to 357.
 template <int S, bool FULL, bool IO16 = false, bool DENSE = false>
 __global__ __launch_bounds__(64, (S == 8 ? 6 : ((S == 16 && DENSE) ? 4 : 2))) void tv2d_fwd_small_kernel(Small2dFwdParams p)
 {
@@ -374,8 +378,8 @@ __global__ __launch_bounds__(64, (S == 8 ? 6 : ((S == 16 && DENSE) ? 4 : 2))) vo
     float lam = 0.f;
     if (pvalid) lam = fmaxf(p.lam[plane % p.lam_count], 0.f);
 
-    float *rowp = T1 + (h * S + idx) * P;      // row idx of the lane's plane, unit step
-    float *colp = T1 + (h * S) * P + idx;      // column idx, step P
+    // row idx of the lane's plane: T1 + (h * S + idx) * P, unit step; column idx: T1 + (h * S) * P + idx, step P
+    auto opaque = [](int at) { asm volatile("" : "+v"(at)); return at; };
     float *park = T1 + lane;                    // the solver's read-only copy of its input, step 64
     float *mine = T2 + lane;                    // lane-private: the correction term, step 64
 
@@ -412,9 +416,11 @@ __global__ __launch_bounds__(64, (S == 8 ? 6 : ((S == 16 && DENSE) ? 4 : 2))) vo
     // a pass's output, T1 -> memory in plane order
     auto put_planes = [&](float *dst) {
         if (FULL && ((uintptr_t)dst % 16) == 0) {
+            int own = lane;
+            asm volatile("" : "+v"(own));       // (addresses formed here, not kept through the solves)
 #pragma unroll
             for (int i = 0; i < S / 4; ++i) {
-                const int e = (i * 64 + lane) * 4;
+                const int e = (i * 64 + own) * 4;
                 const float *s = T1 + (e / S) * P + (e % S);
                 if (e / (S * S) < n_here) store16(dst + e, make_float4(s[0], s[1], s[2], s[3]), p.stream != 0);
             }
@@ -426,12 +432,24 @@ __global__ __launch_bounds__(64, (S == 8 ? 6 : ((S == 16 && DENSE) ? 4 : 2))) vo
         }
     };
 
-    float v[S], xs[S];
-    RowSolver<S, FULL> sv;
+    // a row (step 1) or column (step P) of the tile, zero past its n samples.  (Lanes that hold none
+    // read what is there: they take no part in the solve.  n through an opaque copy: as loop
+    // invariants the S comparisons fill the scalar registers, 215 of which were spilled.)
+    auto take = [&](const float *from, int step, int n, float (&t)[S]) {
+        int nn = n;
+        if (!FULL) asm volatile("" : "+s"(nn));
+#pragma unroll
+        for (int k = 0; k < S; ++k) {
+            t[k] = from[k * step];
+            if (!FULL) t[k] = k < nn ? t[k] : 0.f;
+        }
+    };
+    float v[S], u0[S];                          // a pass's input, and the dual it starts from
     bool valid = pvalid && (FULL || idx < H);   // first pass: rows, of W samples
     int n = W;
+    take(T1 + opaque((h * S + idx) * P), 1, n, v);
 #pragma unroll
-    for (int k = 0; k < S; ++k) v[k] = (valid && (FULL || k < n)) ? rowp[k] : 0.f;
+    for (int k = 0; k < S; ++k) u0[k] = 0.f;
 
     const int n_pass = 2 * p.sweeps;
     for (int i = 0; i < n_pass; ++i) {
@@ -441,12 +459,18 @@ __global__ __launch_bounds__(64, (S == 8 ? 6 : ((S == 16 && DENSE) ? 4 : 2))) vo
         for (int k = 0; k < S; ++k) park[k * 64] = v[k];
         wave_lds_sync();
 
+        RowSolver<S, FULL> sv;
+        float xs[S];
         sv.yl = park; sv.gtab = gtab; sv.lam = lam; sv.m = n - 1;
         sv.alpha_try = 1.f; sv.steps = 0; sv.flags = 0; sv.nfail = 0;
         sv.active = valid; sv.prev_unclipped = false;
         if (i < 2) sv.start(v, rtab[n]);        // first sweep: no correction term yet
-        else sv.start_warm(v);
-        for (int it = 0; !sv.iterate(it); ++it) {}
+        else {
+#pragma unroll
+            for (int k = 0; k < S - 1; ++k) sv.u[k] = u0[k];
+            sv.start_warm(v);
+        }
+        sv.solve();
         sv.recover(xs);
 
         {   // segment code of the row / column (as the short-row kernel builds it)
@@ -467,48 +491,32 @@ __global__ __launch_bounds__(64, (S == 8 ? 6 : ((S == 16 && DENSE) ? 4 : 2))) vo
         // the pass's new correction term (input - output); needed by the same direction's pass
         // of the next sweep
         const bool keep = i + 2 < n_pass;
-        if (keep) {
+        float corr[S];                          // (formed always: conditionally it would tie up v during the solve)
 #pragma unroll
-            for (int k = 0; k < S; ++k) v[k] = park[k * 64] - xs[k];
-        }
+        for (int k = 0; k < S; ++k) corr[k] = park[k * 64] - xs[k];
         wave_lds_sync();                        // the parked inputs have been read
+        // (each view through its own opaque address: merged, the two would be S selected addresses)
         if (col) {
+            float *to = T1 + opaque((h * S) * P + idx);
 #pragma unroll
-            for (int k = 0; k < S; ++k) colp[k * P] = xs[k];
+            for (int k = 0; k < S; ++k) to[k * P] = xs[k];
         } else {
+            float *to = T1 + opaque((h * S + idx) * P);
 #pragma unroll
-            for (int k = 0; k < S; ++k) rowp[k] = xs[k];
+            for (int k = 0; k < S; ++k) to[k] = xs[k];
         }
         wave_lds_sync();
         // (planes of at most 32 x 32: the reverse sweep reads the codes written above)
         if (p.keep_passes) put_planes(p.saved + (size_t)i * p.saved_stride + plane0 * HW);
-        if (i + 1 == n_pass) {
-            if constexpr (IO16) {
-                uint16_t *dst = reinterpret_cast<uint16_t *>(p.x) + plane0 * HW;
-                if (FULL && ((uintptr_t)dst % 16) == 0) {
-                    tile_into_planes16<S>(T1, dst, n_here, lane, p.stream != 0);
-                } else if (pvalid && idx < W) {
-                    uint16_t *colo = dst + h * HW + idx;
-                    for (int r = 0; r < H; ++r) colo[r * W] = f32_to_bf16_bits(T1[(h * S + r) * P + idx]);
-                }
-            } else {
-                put_planes(p.x + plane0 * HW);
-            }
-            break;
-        }
-
         // input of the next pass: this output seen the other way, plus that direction's
         // correction term, whose negated running sum is the dual to start from
+        // (formed behind the last pass too: leaving the loop before it would tie up registers for
+        // this state during every solve)
         valid = pvalid && (FULL || idx < (col ? H : W));
         n = col ? W : H;
         float t[S];
-        if (col) {
-#pragma unroll
-            for (int k = 0; k < S; ++k) t[k] = (valid && (FULL || k < n)) ? rowp[k] : 0.f;
-        } else {
-#pragma unroll
-            for (int k = 0; k < S; ++k) t[k] = (valid && (FULL || k < n)) ? colp[k * P] : 0.f;
-        }
+        if (col) take(T1 + opaque((h * S + idx) * P), 1, n, t);
+        else take(T1 + opaque((h * S) * P + idx), P, n, t);
         if (i >= 1) {
             float run = 0.f;
 #pragma unroll
@@ -516,15 +524,29 @@ __global__ __launch_bounds__(64, (S == 8 ? 6 : ((S == 16 && DENSE) ? 4 : 2))) vo
                 const float c = mine[k * 64];
                 t[k] += c;
                 run -= c;
-                if (k < S - 1) sv.u[k] = run;
+                u0[k] = run;
             }
+        } else {
+#pragma unroll
+            for (int k = 0; k < S; ++k) u0[k] = 0.f;
         }
         if (keep) {
 #pragma unroll
-            for (int k = 0; k < S; ++k) mine[k * 64] = v[k];
+            for (int k = 0; k < S; ++k) mine[k * 64] = corr[k];
         }
 #pragma unroll
         for (int k = 0; k < S; ++k) v[k] = t[k];
+    }
+    if constexpr (IO16) {
+        uint16_t *dst = reinterpret_cast<uint16_t *>(p.x) + plane0 * HW;
+        if (FULL && ((uintptr_t)dst % 16) == 0) {
+            tile_into_planes16<S>(T1, dst, n_here, lane, p.stream != 0);
+        } else if (pvalid && idx < W) {
+            uint16_t *colo = dst + h * HW + idx;
+            for (int r = 0; r < H; ++r) colo[r * W] = f32_to_bf16_bits(T1[(h * S + r) * P + idx]);
+        }
+    } else {
+        put_planes(p.x + plane0 * HW);
     }
 }
 
