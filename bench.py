@@ -375,9 +375,10 @@ def dispatch_probe(dev) -> int:
     # small batches: a plane per workgroup up to these plane counts
     n = defaults["plane_per_group_planes"]
     for K in (1, 4):
-        case("plane_per_group_planes", "at_threshold_k%d" % K, lambda: two_d(n, 32, 32, K), 0,
+        most = n if K == 1 else n + n // 3      # (a third more with several sweeps)
+        case("plane_per_group_planes", "at_threshold_k%d" % K, lambda: two_d(most, 32, 32, K), 0,
              "a plane per workgroup", "the row-per-lane kernels")
-        case("plane_per_group_planes", "beyond_k%d" % K, lambda: two_d(n + n // 4, 32, 32, K), big,
+        case("plane_per_group_planes", "beyond_k%d" % K, lambda: two_d(most + most // 4, 32, 32, K), big,
              "the row-per-lane kernels", "a plane per workgroup")
     case("plane_per_group_planes", "at_a_fifth_k4", lambda: two_d(n // 5, 32, 32, 4), 0,
          "a plane per workgroup", "the row-per-lane kernels")
@@ -408,8 +409,11 @@ def dispatch_probe(dev) -> int:
     case("fused32_ragged_planes", "at_threshold_k1", lambda: two_d(n, 28, 28, 1), 0, "one launch", "pass by pass")
     case("fused32_ragged_planes", "beyond_k1", lambda: two_d(n + n // 4, 28, 28, 1), big, "pass by pass", "one launch")
     n = defaults["fused16_one_sweep_planes"]
-    case("fused16_one_sweep_planes", "at_threshold_k1", lambda: two_d(n, 16, 16, 1), 0, "one launch", "pass by pass")
-    case("fused16_one_sweep_planes", "beyond_k1", lambda: two_d(n + n // 4, 16, 16, 1), big, "pass by pass", "one launch")
+    if n > (1 << 20):               # "always", as above
+        case("fused16_one_sweep_planes", "at_262144_planes_k1", lambda: two_d(262144, 16, 16, 1), 0, "one launch", "pass by pass")
+    else:
+        case("fused16_one_sweep_planes", "at_threshold_k1", lambda: two_d(n, 16, 16, 1), 0, "one launch", "pass by pass")
+        case("fused16_one_sweep_planes", "beyond_k1", lambda: two_d(n + n // 4, 16, 16, 1), big, "pass by pass", "one launch")
     n = defaults["fused16_dense_planes"]
     case("fused16_dense_planes", "at_threshold_k2", lambda: two_d(n, 16, 16, 2), big, "four waves per SIMD", "three")
     case("fused16_dense_planes", "just_below_k2", lambda: two_d(n - n // 4, 16, 16, 2), 0, "three waves per SIMD", "four")

@@ -1,7 +1,7 @@
 // Every size at which the library switches from one kernel mapping to another, in one place,
 // each with the measurement that set it (one MI355X; times in microseconds, forward unless
-// noted).  They are crossover points of two ways to compute the same bits, never a matter of
-// results.  The values are variables so that the benchmark can time both sides of a threshold
+// noted).  They are crossover points of two ways to compute the same minimiser (to the last bits
+// of fp32), never a matter of results.  The values are variables so that the benchmark can time both sides of a threshold
 // at the threshold (tv_dispatch_override); nothing else writes them.
 #pragma once
 #include <stdint.h>
@@ -64,24 +64,25 @@ inline Threshold table[kCount] = {
     // memory round trips between the passes, which weighs more the more sweeps there are.
     // One launch against pass by pass, forward + backward, feature-map-like data:
     //   K = 1:  4096 planes  69 /  76,  4352:  91 /  82,  6144: 115 /  95, 16 384: 235 / 188;
-    //   K = 2:  4096 planes 108 / 146, 20 480: 442 / 465, 32 768: 700 / 704, 49 152: 1000 / 975;
-    //   K = 4:  4096 planes 183 / 290, 32 768: 1162 / 1257, 65 536: 2206 / 2305, 81 920: 2767 / 2881
-    //   (with three sweeps or more the one launch wins at every count: the value means "always").
+    //   K = 2:  4096 planes 106 / 144, 16 384: 334 / 346, 24 576: 493 / 482, 32 768: 643 / 612;
+    //   K = 4:  4096 planes 183 / 290, 16 384: 580 / 660, 65 536: 2125 / 2240
+    //   (with three sweeps or more the one launch wins or is even at every count: the value means
+    //   "always").
     // (The one launch holds 4096 planes at once: with a single sweep it loses over its second
     // round of waves what the saved launches gained.)
     {"fused32_full_planes", 4096, "2D planes of 32 x 32, one sweep: all passes in one launch up to this many planes"},
-    {"fused32_full_planes_k2", 32768, "... two sweeps"},
+    {"fused32_full_planes_k2", 20480, "... two sweeps"},
     {"fused32_full_planes_k3", (int64_t)1 << 40, "... three sweeps or more"},
     // 2D, planes of 17-32 samples a side that do not fill 32 x 32, single sweep (with two sweeps
     // or more the one launch always wins: 28 x 28, 32 768 planes, K = 4: 1.46 ms against 1.94).
-    // 28 x 28, K = 1, one launch against pass by pass, forward + backward: 2048 planes 91 / 98,
-    // 4096: 96 / 101, 4352: 127 / 105, 5120: 140 / 120, 6144: 154 / 122.
-    {"fused32_ragged_planes", 4096, "2D ragged planes padded to 32 x 32, one sweep: one launch up to this many planes"},
-    // 2D, planes of 9-16 samples a side, single sweep, forward + backward: 16 384 planes 58 in one
-    // launch against 58 pass by pass, 24 576: 70 / 75, 32 768: 88 / 86 (K = 3: 166 against 206
-    // forward, so several sweeps always take the one launch).  With the four-waves variant of
-    // the one-launch kernel (fused16_dense_planes below): 49 152 planes 110 / 113, 61 440: 132 / 134.
-    {"fused16_one_sweep_planes", 49152, "2D planes of at most 16 x 16, one sweep: one launch up to this many planes"},
+    // 28 x 28, K = 1, one launch against pass by pass, forward + backward: 4096 planes 75 / 94,
+    // 4352: 95 / 97, 6144: 116 / 114, 8192: 127 / 147, 10 240: 0.98 of it, 12 288: 1.00 and 0.97 (two
+    // kinds of data), 16 384: 223 / 220, 32 768: 1.00 and 1.01.
+    {"fused32_ragged_planes", 12288, "2D ragged planes padded to 32 x 32, one sweep: one launch up to this many planes"},
+    // 2D, planes of 9-16 samples a side, single sweep, forward + backward, one launch against pass
+    // by pass: 16 x 16, 24 576 planes 67 / 73, 49 152: 101 / 107, 98 304: 178 / 180, 262 144: 445 / 500;
+    // 14 x 14, 49 152 planes 111 / 118, 262 144: 507 / 579 (the value means "always").
+    {"fused16_one_sweep_planes", (int64_t)1 << 40, "2D planes of at most 16 x 16, one sweep: one launch up to this many planes"},
     // ... and from this many planes on the one-launch kernel for planes of 9-16 a side is the
     // variant held to 128 VGPRs, four waves per SIMD (planes that do not fill their square take 129
     // left alone; 16 384 planes of 14 x 14, K = 4: 101 us against 78).  The crossover is where the
@@ -94,31 +95,30 @@ inline Threshold table[kCount] = {
     // short chains and one launch.  Its time is set by the slowest row of each pass (a barrier
     // between passes), so it stops paying once the other kernels fill the chip.  Forward, this
     // kernel / the library's choice without it, feature-map-like data:
-    //   32 x 32, K = 1:  512 planes 22 /  42,  1024: 33 /  45,  1536:  44 /  46,  1792:  50 /  45;
-    //            K = 2:  512 planes 32 /  68,  1024: 51 /  75,  1536:  69 /  80,  2048:  88 /  77;
-    //            K = 4:  512 planes 51 / 119,  1024: 81 / 130,  1536: 110 / 129,  2048: 143 / 133;
-    //   28 x 30, K = 1: 1280 planes 37 /  59,  2048: 52 /  68;  K = 3: 2048 planes 108 / 153;
-    //   20 x 32, K = 1: 2048 planes 47 /  59,  4096: 80 /  67;  K = 4: 2048 planes 120 / 177.
+    //   32 x 32, K = 1: 1024 planes 31 /  43,  1536:  41 /  43,  2048:  49 /  44;
+    //            K = 4: 1024 planes 72 / 132,  1536:  96 / 128,  2048: 118 / 119 (N(0, 1) data: 0.73 of
+    //                   it), 2560: 142 / 130 (0.82);
+    //   28 x 30, K = 1: 1536 planes 39 /  48,  2048: 45 /  47, 2560: 54 / 50;  K = 3: 2048 planes 91 / 105;
+    //   20 x 32, K = 4: 2048 planes 104 / 163.
+    // (With two sweeps or more the library takes a third more planes than the value says.)
     {"plane_per_group_planes", 1536, "2D planes of 17-32 a side: one launch, a plane per workgroup, up to this many planes"},
-    //   64 x 64, K = 1:  128 planes  34 /  49, 1024:  85 / 104, 1536: 121 / 129, 2048: 158 / 159, 2560: 193 / 172;
-    //            K = 2:  128 planes  53 /  91, 1024: 134 / 181, 2048: 248 / 276, 4096: 472 / 474;
-    //            K = 4:  128 planes  83 / 157, 1024: 219 / 314, 2048: 415 / 484, 4096: 790 / 827;
-    //   48 x 48, K = 1: 1536 planes  98 /  97, 2048: 128 / 116;
-    //            K = 2: 1536 planes 162 / 177, 2048: 207 / 203, 3072: 295 / 273;
-    //            K = 4: 1536 planes 266 / 313, 2048: 350 / 360, 3072: 509 / 483.
-    {"plane_per_group64_planes", 1536, "2D planes of 33-64 a side, one sweep: one launch, a plane per workgroup, up to this many planes"},
-    {"plane_per_group64_planes_k2", 1536, "... two sweeps or more, planes smaller than 64 x 64"},
-    //   64 x 64 again, to larger batches (full planes keep every lane of the 8 x 8 mapping busy):
-    //            K = 2: 2560 planes 321 / 339, 3072: 386 / 401, 3584: 443 / 446, 4096: 503 / 488;
-    //            K = 3: 3072 planes 513 / 540, 4096: 661 / 694, 5120: 819 / 807;
-    //            K = 4: 4096 planes 820 / 876, 5120: 1011 / 1020;  K = 6: 4096: 1107 / 1218, 5120: 1364 / 1416.
-    //   (48 x 48 once more, forward + reverse sweep: K = 2, 2048 planes 291 / 275;  K = 4: 486 / 473)
-    {"plane_per_group64_full_planes_k2", 3584, "... planes of 64 x 64, two sweeps"},
-    //            K = 4: 8192 planes 1587 / 1637, 16384: 3030 / 3034, 32768: 6064 / 5790;
-    //            K = 6: 8192 planes 2121 / 2300, 16384: 4172 / 4185, 32768: 8403 / 8207;
-    //            K = 10: 8192 planes 3237 / 3479, 16384: 6377 / 6548, 32768: 12837 / 12927.
-    {"plane_per_group64_full_planes_k3", 8192, "... planes of 64 x 64, three or four sweeps"},
-    {"plane_per_group64_full_planes_k5", 12288, "... planes of 64 x 64, five sweeps or more"},
+    //   64 x 64, K = 1:  512 planes  47 /  50,  768:  67 /  60, 1024:  78 /  73, 1536: 109 / 94;
+    //   48 x 48, K = 1:  512 planes  35 /  38,  768:  55 /  54, 1024:  64 /  57.
+    {"plane_per_group64_planes", 512, "2D planes of 33-64 a side, one sweep: one launch, a plane per workgroup, up to this many planes"},
+    // Several sweeps, forward + reverse sweep, ratio of this kernel to pass by pass on post-ReLU
+    // maps and on N(0, 1) data:
+    //   48 x 48, K = 2: 1024 planes 0.95 1.01, 1280: 1.02 1.06, 1536: 1.06 1.07;
+    //            K = 4: 1280 planes 0.93 0.99, 1536: 0.97 1.01, 2048: 1.05 1.07;
+    //   64 x 40, K = 3: 1280 planes 0.93 0.99, 1536: 0.96 1.01, 2048: 1.04 1.06.
+    {"plane_per_group64_planes_k2", 1280, "... two sweeps or more, planes smaller than 64 x 64"},
+    //   64 x 64, K = 2:  512 planes 0.78 0.79, 1024: 0.90 0.97, 1280: 0.99 1.02, 2048: 1.04 1.06.
+    {"plane_per_group64_full_planes_k2", 1280, "... planes of 64 x 64, two sweeps"},
+    //            K = 3: 1536 planes 0.95 1.00, 2048: 0.99 1.03, 3072: 1.02 1.02, 4096: 1.04 1.08;
+    //            K = 4: 1536 planes 0.92 0.97, 2048: 0.97 1.02, 3072: 0.99 1.03, 8192: 1.03 1.04.
+    {"plane_per_group64_full_planes_k3", 2048, "... planes of 64 x 64, three or four sweeps"},
+    //            K = 5: 2048 planes 0.96 1.02, 4096: 1.01 1.04, 12 288: 1.02 1.04;
+    //            K = 8: 2048 planes 0.94 0.98, 4096: 0.98 1.02, 12 288: 1.00 1.01.
+    {"plane_per_group64_full_planes_k5", 4096, "... planes of 64 x 64, five sweeps or more"},
     // 2D reverse sweep of small batches with a plane per workgroup (tv_plane2d.hpp): both adjoint
     // state tensors of the plane in LDS, 16 x 2 or 8 x 8 threads x samples per row, the segment
     // sums across a row's threads by row shifts.  Against the row-per-lane one-launch kernel (a
@@ -149,15 +149,19 @@ inline Threshold table[kCount] = {
     // thread_per_sample_1d_rows): 16 threads x 2 samples up to this many rows, 8 x 4 beyond
     // (8192 rows of 32 samples as 256 planes, ten passes each way: 204 -> 180 with 16 x 2).
     {"thread_per_sample_wide_rows", 16384, "short rows on the long-row kernels: 16 threads per row up to this many rows"},
-    // 1D calls on rows of 2-32 samples (without segment codes): up to this many rows sixteen
-    // threads per row on the long-row kernels instead of a lane per row, whose few waves are bound
-    // by their dependency chains.  Forward, lane per row / threads per row: 8192 rows x 32 (the
-    // paper's timing batch) 23.6 / 11.7, 32 768 rows 25.0 / 18.0, 65 536 rows 26.6 / 26.6, 131 072
-    // rows 34.7 / 43.7; rows of 20 samples: 8192 rows 30.2 / 11.3, 65 536 rows 32.8 / 24.0; rows of
-    // 12 samples: 8192 rows 12.8 / 11.9, 32 768 rows 14.0 / 13.7, 65 536 rows 14.4 / 20.0; N(0,1) rows
-    // of 32 samples in 128 lambda slots, forward + backward: 40 960 rows 39.6 / 38.2, 49 152 rows
-    // 38.2 / 39.6.
-    {"thread_per_sample_1d_rows", 40960, "1D rows of at most 32 samples: a few threads per row up to this many rows"},
+    // 1D calls on rows of 2-32 samples: up to this many rows eight or sixteen threads per row on
+    // the long-row kernels instead of a lane per row, whose few waves are bound by their dependency
+    // chains.  Forward, threads per row / lane per row: 8192 rows x 32 (the
+    // paper's timing batch) 11.4 / 23.6, 32 768 rows 14.4 / 23.6, 65 536: 21.0 / 24.3, 81 920: 22.7 /
+    // 26.2, 98 304: 25.1 / 25.7;  rows of 20: 32 768 rows 13.1 / 24.9, 81 920: 20.6 / 28.9;  rows of 16
+    // or less, whose lanes have the shorter chains: 12 samples, 32 768 rows 11.8 / 13.5, 49 152: 14.0 /
+    // 14.0, 65 536: 17.1 / 15.0;  7 samples, 40 960 rows 11.6 / 11.6, 57 344: 14.9 / 11.4.  So these
+    // change over at half the value.  Strided rows (columns) whose lanes do well, those of 32 samples
+    // and of 16 or less, change over at half of that again, the threads' strided accesses being the
+    // worse ones: 32 samples, random walks, 40 960 columns 23.2 / 24.1, 65 536: 27.8 / 24.2; 12
+    // samples, 24 576 columns 14.1 / 13.4, N(0, 1) 0.93 of it, 40 960: 17.6 / 12.9; but 20 samples,
+    // 81 920 columns 28.6 / 33.7, 28 samples 30.3 / 30.9.
+    {"thread_per_sample_1d_rows", 81920, "1D rows of at most 32 samples: a few threads per row up to this many rows (half of it: rows of at most 16, columns of 32; a quarter: columns of at most 16)"},
     // Multilevel start of unit-stride rows: from this length on.  4096 rows x 16384: 1410 -> 880.
     // 8M samples in rows of n, lambda 10^U(-3, 1) per row, cold / multilevel, for random walks,
     // white noise and noisy steps of 64 samples: n = 768: 106 / 101, 113 / 116, 88 / 103; 1024:

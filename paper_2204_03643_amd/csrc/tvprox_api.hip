@@ -855,7 +855,10 @@ int fwd_entry(const float *y, float *x, tv_rows rows, tv_lambda lam, const tv_fw
     // small batches of short rows: a few threads per row (see tv_dispatch.hpp)
     // (not when the caller hands over the slot-order workspace or asks for the parallel step-size
     // search: both belong to the row-per-lane kernels)
-    const bool few = n_rows <= tvd::get(tvd::kThreadPerSample1dRows) && !e.ws && !(e.flags & TV_FWD_PARALLEL_SEARCH);
+    int64_t few_rows = tvd::get(tvd::kThreadPerSample1dRows);
+    if (rows.length <= 16) few_rows /= 2;
+    if (rows.elem_stride != 1 && (rows.length <= 16 || rows.length == 32)) few_rows /= 2;
+    const bool few = n_rows <= few_rows && !e.ws && !(e.flags & TV_FWD_PARALLEL_SEARCH);
     return run_fwd(y, nullptr, x, nullptr, e.info, reinterpret_cast<uint2 *>(e.seg), order_ws, rows,
                    lam, n_rows, s, nullptr, false, (char *)e.ws, false, few,
                    (e.flags & TV_FWD_ORDER_READY) != 0, (e.flags & TV_FWD_PARALLEL_SEARCH) != 0);
@@ -1180,7 +1183,11 @@ static int small_side(int64_t H, int64_t W)
 // segment codes for the reverse sweep, larger ones their pass outputs.
 static bool plane_per_group_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
 {
-    if (small_planes(H, W)) return small_side(H, W) == 32 && planes <= tvd::get(tvd::kPlanePerGroupPlanes);
+    if (small_planes(H, W)) {
+        // (from two sweeps on a third more)
+        const int64_t most = tvd::get(tvd::kPlanePerGroupPlanes);
+        return small_side(H, W) == 32 && planes <= (sweeps == 1 ? most : most + most / 3);
+    }
     if (H > 64 || W > 64) return false;
     if (sweeps == 1) return planes <= tvd::get(tvd::kPlanePerGroup64Planes);
     if (H == 64 && W == 64)
@@ -1262,8 +1269,9 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
         TV_SMALL2D_LAUNCH(tvk::tv2d_fwd_small_kernel, q, planes, H, W, stream);
         return launch_status();
     }
-    // one lambda for all planes: its gradient hinges on the last bits of x (see tv_long_tri.hpp)
-    const bool tri = lam.count == 1 && sweeps >= 3 && H <= 768 && W <= 768;
+    // one lambda for all planes: its gradient hinges on the last bits of x (see tv_long_tri.hpp;
+    // not for planes of at most 64 x 64, whose smaller batches are solved by block means anyway)
+    const bool tri = lam.count == 1 && sweeps >= 3 && H <= 768 && W <= 768 && (H > 64 || W > 64);
     for (int k = 0; k < sweeps; ++k) {
         const bool last = (k == sweeps - 1);
         const float *Yk = (k == 0) ? y : saved(2 * k - 1);

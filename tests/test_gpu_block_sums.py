@@ -51,3 +51,47 @@ def test_2d_passes_with_one_and_with_several_lambdas(H, W, count):
     g = rng.normal(size=y.shape).astype(np.float32)
     lam = np.array([0.15, 0.02, 0.6], np.float32)[:count]
     check_2d(y, lam, 3, g, run_2d(y, lam, 3, g), "%dx%d, %d lambdas" % (H, W, count))
+
+
+@pytest.mark.parametrize("n,axis,limit", [(12, -1, 128), (16, -1, 128), (17, -1, 256), (32, -1, 256),
+                                          (12, 0, 64), (16, 0, 64), (17, 0, 256), (31, 0, 256), (32, 0, 128)])
+def test_short_rows_change_mapping_at_their_row_count(n, axis, limit):
+    """With the threshold at 256 rows, shorter rows and columns change over at a half or a quarter of
+    it: on either side the result has the bits of the mapping that belongs there."""
+    import paper_2204_03643_amd as tv
+    rng = np.random.default_rng(n)
+    lam = np.array([0.4], np.float32)
+    saved = tv.tv_dispatch_threshold("thread_per_sample_1d_rows")
+    try:
+        for rows in (limit, limit + 1):
+            y = rng.normal(size=(rows, n)).astype(np.float32)
+            data = y if axis == -1 else np.ascontiguousarray(y.T)
+            x = {}
+            for value in (256, 1 << 40, 0):
+                tv.tv_dispatch_override("thread_per_sample_1d_rows", value)
+                x[value] = rows_view(run_1d(data, lam, 1, axis=axis)["x"], axis)
+            assert np.array_equal(x[256], x[1 << 40 if rows == limit else 0])
+            assert not np.array_equal(x[1 << 40], x[0])        # (the mappings round differently)
+            ref = oracle.prox1d_batch(y.astype(np.float64), lam.astype(np.float64))
+            floor = 16 * EPS * (np.abs(y).max(axis=1) + lam[0])            # as above
+            assert np.all(np.abs(x[256] - ref).max(axis=1) <= floor)
+    finally:
+        tv.tv_dispatch_override("thread_per_sample_1d_rows", saved)
+
+
+@pytest.mark.parametrize("H,W", [(64, 64), (33, 64), (48, 40)])
+def test_2d_planes_of_64_pass_by_pass_with_one_lambda(H, W):
+    import paper_2204_03643_amd as tv
+    names = ("plane_per_group64_planes_k2", "plane_per_group64_full_planes_k3")
+    saved = {k: tv.tv_dispatch_threshold(k) for k in names}
+    rng = np.random.default_rng(H + W)
+    y = np.maximum(rng.normal(size=(5, H, W)), 0).astype(np.float32)
+    g = rng.normal(size=y.shape).astype(np.float32)
+    lam = np.array([0.2], np.float32)
+    try:
+        for k in names:
+            tv.tv_dispatch_override(k, 0)
+        check_2d(y, lam, 3, g, run_2d(y, lam, 3, g), "%dx%d" % (H, W))
+    finally:
+        for k, v in saved.items():
+            tv.tv_dispatch_override(k, v)
