@@ -130,14 +130,14 @@ struct LongSmemBwd {
 
 // Waves per SIMD that the forward kernel asks the register allocator for (the second argument
 // of __launch_bounds__; 1 = no request).  Left alone, the kernels with 8 samples per thread take
-// 85-96 VGPRs and those with 12 take 100-108: a few registers above the step to one more
-// resident wave (80 for six, 96 for five).  These kernels wait 40-50 % of their time (barriers,
-// LDS exchanges, the drain of a launch in partly filled rounds), so where the allocator can
-// get below the step with at most a handful of spilled registers the extra wave pays:
-// 12 288 columns of 512 samples 57 -> 52 us (three 512-thread workgroups per CU, two rounds
-// instead of three), warm row passes of the same 2-3 %, 3000 rows of 3000 samples 910 -> 730 us.
-// Not requested where it costs 10-18 spilled registers (128 threads x 12 samples, and the
-// transposing kernel with 32 x 12): those ran 2-3 % slower with it.
+// 77-89 VGPRs and those with 12 take 102-116: a few registers above the step to one more
+// resident wave (80 for six, 96 for five).  These kernels wait much of their time (barriers,
+// LDS exchanges, the drain of a launch in partly filled rounds), so the extra wave pays although
+// the cold-start kernels spill 5-13 registers for it: without the request, 8M samples in rows of
+// 520 (64 threads x 12 samples), random walks, 80.8 us instead of 76.9, 144 (16 x 12) 75.4 / 72.4,
+// 300 (32 x 12) 74.2 / 71.3, 768 59.5 / 58.0; 12 288 columns of 512 samples 57 -> 52 (three
+// 512-thread workgroups per CU, two rounds instead of three).  Not requested for 128 threads x 12
+// samples and the transposing kernel with 32 x 12, which ran 2-3 % slower with it.
 template <int T, int C, int G, bool COLS, bool XPOSE>
 constexpr int fwd_waves_per_simd()
 {
@@ -572,8 +572,8 @@ inline hipError_t launch_fwd_long(const FwdParams &p, hipStream_t s)
 }
 
 // The forward launch with step records (cold start, unit-stride rows): one mapping of each kind
-// -- rows inside a wave (wave-level fences, PCR over the wave's separators), and a workgroup per
-// row with 256 and with 1024 threads (workgroup barriers, PCR in LDS across waves).
+// -- rows inside a wave (wave-level fences, scans inside the wave), and a workgroup per
+// row with 256 and with 1024 threads (workgroup barriers, the waves' totals through LDS).
 inline hipError_t launch_fwd_long_debug(const FwdParams &p, hipStream_t s)
 {
     const int n = p.L.n;

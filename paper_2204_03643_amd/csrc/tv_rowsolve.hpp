@@ -69,7 +69,7 @@ __device__ __forceinline__ float from_right(float v, int t)
     return (T < 16 && t + S >= T) ? 0.f : r;
 }
 // (Rows of 32 and 64 threads could fetch their direct neighbours by a shift of the whole wave
-// (wave_shr:1); measured, that changes nothing for them: their time goes into the PCR steps at
+// (wave_shr:1); measured, that changes nothing for them: their time goes into the scan steps at
 // distances that no single shift covers.)
 
 // OR over the T <= 16 lanes of a row (rows are aligned groups of T lanes), the result in all of them.
