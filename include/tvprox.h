@@ -81,6 +81,9 @@ typedef struct {
  * length == 1 copies the row.  Zero rows: TV_OK without a launch.
  * A row whose input holds NaN/Inf gets unspecified values in that row (NaN at least at
  * the non-finite samples); other rows are unaffected and the call still terminates.
+ * Rows of more than 32 samples, and shorter ones on the kernels for small batches, have the same
+ * bits whatever the other rows of the call hold; on the row-per-lane kernels the rows of a wave
+ * agree with that to rounding.
  * Within a maximal constant run of the result all samples are bit-identical, which
  * is what tv1d_prox_bwd relies on to recover the segments.
  */

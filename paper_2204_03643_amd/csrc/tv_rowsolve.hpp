@@ -573,6 +573,7 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
     using Mp = LongMap<T, G, COLS>;
     using Rw = RowWave<T, G, COLS>;
     constexpr bool MULTI = Rw::MULTI;
+    constexpr bool SHARED = MULTI ? G > 1 : Rw::TW < 64;       // rows share a wave
     static_assert(!POLISH || !MULTI, "rows inside one wave");
     // (the flags of FwdParams::info, shifted into the range of inline constants)
     constexpr int kConverged = kInfoConverged >> 16, kStalled = kInfoStalled >> 16, kCapped = kInfoCapped >> 16,
@@ -750,7 +751,10 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
     const float scale = 1.f + fmaxf(gtol * (1.0f / kGradNoise) - lam, 0.f);
     sm.park(tid, y);
     const float noise = (float)n * gtol * gtol * (1.f / 64.f);     // n samples moved by 2 ulp of max|y| + lam each
-    bool active = valid;
+    // A row that has landed is done: it ends on the block means of the x it landed from, whatever the rows
+    // that share its wave or workgroup still do.  While they go on, its dual stays where it landed from
+    // and every trip forms the same means from it.
+    bool active = valid, done = false;
     int steps = 0, flags = 0, quiet = 0;
     if constexpr (DEBUG) {
         if (rec && t == 0) { rec[0] = 0.f; rec[1] = lam; rec[kRecF] = fcur; }
@@ -963,6 +967,15 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
         };
         constexpr bool TINY = POLISH || WARM == 3;
         bool landed;
+        //      Rows that share a wave: a last step that moves the samples by more than a quarter of max|y| (root
+        //      of the mean square) comes from an x of large duals, lambda >> the data as a rule, whose
+        //      rounding is in its block means, so that one gets another look as well.  (Rows of 20, 0/1
+        //      samples, lambda 10^U(-2, 1): relative error 2.7e-8, without it 1.9e-7.  A look behind every
+        //      last step is hardly closer, 4.4e-8 against 4.6e-8 on N(0, 1), and 9 % slower on planes of 64 x 64.)
+        auto far = [&]() {
+            const float ym = gtol * (1.0f / kGradNoise) - lam;
+            return SHARED && dec > 0.0625f * (float)n * ym * ym;
+        };
         if constexpr (MULTI) {
             // the votes ride on the exchange of the trial's chunk edges
             const float vfirst = x0 + head_v;
@@ -1012,6 +1025,7 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
             }
             quiet += dec <= noise ? 1 : 0;
             landed = (!clipped || (TINY && dec <= gtol * gtol) || quiet > 2) && !p;
+            soft |= far();
         } else {
             clipped = rw.any(clipped);
             dec = wave_sum_all<Mp::LANES>(decp);
@@ -1020,12 +1034,14 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
             const bool may = active && (!clipped || (TINY && dec <= gtol * gtol) || quiet > 2);
             if (wave_any(may)) {
                 landed = may & !rw.any(pushed(rw.next(x0 + head_v) - x0));
-                soft = rw.any(soft);
+                soft = rw.any(soft) || far();
             }
         }
         if (WARM == 2 && lam > 0.25f * scale && !(dec <= fmaxf(gtol * gtol, 4e-4f * scale * scale))) landed = false;
         const bool look_again = active && landed && soft;
-        if (active && landed) { active = false; flags = kConverged; ++steps; }
+        bool landed_now = false;
+        if (active && landed) { active = false; flags = kConverged; ++steps; landed_now = !soft; }
+        done |= landed_now;
         if (go) go = wave_any(active || look_again);
 
         if (!go) {                                             // every row of the wave (workgroup) has stopped
@@ -1034,7 +1050,22 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
             for (int i = 0; i < C; ++i) held |= bnd[i] ? 1u << i : 0u;
             head_x = ref + head_m;
             tail_x = tail_ref + tail_m;
+            if constexpr (SHARED) {
+                if (done) {                                    // the landing step again, for the caller
+#pragma unroll
+                    for (int i = 0; i < C; ++i) uc[i] = __builtin_amdgcn_fmed3f(fmaf(-1.f, d[i], u[i]), -lam, lam);
+                }
+            }
             break;
+        }
+        if constexpr (SHARED) {
+            if (wave_any(landed_now)) {                        // (uniform in the workgroup where rows span waves)
+                if (landed_now) {
+#pragma unroll
+                    for (int i = 0; i < C; ++i) uc[i] = u[i];
+                }
+                if constexpr (MULTI) edges(uc[0], uc[C - 1], ucleft, ucright);
+            }
         }
 
         // ---- the trial point, its x and its objective; Armijo test with quadratic interpolation
