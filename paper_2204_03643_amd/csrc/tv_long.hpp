@@ -258,8 +258,9 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>()))
     // (workload 4, K = 10, warm passes with them: 700 -> 740 us; rows of 900 from the coarse level:
     // 120 -> 123).  Rows that span waves would need one more exchange through a barrier for them.
     constexpr bool POLISH = Mp::PRIVATE && (WARM == 0 || WARM == 3) && !DEBUG;
+    constexpr bool DUAL = !COLS && (WARM == 0 || WARM == 2);
     float xs[C];
-    const int info = row_solve<T, C, G, MCOLS, WARM, POLISH, DEBUG>(y, u, wsum, lam, n, j, t, rvalid, sm, cu,
+    const int info = row_solve<T, C, G, MCOLS, WARM, POLISH, DEBUG, DUAL>(y, u, wsum, lam, n, j, t, rvalid, sm, cu,
                                                                    p.coarse_n, rec, xs);
 
     // (rows of at most 32 samples, small batches: the segment code comes from the registers; a kernel
@@ -270,7 +271,7 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>()))
             if (rvalid && t == 0) p.seg[row] = code;
         }
     }
-    if (p.dual_out) chunk_store<C>(p.dual_out, (int64_t)row * p.dual_pitch, 1, k0, n, rvalid, u);
+    if (DUAL && p.dual_out) chunk_store<C>(p.dual_out, (int64_t)row * p.dual_pitch, 1, k0, n, rvalid, u);
 
     if constexpr (XPOSE) {
         // a wave writes only its own row of the tile; the barrier then hands the tile over

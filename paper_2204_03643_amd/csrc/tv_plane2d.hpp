@@ -70,7 +70,7 @@ __global__ __launch_bounds__(T * T * C, C <= 4 ? 8 : 4) void tv2d_fwd_plane_kern
         }
         int info;
         if (i < 2) {
-            info = row_solve<T, C, S, false, 0, true, false>(y, u, 0.f, lam, n, j, t, valid, sm, nullptr, 0, nullptr, xs);
+            info = row_solve<T, C, S, false, 0, true, false, false>(y, u, 0.f, lam, n, j, t, valid, sm, nullptr, 0, nullptr, xs);
         } else {
             // input = the other direction's output plus this direction's correction term, which
             // is D^T u of this direction's pass one sweep earlier: start from that dual
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(T * T * C, C <= 4 ? 8 : 4) void tv2d_fwd_plane_kern
                 wsum -= cr;
                 u[c] = wsum;
             }
-            info = row_solve<T, C, S, false, 1, true, false>(y, u, wsum, lam, n, j, t, valid, sm, nullptr, 0, nullptr, xs);
+            info = row_solve<T, C, S, false, 1, true, false, false>(y, u, wsum, lam, n, j, t, valid, sm, nullptr, 0, nullptr, xs);
         }
         (void)info;
         if (i + 2 < n_pass) {

@@ -557,7 +557,7 @@ __device__ __forceinline__ void row_totals(const RowWave<T, G, COLS> &rw, RowSme
 
 // One row solved by the T threads that hold it.  y: the thread's chunk of the row (zero past the
 // end, n samples in the row); every thread of the workgroup calls, rows that do not exist with
-// valid = false.  xs receives the chunk of the minimiser, u the final dual (and sm.fetch has y
+// valid = false.  xs receives the chunk of the minimiser, u the final dual (DUAL; and sm.fetch has y
 // again, which frees its registers during the solve).  Returns the step count and flags of
 // FwdParams::info.
 //   WARM 0: from the bounds the local differences point to.  1: from the dual whose negated running
@@ -565,7 +565,8 @@ __device__ __forceinline__ void row_totals(const RowWave<T, G, COLS> &rw, RowSme
 //   given, from the dual cu (coarse_n entries) of the row averaged in groups of kMlFactor.
 //   3: as 0, or from the constant row's dual (see there).
 //   POLISH: a clipped trial point is polished by two Gauss-Seidel sweeps.  DEBUG: rec, if not null, receives the row's step record.
-template <int T, int C, int G, bool COLS, int WARM, bool POLISH, bool DEBUG>
+//   DUAL: the caller wants u (coarse levels, whose rows have unit stride); else it is left where the row landed.
+template <int T, int C, int G, bool COLS, int WARM, bool POLISH, bool DEBUG, bool DUAL>
 __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], float wsum, float lam, int n, int j,
                                          int t, bool valid, RowSmem<T, C, G, COLS> &sm, const float *cu,
                                          int coarse_n, float *rec, float (&xs)[C])
@@ -574,6 +575,7 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
     using Rw = RowWave<T, G, COLS>;
     constexpr bool MULTI = Rw::MULTI;
     constexpr bool SHARED = MULTI ? G > 1 : Rw::TW < 64;       // rows share a wave
+    constexpr bool KEEP = DUAL && SHARED;
     static_assert(!POLISH || !MULTI, "rows inside one wave");
     // (the flags of FwdParams::info, shifted into the range of inline constants)
     constexpr int kConverged = kInfoConverged >> 16, kStalled = kInfoStalled >> 16, kCapped = kInfoCapped >> 16,
@@ -753,7 +755,9 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
     const float noise = (float)n * gtol * gtol * (1.f / 64.f);     // n samples moved by 2 ulp of max|y| + lam each
     // A row that has landed is done: it ends on the block means of the x it landed from, whatever the rows
     // that share its wave or workgroup still do.  While they go on, its dual stays where it landed from
-    // and every trip forms the same means from it.
+    // and every trip forms the same means from it.  (DUAL forms the landing step anew in every trip, so that
+    // the last one has it; formed once more at the end instead, the three arrays it takes were 4-9 registers
+    // spilled in the kernels of 8 and 12 samples a thread.)
     bool active = valid, done = false;
     int steps = 0, flags = 0, quiet = 0;
     if constexpr (DEBUG) {
@@ -924,7 +928,7 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
             }
         }
         // ---- the step, projected
-        float alpha = active ? 1.f : 0.f;
+        float alpha = active || (KEEP && done) ? 1.f : 0.f;
         float ucleft, ucright, dec;
         bool clipped = false;
 #pragma unroll
@@ -1050,17 +1054,12 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
             for (int i = 0; i < C; ++i) held |= bnd[i] ? 1u << i : 0u;
             head_x = ref + head_m;
             tail_x = tail_ref + tail_m;
-            if constexpr (SHARED) {
-                if (done) {                                    // the landing step again, for the caller
-#pragma unroll
-                    for (int i = 0; i < C; ++i) uc[i] = __builtin_amdgcn_fmed3f(fmaf(-1.f, d[i], u[i]), -lam, lam);
-                }
-            }
             break;
         }
         if constexpr (SHARED) {
-            if (wave_any(landed_now)) {                        // (uniform in the workgroup where rows span waves)
-                if (landed_now) {
+            const bool freeze = KEEP ? done : landed_now;
+            if (wave_any(freeze)) {                            // (uniform in the workgroup where rows span waves)
+                if (freeze) {
 #pragma unroll
                     for (int i = 0; i < C; ++i) uc[i] = u[i];
                 }
