@@ -84,6 +84,8 @@ typedef struct {
  * Rows of more than 32 samples, and shorter ones on the kernels for small batches, have the same
  * bits whatever the other rows of the call hold; on the row-per-lane kernels the rows of a wave
  * agree with that to rounding.
+ * Samples and lambdas of 1e-20 to 1e15 are safe with any length; outside, squares that underflow or
+ * overflow can bring a row to the step cap (tv1d_prox_fwd_info tells).
  * Within a maximal constant run of the result all samples are bit-identical, which
  * is what tv1d_prox_bwd relies on to recover the segments.
  */

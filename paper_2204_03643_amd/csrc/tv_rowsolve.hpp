@@ -752,7 +752,9 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
     // (the data's scale, taken back out of gtol)
     const float scale = 1.f + fmaxf(gtol * (1.0f / kGradNoise) - lam, 0.f);
     sm.park(tid, y);
-    const float noise = (float)n * gtol * gtol * (1.f / 64.f);     // n samples moved by 2 ulp of max|y| + lam each
+    // n samples moved by 2 ulp of max|y| + lam each.  (It is 0, as gtol^2 is, where such squares underflow:
+    // the tests against both are strict, or every clipped point of a row of 1e-24 would pass for the end.)
+    const float noise = (float)n * gtol * gtol * (1.f / 64.f);
     // A row that has landed is done: it ends on the block means of the x it landed from, whatever the rows
     // that share its wave or workgroup still do.  While they go on, its dual stays where it landed from
     // and every trip forms the same means from it.  (DUAL forms the landing step anew in every trip, so that
@@ -1027,15 +1029,15 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
             } else {
                 for (int w = 0; w < Rw::NWR; ++w) dec += look(w);
             }
-            quiet += dec <= noise ? 1 : 0;
-            landed = (!clipped || (TINY && dec <= gtol * gtol) || quiet > 2) && !p;
+            quiet += dec < noise ? 1 : 0;
+            landed = (!clipped || (TINY && dec < gtol * gtol) || quiet > 2) && !p;
             soft |= far();
         } else {
             clipped = rw.any(clipped);
             dec = wave_sum_all<Mp::LANES>(decp);
             landed = false;
-            quiet += dec <= noise ? 1 : 0;
-            const bool may = active && (!clipped || (TINY && dec <= gtol * gtol) || quiet > 2);
+            quiet += dec < noise ? 1 : 0;
+            const bool may = active && (!clipped || (TINY && dec < gtol * gtol) || quiet > 2);
             if (wave_any(may)) {
                 landed = may & !rw.any(pushed(rw.next(x0 + head_v) - x0));
                 soft = rw.any(soft) || far();
