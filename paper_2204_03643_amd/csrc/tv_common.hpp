@@ -102,8 +102,9 @@ constexpr int kMlFactor = 4;
 //   [kRecF + i], i = 0 .. [0]: the dual objective f = 1/2 ||x(u)||^2 at the start and after
 //        every accepted step (at most kRecMaxF entries; later ones are dropped);
 //   [kRecU + k], k < n - 1: the dual the first iteration starts from;
-//   [kRecU + n + k]: the Newton direction d of the first iteration (u <- clip(u - alpha d)); not
-//        written for a row whose start already passes the optimality test (it takes no step);
+//   [kRecU + n + k]: the Newton direction d of the first iteration (u <- clip(u - alpha d), before any
+//        polish of a clipped point); not written by the row-per-lane kernel for a row whose start
+//        already passes the optimality test (it takes no step there);
 //   [kRecU + 2n + k]: 1 where the first iteration holds dual k on its bound, else 0.
 constexpr int kRecF = 8, kRecMaxF = 40, kRecU = 48;
 __host__ __device__ constexpr int64_t step_record_floats(int64_t n) { return kRecU + 3 * n; }

@@ -257,7 +257,7 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>()))
     // 256 / 512, lambda = 0.1 on images: 42 / 42 -> 38 / 40), not where it starts from a good dual
     // (workload 4, K = 10, warm passes with them: 700 -> 740 us; rows of 900 from the coarse level:
     // 120 -> 123).  Rows that span waves would need one more exchange through a barrier for them.
-    constexpr bool POLISH = Mp::PRIVATE && (WARM == 0 || WARM == 3) && !DEBUG;
+    constexpr bool POLISH = Mp::PRIVATE && (WARM == 0 || WARM == 3);
     constexpr bool DUAL = !COLS && (WARM == 0 || WARM == 2);
     float xs[C];
     const int info = row_solve<T, C, G, MCOLS, WARM, POLISH, DEBUG, DUAL>(y, u, wsum, lam, n, j, t, rvalid, sm, cu,

@@ -1045,6 +1045,25 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
         }
         if (WARM == 2 && lam > 0.25f * scale && !(dec <= fmaxf(gtol * gtol, 4e-4f * scale * scale))) landed = false;
         const bool look_again = active && landed && soft;
+        if constexpr (DEBUG) {                                 // the objective behind the last step
+            if (wave_any(active && landed)) {                  // (uniform in the workgroup: one row, or a row per wave)
+                if constexpr (!MULTI) edges(uc[0], uc[C - 1], ucleft, ucright);
+                float yl[C], acc = 0.f;
+                sm.fetch(tid, y, yl);
+#pragma unroll
+                for (int i = 0; i < C; ++i) {
+                    const float xi = yl[i] + uc[i] - (i > 0 ? uc[i - 1] : ucleft);
+                    acc = fmaf(xi, xi, acc);
+                }
+                bool none = false;
+                if constexpr (MULTI) row_totals(rw, sm, j, tid, par, acc, none);
+                else acc = wave_sum_all<Mp::LANES>(acc);
+                if (rec && t == 0 && active && landed) {
+                    const int c = (int)rec[0] + 1;
+                    if (c < kRecMaxF) { rec[kRecF + c] = 0.5f * acc; rec[0] = (float)c; }
+                }
+            }
+        }
         bool landed_now = false;
         if (active && landed) { active = false; flags = kConverged; ++steps; landed_now = !soft; }
         done |= landed_now;
