@@ -458,6 +458,20 @@ def dispatch_probe(dev) -> int:
         res["order_min_rows"]["at_half"] = {
             "chosen": "natural order", "chosen_us": a, "other": "slot order (workspace passed)", "other_us": b,
             "chosen_not_slower": a["fwd_us"] <= 1.03 * b["fwd_us"]}
+    # one lambda, ten sweeps: the solver kept for it against the others' (24 planes of 512 x 512)
+    def one_lambda():
+        rng = np.random.default_rng(5)
+        yt = torch.from_numpy(rng.normal(size=(24, 512, 512)).astype(np.float32)).to(dev)
+        lt = torch.tensor([0.1], device=dev)
+        xt = torch.empty_like(yt)
+        L = tv.tv_lambda(lt.data_ptr(), 1, 1)
+        wsb = tv.tv2d_workspace_bytes(24, 512, 512, 10)
+        ws = torch.empty(wsb, dtype=torch.uint8, device=dev)
+        tf = timed(lambda: tv.tv2d_prox_fwd(yt, xt, 24, 512, 512, L, 10, ws, wsb))
+        return {"fwd_us": tf, "bwd_us": 0.0, "fwd_bwd_us": tf}
+
+    # (kept for its lambda gradient, not for its time: tv_dispatch.hpp)
+    case("one_lambda_tri_side", "24_planes_of_512_k10", one_lambda, 0, "tridiagonal elimination", "block means")
     # multilevel start: rows of ml_min_length samples through the plain call (the levels live in
     # the rows of x) against the same call with the start switched off
     n = defaults["ml_min_length"]

@@ -260,6 +260,10 @@ int tv1d_prox_bwd_seg_bf16(const uint16_t *g_up, const uint64_t *seg, uint16_t *
  * from that dual.  Planes of at most 64 x 64 run all their passes in one launch where that is
  * faster (small batches with a plane per workgroup, larger ones of planes of at most 32 x 32
  * with a row per lane; the plane counts: csrc/tv_dispatch.hpp).
+ * With lam.count == 1 and three sweeps or more, planes with a side of 65 to 768 samples (and none
+ * longer) run another solver than with two lambdas and more ("one_lambda_tri_side"): one lambda and the same
+ * lambda repeated give outputs that agree to rounding, not bit for bit, and the gradients of
+ * segments whose levels agree to the last bits of fp32, and with them grad_lam, can differ by more.
  */
 size_t tv2d_workspace_bytes(int64_t planes, int64_t H, int64_t W, int sweeps);
 int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W,

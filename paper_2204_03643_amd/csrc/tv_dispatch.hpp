@@ -37,6 +37,7 @@ enum {
     kFusedKeepsPasses,
     kThreadPerSampleWideRows,
     kThreadPerSample1dRows,
+    kOneLambdaTriSide,
     kMlMinLength,
     kMlCoarsest,
     kCount
@@ -162,6 +163,14 @@ inline Threshold table[kCount] = {
     // samples, 24 576 columns 14.1 / 13.4, N(0, 1) 0.93 of it, 40 960: 17.6 / 12.9; but 20 samples,
     // 81 920 columns 28.6 / 33.7, 28 samples 30.3 / 30.9.
     {"thread_per_sample_1d_rows", 81920, "1D rows of at most 32 samples: a few threads per row up to this many rows (half of it: rows of at most 16, columns of 32; a quarter: columns of at most 16)"},
+    // 2D pass by pass with ONE lambda for all planes and three sweeps or more: sides up to this many
+    // samples (768 at most, and beyond 64) are solved by tridiagonal elimination (tv_long_tri.hpp), not
+    // by block means.  The slower one of the two is kept here for the sake of one number, the
+    // gradient of that lambda: a signed sum over all planes that cancels to a few of its terms, and
+    // which jumps of the size of the last bit take part is a matter of rounding in either solver.
+    // 24 planes of 512 x 512, N(0, 1), lambda 0.1, K = 10, forward: 633 by elimination, 564 by block
+    // means.  0: block means everywhere.
+    {"one_lambda_tri_side", 768, "2D with one lambda and three sweeps or more: sides of 65 to this many samples (at most 768) by tridiagonal elimination"},
     // Multilevel start of unit-stride rows: from this length on.  4096 rows x 16384: 1410 -> 880.
     // 8M samples in rows of n, lambda 10^U(-3, 1) per row, cold / multilevel, for random walks,
     // white noise and noisy steps of 64 samples: n = 768: 106 / 101, 113 / 116, 88 / 103; 1024:

@@ -1271,7 +1271,9 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
     }
     // one lambda for all planes: its gradient hinges on the last bits of x (see tv_long_tri.hpp;
     // not for planes of at most 64 x 64, whose smaller batches are solved by block means anyway)
-    const bool tri = lam.count == 1 && sweeps >= 3 && H <= 768 && W <= 768 && (H > 64 || W > 64);
+    const int64_t longest = H > W ? H : W;
+    const bool tri = lam.count == 1 && sweeps >= 3 && longest > 64 && longest <= 768 &&
+                     longest <= tvd::get(tvd::kOneLambdaTriSide);
     for (int k = 0; k < sweeps; ++k) {
         const bool last = (k == sweeps - 1);
         const float *Yk = (k == 0) ? y : saved(2 * k - 1);

@@ -53,6 +53,31 @@ def test_2d_passes_with_one_and_with_several_lambdas(H, W, count):
     check_2d(y, lam, 3, g, run_2d(y, lam, 3, g), "%dx%d, %d lambdas" % (H, W, count))
 
 
+@pytest.mark.parametrize("H,W", [(65, 100), (200, 257), (513, 70)])
+def test_one_lambda_and_the_same_lambda_repeated(H, W):
+    """The two solvers agree to rounding; with the threshold at 0 there is one, and the bits agree."""
+    import paper_2204_03643_amd as tv
+    rng = np.random.default_rng(H + W)
+    y = (np.repeat(np.repeat(rng.uniform(-1, 1, size=(3, H // 8 + 1, W // 8 + 1)), 8, 1), 8, 2)[:, :H, :W]
+         + rng.normal(0, 0.2, size=(3, H, W))).astype(np.float32)
+    g = rng.normal(size=y.shape).astype(np.float32)
+    lam = np.full(3, 0.2, np.float32)
+    many = run_2d(y, lam, 3, g)
+    tri = run_2d(y, lam[:1], 3, g)
+    saved = tv.tv_dispatch_threshold("one_lambda_tri_side")
+    try:
+        tv.tv_dispatch_override("one_lambda_tri_side", 0)
+        one = run_2d(y, lam[:1], 3, g)
+    finally:
+        tv.tv_dispatch_override("one_lambda_tri_side", saved)
+    check_2d(y, lam[:1], 3, g, tri, "%dx%d, tridiagonal" % (H, W))
+    check_2d(y, lam[:1], 3, g, one, "%dx%d, block means" % (H, W))
+    assert np.array_equal(one["x"], many["x"]) and np.array_equal(one["gy"], many["gy"])
+    # six passes, each off by its floor at most on both sides; a prox does not stretch distances (2-norm)
+    floor = 2 * 6 * 16 * EPS * (np.abs(y).max() + 2 * lam[0]) * np.sqrt(y.size)
+    assert np.linalg.norm(tri["x"].astype(np.float64) - one["x"]) <= floor
+
+
 @pytest.mark.parametrize("n,axis,limit", [(12, -1, 128), (16, -1, 128), (17, -1, 256), (32, -1, 256),
                                           (12, 0, 64), (16, 0, 64), (17, 0, 256), (31, 0, 256), (32, 0, 128)])
 def test_short_rows_change_mapping_at_their_row_count(n, axis, limit):
