@@ -973,14 +973,14 @@ __device__ __forceinline__ int row_solve(const float (&y)[C], float (&u)[C], flo
         };
         constexpr bool TINY = POLISH || WARM == 3;
         bool landed;
-        //      Rows that share a wave: a last step that moves the samples by more than a quarter of max|y| (root
-        //      of the mean square) comes from an x of large duals, lambda >> the data as a rule, whose
+        //      Rows that share a wave: a last step that moves the samples by more than max|y| / 16 (root of
+        //      the mean square) comes from an x of large duals, lambda >> the data as a rule, whose
         //      rounding is in its block means, so that one gets another look as well.  (Rows of 20, 0/1
         //      samples, lambda 10^U(-2, 1): relative error 2.7e-8, without it 1.9e-7.  A look behind every
-        //      last step is hardly closer, 4.4e-8 against 4.6e-8 on N(0, 1), and 9 % slower on planes of 64 x 64.)
+        //      last step is hardly closer, 4.41e-8 against 4.44e-8 on N(0, 1), and 9 % slower on planes of 64 x 64.)
         auto far = [&]() {
             const float ym = gtol * (1.0f / kGradNoise) - lam;
-            return SHARED && dec > 0.0625f * (float)n * ym * ym;
+            return SHARED && dec > (1.f / 256.f) * (float)n * ym * ym;
         };
         if constexpr (MULTI) {
             // the votes ride on the exchange of the trial's chunk edges
