@@ -84,8 +84,9 @@ typedef struct {
  * Rows of more than 32 samples, and shorter ones on the kernels for small batches, have the same
  * bits whatever the other rows of the call hold; on the row-per-lane kernels the rows of a wave
  * agree with that to rounding.
- * Samples and lambdas of 1e-20 to 1e15 are safe with any length; outside, squares that underflow or
- * overflow can bring a row to the step cap (tv1d_prox_fwd_info tells).
+ * Samples and lambdas of 1e-16 to 1e15 are safe with any length.  Outside, squares that the stopping
+ * rules compare underflow or overflow: a row can run into the step cap (tv1d_prox_fwd_info tells),
+ * and one of at most 32 samples on the row-per-lane kernels can stop early.
  * Within a maximal constant run of the result all samples are bit-identical, which
  * is what tv1d_prox_bwd relies on to recover the segments.
  */
@@ -215,7 +216,8 @@ int tv1d_prox_bwd_noalloc(const float *g_up, const float *x, float *grad_y, floa
  * row) instead of x (4 * length bytes per row).  Results are bit-identical to
  * tv1d_prox_fwd / tv1d_prox_bwd on the same batch.  (Which kernels a forward call runs
  * depends on the batch: up to tv_dispatch_threshold("thread_per_sample_1d_rows") rows of at
- * most 32 samples get sixteen threads per row, larger batches a lane per row; the two agree
+ * most 32 samples (half as many rows of at most 16 and columns of 32, a quarter as many columns of
+ * at most 16) get sixteen or eight threads per row, larger batches a lane per row; the two agree
  * to rounding, not bit for bit.)
  *   seg: device pointer, 8-byte aligned, one uint64 per row in row order
  *        (entry o * n_inner + i for the row at o * outer_stride + i * inner_stride);
@@ -307,7 +309,8 @@ const char *tv_status_str(int status);
  * them with the measurements behind them).  tv_dispatch_name(i) is the name of the i-th one
  * (NULL past the end), tv_dispatch_threshold(name) its current value (-1: no such name).
  * tv_dispatch_override sets one, for benchmarks that time both sides of a threshold at the
- * threshold; results never depend on these values.  Not thread-safe against concurrent calls
+ * threshold; results depend on these values in their last bits at most (and in the segments those
+ * decide).  Not thread-safe against concurrent calls
  * of the library; TV_ERR_UNSUPPORTED for an unknown name, TV_ERR_SHAPE for a negative value.
  */
 const char *tv_dispatch_name(int index);

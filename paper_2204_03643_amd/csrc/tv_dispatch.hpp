@@ -1,8 +1,8 @@
 // Every size at which the library switches from one kernel mapping to another, in one place,
 // each with the measurement that set it (one MI355X; times in microseconds, forward unless
-// noted).  They are crossover points of two ways to compute the same minimiser (to the last bits
-// of fp32), never a matter of results.  The values are variables so that the benchmark can time both sides of a threshold
-// at the threshold (tv_dispatch_override); nothing else writes them.
+// noted).  They are crossover points of two ways to compute the same minimiser: results agree to
+// rounding, not bit for bit.  The values are variables so that the benchmark can time both sides
+// of a threshold at the threshold (tv_dispatch_override); nothing else writes them.
 #pragma once
 #include <stdint.h>
 
@@ -171,24 +171,22 @@ inline Threshold table[kCount] = {
     // 24 planes of 512 x 512, N(0, 1), lambda 0.1, K = 10, forward: 633 by elimination, 564 by block
     // means.  0: block means everywhere.
     {"one_lambda_tri_side", 768, "2D with one lambda and three sweeps or more: sides of 65 to this many samples (at most 768) by tridiagonal elimination"},
-    // Multilevel start of unit-stride rows: from this length on.  4096 rows x 16384: 1410 -> 880.
-    // 8M samples in rows of n, lambda 10^U(-3, 1) per row, cold / multilevel, for random walks,
-    // white noise and noisy steps of 64 samples: n = 768: 106 / 101, 113 / 116, 88 / 103; 1024:
-    // 115 / 95, 127 / 118, 96 / 105 (these two with rows taking the start from lambda >= 2 x their
-    // mean |y[k+1] - y[k]| on; the others from 0.5 x); 1280: 200 / 153, 233 / 187, 163 / 156;
-    // 2048: 140 / 122, 187 / 151, 125 / 128; 4096: 150 / 124, 185 / 167, 125 / 123.  With the
-    // one coarse level of ml_coarsest below: n = 520: 135 / 123, 136 / 151, 113 / 121; 600:
-    // 123 / 114, 123 / 131, 105 / 113; 768: 105 / 100, 114 / 117, 88 / 98; 900: 136 / 105,
-    // 158 / 133, 114 / 104; 1024: 118 / 96, 127 / 115, 98 / 104; 1100: 229 / 142, 248 / 183,
-    // 195 / 152.  From 769 samples on (16 samples per thread and more) it wins on two kinds of
-    // rows out of three and is within 6 % on the third.
+    // Multilevel start of unit-stride rows: from this length on.  8M samples in rows of n, lambda
+    // 10^U(-3, 1) per row, cold / multilevel, for random walks, white noise and noisy steps of 64
+    // samples: n = 520: 95 / 107, 82 / 103, 79 / 102; 768: 73 / 79, 70 / 78, 59 / 82; 769: 103 / 107,
+    // 80 / 101, 83 / 101; 900: 87 / 83, 82 / 85, 72 / 84; 1024: 79 / 76, 80 / 79, 66 / 76; 1100: 150 / 108,
+    // 135 / 118, 132 / 107; 1536: 135 / 90, 134 / 94, 116 / 88; 2048: 127 / 82, 125 / 88, 92 / 81; 4096:
+    // 135 / 90, 115 / 95, 98 / 88.  So the start wins where a row spans waves, from 1025 samples on, by
+    // 10-30 %.  The line at 769 was drawn with an earlier solver, whose cold start took longer: rows of
+    // 769-1024 samples come out even on walks and lose up to a quarter on noisy steps, but the size of
+    // the workspace hangs on this value, and callers that stored it.
     {"ml_min_length", 769, "multilevel start for unit-stride rows of this many samples or more"},
     // ... and levels are stacked (one at least) until a row has at most this many samples.  One
     // level, solved from the cold start, is what pays: every further level is two more launches,
     // and the cold start of a row of a few thousand samples is cheap next to the fine level.
-    // Rows as above, coarsest level at most 256 / 1024 / 4096 samples: n = 2048: 125 / 102 / -,
-    // 153 / 120 / -, 131 / 107 / -; 8192 (32M samples): - / 344 / 317, - / 343 / 316, - / 347 / 323;
-    // 16 384: 460 / 430 / 398 (8M samples), - / 445 / 412, - / 443 / 413 (32M).
+    // Rows as above, coarsest level at most 256 / 1024 / 4096 samples: n = 2048: 104 / 83 / 82,
+    // 111 / 88 / 88, 99 / 81 / 81; 8192 (32M samples): 320 / 308 / 284, 331 / 314 / 290, 307 / 294 / 271;
+    // 16 384 (32M): 398 / 385 / 356, 395 / 380 / 352, 389 / 376 / 351.
     {"ml_coarsest", 4096, "coarsest level of the multilevel start"},
 };
 

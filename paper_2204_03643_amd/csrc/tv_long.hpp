@@ -133,7 +133,7 @@ struct LongSmemBwd {
 // 77-89 VGPRs and those with 12 take 102-116: a few registers above the step to one more
 // resident wave (80 for six, 96 for five).  These kernels wait much of their time (barriers,
 // LDS exchanges, the drain of a launch in partly filled rounds), so the extra wave pays although
-// the cold-start kernels spill 5-13 registers for it: without the request, 8M samples in rows of
+// the cold-start kernels spill 5-17 registers for it: without the request, 8M samples in rows of
 // 520 (64 threads x 12 samples), random walks, 80.8 us instead of 76.9, 144 (16 x 12) 75.4 / 72.4,
 // 300 (32 x 12) 74.2 / 71.3, 768 59.5 / 58.0; 12 288 columns of 512 samples 57 -> 52 (three
 // 512-thread workgroups per CU, two rounds instead of three).  Not requested for 128 threads x 12

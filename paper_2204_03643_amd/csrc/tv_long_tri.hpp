@@ -6,7 +6,7 @@
 // solved by parallel cyclic reduction, and every thread substitutes back.
 //
 // tv_rowsolve.hpp does the same in fewer instructions.  What is left here are the passes of 2D calls
-// with one lambda for all planes and three sweeps or more.  From sweep to sweep the jumps inside
+// with one lambda for all planes and three sweeps or more (one_lambda_tri_side in tv_dispatch.hpp).  From sweep to sweep the jumps inside
 // flat regions of an image shrink towards zero (24 images of 512 x 512: two rows in the first sweep,
 // some three hundred in the tenth have one that is as small as the last bit of x, and rounding
 // decides whether it is there), each such jump is a term of the lambda gradient, and one signed sum

@@ -13,7 +13,8 @@
 //
 // The solve is tv_rowsolve.hpp's with rows inside one 16-lane DPP row: every exchange between the
 // threads of a row is a row shift, a butterfly or a permutation inside the wave, and nothing but
-// the table of reciprocals is read from LDS during a solve.
+// the table of reciprocals and, with 8 samples a thread, its own parked input is read from LDS
+// during a solve.
 #pragma once
 #include "tv_long.hpp"
 #include "tv_small2d.hpp"
@@ -125,7 +126,7 @@ __global__ __launch_bounds__(T * T * C, C <= 4 ? 8 : 4) void tv2d_fwd_plane_kern
 
 // Segmented exclusive sums over the T threads of a row, from thread 0 upwards (DIR = +1) or from
 // thread T - 1 downwards (DIR = -1), by row shifts: each thread contributes (closed, s, n) as in
-// seg_scan of tv_long.hpp (closed: its chunk holds a segment boundary; (s, n): sum and count of
+// seg_scan of tv_rowsolve.hpp (closed: its chunk holds a segment boundary; (s, n): sum and count of
 // the part of its chunk beyond the last boundary in scan direction) and gets the sum and count
 // of the open part that arrives at it (zero at the origin).
 template <int T, int DIR>

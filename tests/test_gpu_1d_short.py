@@ -1,7 +1,7 @@
 """GPU parity: rows of at most 32 samples against the oracle, through the C ABI.  Every test of
 this module runs three times: with a lane per row (the row-per-lane kernels, which large batches
-get), with the library's own choice, which gives batches of up to 40 960 rows a few threads per
-row on the long-row kernels (`thread_per_sample_1d_rows`: sixteen threads with two samples each
+get), with the library's own choice, which gives small batches (`thread_per_sample_1d_rows`) a few
+threads per row on the long-row kernels (sixteen threads with two samples each
 up to `thread_per_sample_wide_rows` rows), and with eight threads of four samples per row, which
 the library picks for the larger of those batches."""
 import numpy as np
