@@ -60,26 +60,15 @@ inline Threshold table[kCount] = {
     // order whenever it is handed the workspace; the layer (layer.py) would hand it over from
     // this many rows on, and the value means "never".
     {"order_min_rows", (int64_t)1 << 40, "the layer passes the slot-order workspace from this many rows on"},
-    // 2D, planes of exactly 32 x 32: the one-launch forward kernel holds two waves per SIMD (17 KB
-    // of LDS per wave) where the pass-by-pass kernels hold three, but pays no launches and no
-    // memory round trips between the passes, which weighs more the more sweeps there are.
-    // One launch against pass by pass, forward + backward, feature-map-like data:
-    //   K = 1:  4096 planes  69 /  76,  4352:  91 /  82,  6144: 115 /  95, 16 384: 235 / 188;
-    //   K = 2:  4096 planes 106 / 144, 16 384: 334 / 346, 24 576: 493 / 482, 32 768: 643 / 612;
-    //   K = 4:  4096 planes 183 / 290, 16 384: 580 / 660, 65 536: 2125 / 2240
-    //   (with three sweeps or more the one launch wins or is even at every count: the value means
-    //   "always").
-    // (The one launch holds 4096 planes at once: with a single sweep it loses over its second
-    // round of waves what the saved launches gained.)
-    {"fused32_full_planes", 4096, "2D planes of 32 x 32, one sweep: all passes in one launch up to this many planes"},
-    {"fused32_full_planes_k2", 20480, "... two sweeps"},
+    // 2D, planes of 17-32 samples a side: the one-launch forward with two lanes a row (tv_pair.hpp, four
+    // waves per SIMD) against pass by pass.  N(0, 1), lambda 10^U(-1.3, 0), forward:
+    //   32 x 32, K = 1: 4096 planes 33 / 53,  8192: 59 / 71, 65 536: 393 / 429;  K = 2: 65 536 planes 696 / 864;
+    //   28 x 28, K = 1: 16 384 planes 98 / 111, 65 536: 348 / 392;  20 x 20, K = 1: 16 384 planes 61 / 76.
+    // The one launch wins at every count: the values mean "always".
+    {"fused32_full_planes", (int64_t)1 << 40, "2D planes of 32 x 32, one sweep: all passes in one launch up to this many planes"},
+    {"fused32_full_planes_k2", (int64_t)1 << 40, "... two sweeps"},
     {"fused32_full_planes_k3", (int64_t)1 << 40, "... three sweeps or more"},
-    // 2D, planes of 17-32 samples a side that do not fill 32 x 32, single sweep (with two sweeps
-    // or more the one launch always wins: 28 x 28, 32 768 planes, K = 4: 1.46 ms against 1.94).
-    // 28 x 28, K = 1, one launch against pass by pass, forward + backward: 4096 planes 75 / 94,
-    // 4352: 95 / 97, 6144: 116 / 114, 8192: 127 / 147, 10 240: 0.98 of it, 12 288: 1.00 and 0.97 (two
-    // kinds of data), 16 384: 223 / 220, 32 768: 1.00 and 1.01.
-    {"fused32_ragged_planes", 12288, "2D ragged planes padded to 32 x 32, one sweep: one launch up to this many planes"},
+    {"fused32_ragged_planes", (int64_t)1 << 40, "2D planes of 17-32 a side other than 32 x 32, one sweep: one launch up to this many planes"},
     // 2D, planes of 9-16 samples a side, single sweep, forward + backward, one launch against pass
     // by pass: 16 x 16, 24 576 planes 67 / 73, 49 152: 101 / 107, 98 304: 178 / 180, 262 144: 445 / 500;
     // 14 x 14, 49 152 planes 111 / 118, 262 144: 507 / 579 (the value means "always").
@@ -91,18 +80,18 @@ inline Threshold table[kCount] = {
     {"fused16_dense_planes", 12288, "2D planes of 9-16 a side in one launch: the four-waves-per-SIMD variant from this many planes on"},
     // 2D, small batches: one plane per workgroup of 512 threads, resident in LDS for all passes,
     // 16 threads x 2 samples per row (sides of 17-32) or 8 x 8 (sides of 33-64); tv_plane2d.hpp.
-    // A lone row-per-lane wave per SIMD issues an instruction every 9 cycles, and pass by pass a
-    // small batch pays a launch and a trip through memory per pass; this mapping has 8x the waves,
-    // short chains and one launch.  Its time is set by the slowest row of each pass (a barrier
-    // between passes), so it stops paying once the other kernels fill the chip.  Forward, this
-    // kernel / the library's choice without it, feature-map-like data:
-    //   32 x 32, K = 1: 1024 planes 31 /  43,  1536:  41 /  43,  2048:  49 /  44;
-    //            K = 4: 1024 planes 72 / 132,  1536:  96 / 128,  2048: 118 / 119 (N(0, 1) data: 0.73 of
-    //                   it), 2560: 142 / 130 (0.82);
-    //   28 x 30, K = 1: 1536 planes 39 /  48,  2048: 45 /  47, 2560: 54 / 50;  K = 3: 2048 planes 91 / 105;
-    //   20 x 32, K = 4: 2048 planes 104 / 163.
+    // A lone wave per SIMD of a kernel with few lanes a row issues an instruction every 9 cycles, and
+    // pass by pass a small batch pays a launch and a trip through memory per pass; this mapping has 4x the
+    // waves of two lanes a row, short chains and one launch.  Its time is set by the slowest row of each
+    // pass (a barrier between passes), so it stops paying once the other kernels fill the chip.  Sides of
+    // 17-32, this kernel / two lanes a row, N(0, 1), lambda 0.3 and 10^U(-1.3, 0), forward:
+    //   32 x 32, K = 1: 512 planes 13 / 16, 16 / 20,   768: 16 / 16, 20 / 21,  1024: 19 / 16, 25 / 21;
+    //            K = 4: 768 planes 42 / 48, 52 / 58,  1024: 51 / 47, 63 / 57;
+    //   28 x 28, K = 1: 512 planes 12 / 14, 15 / 19,   768: 16 / 15, 20 / 19;
+    //            K = 4: 768 planes 41 / 41, 49 / 55,  1024: 49 / 41, 59 / 55;
+    //   20 x 30, K = 4: 1024 planes 46 / 51, 54 / 60, 1280: 57 / 58, 68 / 70.
     // (With two sweeps or more the library takes a third more planes than the value says.)
-    {"plane_per_group_planes", 1536, "2D planes of 17-32 a side: one launch, a plane per workgroup, up to this many planes"},
+    {"plane_per_group_planes", 768, "2D planes of 17-32 a side: one launch, a plane per workgroup, up to this many planes"},
     //   64 x 64, K = 1:  512 planes  47 /  50,  768:  67 /  60, 1024:  78 /  73, 1536: 109 / 94;
     //   48 x 48, K = 1:  512 planes  35 /  38,  768:  55 /  54, 1024:  64 /  57.
     {"plane_per_group64_planes", 512, "2D planes of 33-64 a side, one sweep: one launch, a plane per workgroup, up to this many planes"},

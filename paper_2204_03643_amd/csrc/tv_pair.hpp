@@ -1,0 +1,584 @@
+// Two neighbouring lanes per row, one from each end: projected Newton on the dual (paper Eq. 3-4) of
+// a row of at most 2 C samples, and the one-launch 2D forward built on it (planes of 17-32 a side).
+//
+// A row-per-lane solve (RowSolver, tv_short.hpp) keeps four arrays of a row's length in registers and
+// walks chains of that length.  Here the row is cut in the middle: the left lane holds samples 0 .. C-1,
+// the right lane samples 2C-1 .. C, outermost first.  Seen from its own end each half is the same
+// problem (a row reversed has the reversed x and the reversed, negated dual), so both lanes run the
+// same instructions on C registers a array and chains of C steps, and meet in the dual between the
+// halves, which both hold, with opposite signs, and form from symmetric expressions, so that the
+// copies stay exact mirrors of one another.  Half the registers make twice the waves, each wave is
+// done when the slowest of 32 rows is (not of 64), and rounding errors run through chains half as long.
+#pragma once
+#include "tv_small2d.hpp"
+
+namespace tvk {
+
+// v of the other lane of the pair (rides on the instruction that reads it)
+__device__ __forceinline__ float pair_other(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));     // quad_perm [1,0,3,2]
+}
+__device__ __forceinline__ uint32_t pair_other(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true);
+}
+// p or the other lane's p (in scalar registers)
+__device__ __forceinline__ bool pair_either(bool p)
+{
+    const uint64_t even = 0x5555555555555555ull;
+    const uint64_t m = __builtin_amdgcn_ballot_w64(p);
+    return __builtin_amdgcn_inverse_ballot_w64(m | ((m >> 1) & even) | ((m & even) << 1));
+}
+
+// Local sample i of a lane is sample i of its row (left lane) or 2C-1-i (right lane); local dual i lies
+// behind local sample i, towards the middle, and dual C-1 is the shared one.  Rows of fewer than 2C
+// samples: those past the end are 0, the dual behind the last one (`cut`, a local index, none if negative)
+// is held at 0, and bit i of `live` says that local dual i lies inside the row.  All that concerns local
+// indices below PADS only: PADS = 0, rows of exactly 2C samples; PADS = C, any.
+template <int C, int PADS>
+struct PairSolver {
+    static constexpr bool FULL = PADS == 0;
+    float X[C];         // x(u) for the current dual
+    float u[C];         // the dual
+    float D[C];         // g, then gamma * w, then the Newton direction
+    float G[C];         // pivots gamma (0 exactly at bound duals; G[C-1]: 0 or 1), then the previous dual
+    const float *yl, *gtab;       // the parked input (sample i at yl[64 i]), gtab[j] = j / (j + 1)
+    float lam, fcur, alpha_try, gtol;
+    uint32_t live;
+    int cut, steps, flags, nfail;
+    bool active, prev_unclipped;
+
+    // (inside: `live`, made opaque in every loop: as loop invariants the C boxes would be kept in registers)
+    __device__ __forceinline__ uint32_t inside() const
+    {
+        uint32_t l = live;
+        if (!FULL) asm volatile("" : "+v"(l));
+        return l;
+    }
+    __device__ __forceinline__ float box(uint32_t inside, int k) const
+    {
+        if (k >= PADS) return lam;
+        return __uint_as_float(__float_as_uint(lam) & (uint32_t)__builtin_amdgcn_sbfe((int)inside, k, 1));
+    }
+    __device__ __forceinline__ float yk(int k) const { return yl[k * 64]; }
+    static __device__ __forceinline__ void reread() { asm volatile("" ::: "memory"); }
+
+    // Two Gauss-Seidel sweeps on the dual, u_k <- clip((u_{k-1} + u_{k+1} + y_{k+1} - y_k) / 2): from both ends
+    // to the middle, and back.  D holds half the differences of y.
+    __device__ __forceinline__ void sweep_in_and_out()
+    {
+        uint32_t in = inside();
+        float up = 0.f;
+#pragma unroll
+        for (int k = 0; k < C - 1; ++k) {
+            const float l = box(in, k);
+            up = __builtin_amdgcn_fmed3f(fmaf(0.5f, up + u[k + 1], D[k]), -l, l);
+            u[k] = up;
+        }
+        float un;
+        {
+            const float l = box(in, C - 1);
+            un = __builtin_amdgcn_fmed3f(fmaf(0.5f, up - pair_other(up), D[C - 1]), -l, l);
+            u[C - 1] = un;
+        }
+        in = inside();
+#pragma unroll
+        for (int k = C - 2; k >= 0; --k) {
+            const float l = box(in, k);
+            const float ul = k > 0 ? u[k - 1] : 0.f;
+            un = __builtin_amdgcn_fmed3f(fmaf(0.5f, ul + un, D[k]), -l, l);
+            u[k] = un;
+        }
+    }
+
+    // x(u) and the dual objective of the starting dual
+    __device__ __forceinline__ void primal_of_start(const float (&y)[C])
+    {
+        float acc = 0.f, prev = 0.f;
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const float xc = y[k] + u[k] - prev;
+            acc = fmaf(xc, xc, acc);
+            X[k] = xc; prev = u[k];
+        }
+        fcur = 0.5f * (acc + pair_other(acc));
+    }
+    __device__ __forceinline__ void set_gtol(const float (&y)[C])
+    {
+        float ymax = 0.f;
+#pragma unroll
+        for (int k = 0; k < C; ++k) ymax = fmaxf(ymax, fabsf(y[k]));
+        ymax = fmaxf(ymax, pair_other(ymax));
+        // (lambda = 0: every dual sits on both of its bounds, no gradient may count as pointing inwards)
+        gtol = lam > 0.f ? kGradNoise * (ymax + lam) : __builtin_inff();
+    }
+
+    // Cold start: the two candidates and the choice of RowSolver::start, then two Gauss-Seidel sweeps.
+    // have: bit i = local sample i exists.
+    __device__ __forceinline__ void start(const float (&y)[C], float inv_n, uint32_t have)
+    {
+        float sum = 0.f;
+#pragma unroll
+        for (int k = 0; k < C; ++k) sum += y[k];
+        set_gtol(y);
+        const float ybar = (sum + pair_other(sum)) * inv_n;
+        float run = 0.f, rmax = 0.f;
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const float m = k >= PADS ? ybar
+                                 : __uint_as_float(__float_as_uint(ybar) & (uint32_t)__builtin_amdgcn_sbfe((int)have, k, 1));
+            run += m - y[k];
+            X[k] = run;
+            rmax = fmaxf(rmax, fabsf(run));
+        }
+        X[C - 1] = 0.5f * (run - pair_other(run));
+        rmax = fmaxf(rmax, pair_other(rmax));
+        const bool free_row = lam >= 0.25f * rmax;
+        const uint32_t in = inside();
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const float l = box(in, k);
+            const float yn = k + 1 < C ? y[k + 1] : pair_other(y[C - 1]);
+            const float hd = 0.5f * (yn - y[k]);
+            u[k] = __builtin_amdgcn_fmed3f(free_row ? X[k] : hd * 1e30f, -l, l);
+            D[k] = hd;
+        }
+        sweep_in_and_out();
+        primal_of_start(y);
+    }
+
+    // Warm start: u holds the negated running sums, from the lane's own end, of the correction term
+    // that the input carries (see RowSolver::start_warm).
+    __device__ __forceinline__ void start_warm(const float (&y)[C])
+    {
+        set_gtol(y);
+        u[C - 1] = 0.5f * (u[C - 1] - pair_other(u[C - 1]));
+        const uint32_t in = inside();
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const float l = box(in, k);
+            u[k] = __builtin_amdgcn_fmed3f(u[k] * kWarmSnap, -l, l);
+        }
+        primal_of_start(y);
+    }
+
+    // Gradient, bound set, elimination and optimality test; true when every row of the wave has stopped.
+    __device__ __forceinline__ bool look(int it, bool &vio, float &dec)
+    {
+        vio = false;
+        uint32_t pos4 = 0, mid4 = 0;                // 4 * position inside the free run
+        {
+            int c = cut;
+            if (!FULL) asm volatile("" : "+v"(c));
+#pragma unroll
+            for (int k = 0; k < C; ++k) {
+                const float g = X[k] - (k + 1 < C ? X[k + 1] : pair_other(X[C - 1]));
+                const float s = copysignf(lam, g);
+                bool bnd = (u[k] == -s) || (k < PADS && k == c);
+                // (the middle: +0 has the same sign in both lanes, where -s would say different things)
+                if (k == C - 1) bnd |= g == 0.f && fabsf(u[k]) == lam;
+                vio |= (u[k] == s) && (fabsf(g) > gtol);
+                D[k] = g;
+                if (k < C - 1) {
+                    pos4 = bnd ? 0u : pos4 + 4u;
+                    G[k] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(gtab) + pos4);
+                    mid4 = pos4;
+                } else {
+                    G[k] = bnd ? 0.f : 1.f;
+                }
+            }
+        }
+        vio = pair_either(vio);
+        // (rows that landed on the minimiser of their free subspace need no elimination to see that they are done)
+        if (active && !vio && prev_unclipped) { active = false; flags = kInfoConverged; }
+        if (!__any(active)) { dec = 0.f; return true; }
+        // from both ends: w_k = g_k + gamma_{k-1} w_{k-1}, kept as t_k = gamma_k w_k
+        float t = 0.f;
+        dec = 0.f;
+#pragma unroll
+        for (int k = 0; k < C - 1; ++k) {
+            const float w = D[k] + t;
+            t = G[k] * w;
+            dec = fmaf(t, w, dec);
+            D[k] = t;
+        }
+        asm volatile("" : "+v"(dec));
+        // the middle: the runs of a - 1 and b - 1 free duals that end on either side of it leave the pivot
+        // 2 - (a - 1) / a - (b - 1) / b = (a + b) / (a b)
+        {
+            const float a = fmaf(0.25f, (float)mid4, 1.f), b = pair_other(a);
+            const float w = D[C - 1] + (t - pair_other(t));
+            const float d = G[C - 1] * w * (a * b) * __builtin_amdgcn_rcpf(a + b);
+            dec = fmaf(w, d, dec + pair_other(dec));
+            D[C - 1] = d;
+        }
+        if (active && !vio && dec <= fmaxf(kDecNoise * fcur, gtol * gtol)) {
+            active = false; flags = kInfoConverged;
+        }
+        if (active && it >= kMaxNewtonSteps) { active = false; flags = kInfoCapped; }
+        return !__any(active);
+    }
+
+    // Direction, projected step, line search (RowSolver::iterate has the reasons for every rule).
+    __device__ __forceinline__ void step(bool vio, float dec)
+    {
+        steps += active ? 1 : 0;
+        reread();
+#pragma unroll
+        for (int k = 0; k < C; ++k) X[k] = yk(k);
+        float dn = D[C - 1];
+#pragma unroll
+        for (int k = C - 2; k >= 0; --k) {
+            dn = fmaf(G[k], dn, D[k]);
+            D[k] = dn;
+        }
+        const float alpha = active ? alpha_try : 0.f;
+        float tmax = 0.f;
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const float uo = u[k];
+            const float t = fmaf(-alpha, D[k], uo);
+            tmax = fmaxf(tmax, fabsf(t));
+            G[k] = uo;
+            u[k] = __builtin_amdgcn_fmed3f(t, -lam, lam);
+        }
+        const bool clipped = fmaxf(tmax, pair_other(tmax)) > lam;
+        const bool polish = clipped && active;
+        if (__any(polish)) {
+            float half = 0.5f;
+            asm volatile("" : "+v"(half));
+#pragma unroll
+            for (int k = 0; k < C; ++k) D[k] = half * ((k + 1 < C ? X[k + 1] : pair_other(X[C - 1])) - X[k]);
+            if (polish) sweep_in_and_out();         // (both lanes of a row or neither)
+        }
+        float acc = 0.f, prev = 0.f;
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const float c = u[k];
+            const float xc = X[k] + c - prev;
+            acc = fmaf(xc, xc, acc);
+            X[k] = xc; prev = c;
+        }
+        const float fc = 0.5f * (acc + pair_other(acc));
+        bool changed = true;
+        if (__any(active && fc == fcur)) {          // (a step that leaves the dual bit-identical also leaves f so)
+            changed = false;
+#pragma unroll
+            for (int k = 0; k < C; ++k) changed |= (u[k] != G[k]);
+            changed = pair_either(changed);
+        }
+        if (active && fc != fc) { active = false; flags = kInfoStalled | kInfoPlain; }      // NaN in the row
+        const bool ok = !active || (alpha == 1.f && !clipped) ||
+                        (fc <= fcur - kArmijoSigma * alpha * dec + kArmijoSlackEps * fabsf(fcur));
+        if (__any(!ok)) {
+            reread();
+            float pv = 0.f;
+#pragma unroll
+            for (int k = 0; k < C; ++k) {
+                const float c = ok ? u[k] : G[k];
+                u[k] = c;
+                X[k] = yk(k) + c - pv;
+                pv = c;
+            }
+            if (!ok) {
+                const float den = 2.f * (fc - fcur + dec * alpha);
+                const float an = den > 0.f ? dec * alpha * alpha / den : 0.5f * alpha;
+                alpha_try = fminf(fmaxf(an, 0.1f * alpha), 0.5f * alpha);
+                prev_unclipped = false;
+                if (++nfail > kMaxBacktracks) { active = false; flags = kInfoStalled | kInfoPlain; }
+            }
+        }
+        if (ok && active) {
+            fcur = fc;
+            prev_unclipped = (alpha == 1.f) && !clipped;
+            alpha_try = 1.f;
+            nfail = 0;
+            if (!changed) {
+                active = false;
+                flags = kInfoStalled | ((alpha == 1.f && (!vio || polish)) ? 0 : kInfoPlain);
+            }
+        }
+    }
+    __device__ __forceinline__ void solve(bool valid)
+    {
+        alpha_try = 1.f; steps = 0; flags = 0; nfail = 0;
+        active = valid; prev_unclipped = false;
+        bool vio;
+        float dec;
+        bool done = look(0, vio, dec);
+        for (int it = 0; !done; ++it) {
+            step(vio, dec);
+            done = look(it + 1, vio, dec);
+        }
+    }
+
+    // Primal recovery: between two bound duals every sample takes the value of the block's sample next to
+    // the middle of the row, the block around the middle the mean of its two.
+    __device__ __forceinline__ void recover(float (&xs)[C])
+    {
+        float val = G[C - 1] == 0.f ? X[C - 1] : 0.5f * (X[C - 1] + pair_other(X[C - 1]));
+        xs[C - 1] = val;
+#pragma unroll
+        for (int k = C - 2; k >= 0; --k) {
+            val = (G[k] == 0.f) ? X[k] : val;
+            xs[k] = val;
+        }
+        const bool plain = (flags & (kInfoCapped | kInfoPlain)) != 0;
+        if (__any(plain)) {
+#pragma unroll
+            for (int k = 0; k < C; ++k) xs[k] = plain ? X[k] : xs[k];
+        }
+    }
+};
+
+// Segment code (FwdParams::seg) of a pair's row of n samples, in both lanes; right: this is the right lane.
+template <int C, bool FULL>
+__device__ __forceinline__ uint2 pair_segment_code(const float (&xs)[C], int n, bool right)
+{
+    // bit i: local dual i (the middle one counts in both lanes); rises: x increases behind that dual, seen from the lane's end
+    uint32_t jm = 0, rises = 0;
+    {
+        const float d = xs[C - 1] - pair_other(xs[C - 1]);
+        rises = __float_as_uint(d) >> 31;
+        jm = __float_as_uint(0.0f - fabsf(d)) >> 31;
+    }
+#pragma unroll
+    for (int k = C - 2; k >= 0; --k) {
+        const float d = xs[k] - xs[k + 1];
+        rises = __builtin_amdgcn_alignbit(rises, __float_as_uint(d), 31);
+        jm = __builtin_amdgcn_alignbit(jm, __float_as_uint(0.0f - fabsf(d)), 31);
+    }
+    // local dual i of the right lane is dual 2C-2-i of the row, and there the row rises where the lane falls
+    const uint32_t turned_jm = __builtin_bitreverse32(jm) >> (33 - 2 * C);
+    const uint32_t turned_up = __builtin_bitreverse32(jm & ~rises) >> (33 - 2 * C);
+    jm = right ? turned_jm : jm;
+    rises = right ? turned_up : rises;
+    jm |= pair_other(jm);
+    rises |= pair_other(rises);
+    if (!FULL) {
+        const uint32_t in = n > 1 ? (0xffffffffu >> (33 - n)) : 0u;
+        jm &= in; rises &= in;
+    }
+    return make_uint2(jm, rises);
+}
+
+// A wave's tile of 32 rows: samples 0 .. C-1 of a row in order, the others from the row's end, 16 places
+// on, so that either lane of a pair finds its half at offsets known at compile time.  With pitch 33 the
+// 16 rows that half a wave works on cover 16 banks, and their other halves the other 16.
+constexpr int kPairPitch = 33;
+template <int C>
+__device__ __forceinline__ int pair_place(int k) { return k < C ? k : 15 + 2 * C - k; }
+
+// Which of a lane's samples exist in a row of n (bit i: local sample i), the local index of the dual
+// behind the row's last sample, and the duals inside the row (PairSolver::live).
+template <int C>
+__device__ __forceinline__ uint32_t pair_samples(int n, bool right)
+{
+    const int pads = 2 * C - n;                 // (the right lane's from its end, then the left lane's from the middle)
+    return right ? ~((1u << (pads < C ? pads : C)) - 1u) : (n < C ? (1u << n) - 1u : ~0u);
+}
+template <int C>
+__device__ __forceinline__ int pair_cut(int n, bool right) { return right ? 2 * C - 1 - n : n - 1; }
+__device__ __forceinline__ uint32_t pair_live(int cut, bool right)
+{
+    if (right) return cut < 0 ? ~0u : ~0u << (cut + 1);         // (cut < 31)
+    return (1u << cut) - 1u;
+}
+template <int PADS>
+__device__ __forceinline__ float pair_masked(float v, uint32_t have, int k)
+{
+    return k >= PADS ? v : __uint_as_float(__float_as_uint(v) & (uint32_t)__builtin_amdgcn_sbfe((int)have, k, 1));
+}
+
+// ---------------------------------------------------------------------------------
+// Forward: K sweeps of paper Alg. 1 in one launch, a plane of at most 2C x 2C per wave.
+//
+// A row pass gives a pair of lanes a row of the plane, a column pass a column.  The plane changes hands
+// between passes through one LDS tile, whose rows and columns both lie as pair_place has them.  As in
+// tv2d_fwd_small_kernel the tile also parks the solver's input, and the correction term that is not in
+// use lives in a lane-private LDS column.
+// ---------------------------------------------------------------------------------
+template <int C, int PADS, bool IO16 = false>
+__global__ __launch_bounds__(64, 4) void tv2d_fwd_pair_kernel(Small2dFwdParams p)
+{
+    constexpr bool FULL = PADS == 0;
+    static_assert(C <= 16 && C >= 2, "planes of at most 32 x 32");
+    constexpr int P = kPairPitch;
+    __shared__ float T1[32 * P], T2[64 * C], gtab[34], rtab[34];
+    static_assert(64 * C <= 32 * P, "the parked input fits the tile");
+    const int lane = threadIdx.x;
+    fill_tables<32>(gtab, rtab);
+    const int H = FULL ? 2 * C : p.H, W = FULL ? 2 * C : p.W, HW = H * W;
+    const int64_t plane = blockIdx.x;
+    const float lam = fmaxf(p.lam[plane % p.lam_count], 0.f);
+
+    auto place = [](int k) { return pair_place<C>(k); };
+    const int at = lane >> 1;                       // the pair's row or column, by place
+    const bool right = (lane & 1) != 0;
+    const int idx = at < 16 ? at : 15 + 2 * C - at;
+    const bool in_half = (at & 15) < C;
+    float *by_row = T1 + at * P + (right ? 16 : 0);             // step 1
+    float *by_col = T1 + (right ? 16 : 0) * P + at;             // step P
+    float *park = T1 + lane, *mine = T2 + lane;                 // step 64
+
+    // memory <-> tile: sample e = lane, lane + 64, ... of the plane
+    auto each_sample = [&](auto &&f) {
+        int r = lane / W, c = lane - r * W;
+        const int dq = 64 / W, dr = 64 - dq * W;
+        for (int e = lane; e < HW; e += 64) {
+            f(e, T1 + place(r) * P + place(c));
+            r += dq; c += dr;
+            if (c >= W) { c -= W; r += 1; }
+        }
+    };
+    auto plane_in = [&](auto &&load) {
+        constexpr int N = (4 * C * C + 63) / 64;
+        float q[N];                                 // every load is issued before the first is waited for
+#pragma unroll
+        for (int i = 0; i < N; ++i) q[i] = i * 64 + lane < HW ? load(i * 64 + lane) : 0.f;
+        int r = lane / W, c = lane - r * W;
+        const int dq = 64 / W, dr = 64 - dq * W;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if (i * 64 + lane < HW) T1[place(r) * P + place(c)] = q[i];
+            r += dq; c += dr;
+            if (c >= W) { c -= W; r += 1; }
+        }
+    };
+    // four samples of a row from column c on, c a multiple of 4, in planes of 32 x 32
+    auto four = [&](int e) { return T1 + place(e >> 5) * P + place(e & 31); };
+    constexpr bool QUADS = FULL && C == 16;
+    if constexpr (IO16) {
+        const uint16_t *src = reinterpret_cast<const uint16_t *>(p.y) + plane * HW;
+        plane_in([&](int e) { return bf16_bits_to_f32(src[e]); });
+    } else {
+        const float *src = p.y + plane * HW;
+        if (QUADS && ((uintptr_t)src % 16) == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = (i * 64 + lane) * 4;
+                const float4 q = load16(src + e, p.stream != 0);
+                float *d = four(e);
+                const int s = (e & 31) < 16 ? 1 : -1;
+                d[0] = q.x; d[s] = q.y; d[2 * s] = q.z; d[3 * s] = q.w;
+            }
+        } else {
+            plane_in([&](int e) { return src[e]; });
+        }
+    }
+    auto put_plane = [&](float *dst) {
+        if (QUADS && ((uintptr_t)dst % 16) == 0) {
+            int own = lane;
+            asm volatile("" : "+v"(own));           // (addresses formed here, not kept through the solves)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = (i * 64 + own) * 4;
+                const float *d = four(e);
+                const int s = (e & 31) < 16 ? 1 : -1;
+                store16(dst + e, make_float4(d[0], d[s], d[2 * s], d[3 * s]), p.stream != 0);
+            }
+        } else {
+            each_sample([&](int e, const float *d) { dst[e] = *d; });
+        }
+    };
+    wave_lds_sync();
+
+    auto samples = [&](int n) -> uint32_t { return FULL ? ~0u : pair_samples<C>(n, right); };
+    auto masked = [](float v, uint32_t have, int k) { return pair_masked<PADS>(v, have, k); };
+
+    float v[C], u0[C];                              // a pass's input, and the dual it starts from
+    bool valid = in_half && (FULL || idx < H);      // first pass: rows, of W samples
+    int n = W;
+    uint32_t have = samples(n);
+#pragma unroll
+    for (int k = 0; k < C; ++k) { v[k] = masked(by_row[k], have, k); u0[k] = 0.f; }
+
+    const int n_pass = 2 * p.sweeps;
+    for (int i = 0; i < n_pass; ++i) {
+        const bool col = (i & 1) != 0;
+        wave_lds_sync();                            // every lane has taken its input out of the tile
+#pragma unroll
+        for (int k = 0; k < C; ++k) park[k * 64] = v[k];
+        wave_lds_sync();
+
+        PairSolver<C, PADS> sv;
+        float xs[C];
+        sv.yl = park; sv.gtab = gtab; sv.lam = lam;
+        if constexpr (!FULL) {
+            sv.cut = pair_cut<C>(n, right);
+            sv.live = pair_live(sv.cut, right);
+        }
+        if (i < 2) sv.start(v, rtab[n], have);
+        else {
+#pragma unroll
+            for (int k = 0; k < C; ++k) sv.u[k] = u0[k];
+            sv.start_warm(v);
+        }
+        sv.solve(valid);
+        sv.recover(xs);
+
+        {
+            const uint2 code = pair_segment_code<C, FULL>(xs, n, right);
+            if (valid) {
+                uint32_t *to = reinterpret_cast<uint32_t *>(p.codes + (size_t)i * p.code_stride + (size_t)plane * (col ? W : H) + idx);
+                to[right ? 1 : 0] = right ? code.y : code.x;
+            }
+        }
+
+        const bool keep = i + 2 < n_pass;
+        float corr[C];
+#pragma unroll
+        for (int k = 0; k < C; ++k) corr[k] = park[k * 64] - xs[k];
+        wave_lds_sync();
+        if (col) {
+#pragma unroll
+            for (int k = 0; k < C; ++k) by_col[k * P] = xs[k];
+        } else {
+#pragma unroll
+            for (int k = 0; k < C; ++k) by_row[k] = xs[k];
+        }
+        wave_lds_sync();
+        if (p.keep_passes) put_plane(p.saved + (size_t)i * p.saved_stride + plane * HW);
+        // input of the next pass: this output seen the other way plus that direction's correction
+        // term, whose negated running sum is the dual to start from
+        valid = in_half && (FULL || idx < (col ? H : W));
+        n = col ? W : H;
+        have = samples(n);
+        float t[C];
+        if (col) {
+#pragma unroll
+            for (int k = 0; k < C; ++k) t[k] = masked(by_row[k], have, k);
+        } else {
+#pragma unroll
+            for (int k = 0; k < C; ++k) t[k] = masked(by_col[k * P], have, k);
+        }
+        if (i >= 1) {
+            float run = 0.f;
+#pragma unroll
+            for (int k = 0; k < C; ++k) {
+                const float c = mine[k * 64];
+                t[k] += c;
+                run -= c;
+                u0[k] = run;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < C; ++k) u0[k] = 0.f;
+        }
+        if (keep) {
+#pragma unroll
+            for (int k = 0; k < C; ++k) mine[k * 64] = corr[k];
+        }
+#pragma unroll
+        for (int k = 0; k < C; ++k) v[k] = t[k];
+    }
+    if constexpr (IO16) {
+        uint16_t *dst = reinterpret_cast<uint16_t *>(p.x) + plane * HW;
+        each_sample([&](int e, const float *d) { dst[e] = f32_to_bf16_bits(*d); });
+    } else {
+        put_plane(p.x + plane * HW);
+    }
+}
+
+}  // namespace tvk

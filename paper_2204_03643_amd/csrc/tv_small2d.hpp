@@ -318,9 +318,10 @@ __global__ __launch_bounds__(64) void tv2d_bwd_small_kernel(Small2dBwdParams p)
 }
 
 // ---------------------------------------------------------------------------------
-// Forward: K sweeps of paper Alg. 1 on planes of at most 32 x 32 in one launch.
+// Forward: K sweeps of paper Alg. 1 on planes of at most 16 x 16 in one launch.  (17-32 a side: two lanes
+// a row, tv_pair.hpp.)
 //
-// A wave owns its planes (two, four or eight, as in the reverse sweep) for the whole call.  A row pass gives each lane a row of its plane, a
+// A wave owns its planes (four or eight, as in the reverse sweep) for the whole call.  A row pass gives each lane a row of its plane, a
 // column pass a column; either way the lane solves its 1D problem exactly as the short-row
 // kernel does (same RowSolver, row in registers).  Between passes the plane changes hands
 // through one LDS tile of odd pitch (side + 1), which both views read and write without bank conflicts.
@@ -347,7 +348,7 @@ struct Small2dFwdParams {
     uint32_t     stream;
 };
 
-// S, FULL: as in the reverse sweep (a wave holds 64 / S planes), S <= 32.
+// S, FULL: as in the reverse sweep (a wave holds 64 / S planes), S <= 16.
 // IO16: y and x are bf16 in memory; the saved pass outputs stay fp32.
 // (Planes of 33-64 samples a side: tv_plane2d.hpp.  A row of 64 samples per lane would take four
 // arrays of 64 registers, the whole register file of a SIMD lane, for one wave per SIMD.)
@@ -358,12 +359,11 @@ struct Small2dFwdParams {
 // What set these counts: every pass solves inside the loop over passes, and whatever the loop or the
 // solver's own loop could leave early kept arrays alive through the half it skips (see
 // RowSolver::solve, and below).  Without that, and with predicates that are formed where they are
-// used, planes of 28 x 28 (5355, K = 4) went from 259 to 186 us (215 spilled scalar registers), 16 x 16
-// (16 384, K = 4) from 95 to 71, 14 x 14 (65 536, K = 2) from 258 to 147, 32 x 32 (16 384, K = 4) from 373 to 357.
+// used, 16 x 16 (16 384, K = 4) went from 95 to 71 us, 14 x 14 (65 536, K = 2) from 258 to 147.
 template <int S, bool FULL, bool IO16 = false, bool DENSE = false>
 __global__ __launch_bounds__(64, (S == 8 ? 6 : ((S == 16 && DENSE) ? 4 : 2))) void tv2d_fwd_small_kernel(Small2dFwdParams p)
 {
-    static_assert(S <= 32, "a row or column per lane: planes of at most 32 x 32");
+    static_assert(S <= 16, "a row or column per lane: planes of at most 16 x 16");
     constexpr int P = S + 1;
     constexpr int PP = 64 / S;
     __shared__ float T1[64 * P], T2[64 * S], gtab[S + 2], rtab[S + 2];

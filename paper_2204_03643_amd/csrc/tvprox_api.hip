@@ -12,6 +12,7 @@
 #include "tv_dispatch.hpp"
 #include "tv_long.hpp"
 #include "tv_long_tri.hpp"
+#include "tv_pair.hpp"
 #include "tv_small2d.hpp"
 #include "tv_plane2d.hpp"
 #include "tv_short.hpp"
@@ -227,6 +228,24 @@ int launch_bwd_short(const BwdParams &p, bool packed_ok, hipStream_t s, bool pla
                      : launch_bwd_short<NMAX, false, true>(p, packed_ok, s, plane_ok, ragged_ok);
     return p.sub ? launch_bwd_short<NMAX, true, false>(p, packed_ok, s, plane_ok, ragged_ok)
                  : launch_bwd_short<NMAX, false, false>(p, packed_ok, s, plane_ok, ragged_ok);
+}
+
+// Planes of 17-32 samples a side, two lanes a row (tv_pair.hpp): halves of 10, 12, 14 or 16 samples.
+template <bool IO16>
+int launch_fwd_pairs_2d(const tvk::Small2dFwdParams &q, hipStream_t stream)
+{
+    const int longer = q.H > q.W ? q.H : q.W, shorter = q.H > q.W ? q.W : q.H;
+    const dim3 grid((uint32_t)q.planes), block(64);
+#define TV_PAIR(C)                                                                                                              \
+    if (longer <= 2 * C) {                                                                                                      \
+        if (shorter == 2 * C) hipLaunchKernelGGL((tvk::tv2d_fwd_pair_kernel<C, 0, IO16>), grid, block, 0, stream, q);           \
+        else if (shorter >= 2 * C - 3) hipLaunchKernelGGL((tvk::tv2d_fwd_pair_kernel<C, 3, IO16>), grid, block, 0, stream, q);  \
+        else hipLaunchKernelGGL((tvk::tv2d_fwd_pair_kernel<C, C, IO16>), grid, block, 0, stream, q);                            \
+        return launch_status();                                                                                                 \
+    }
+    TV_PAIR(10) TV_PAIR(12) TV_PAIR(14) TV_PAIR(16)
+#undef TV_PAIR
+    return TV_ERR_UNSUPPORTED;
 }
 
 // ---- slot order for the grouped grid -----------------------------------------------
@@ -920,6 +939,41 @@ int bwd_entry(const float *g_up, const float *x, const uint64_t *seg, bool with_
                    rows, lam, n_rows, (float *)ws, stream);
 }
 
+// Planes of at most 32 x 32 are padded to squares of side 8, 16 or 32; a wave holds 64 / side of them.
+int small_side(int64_t H, int64_t W)
+{
+    const int64_t m = H > W ? H : W;
+    return m <= 8 ? 8 : (m <= 16 ? 16 : 32);
+}
+
+#define TV_SMALL2D_SIDE(S, KERNEL, q, H, W, grid, stream, ...)                                                    \
+    do {                                                                                                          \
+        if ((H) == S && (W) == S) hipLaunchKernelGGL((KERNEL<S, true, ##__VA_ARGS__>), grid, dim3(64), 0, stream, q); \
+        else hipLaunchKernelGGL((KERNEL<S, false, ##__VA_ARGS__>), grid, dim3(64), 0, stream, q);                  \
+    } while (0)
+
+// Kernels of up to 64 / side planes a wave; __VA_ARGS__: further template arguments, after S and FULL.
+#define TV_SMALL2D_LAUNCH(KERNEL, q, planes, H, W, stream, ...)                                                   \
+    do {                                                                                                          \
+        const int side = small_side(H, W);                                                                        \
+        const dim3 grid((uint32_t)(((planes) + 64 / side - 1) / (64 / side)));                                    \
+        if (side == 8) TV_SMALL2D_SIDE(8, KERNEL, q, H, W, grid, stream, ##__VA_ARGS__);                          \
+        else if (side == 16) TV_SMALL2D_SIDE(16, KERNEL, q, H, W, grid, stream, ##__VA_ARGS__);                   \
+        else TV_SMALL2D_SIDE(32, KERNEL, q, H, W, grid, stream, ##__VA_ARGS__);                                   \
+    } while (0)
+
+// The one-launch forward of planes of at most 32 x 32: a lane a row up to 16 x 16, two lanes a row beyond.
+template <bool IO16>
+int launch_fwd_small_2d(const tvk::Small2dFwdParams &q, hipStream_t stream)
+{
+    const int side = small_side(q.H, q.W);
+    if (side == 32) return launch_fwd_pairs_2d<IO16>(q, stream);
+    const dim3 grid((uint32_t)((q.planes + 64 / side - 1) / (64 / side)));
+    if (side == 8) TV_SMALL2D_SIDE(8, tvk::tv2d_fwd_small_kernel, q, q.H, q.W, grid, stream, IO16);
+    else TV_SMALL2D_SIDE(16, tvk::tv2d_fwd_small_kernel, q, q.H, q.W, grid, stream, IO16);
+    return launch_status();
+}
+
 }  // namespace
 
 extern "C" {
@@ -1136,48 +1190,6 @@ size_t tv2d_workspace_bytes(int64_t planes, int64_t H, int64_t W, int sweeps)
     return tb * (size_t)(2 * sweeps + 2) + (pb + cb) * (size_t)(2 * sweeps) + kSplitScratchBytes;
 }
 
-// Planes of at most 32 x 32 are padded to squares of side 8, 16 or 32; a wave holds 64 / side of them.
-static int small_side(int64_t H, int64_t W)
-{
-    const int64_t m = H > W ? H : W;
-    return m <= 8 ? 8 : (m <= 16 ? 16 : 32);
-}
-
-#define TV_SMALL2D_LAUNCH(KERNEL, q, planes, H, W, stream)                                          \
-    do {                                                                                            \
-        const int side = small_side(H, W);                                                          \
-        const bool full = (H) == side && (W) == side;                                               \
-        const dim3 grid((uint32_t)(((planes) + 64 / side - 1) / (64 / side)));                      \
-        if (side == 8) {                                                                            \
-            if (full) hipLaunchKernelGGL((KERNEL<8, true>), grid, dim3(64), 0, stream, q);          \
-            else hipLaunchKernelGGL((KERNEL<8, false>), grid, dim3(64), 0, stream, q);              \
-        } else if (side == 16) {                                                                    \
-            if (full) hipLaunchKernelGGL((KERNEL<16, true>), grid, dim3(64), 0, stream, q);         \
-            else hipLaunchKernelGGL((KERNEL<16, false>), grid, dim3(64), 0, stream, q);             \
-        } else {                                                                                    \
-            if (full) hipLaunchKernelGGL((KERNEL<32, true>), grid, dim3(64), 0, stream, q);         \
-            else hipLaunchKernelGGL((KERNEL<32, false>), grid, dim3(64), 0, stream, q);             \
-        }                                                                                           \
-    } while (0)
-
-// the same for kernels with further template arguments (bool..., after S and FULL)
-#define TV_SMALL2D_LAUNCH_X(KERNEL, q, planes, H, W, stream, ...)                                    \
-    do {                                                                                            \
-        const int side = small_side(H, W);                                                          \
-        const bool full = (H) == side && (W) == side;                                               \
-        const dim3 grid((uint32_t)(((planes) + 64 / side - 1) / (64 / side)));                      \
-        if (side == 8) {                                                                            \
-            if (full) hipLaunchKernelGGL((KERNEL<8, true, __VA_ARGS__>), grid, dim3(64), 0, stream, q);   \
-            else hipLaunchKernelGGL((KERNEL<8, false, __VA_ARGS__>), grid, dim3(64), 0, stream, q);       \
-        } else if (side == 16) {                                                                    \
-            if (full) hipLaunchKernelGGL((KERNEL<16, true, __VA_ARGS__>), grid, dim3(64), 0, stream, q);  \
-            else hipLaunchKernelGGL((KERNEL<16, false, __VA_ARGS__>), grid, dim3(64), 0, stream, q);      \
-        } else {                                                                                    \
-            if (full) hipLaunchKernelGGL((KERNEL<32, true, __VA_ARGS__>), grid, dim3(64), 0, stream, q);  \
-            else hipLaunchKernelGGL((KERNEL<32, false, __VA_ARGS__>), grid, dim3(64), 0, stream, q);      \
-        }                                                                                           \
-    } while (0)
-
 // Small batches of planes of 17-64 samples a side: one launch with a plane per workgroup
 // (tv_plane2d.hpp), up to the plane counts of tv_dispatch.hpp.  Planes of at most 32 x 32 leave
 // segment codes for the reverse sweep, larger ones their pass outputs.
@@ -1196,15 +1208,10 @@ static bool plane_per_group_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
     return planes <= tvd::get(tvd::kPlanePerGroup64PlanesK2);
 }
 
-// When the one-launch forward kernel is used: while its lower occupancy (17 KB of LDS per wave
-// for planes padded to 32 x 32: two waves per SIMD against three) costs less than the launches and
-// memory round trips it saves.  The plane counts, and the measurements behind them, are in
-// tv_dispatch.hpp; planes of at most 8 x 8 are always better off in one launch.
+// Whether all passes of the forward call on planes of at most 32 x 32 go in one launch: the plane counts,
+// and the measurements behind them, are in tv_dispatch.hpp; planes of at most 8 x 8 are always better off so.
 static bool fused_fwd_applies(int side, bool full, int64_t planes, int sweeps)
 {
-    // (planes smaller than their 32 x 32 square go pass by pass through the slower general
-    // variants of the row-per-lane kernels, so there the one launch wins whenever there is more
-    // than one sweep: 28 x 28, 32 768 planes, K = 4: 1.46 ms against 1.94)
     if (side == 32) {
         if (!full) return sweeps >= 2 || planes <= tvd::get(tvd::kFused32RaggedPlanes);
         return planes <= tvd::get(sweeps == 1 ? tvd::kFused32FullPlanes
@@ -1266,8 +1273,7 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
             else hipLaunchKernelGGL((tvk::tv2d_fwd_small_kernel<16, false, false, true>), grid, dim3(64), 0, stream, q);
             return launch_status();
         }
-        TV_SMALL2D_LAUNCH(tvk::tv2d_fwd_small_kernel, q, planes, H, W, stream);
-        return launch_status();
+        return launch_fwd_small_2d<false>(q, stream);
     }
     // one lambda for all planes: its gradient hinges on the last bits of x (see tv_long_tri.hpp;
     // not for planes of at most 64 x 64, whose smaller batches are solved by block means anyway)
@@ -1322,7 +1328,7 @@ int tv2d_prox_fwd_bf16(const uint16_t *y, uint16_t *x, int64_t planes, int64_t H
     if (plane_per_group_2d(planes, H, W, sweeps))       // a small batch: a plane per workgroup
         hipLaunchKernelGGL((tvk::tv2d_fwd_plane_kernel<16, 2, true>), dim3((uint32_t)planes), dim3(512), 0, stream, q);
     else
-        TV_SMALL2D_LAUNCH_X(tvk::tv2d_fwd_small_kernel, q, planes, H, W, stream, true);
+        return launch_fwd_small_2d<true>(q, stream);
     return launch_status();
 }
 
@@ -1352,7 +1358,7 @@ int tv2d_prox_bwd_bf16(const uint16_t *g_up, uint16_t *grad_y, float *grad_lam, 
     if (small_side(H, W) == 32 && planes <= tvd::get(tvd::kPlanePerGroupBwdPlanes))
         hipLaunchKernelGGL((tvk::tv2d_bwd_plane_kernel<16, 2, true>), dim3((uint32_t)planes), dim3(512), 0, stream, q);
     else
-        TV_SMALL2D_LAUNCH_X(tvk::tv2d_bwd_small_kernel, q, planes, H, W, stream, false, true);
+        TV_SMALL2D_LAUNCH(tvk::tv2d_bwd_small_kernel, q, planes, H, W, stream, false, true);
     if (launch_status() != TV_OK) return TV_ERR_HIP;
     if (!grad_lam) return TV_OK;
     const tv_lambda lp = {lam.lam, lam.count, 1};
