@@ -406,8 +406,11 @@ def dispatch_probe(dev) -> int:
         case(name, "at_threshold_k%d" % K, lambda: two_d(n, 32, 32, K), 0, "one launch", "pass by pass")
         case(name, "beyond_k%d" % K, lambda: two_d(n + n // 4, 32, 32, K), big, "pass by pass", "one launch")
     n = defaults["fused32_ragged_planes"]
-    case("fused32_ragged_planes", "at_threshold_k1", lambda: two_d(n, 28, 28, 1), 0, "one launch", "pass by pass")
-    case("fused32_ragged_planes", "beyond_k1", lambda: two_d(n + n // 4, 28, 28, 1), big, "pass by pass", "one launch")
+    if n > (1 << 20):               # "always", as above
+        case("fused32_ragged_planes", "at_65536_planes_k1", lambda: two_d(65536, 28, 28, 1), 0, "one launch", "pass by pass")
+    else:
+        case("fused32_ragged_planes", "at_threshold_k1", lambda: two_d(n, 28, 28, 1), 0, "one launch", "pass by pass")
+        case("fused32_ragged_planes", "beyond_k1", lambda: two_d(n + n // 4, 28, 28, 1), big, "pass by pass", "one launch")
     n = defaults["fused16_one_sweep_planes"]
     if n > (1 << 20):               # "always", as above
         case("fused16_one_sweep_planes", "at_262144_planes_k1", lambda: two_d(262144, 16, 16, 1), 0, "one launch", "pass by pass")
@@ -423,14 +426,20 @@ def dispatch_probe(dev) -> int:
          "16 threads x 2 samples per row", "8 x 4")
     case("thread_per_sample_wide_rows", "beyond", lambda: one_d((n // (128 * 32) + 1, 128, 32, 32), 128, 32, False), big,
          "8 threads x 4 samples per row", "16 x 2")
-    # small batches of short rows: sixteen threads per row up to thread_per_sample_1d_rows rows
-    n = defaults["thread_per_sample_1d_rows"]
-    case("thread_per_sample_1d_rows", "at_threshold", lambda: one_d((n // (128 * 32), 128, 32, 32), 128, 32, False), 0,
+    # small batches of short rows: sixteen threads per row up to half of thread_per_sample_1d_rows rows of
+    # 16 samples, and up to pair_1d_rows rows of 32
+    n = defaults["thread_per_sample_1d_rows"] // 2
+    case("thread_per_sample_1d_rows", "at_threshold_16", lambda: one_d((n // (64 * 16), 64, 16, 16), 64, 16, False), 0,
          "16 threads per row", "a lane per row")
-    case("thread_per_sample_1d_rows", "beyond", lambda: one_d((n // (128 * 32) + n // (128 * 128), 128, 32, 32), 128, 32, False),
+    case("thread_per_sample_1d_rows", "beyond_16", lambda: one_d((n // (64 * 16) + n // (64 * 64), 64, 16, 16), 64, 16, False),
          big, "a lane per row", "16 threads per row")
-    case("thread_per_sample_1d_rows", "at_a_quarter", lambda: one_d((n // (128 * 128), 128, 32, 32), 128, 32, False), 0,
-         "16 threads per row", "a lane per row")
+    n = defaults["pair_1d_rows"]
+    case("pair_1d_rows", "at_threshold", lambda: one_d((n // (128 * 32), 128, 32, 32), 128, 32, False), 0,
+         "16 threads per row", "two lanes per row")
+    case("pair_1d_rows", "beyond", lambda: one_d((n // (128 * 32) + n // (128 * 128), 128, 32, 32), 128, 32, False),
+         big, "two lanes per row", "16 threads per row")
+    case("pair_1d_rows", "at_a_quarter", lambda: one_d((n // (128 * 128), 128, 32, 32), 128, 32, False), 0,
+         "16 threads per row", "two lanes per row")
     # a tensor of exactly stream_bytes bytes: rows of 32 samples in 128 lambda slots
     nb = max(2, defaults["stream_bytes"] // (128 * 32 * 32 * 4))
     case("stream_bytes", "at_threshold", lambda: one_d((nb, 128, 32, 32), 128, 32, False), big,

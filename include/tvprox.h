@@ -217,8 +217,9 @@ int tv1d_prox_bwd_noalloc(const float *g_up, const float *x, float *grad_y, floa
  * tv1d_prox_fwd / tv1d_prox_bwd on the same batch.  (Which kernels a forward call runs
  * depends on the batch: up to tv_dispatch_threshold("thread_per_sample_1d_rows") rows of at
  * most 32 samples (half as many rows of at most 16 and columns of 32, a quarter as many columns of
- * at most 16) get sixteen or eight threads per row, larger batches a lane per row; the two agree
- * to rounding, not bit for bit.)
+ * at most 16; of 17-32 samples n, no more than (n - 12) / 20 of "pair_1d_rows", columns three quarters
+ * of that) get sixteen or eight threads per row, larger batches two lanes per row (17-32 samples) or
+ * one; they agree to rounding, not bit for bit.)
  *   seg: device pointer, 8-byte aligned, one uint64 per row in row order
  *        (entry o * n_inner + i for the row at o * outer_stride + i * inner_stride);
  *        bit k (k < 31) is set when x[k+1] != x[k], bit 32 + k when x[k+1] > x[k].
@@ -235,7 +236,7 @@ int tv1d_prox_bwd_seg(const float *g_up, const uint64_t *seg, float *grad_y, flo
  * solve and the segment averaging run as in the fp32 kernels, the outputs are rounded to
  * nearest even): y, x, g_up and grad_y are arrays of bf16 bit patterns (uint16_t), 16-byte
  * aligned.  The paper computes in fp32; this halves the bytes the pair moves.  x is bit for bit
- * the rounded output of tv1d_prox_fwd_seg (its row-per-lane kernel) on the widened input, the codes are identical, and
+ * the rounded output of tv1d_prox_fwd_seg (its kernel with two lanes per row) on the widened input, the codes are identical, and
  * the backward pass uses the codes (segments of the unrounded x), so rounding never merges or
  * splits a segment.  Only packed rows of exactly 32 samples (unit element stride, rows back
  * to back): TV_ERR_UNSUPPORTED otherwise.  ws / ws_bytes of the forward call: as in

@@ -56,11 +56,12 @@ struct TileMap {
     uint32_t hop;
     uint32_t grouped;     // 0: identity
     uint32_t count;       // lam.count (grouped only)
-    // first row of tile (qb, slot)
+    // first row of tile (qb, slot), for tiles of ROWS rows (lg at most log2 ROWS where grouped)
+    template <uint32_t ROWS = 64u>
     __device__ __forceinline__ uint32_t first(uint32_t qb, uint32_t slot) const
     {
-        if (!grouped) return qb * 64u;
-        return ((qb * (64u >> lg)) * count + slot) << lg;
+        if (!grouped) return qb * ROWS;
+        return ((qb * (ROWS >> lg)) * count + slot) << lg;
     }
     __device__ __forceinline__ uint32_t row(uint32_t first_row, uint32_t t) const
     {

@@ -37,6 +37,7 @@ enum {
     kFusedKeepsPasses,
     kThreadPerSampleWideRows,
     kThreadPerSample1dRows,
+    kPair1dRows,
     kOneLambdaTriSide,
     kMlMinLength,
     kMlCoarsest,
@@ -139,19 +140,24 @@ inline Threshold table[kCount] = {
     // thread_per_sample_1d_rows): 16 threads x 2 samples up to this many rows, 8 x 4 beyond
     // (8192 rows of 32 samples as 256 planes, ten passes each way: 204 -> 180 with 16 x 2).
     {"thread_per_sample_wide_rows", 16384, "short rows on the long-row kernels: 16 threads per row up to this many rows"},
-    // 1D calls on rows of 2-32 samples: up to this many rows eight or sixteen threads per row on
-    // the long-row kernels instead of a lane per row, whose few waves are bound by their dependency
-    // chains.  Forward, threads per row / lane per row: 8192 rows x 32 (the
-    // paper's timing batch) 11.4 / 23.6, 32 768 rows 14.4 / 23.6, 65 536: 21.0 / 24.3, 81 920: 22.7 /
-    // 26.2, 98 304: 25.1 / 25.7;  rows of 20: 32 768 rows 13.1 / 24.9, 81 920: 20.6 / 28.9;  rows of 16
-    // or less, whose lanes have the shorter chains: 12 samples, 32 768 rows 11.8 / 13.5, 49 152: 14.0 /
-    // 14.0, 65 536: 17.1 / 15.0;  7 samples, 40 960 rows 11.6 / 11.6, 57 344: 14.9 / 11.4.  So these
-    // change over at half the value.  Strided rows (columns) whose lanes do well, those of 32 samples
-    // and of 16 or less, change over at half of that again, the threads' strided accesses being the
-    // worse ones: 32 samples, random walks, 40 960 columns 23.2 / 24.1, 65 536: 27.8 / 24.2; 12
-    // samples, 24 576 columns 14.1 / 13.4, N(0, 1) 0.93 of it, 40 960: 17.6 / 12.9; but 20 samples,
-    // 81 920 columns 28.6 / 33.7, 28 samples 30.3 / 30.9.
+    // 1D calls on rows of 2-16 samples: up to half this many rows eight or sixteen threads per row on the
+    // long-row kernels instead of a lane per row, whose few waves are bound by their dependency
+    // chains.  Forward, threads per row / lane per row: 12 samples, 32 768 rows 11.8 / 13.5, 49 152: 14.0 /
+    // 14.0, 65 536: 17.1 / 15.0;  7 samples, 40 960 rows 11.6 / 11.6, 57 344: 14.9 / 11.4.  Strided rows
+    // (columns) of 16 or less, the threads' strided accesses being the worse ones, change over at half of
+    // that again: 24 576 columns of 12 14.1 / 13.4, N(0, 1) 0.93 of it, 40 960: 17.6 / 12.9.
+    // Rows of 17-32 samples: up to this many (columns of 32: half), and not beyond pair_1d_rows.
     {"thread_per_sample_1d_rows", 81920, "1D rows of at most 32 samples: a few threads per row up to this many rows (half of it: rows of at most 16, columns of 32; a quarter: columns of at most 16)"},
+    // 1D calls on rows of 17-32 samples: beyond this many rows, times (n - 12) / 20 for rows of n, and
+    // three quarters of that for strided rows, two lanes a row (tv_pair.hpp) instead of sixteen threads.
+    // The sixteen threads take about the same time for any n, the pairs' chains grow with it.  N(0, 1),
+    // lambda 1, forward, sixteen threads / two lanes:
+    //   17 samples,  8192 rows  7.2 /  8.7, 16 384:  8.6 /  9.0, 24 576: 10.6 /  9.4;  columns, 16 384:  9.3 /  9.0
+    //   20 samples, 16 384 rows  8.8 /  9.1, 24 576: 10.2 /  9.3;                      columns, 16 384:  9.2 /  9.7
+    //   24 samples, 24 576 rows 10.8 / 10.5, 32 768: 11.6 / 10.7;                      columns, 24 576: 12.2 / 10.7
+    //   28 samples, 32 768 rows 11.8 / 12.3, 40 960: 13.2 / 12.9;                      columns, 24 576: 12.9 / 12.5
+    //   32 samples, 32 768 rows 12.3 / 15.7, 49 152: 15.4 / 16.1 (lambda 0.3: 11.5 / 11.0); columns, 32 768: 13.5 / 14.8
+    {"pair_1d_rows", 40960, "1D rows of 17-32 samples: two lanes a row beyond this many rows x (n - 12) / 20 (three quarters of it: strided rows)"},
     // 2D pass by pass with ONE lambda for all planes and three sweeps or more: sides up to this many
     // samples (768 at most, and beyond 64) are solved by tridiagonal elimination (tv_long_tri.hpp), not
     // by block means.  The slower one of the two is kept here for the sake of one number, the

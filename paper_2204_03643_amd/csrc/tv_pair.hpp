@@ -394,6 +394,9 @@ __device__ __forceinline__ uint2 pair_segment_code(const float (&xs)[C], int n, 
 constexpr int kPairPitch = 33;
 template <int C>
 __device__ __forceinline__ int pair_place(int k) { return k < C ? k : 15 + 2 * C - k; }
+// step between neighbouring samples of the tile from sample k on (groups of four that the middle does not split)
+template <int C>
+__device__ __forceinline__ int pair_step(int k) { return k < C ? 1 : -1; }
 
 // Which of a lane's samples exist in a row of n (bit i: local sample i), the local index of the dual
 // behind the row's last sample, and the duals inside the row (PairSolver::live).
@@ -603,6 +606,240 @@ __global__ __launch_bounds__(64, 4) void tv2d_fwd_pair_kernel(Small2dFwdParams p
         each_sample([&](int e, const float *d) { dst[e] = f32_to_bf16_bits(*d); });
     } else {
         put_plane(p.x + plane * HW);
+    }
+}
+
+// ---------------------------------------------------------------------------------
+// Forward on a batch of rows, 32 to a wave: plain calls (input y, output x, optionally info words and
+// segment codes).  Grid and tiles: TileMap with tiles of 32 rows.
+// MODE: how the rows lie in memory.  kPairPacked: row r starts n r samples after the base; a wave's rows are
+// moved through the tile with coalesced accesses (kPairPacked4: of 16 bytes).  kPairPlane: the rows are the columns of contiguous 32 x 32
+// planes, a plane a wave.  kPairStrided: anything else, read and written sample by sample.  (PADS < C:
+// n > 2C - 1 - PADS.)
+// IO16: y and x are bf16 (packed rows of 32).
+// ---------------------------------------------------------------------------------
+constexpr int kPairStrided = 0, kPairPacked = 1, kPairPlane = 2, kPairPacked4 = 3;
+
+template <int C, int PADS, int MODE, bool IO16 = false>
+__global__ __launch_bounds__(64, 4) void tv1d_fwd_pair_kernel(FwdParams p)
+{
+    constexpr int P = kPairPitch;
+    constexpr bool FULL = PADS == 0;
+    constexpr bool WHOLE = FULL && C == 16;         // rows of exactly 32
+    static_assert(MODE != kPairPlane || WHOLE, "plane columns: 32 x 32 planes");
+    static_assert(!IO16 || (WHOLE && MODE == kPairPacked4), "bf16 storage: packed rows of 32");
+    __shared__ __align__(16) float tile[MODE == kPairStrided ? 64 * C : 32 * P];
+    __shared__ float gtab[34], rtab[34];
+    const int lane = threadIdx.x;
+    fill_tables<32>(gtab, rtab);
+
+    const uint32_t slot = p.order ? min(p.order[blockIdx.y], gridDim.y - 1u) : blockIdx.y;
+    const uint32_t r0 = p.tm.first<32>(__builtin_amdgcn_readfirstlane(blockIdx.x), slot);
+    const int at = lane >> 1;
+    const bool right = (lane & 1) != 0;
+    // (plane columns lie in the tile by place, like the planes' rows)
+    const uint32_t row = p.tm.row(r0, (uint32_t)(MODE == kPairPlane ? pair_place<16>(at) : at));
+    const bool valid = row < p.L.n_rows;
+    const int n = FULL ? 2 * C : p.L.n;
+    float lam = 0.f;
+    if (p.tm.grouped) lam = fmaxf(p.lam[slot], 0.f);            // one slot per tile
+    else if (valid) lam = load_lambda(p.lam, p.L, row);
+    const uint32_t have = FULL ? ~0u : pair_samples<C>(n, right);
+    const bool stream = p.L.stream != 0;
+
+    // the lane's samples in the tile (kPairPacked: the right lane's backwards from place 2C - 1 of its row)
+    float *half = MODE == kPairPlane    ? tile + (right ? 16 * P : 0) + at
+                  : MODE == kPairPacked ? tile + at * n + (right ? 2 * C - 1 : 0)
+                                        : tile + at * P + (right ? 16 : 0);
+    const int half_step = MODE == kPairPlane ? P : (MODE == kPairPacked && right ? -1 : 1);
+    float *park = tile + lane;
+
+    // kPairPacked4: four samples at a time, group c of the wave's row r.  (Past the last group, and past the
+    // last row, the last one again: nothing is read out of bounds, and a tile entry gets the same value twice.)
+    auto move_fours = [&](auto &&f) {
+        int own = lane;
+        asm volatile("" : "+v"(own));               // (addresses formed here, not kept through the solve)
+        const int per = n / 4;                      // groups a row
+        int r = own / per, c = own - r * per;
+        const int dq = 64 / per, dr = 64 - dq * per;
+#pragma unroll
+        for (int i = 0; i < (C + 3) / 4; ++i) {     // (32 rows of at most 2C samples)
+            const int rr = min(r, 31);
+            const uint32_t g = min(p.tm.row(r0, (uint32_t)rr), p.L.n_rows - 1u);
+            f(i, (size_t)g * n + c * 4, rr, c * 4);
+            r += dq; c += dr;
+            if (c >= per) { c -= per; r += 1; }
+        }
+    };
+    const bool all_there = p.tm.row(r0, 31u) < p.L.n_rows;
+    // kPairPacked: the wave's rows lie in the tile as in memory, one block of samples
+    const int total = MODE == kPairPacked ? (int)min(32u, p.L.n_rows - r0) * n : 0;
+    const bool aligned = MODE == kPairPacked && all_there && ((uintptr_t)p.y | (uintptr_t)p.x) % 16 == 0;
+    // (C = 10, 14: the middle splits a group of four)
+    auto put4 = [&](int r, int c, const float4 &q) {
+        float *d = tile + r * P;
+        if constexpr (C % 4 == 0) {
+            const int s = pair_step<C>(c);
+            d += pair_place<C>(c);
+            d[0] = q.x; d[s] = q.y; d[2 * s] = q.z; d[3 * s] = q.w;
+        } else {
+            d[pair_place<C>(c)] = q.x; d[pair_place<C>(c + 1)] = q.y;
+            d[pair_place<C>(c + 2)] = q.z; d[pair_place<C>(c + 3)] = q.w;
+        }
+    };
+    auto get4 = [&](int r, int c) {
+        const float *d = tile + r * P;
+        if constexpr (C % 4 == 0) {
+            const int s = pair_step<C>(c);
+            d += pair_place<C>(c);
+            return make_float4(d[0], d[s], d[2 * s], d[3 * s]);
+        } else {
+            return make_float4(d[pair_place<C>(c)], d[pair_place<C>(c + 1)], d[pair_place<C>(c + 2)], d[pair_place<C>(c + 3)]);
+        }
+    };
+    // plane columns: the plane's samples 4 (i * 64 + lane) ..
+    const int64_t plane_at = MODE == kPairPlane ? (int64_t)(r0 >> 5) * p.L.outer_stride : 0;
+    const bool plane_there = MODE == kPairPlane && r0 < p.L.n_rows;
+    const int64_t off = MODE == kPairStrided && valid ? row_offset(p.L, row) + (right ? (int64_t)(2 * C - 1) * p.L.elem_stride : 0) : 0;
+    const int64_t step = right ? -p.L.elem_stride : p.L.elem_stride;
+
+    float y[C];
+    if constexpr (MODE == kPairStrided) {
+#pragma unroll
+        for (int k = 0; k < C; ++k) y[k] = valid && ((have >> k) & 1u) ? p.y[off + k * step] : 0.f;
+    } else {
+        if constexpr (MODE == kPairPlane) {
+            float4 q[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                q[i] = plane_there ? load16(p.y + plane_at + (i * 64 + lane) * 4, stream) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = (i * 64 + lane) * 4;
+                put4(pair_place<16>(e >> 5), e & 31, q[i]);
+            }
+        } else if constexpr (IO16) {
+            const uint16_t *src = reinterpret_cast<const uint16_t *>(p.y);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int e = (i * 64 + lane) * 8;
+                const uint32_t g = p.tm.row(r0, (uint32_t)e >> 5);
+                if (g >= p.L.n_rows) continue;
+                const float4 q = load16(reinterpret_cast<const float *>(src + (size_t)g * 32 + (e & 31)), stream);
+                const uint32_t w[4] = {__float_as_uint(q.x), __float_as_uint(q.y), __float_as_uint(q.z), __float_as_uint(q.w)};
+                float *d = tile + (e >> 5) * P + pair_place<C>(e & 31);
+                const int s = pair_step<C>(e & 31);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    d[2 * j * s] = __uint_as_float(w[j] << 16);
+                    d[(2 * j + 1) * s] = __uint_as_float(w[j] & 0xffff0000u);
+                }
+            }
+        } else if constexpr (MODE == kPairPacked4) {
+            float4 q[(C + 3) / 4];                  // (every load is issued before the first is waited for)
+            move_fours([&](int i, size_t a, int, int) { q[i] = load16(p.y + a, stream); });
+            move_fours([&](int i, size_t, int r, int c) { put4(r, c, q[i]); });
+        } else {
+            const float *blk = p.y + (size_t)r0 * n;
+            if (aligned) {
+                float4 q[(C + 3) / 4];
+#pragma unroll
+                for (int i = 0; i < (C + 3) / 4; ++i) {
+                    const int e = (i * 64 + lane) * 4;
+                    q[i] = e < total ? load16(blk + e, stream) : make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+#pragma unroll
+                for (int i = 0; i < (C + 3) / 4; ++i) {
+                    const int e = (i * 64 + lane) * 4;
+                    if (e < total) *reinterpret_cast<float4 *>(tile + e) = q[i];
+                }
+            } else {
+#pragma unroll 4
+                for (int e = lane; e < total; e += 64) tile[e] = blk[e];
+            }
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int k = 0; k < C; ++k) y[k] = pair_masked<PADS>(half[k * half_step], have, k);
+        if (!valid) {                               // (its part of the tile was not written)
+#pragma unroll
+            for (int k = 0; k < C; ++k) y[k] = 0.f;
+        }
+        wave_lds_sync();
+    }
+#pragma unroll
+    for (int k = 0; k < C; ++k) park[k * 64] = y[k];
+    wave_lds_sync();
+
+    PairSolver<C, PADS> sv;
+    sv.yl = park; sv.gtab = gtab; sv.lam = lam;
+    if constexpr (!FULL) {
+        sv.cut = pair_cut<C>(n, right);
+        sv.live = pair_live(sv.cut, right);
+    }
+    sv.start(y, rtab[n], have);
+    sv.solve(valid);
+    float xs[C];
+    sv.recover(xs);
+
+    if (p.info && valid && !right) p.info[row] = sv.steps | sv.flags;
+    if (p.seg) {
+        const uint2 code = pair_segment_code<C, FULL>(xs, n, right);
+        if (valid) reinterpret_cast<uint32_t *>(p.seg + row)[right ? 1 : 0] = right ? code.y : code.x;
+    }
+    if constexpr (MODE == kPairStrided) {
+#pragma unroll
+        for (int k = 0; k < C; ++k)
+            if (valid && ((have >> k) & 1u)) p.x[off + k * step] = xs[k];
+        return;
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < C; ++k)
+        if (MODE != kPairPacked || k >= PADS || ((have >> k) & 1u)) half[k * half_step] = xs[k];
+    wave_lds_sync();
+    if constexpr (MODE == kPairPlane) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            int own = lane;
+            asm volatile("" : "+v"(own));
+            const int e = (i * 64 + own) * 4;
+            const float4 q = get4(pair_place<16>(e >> 5), e & 31);
+            if (plane_there) store16(p.x + plane_at + e, q, stream);
+        }
+    } else if constexpr (IO16) {
+        uint16_t *dst = reinterpret_cast<uint16_t *>(p.x);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int e = (i * 64 + lane) * 8;
+            const uint32_t g = p.tm.row(r0, (uint32_t)e >> 5);
+            if (g >= p.L.n_rows) continue;
+            const float *d = tile + (e >> 5) * P + pair_place<C>(e & 31);
+            const int s = pair_step<C>(e & 31);
+            uint32_t w[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[j] = f32x2_to_bf16x2(d[2 * j * s], d[(2 * j + 1) * s]);
+            store16(reinterpret_cast<float *>(dst + (size_t)g * 32 + (e & 31)),
+                    make_float4(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]), __uint_as_float(w[3])), stream);
+        }
+    } else if constexpr (MODE == kPairPacked4) {
+        if (all_there) move_fours([&](int, size_t a, int r, int c) { store16(p.x + a, get4(r, c), stream); });
+        else move_fours([&](int, size_t a, int r, int c) {
+            if (p.tm.row(r0, (uint32_t)r) < p.L.n_rows) store16(p.x + a, get4(r, c), stream);
+        });
+    } else {
+        float *blk = p.x + (size_t)r0 * n;
+        int own = lane;
+        asm volatile("" : "+v"(own));
+        if (aligned) {
+#pragma unroll
+            for (int i = 0; i < (C + 3) / 4; ++i) {
+                const int e = (i * 64 + own) * 4;
+                if (e < total) store16(blk + e, *reinterpret_cast<const float4 *>(tile + e), stream);
+            }
+        } else {
+            for (int e = own; e < total; e += 64) blk[e] = tile[e];
+        }
     }
 }
 

@@ -998,15 +998,13 @@ struct RowSolver {
 // for each other.  With a grouped grid the slots may be visited in a given order (p.order).
 // ---------------------------------------------------------------------------------
 // WARM: p.addend is given and the solve starts from the dual it encodes (see start_warm).
-// PLANE (NMAX = 32, FULL, not PACKED, not WARM): the rows are the columns of contiguous 32 x 32 planes.
-// IO16 (NMAX = 32, FULL, PACKED, no addend / second output / residual): y and x are bf16.
+// (Rows of 17-32 samples without addend, second output or residual: tv_pair.hpp.)
 // DEBUG: the first p.debug_rows rows leave a step record in p.debug (see step_record_floats).
 // PSEARCH: the step size comes from the parallel search over halving step sizes (iterate_psearch).
 // (The variants for rows of exactly NMAX samples are asked to leave room for 3 waves per SIMD
 // : the 32-sample one fits 150 registers when told so and takes
 // some 200 when left alone.  The others are left alone; held to that budget they spill.)
-template <int NMAX, bool FULL, bool PACKED, bool WARM = false, bool PLANE = false, bool IO16 = false,
-          bool DEBUG = false, bool PSEARCH = false>
+template <int NMAX, bool FULL, bool PACKED, bool WARM = false, bool DEBUG = false, bool PSEARCH = false>
 __global__ __launch_bounds__(kShortBlock) __attribute__((amdgpu_waves_per_eu((FULL && !DEBUG && !PSEARCH) ? 3 : 1)))
 void tv1d_fwd_short_kernel(FwdParams p)
 {
@@ -1028,13 +1026,6 @@ void tv1d_fwd_short_kernel(FwdParams p)
     if (p.tm.grouped) lam = fmaxf(p.lam[slot], 0.f);            // one slot per tile
     else if (valid) lam = load_lambda(p.lam, p.L, row);
     const int64_t off = (!PACKED && valid) ? row_offset(p.L, row) : 0;
-    static_assert(!PLANE || (NMAX == 32 && FULL && !PACKED), "plane columns: 32 x 32 planes only");
-    PlanePair pp = {{0u, 0u}};
-    if constexpr (PLANE) {
-        pp.row[0] = __builtin_amdgcn_readfirstlane(p.tm.row(r0, 0));
-        pp.row[1] = __builtin_amdgcn_readfirstlane(p.tm.row(r0, 32));
-    }
-
     float y[NMAX], xs[NMAX];
     RowSolver<NMAX, FULL, DEBUG> sv;
     if constexpr (DEBUG) {
@@ -1043,29 +1034,7 @@ void tv1d_fwd_short_kernel(FwdParams p)
             sv.rec[0] = 0.f; sv.rec[1] = lam;
         }
     }
-    if constexpr (PLANE) {
-        // (no warm-start variant: the solver's bound masks already fill the scalar registers, the
-        // extra pointers of a warm pass spill them, and the spill costs a wave of occupancy)
-        static_assert(!(PLANE && WARM), "plane columns: cold start only");
-        TileRegs<32> t;
-        planes_fetch(p.y, pp, p.L, lane, t);
-        if (p.addend) {
-            TileRegs<32> a;
-            planes_fetch(p.addend, pp, p.L, lane, a);
-            tile_add<32>(t, a, 1.f);
-        }
-        planes_into_tile(t, tile, lane);
-        const float *col = plane_column(tile, lane);
-#pragma unroll
-        for (int k = 0; k < NMAX; ++k) y[k] = col[k * 33];
-    } else if constexpr (IO16) {
-        static_assert(!IO16 || (NMAX == 32 && FULL && PACKED && !WARM), "bf16 storage: packed rows of 32");
-        wave_lds_sync();
-        tile16_fetch(reinterpret_cast<const uint16_t *>(p.y), p.tm, r0, p.L.n_rows, lane, tile, p.L.stream);
-        wave_lds_sync();
-#pragma unroll
-        for (int k = 0; k < NMAX; ++k) y[k] = tile[lane * (NMAX + 1) + k];
-    } else if constexpr (PACKED && !FULL) {
+    if constexpr (PACKED && !FULL) {
         // (rows in natural order: the host asks for this variant with the identity tile map only)
         if (WARM || p.addend) {
             float a[NMAX];
@@ -1121,16 +1090,7 @@ void tv1d_fwd_short_kernel(FwdParams p)
 #pragma unroll
         for (int k = 0; k < NMAX; ++k) rs[k] = tile[k * 64 + lane] - xs[k];
     }
-    if constexpr (PLANE) {
-        columns_to_planes(xs, tile, lane, p.x, p.x2, pp, p.L);
-        if (want_resid) columns_to_planes(rs, tile, lane, p.resid, nullptr, pp, p.L);
-    } else if constexpr (IO16) {
-        wave_lds_sync();
-#pragma unroll
-        for (int k = 0; k < NMAX; ++k) tile[lane * (NMAX + 1) + k] = xs[k];
-        wave_lds_sync();
-        tile16_put(reinterpret_cast<uint16_t *>(p.x), p.tm, r0, p.L.n_rows, lane, tile, p.L.stream);
-    } else if constexpr (PACKED && !FULL) {
+    if constexpr (PACKED && !FULL) {
         ragged_put<NMAX>(p.x, r0, p.L.n_rows, n, lane, tile, xs);
         if (p.x2) ragged_put<NMAX>(p.x2, r0, p.L.n_rows, n, lane, tile, xs);
         if (want_resid) ragged_put<NMAX>(p.resid, r0, p.L.n_rows, n, lane, tile, rs);

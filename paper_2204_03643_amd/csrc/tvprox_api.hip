@@ -95,11 +95,11 @@ Layout make_layout(const tv_rows &r, const tv_lambda &l, int64_t n_rows)
 
 // Tiles of 64 rows for the row-per-lane forward kernel: grouped by lambda slot when the slot
 // pattern allows it (lam.div a power of two below 64, every slot a whole number of tiles).
-tvk::TileMap make_tile_map(const tv_lambda &l, int64_t n_rows)
+tvk::TileMap make_tile_map(const tv_lambda &l, int64_t n_rows, int64_t tile_rows = 64)
 {
     tvk::TileMap tm = {6u, 0u, 0u, 1u};
     const int64_t div = l.div, count = l.count;
-    if (count > 1 && div < 64 && (div & (div - 1)) == 0 && n_rows % (64 * count) == 0 &&
+    if (count > 1 && div <= tile_rows && div < 64 && (div & (div - 1)) == 0 && n_rows % (tile_rows * count) == 0 &&
         count * div <= 0x7fffffff && count <= 65535) {
         uint32_t lg = 0;
         while ((1 << lg) < div) ++lg;
@@ -135,8 +135,7 @@ int launch_status()
 // ---- short rows: one row per lane ---------------------------------------------------
 
 template <int NMAX>
-int launch_fwd_short(const FwdParams &p, bool packed_ok, hipStream_t s, bool plane_ok = false,
-                     bool ragged_ok = false)
+int launch_fwd_short(const FwdParams &p, bool packed_ok, hipStream_t s, bool ragged_ok = false)
 {
     // ragged_ok: packed rows shorter than NMAX in natural order (any 4-byte alignment); rows of up
     // to 8 samples lie so close together that the plain per-lane accesses do as well
@@ -147,25 +146,13 @@ int launch_fwd_short(const FwdParams &p, bool packed_ok, hipStream_t s, bool pla
     if (p.tm.grouped) grid = dim3(n_tiles / p.tm.count, p.tm.count);
     const bool full = p.L.n == NMAX;
     if constexpr (NMAX == 32) {
-        if (p.io16) {                     // the entry point has checked: packed rows of exactly 32
-            hipLaunchKernelGGL((tvk::tv1d_fwd_short_kernel<32, true, true, false, false, true>), grid, block, 0, s, p);
-            return launch_status();
-        }
         if (p.psearch) {                  // the entry point has checked: no addend, rows of up to 32 samples
             if (full && packed_ok)
-                hipLaunchKernelGGL((tvk::tv1d_fwd_short_kernel<32, true, true, false, false, false, false, true>), grid,
+                hipLaunchKernelGGL((tvk::tv1d_fwd_short_kernel<32, true, true, false, false, true>), grid,
                                    block, 0, s, p);
             else
-                hipLaunchKernelGGL((tvk::tv1d_fwd_short_kernel<32, false, false, false, false, false, false, true>), grid,
+                hipLaunchKernelGGL((tvk::tv1d_fwd_short_kernel<32, false, false, false, false, true>), grid,
                                    block, 0, s, p);
-            return launch_status();
-        }
-    }
-    if constexpr (NMAX == 32) {
-        // (the warm-start variant of the plane mode runs out of scalar registers and loses a wave of
-        // occupancy to the spill; warm column passes keep the strided accesses)
-        if (plane_ok && full && !p.warm) {
-            hipLaunchKernelGGL((tvk::tv1d_fwd_short_kernel<32, true, false, false, true>), grid, block, 0, s, p);
             return launch_status();
         }
     }
@@ -228,6 +215,39 @@ int launch_bwd_short(const BwdParams &p, bool packed_ok, hipStream_t s, bool pla
                      : launch_bwd_short<NMAX, false, true>(p, packed_ok, s, plane_ok, ragged_ok);
     return p.sub ? launch_bwd_short<NMAX, true, false>(p, packed_ok, s, plane_ok, ragged_ok)
                  : launch_bwd_short<NMAX, false, false>(p, packed_ok, s, plane_ok, ragged_ok);
+}
+
+// Rows of 17-32 samples, plain calls: two lanes a row (tv_pair.hpp), halves of 10, 12, 14 or 16 samples.
+int launch_fwd_pairs(FwdParams p, const tv_rows &r, const tv_lambda &l, int64_t n_rows, hipStream_t s)
+{
+    const int n = p.L.n;
+    const bool packed = rows_packed(r), quads = packed && n % 4 == 0 && aligned16(p.y) && aligned16(p.x);
+    const bool planes = rows_are_plane_columns(r) && aligned16(p.y) && aligned16(p.x);
+    // (packed rows of other lengths move as one block: rows in natural order)
+    p.tm = packed && !quads ? tvk::TileMap{6u, 0u, 0u, 1u} : make_tile_map(l, n_rows, 32);
+    const uint32_t n_tiles = (p.L.n_rows + 31u) / 32u;
+    dim3 grid(n_tiles), block(64);
+    if (p.tm.grouped) grid = dim3(n_tiles / p.tm.count, p.tm.count);
+    else p.order = nullptr;
+    if (p.io16) {                           // the entry point has checked: packed rows of exactly 32
+        hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<16, 0, tvk::kPairPacked4, true>), grid, block, 0, s, p);
+        return launch_status();
+    }
+    if (planes && (!p.tm.grouped || p.tm.lg == 5)) {
+        hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<16, 0, tvk::kPairPlane>), grid, block, 0, s, p);
+        return launch_status();
+    }
+#define TV_PAIR(C)                                                                                                                  \
+    if (n <= 2 * C) {                                                                                                               \
+        if (quads) hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<C, 0, tvk::kPairPacked4>), grid, block, 0, s, p);                  \
+        else if (packed) hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<C, 3, tvk::kPairPacked>), grid, block, 0, s, p);             \
+        else if (n == 2 * C) hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<C, 0, tvk::kPairStrided>), grid, block, 0, s, p);        \
+        else hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<C, 3, tvk::kPairStrided>), grid, block, 0, s, p);                        \
+        return launch_status();                                                                                                     \
+    }
+    TV_PAIR(10) TV_PAIR(12) TV_PAIR(14) TV_PAIR(16)
+#undef TV_PAIR
+    return TV_ERR_UNSUPPORTED;
 }
 
 // Planes of 17-32 samples a side, two lanes a row (tv_pair.hpp): halves of 10, 12, 14 or 16 samples.
@@ -617,15 +637,12 @@ int run_fwd(const float *y, const float *addend, float *x, float *resid, int32_t
     const bool packed = rows_packed(r) && aligned16(y) && aligned16(x) &&
                         (!addend || aligned16(addend)) && (!resid || aligned16(resid));
     const bool ragged = rows_packed(r);
-    if (psearch) return launch_fwd_short<32>(p, packed, s, false, false);   // every length up to 32
-    if (r.length <= 8) return launch_fwd_short<8>(p, packed, s, false, ragged);
-    if (r.length <= 16) return launch_fwd_short<16>(p, packed, s, false, ragged);
-    if (r.length <= 32) {
-        const bool planes = rows_are_plane_columns(r) && aligned16(y) && aligned16(x) &&
-                            (!addend || aligned16(addend)) && (!resid || aligned16(resid)) &&
-                            (!x2 || aligned16(x2));
-        return launch_fwd_short<32>(p, packed, s, planes, ragged);
-    }
+    if (psearch) return launch_fwd_short<32>(p, packed, s);     // every length up to 32
+    if (r.length > 16 && r.length <= 32 && !addend && !resid && !x2)
+        return launch_fwd_pairs(p, r, l, n_rows, s);
+    if (r.length <= 8) return launch_fwd_short<8>(p, packed, s, ragged);
+    if (r.length <= 16) return launch_fwd_short<16>(p, packed, s, ragged);
+    if (r.length <= 32) return launch_fwd_short<32>(p, packed, s, ragged);
     if (tri) return tvk::launch_fwd_tri(p, s) == hipSuccess ? TV_OK : TV_ERR_HIP;      // (up to 768 samples)
     MlPlan pl;
     if (!p.warm && !addend && ml_plan(r, n_rows, &pl)) {
@@ -877,6 +894,11 @@ int fwd_entry(const float *y, float *x, tv_rows rows, tv_lambda lam, const tv_fw
     int64_t few_rows = tvd::get(tvd::kThreadPerSample1dRows);
     if (rows.length <= 16) few_rows /= 2;
     if (rows.elem_stride != 1 && (rows.length <= 16 || rows.length == 32)) few_rows /= 2;
+    if (rows.length > 16 && rows.length <= 32) {        // (beyond that two lanes a row)
+        int64_t most = tvd::get(tvd::kPair1dRows) * (rows.length - 12) / 20;
+        if (rows.elem_stride != 1) most = most / 4 * 3;
+        if (few_rows > most) few_rows = most;
+    }
     const bool few = n_rows <= few_rows && !e.ws && !(e.flags & TV_FWD_PARALLEL_SEARCH);
     return run_fwd(y, nullptr, x, nullptr, e.info, reinterpret_cast<uint2 *>(e.seg), order_ws, rows,
                    lam, n_rows, s, nullptr, false, (char *)e.ws, false, few,
@@ -1078,10 +1100,10 @@ int tv1d_prox_fwd_steps(const float *y, float *x, int32_t *info, float *record, 
         // the general variant of the row-per-lane kernel (any length up to 32, any strides)
         const dim3 grid((uint32_t)((n_rows + 63) / 64)), block(tvk::kShortBlock);
         if (rows.length == 32)
-            hipLaunchKernelGGL((tvk::tv1d_fwd_short_kernel<32, true, false, false, false, false, true>), grid, block, 0,
+            hipLaunchKernelGGL((tvk::tv1d_fwd_short_kernel<32, true, false, false, true>), grid, block, 0,
                                stream, p);
         else
-            hipLaunchKernelGGL((tvk::tv1d_fwd_short_kernel<32, false, false, false, false, false, true>), grid, block, 0,
+            hipLaunchKernelGGL((tvk::tv1d_fwd_short_kernel<32, false, false, false, true>), grid, block, 0,
                                stream, p);
         return launch_status();
     }

@@ -1,29 +1,32 @@
-"""GPU parity of the kernels that solve a row with two lanes, one from each end (planes of 17-32 samples
-a side in one launch), at the sizes where their parts meet: rows that fill the two halves, that lack a
-sample or a few, that lie in one half only, and ties across the middle of the row."""
+"""GPU parity of the kernels that solve a row with two lanes, one from each end (1D rows of 17-32 samples
+in large batches; planes of 17-32 samples a side in one launch), at the sizes where their parts meet:
+rows that fill the two halves, that lack a sample or a few, that lie in one half only, ties across the
+middle of the row, and every way the rows can lie in memory."""
 import numpy as np
 import pytest
 
-from gpuutil import run_2d
-from parity import check_2d
+from gpuutil import lam_per_row, run_2d
+from parity import check_2d, check_batch
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.fixture
-def no_plane_per_workgroup():
+def pairs():
     import paper_2204_03643_amd as tv
-    saved = tv.tv_dispatch_threshold("plane_per_group_planes")
-    tv.tv_dispatch_override("plane_per_group_planes", 0)
+    saved = {k: tv.tv_dispatch_threshold(k) for k in ("plane_per_group_planes", "thread_per_sample_1d_rows")}
+    for k in saved:
+        tv.tv_dispatch_override(k, 0)
     yield
-    tv.tv_dispatch_override("plane_per_group_planes", saved)
+    for k, v in saved.items():
+        tv.tv_dispatch_override(k, v)
 
 
 # (halves of 10, 12, 14 and 16 samples: rows of 20, 24, 28 and 32, and their neighbours)
 @pytest.mark.parametrize("H,W", [(17, 17), (19, 18), (20, 20), (20, 17), (21, 21), (24, 24), (23, 22), (25, 28), (28, 28),
                                  (27, 26), (29, 32), (30, 30), (31, 31), (32, 32), (32, 31), (32, 16), (17, 32), (32, 15),
                                  (5, 20), (24, 12), (28, 1), (1, 19), (32, 2)])
-def test_planes_of_17_to_32_a_side(H, W, no_plane_per_workgroup):
+def test_planes_of_17_to_32_a_side(H, W, pairs):
     rng = np.random.default_rng(1000 * H + W)
     y = rng.normal(size=(9, H, W)).astype(np.float32)
     y[3:6] = np.maximum(np.round(y[3:6], 1), 0)               # ties, across the middle too
@@ -31,3 +34,78 @@ def test_planes_of_17_to_32_a_side(H, W, no_plane_per_workgroup):
     g = rng.normal(size=y.shape).astype(np.float32)
     lam = np.array([0.2, 0.013, 1.7, 0.5], np.float32)
     check_2d(y, lam, 3, g, run_2d(y, lam, 3, g), "pairs %dx%d" % (H, W))
+
+
+# how the rows of n lie, as (outer stride, inner stride, element stride) of 7 x 16 rows, in samples:
+# packed, packed at a 4-byte offset, rows with gaps, columns, columns with gaps
+LAYOUTS = {"packed": lambda n: (16 * n, n, 1, 0), "shifted": lambda n: (16 * n, n, 1, 1), "gaps": lambda n: (20 * (n + 3), n + 3, 1, 0),
+           "columns": lambda n: (16 * n, 1, 16, 0), "gap columns": lambda n: (37 * n, 2, 36, 3)}
+
+
+@pytest.mark.parametrize("n", [17, 18, 19, 20, 21, 23, 24, 25, 27, 28, 29, 30, 31, 32])
+@pytest.mark.parametrize("layout", sorted(LAYOUTS))
+@pytest.mark.parametrize("count,div", [(1, 1), (112, 1), (7, 16), (2, 8)])
+def test_rows_of_17_to_32_in_every_layout(n, layout, count, div, pairs):
+    """112 rows (the last wave half empty, except where the rows of a lambda are grouped): output, info
+    words, segment codes and both gradients; nothing is written outside the rows."""
+    import torch
+    import paper_2204_03643_amd as tv
+    so, si, se, at = LAYOUTS[layout](n)
+    outer = 8 if (count, div) == (2, 8) else 7                # 128 rows: two slots of two whole waves each
+    rows_n = outer * 16
+    rng = np.random.default_rng(100 * n + count)
+    yr = rng.normal(size=(rows_n, n)).astype(np.float32)
+    yr[::3] = np.round(yr[::3], 1)
+    gr = rng.normal(size=yr.shape).astype(np.float32)
+    lam = (10 ** rng.uniform(-2, 0.7, size=count)).astype(np.float32)
+    where = at + (np.arange(rows_n) // 16 * so + np.arange(rows_n) % 16 * si)[:, None] + np.arange(n) * se
+    size = int(where.max()) + 8
+    dev = torch.device("cuda:0")
+
+    def spread(a):
+        b = np.full(size, np.nan, np.float32)
+        b[where] = a
+        return torch.from_numpy(b).to(dev)
+
+    y, g = spread(yr), spread(gr)
+    x, gy = torch.full_like(y, np.nan), torch.full_like(y, np.nan)
+    lt = torch.from_numpy(lam).to(dev)
+    gl = torch.empty_like(lt)
+    rows, L = tv.tv_rows(outer, so, 16, si, n, se), tv.tv_lambda(lt.data_ptr(), count, div)
+    info = torch.zeros(rows_n, dtype=torch.int32, device=dev)
+    seg = torch.full((rows_n,), -1, dtype=torch.int64, device=dev)
+    wsb = tv.tv1d_bwd_workspace_bytes(rows, L)
+    ws = torch.empty(wsb, dtype=torch.uint8, device=dev)
+    tv.tv1d_prox_fwd_ex(y[at:], x[at:], rows, L, info=info, seg=seg)
+    tv.tv1d_prox_bwd_seg(g[at:], seg, gy[at:], gl, rows, L, ws, wsb)
+    torch.cuda.synchronize()
+    out = x.cpu().numpy()
+    xr, gyr = out[where], gy.cpu().numpy()[where]
+    rest = np.ones(size, bool)
+    rest[where] = False
+    assert np.isnan(out[rest]).all() and np.isnan(gy.cpu().numpy()[rest]).all()
+    code = np.zeros(rows_n, np.uint64)
+    for k in range(n - 1):
+        code |= (xr[:, k + 1] != xr[:, k]).astype(np.uint64) << np.uint64(k)
+        code |= (xr[:, k + 1] > xr[:, k]).astype(np.uint64) << np.uint64(32 + k)
+    assert np.array_equal(seg.cpu().numpy().view(np.uint64), code)
+    assert not (info.cpu().numpy() >> 18).any()               # no row stopped short
+    check_batch(yr, lam_per_row(lam, rows_n, div), gr, xr, gyr, gl_gpu=gl.cpu().numpy(), lam_count=count, lam_div=div,
+                label="pairs n=%d %s" % (n, layout))
+
+
+@pytest.mark.parametrize("div,count", [(32, 2), (8, 4), (1, 32), (16, 2)])
+def test_plane_columns_with_several_lambdas_a_plane(div, count, pairs):
+    """Columns of 32 x 32 planes whose lambda changes inside a plane: a wave that held the columns of one
+    lambda would not hold a plane."""
+    import torch
+    import paper_2204_03643_amd as tv
+    rng = np.random.default_rng(div)
+    y = rng.normal(size=(8, 32, 32)).astype(np.float32)
+    lam = (10 ** rng.uniform(-2, 0.5, size=count)).astype(np.float32)
+    yt, lt = torch.from_numpy(y).cuda(), torch.from_numpy(lam).cuda()
+    x = torch.full_like(yt, float("nan"))
+    tv.tv1d_prox_fwd(yt, x, tv.tv_rows(8, 1024, 32, 1, 32, 32), tv.tv_lambda(lt.data_ptr(), count, div))
+    torch.cuda.synchronize()
+    cols = lambda a: a.transpose(0, 2, 1).reshape(-1, 32)
+    check_batch(cols(y), lam_per_row(lam, 256, div), None, cols(x.cpu().numpy()), None, label="plane columns")
