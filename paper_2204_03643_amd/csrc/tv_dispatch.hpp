@@ -38,6 +38,7 @@ enum {
     kThreadPerSampleWideRows,
     kThreadPerSample1dRows,
     kPair1dRows,
+    kPair1dLongRows,
     kOneLambdaTriSide,
     kMlMinLength,
     kMlCoarsest,
@@ -102,14 +103,19 @@ inline Threshold table[kCount] = {
     //            K = 4: 1280 planes 0.93 0.99, 1536: 0.97 1.01, 2048: 1.05 1.07;
     //   64 x 40, K = 3: 1280 planes 0.93 0.99, 1536: 0.96 1.01, 2048: 1.04 1.06.
     {"plane_per_group64_planes_k2", 1280, "... two sweeps or more, planes smaller than 64 x 64"},
-    //   64 x 64, K = 2:  512 planes 0.78 0.79, 1024: 0.90 0.97, 1280: 0.99 1.02, 2048: 1.04 1.06.
-    {"plane_per_group64_full_planes_k2", 1280, "... planes of 64 x 64, two sweeps"},
-    //            K = 3: 1536 planes 0.95 1.00, 2048: 0.99 1.03, 3072: 1.02 1.02, 4096: 1.04 1.08;
-    //            K = 4: 1536 planes 0.92 0.97, 2048: 0.97 1.02, 3072: 0.99 1.03, 8192: 1.03 1.04.
-    {"plane_per_group64_full_planes_k3", 2048, "... planes of 64 x 64, three or four sweeps"},
-    //            K = 5: 2048 planes 0.96 1.02, 4096: 1.01 1.04, 12 288: 1.02 1.04;
-    //            K = 8: 2048 planes 0.94 0.98, 4096: 0.98 1.02, 12 288: 1.00 1.01.
-    {"plane_per_group64_full_planes_k5", 4096, "... planes of 64 x 64, five sweeps or more"},
+    // Planes whose shorter side fills four fifths of 40, 48, 56 or 64 (pairs_2d_apply) go in one launch with two
+    // lanes a row beyond these counts (two waves a plane, four planes a CU: up to 1024 planes cost what one
+    // plane a CU costs, where this kernel pays a second round beyond 512).  This kernel / two lanes, N(0, 1),
+    // lambda 0.3 and 10^U(-1.3, 0), forward:
+    //   64 x 64, K = 2: 512 planes  46 /  57,  61 /  85,  640:  70 /  58,  88 /  81;
+    //            K = 4: 512 planes  78 /  97, 101 / 135,  640: 118 / 101, 150 / 136, 1024: 146 / 103, 187 / 138;
+    //            K = 8: 512 planes 135 / 169, 180 / 240,  640: 206 / 171, 258 / 235;
+    //   48 x 48, K = 4: 512 planes  69 /  79,  86 / 101,  640: 105 /  79, 131 / 102;
+    //   40 x 36, K = 4: 512 planes  62 /  81,  74 /  98,  640:  94 /  81, 114 /  98;
+    //   56 x 52, K = 4: 640 planes 109 / 117, 137 / 150,  896: 134 / 118, 170 / 155.
+    {"plane_per_group64_full_planes_k2", 512, "... planes that two lanes a row take over, two sweeps"},
+    {"plane_per_group64_full_planes_k3", 512, "... three or four sweeps"},
+    {"plane_per_group64_full_planes_k5", 512, "... five sweeps or more"},
     // 2D reverse sweep of small batches with a plane per workgroup (tv_plane2d.hpp): both adjoint
     // state tensors of the plane in LDS, 16 x 2 or 8 x 8 threads x samples per row, the segment
     // sums across a row's threads by row shifts.  Against the row-per-lane one-launch kernel (a
@@ -158,6 +164,16 @@ inline Threshold table[kCount] = {
     //   28 samples, 32 768 rows 11.8 / 12.3, 40 960: 13.2 / 12.9;                      columns, 24 576: 12.9 / 12.5
     //   32 samples, 32 768 rows 12.3 / 15.7, 49 152: 15.4 / 16.1 (lambda 0.3: 11.5 / 11.0); columns, 32 768: 13.5 / 14.8
     {"pair_1d_rows", 40960, "1D rows of 17-32 samples: two lanes a row beyond this many rows x (n - 12) / 20 (three quarters of it: strided rows)"},
+    // 1D calls on rows of 33-64 samples: beyond this many rows, times 1, 2, 3, 4 for rows of up to 40, 48, 56, 64
+    // samples (and three quarters of that for strided rows), two lanes a row instead of eight threads with
+    // 8 or 12 samples each: an elimination takes half the instructions of sums over blocks that cross
+    // threads, but a wave holds 32 rows and the longer halves chains of 32.  N(0, 1), lambda 0.3 / 1, forward,
+    // eight threads / two lanes:
+    //   40 samples, 16 384 rows  10 /  10,  14 /  17,   32 768:  14 /  11,  17 /  18,  524 288: 102 /  51, 148 /  74
+    //   48 samples, 32 768 rows  13 /  13,  18 /  19,  131 072:  32 /  25,  46 /  37,  524 288: 105 /  69, 152 /  98
+    //   56 samples, 32 768 rows  14 /  15,  19 /  23,  131 072:  32 /  28,  46 /  42,  524 288: 110 /  79, 158 / 113
+    //   64 samples, 65 536 rows  20 /  21,  28 /  30,  131 072:  32 /  35,  46 /  50,  524 288: 117 /  99, 165 / 144
+    {"pair_1d_long_rows", 24576, "1D rows of 33-64 samples: two lanes a row beyond this many rows x 1, 2, 3, 4 (up to 40, 48, 56, 64 samples; three quarters of it: strided rows)"},
     // 2D pass by pass with ONE lambda for all planes and three sweeps or more: sides up to this many
     // samples (768 at most, and beyond 64) are solved by tridiagonal elimination (tv_long_tri.hpp), not
     // by block means.  The slower one of the two is kept here for the sake of one number, the

@@ -1,5 +1,6 @@
 // Two neighbouring lanes per row, one from each end: projected Newton on the dual (paper Eq. 3-4) of
-// a row of at most 2 C samples, and the one-launch 2D forward built on it (planes of 17-32 a side).
+// a row of at most 2 C samples, and the kernels built on it: the one-launch 2D forward on planes of 17-64
+// samples a side, and the forward on large batches of rows of 17-64 samples.
 //
 // A row-per-lane solve (RowSolver, tv_short.hpp) keeps four arrays of a row's length in registers and
 // walks chains of that length.  Here the row is cut in the middle: the left lane holds samples 0 .. C-1,
@@ -40,19 +41,26 @@ __device__ __forceinline__ bool pair_either(bool p)
     return __builtin_amdgcn_inverse_ballot_w64(m | ((m >> 1) & even) | ((m & even) << 1));
 }
 
+template <int PADS>
+__device__ __forceinline__ float pair_masked(float v, uint32_t have, int k)
+{
+    return k >= PADS ? v : __uint_as_float(__float_as_uint(v) & (uint32_t)__builtin_amdgcn_sbfe((int)have, k, 1));
+}
+
 // Local sample i of a lane is sample i of its row (left lane) or 2C-1-i (right lane); local dual i lies
 // behind local sample i, towards the middle, and dual C-1 is the shared one.  Rows of fewer than 2C
 // samples: those past the end are 0, the dual behind the last one (`cut`, a local index, none if negative)
 // is held at 0, and bit i of `live` says that local dual i lies inside the row.  All that concerns local
 // indices below PADS only: PADS = 0, rows of exactly 2C samples; PADS = C, any.
-template <int C, int PADS>
+// STRIDE: between the parked samples of a lane (the threads of the workgroup).
+template <int C, int PADS, int STRIDE = 64>
 struct PairSolver {
     static constexpr bool FULL = PADS == 0;
     float X[C];         // x(u) for the current dual
     float u[C];         // the dual
     float D[C];         // g, then gamma * w, then the Newton direction
     float G[C];         // pivots gamma (0 exactly at bound duals; G[C-1]: 0 or 1), then the previous dual
-    const float *yl, *gtab;       // the parked input (sample i at yl[64 i]), gtab[j] = j / (j + 1)
+    const float *yl, *gtab;       // the parked input (sample i at yl[STRIDE i]), gtab[j] = j / (j + 1)
     float lam, fcur, alpha_try, gtol;
     uint32_t live;
     int cut, steps, flags, nfail;
@@ -70,7 +78,7 @@ struct PairSolver {
         if (k >= PADS) return lam;
         return __uint_as_float(__float_as_uint(lam) & (uint32_t)__builtin_amdgcn_sbfe((int)inside, k, 1));
     }
-    __device__ __forceinline__ float yk(int k) const { return yl[k * 64]; }
+    __device__ __forceinline__ float yk(int k) const { return yl[k * STRIDE]; }
     static __device__ __forceinline__ void reread() { asm volatile("" ::: "memory"); }
 
     // Two Gauss-Seidel sweeps on the dual, u_k <- clip((u_{k-1} + u_{k+1} + y_{k+1} - y_k) / 2): from both ends
@@ -129,15 +137,20 @@ struct PairSolver {
     {
         float sum = 0.f;
 #pragma unroll
-        for (int k = 0; k < C; ++k) sum += y[k];
+        for (int k = 0; k < C; ++k) {
+            sum -= y[k];
+            X[k] = sum;
+        }
         set_gtol(y);
-        const float ybar = (sum + pair_other(sum)) * inv_n;
-        float run = 0.f, rmax = 0.f;
+        const float ybar = -(sum + pair_other(sum)) * inv_n;
+        float run = 0.f, rmax = 0.f, past = 0.f;
 #pragma unroll
         for (int k = 0; k < C; ++k) {
-            const float m = k >= PADS ? ybar
-                                 : __uint_as_float(__float_as_uint(ybar) & (uint32_t)__builtin_amdgcn_sbfe((int)have, k, 1));
-            run += m - y[k];
+            if (PADS == 0) run = fmaf(ybar, (float)(k + 1), X[k]);      // sum over i <= k of ybar - y_i
+            else {
+                past += pair_masked<PADS>(ybar, have, k);
+                run = past + X[k];
+            }
             X[k] = run;
             rmax = fmaxf(rmax, fabsf(run));
         }
@@ -222,7 +235,8 @@ struct PairSolver {
             dec = fmaf(w, d, dec + pair_other(dec));
             D[C - 1] = d;
         }
-        if (active && !vio && dec <= fmaxf(kDecNoise * fcur, gtol * gtol)) {
+        const float small = C > 16 ? gtol * gtol : fmaxf(kDecNoise * fcur, gtol * gtol);
+        if (active && !vio && (C > 16 ? dec < small : dec <= small)) {
             active = false; flags = kInfoConverged;
         }
         if (active && it >= kMaxNewtonSteps) { active = false; flags = kInfoCapped; }
@@ -324,24 +338,34 @@ struct PairSolver {
 
     // Primal recovery: between two bound duals every sample takes the mean of the block's x.  The running
     // mean of a block needs no count: behind j free duals it takes 1 / (j + 1) of the new sample, and the
-    // pivot in G is j / (j + 1) (0 where a block begins, whose first sample is then taken as it is).
+    // pivot in G is j / (j + 1) (0 where a block begins, whose first sample is then taken as it is).  It is kept
+    // as its distance from the sample, off: x is constant on a block up to rounding, so those distances are
+    // exact and small, and the mean is rounded once.
     // (Instead of the value of one sample: planes of 32 x 32, N(0, 1), K = 3, error against 64 bits 3.1e-7 ->
-    // 9e-8, for two more instructions a sample and solve.)
+    // 9e-8.  A running mean that is rounded at every sample, two instructions a sample less, is 8-30 % further
+    // off on rows of a few long blocks.)
     __device__ __forceinline__ void recover(float (&xs)[C])
     {
-        float mean = X[0];
-        xs[0] = mean;
+        // (made opaque: the differences below are those of the last look, and the compiler would keep them, C
+        // more registers, through everything in between)
+#pragma unroll
+        for (int k = 0; k < C; ++k) asm volatile("" : "+v"(X[k]));
+        float off = 0.f;
+        xs[0] = X[0];
 #pragma unroll
         for (int k = 1; k < C; ++k) {
-            mean = fmaf(G[k - 1], mean - X[k], X[k]);
-            xs[k] = mean;
+            off = G[k - 1] * (off + (X[k - 1] - X[k]));
+            xs[k] = X[k] + off;
         }
         // the block around the middle: both lanes form the mean of its parts from the left lane's side
+        float mean;
         {
             const float part = C > 1 ? 1.f - G[C - 2] : 1.f;            // 1 / samples of the lane's part
-            const float ml = pair_left(mean), mr = pair_right(mean), pl = pair_left(part), pr = pair_right(part);
-            const float both = fmaf(mr - ml, pl * __builtin_amdgcn_rcpf(pl + pr), ml);
-            mean = G[C - 1] == 0.f ? mean : both;
+            const float xl = pair_left(X[C - 1]), ol = pair_left(off), pl = pair_left(part);
+            const float xr = pair_right(X[C - 1]), orr = pair_right(off), pr = pair_right(part);
+            const float apart = (xr - xl) + (orr - ol);
+            const float both = xl + fmaf(apart, pl * __builtin_amdgcn_rcpf(pl + pr), ol);
+            mean = G[C - 1] == 0.f ? xs[C - 1] : both;
         }
         xs[C - 1] = mean;
 #pragma unroll
@@ -388,15 +412,34 @@ __device__ __forceinline__ uint2 pair_segment_code(const float (&xs)[C], int n, 
     return make_uint2(jm, rises);
 }
 
-// A wave's tile of 32 rows: samples 0 .. C-1 of a row in order, the others from the row's end, 16 places
-// on, so that either lane of a pair finds its half at offsets known at compile time.  With pitch 33 the
-// 16 rows that half a wave works on cover 16 banks, and their other halves the other 16.
-constexpr int kPairPitch = 33;
+// The tile in LDS: samples 0 .. C-1 of a row in order, the others from the row's end, HALF places on, so
+// that either lane of a pair finds its half at offsets known at compile time.  With HALF = 16 the 16 rows
+// that half a wave works on cover 16 banks, and their other halves the other 16.  (HALF = 32: two by two
+// the same; the tile is crossed twice a pass, the solve in between reads lane-private columns.)
 template <int C>
-__device__ __forceinline__ int pair_place(int k) { return k < C ? k : 15 + 2 * C - k; }
-// step between neighbouring samples of the tile from sample k on (groups of four that the middle does not split)
+struct PairTile {
+    static constexpr int HALF = C <= 16 ? 16 : 32, PITCH = 2 * HALF + 1;
+    static_assert(C >= 2 && C <= 32, "rows of at most 64 samples");
+    __device__ static __forceinline__ int place(int k) { return k < C ? k : HALF + 2 * C - 1 - k; }
+    // step between neighbouring samples from sample k on (groups of four that the middle does not split)
+    __device__ static __forceinline__ int step(int k) { return k < C ? 1 : -1; }
+};
+
+// gtab: pivots j / (j + 1) of a free run, from memory (a division a wave is 2 % of a short solve)
+struct PairPivots {
+    float g[34];
+    constexpr PairPivots() : g()
+    {
+        for (int j = 0; j < 34; ++j) g[j] = (float)j / (float)(j + 1);
+    }
+};
+static __device__ const PairPivots pair_pivots;
 template <int C>
-__device__ __forceinline__ int pair_step(int k) { return k < C ? 1 : -1; }
+__device__ __forceinline__ void pair_fill_table(float *gtab, int tid)
+{
+    static_assert(C < 34, "");
+    if (tid <= C) gtab[tid] = pair_pivots.g[tid];
+}
 
 // Which of a lane's samples exist in a row of n (bit i: local sample i), the local index of the dual
 // behind the row's last sample, and the duals inside the row (PairSolver::live).
@@ -404,92 +447,97 @@ template <int C>
 __device__ __forceinline__ uint32_t pair_samples(int n, bool right)
 {
     const int pads = 2 * C - n;                 // (the right lane's from its end, then the left lane's from the middle)
-    return right ? ~((1u << (pads < C ? pads : C)) - 1u) : (n < C ? (1u << n) - 1u : ~0u);
+    if (right) return pads < C ? ~0u << pads : 0u;
+    return n < C ? (1u << n) - 1u : ~0u;
 }
 template <int C>
 __device__ __forceinline__ int pair_cut(int n, bool right) { return right ? 2 * C - 1 - n : n - 1; }
 __device__ __forceinline__ uint32_t pair_live(int cut, bool right)
 {
-    if (right) return cut < 0 ? ~0u : ~0u << (cut + 1);         // (cut < 31)
-    return (1u << cut) - 1u;
-}
-template <int PADS>
-__device__ __forceinline__ float pair_masked(float v, uint32_t have, int k)
-{
-    return k >= PADS ? v : __uint_as_float(__float_as_uint(v) & (uint32_t)__builtin_amdgcn_sbfe((int)have, k, 1));
+    if (right) return cut < 31 ? ~0u << (cut + 1) : 0u;
+    return cut < 32 ? (1u << cut) - 1u : ~0u;
 }
 
 // ---------------------------------------------------------------------------------
-// Forward: K sweeps of paper Alg. 1 in one launch, a plane of at most 2C x 2C per wave.
+// Forward: K sweeps of paper Alg. 1 in one launch, a plane of at most 2C x 2C per wave (C <= 16) or per
+// workgroup of two waves.
 //
 // A row pass gives a pair of lanes a row of the plane, a column pass a column.  The plane changes hands
-// between passes through one LDS tile, whose rows and columns both lie as pair_place has them.  As in
+// between passes through one LDS tile, whose rows and columns both lie as PairTile has them.  As in
 // tv2d_fwd_small_kernel the tile also parks the solver's input, and the correction term that is not in
-// use lives in a lane-private LDS column.
+// use lives in a lane-private LDS column.  Planes of at most 32 x 32 leave segment codes for the reverse
+// sweep, larger ones their pass outputs.
+// Registers: four waves a SIMD up to 32 x 32 (a fifth, at 96 registers, spills and is 10 % slower), two beyond,
+// where LDS holds no more (33 KB a plane).
 // ---------------------------------------------------------------------------------
 template <int C, int PADS, bool IO16 = false>
-__global__ __launch_bounds__(64, 4) void tv2d_fwd_pair_kernel(Small2dFwdParams p)
+__global__ __launch_bounds__(C > 16 ? 128 : 64, C > 16 ? 2 : 4) void tv2d_fwd_pair_kernel(Small2dFwdParams p)
 {
+    using Tile = PairTile<C>;
     constexpr bool FULL = PADS == 0;
-    static_assert(C <= 16 && C >= 2, "planes of at most 32 x 32");
-    constexpr int P = kPairPitch;
-    __shared__ float T1[32 * P], T2[64 * C], gtab[34], rtab[34];
-    static_assert(64 * C <= 32 * P, "the parked input fits the tile");
-    const int lane = threadIdx.x;
-    fill_tables<32>(gtab, rtab);
-    const int H = FULL ? 2 * C : p.H, W = FULL ? 2 * C : p.W, HW = H * W;
+    constexpr int HO = Tile::HALF, P = Tile::PITCH, S = 2 * C, NT = 4 * HO;
+    static_assert(!IO16 || C <= 16, "bf16 storage: planes of at most 32 x 32");
+    __shared__ float T1[2 * HO * P], T2[NT * C], gtab[C + 2];
+    static_assert(NT * C <= 2 * HO * P, "the parked input fits the tile");
+    const int tid = threadIdx.x;
+    pair_fill_table<C>(gtab, tid);
+    const int H = FULL ? S : p.H, W = FULL ? S : p.W, HW = H * W;
     const int64_t plane = blockIdx.x;
     const float lam = fmaxf(p.lam[plane % p.lam_count], 0.f);
+    auto sync = []() { if (C > 16) __syncthreads(); else wave_lds_sync(); };
 
-    auto place = [](int k) { return pair_place<C>(k); };
-    const int at = lane >> 1;                       // the pair's row or column, by place
-    const bool right = (lane & 1) != 0;
-    const int idx = at < 16 ? at : 15 + 2 * C - at;
-    const bool in_half = (at & 15) < C;
-    float *by_row = T1 + at * P + (right ? 16 : 0);             // step 1
-    float *by_col = T1 + (right ? 16 : 0) * P + at;             // step P
-    float *park = T1 + lane, *mine = T2 + lane;                 // step 64
+    auto place = [](int k) { return Tile::place(k); };          // of row or column k in the tile
+    const int at = tid >> 1;                        // the pair's row or column, by place
+    const bool right = (tid & 1) != 0;
+    const int idx = at < HO ? at : HO + S - 1 - at;
+    const bool in_half = (at & (HO - 1)) < C;
+    float *by_row = T1 + at * P + (right ? HO : 0);             // step 1
+    float *by_col = T1 + (right ? HO : 0) * P + at;             // step P
+    float *park = T1 + tid, *mine = T2 + tid;                   // step NT
 
-    // memory <-> tile: sample e = lane, lane + 64, ... of the plane
+    // memory <-> tile: sample e = tid, tid + NT, ... of the plane
     auto each_sample = [&](auto &&f) {
-        int r = lane / W, c = lane - r * W;
-        const int dq = 64 / W, dr = 64 - dq * W;
-        for (int e = lane; e < HW; e += 64) {
+        int r = tid / W, c = tid - r * W;
+        const int dq = NT / W, dr = NT - dq * W;
+        for (int e = tid; e < HW; e += NT) {
             f(e, T1 + place(r) * P + place(c));
             r += dq; c += dr;
             if (c >= W) { c -= W; r += 1; }
         }
     };
     auto plane_in = [&](auto &&load) {
-        constexpr int N = (4 * C * C + 63) / 64;
+        constexpr int N = (S * S + NT - 1) / NT;
         float q[N];                                 // every load is issued before the first is waited for
 #pragma unroll
-        for (int i = 0; i < N; ++i) q[i] = i * 64 + lane < HW ? load(i * 64 + lane) : 0.f;
-        int r = lane / W, c = lane - r * W;
-        const int dq = 64 / W, dr = 64 - dq * W;
+        for (int i = 0; i < N; ++i) q[i] = i * NT + tid < HW ? load(i * NT + tid) : 0.f;
+        int r = tid / W, c = tid - r * W;
+        const int dq = NT / W, dr = NT - dq * W;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            if (i * 64 + lane < HW) T1[place(r) * P + place(c)] = q[i];
+            if (i * NT + tid < HW) T1[place(r) * P + place(c)] = q[i];
             r += dq; c += dr;
             if (c >= W) { c -= W; r += 1; }
         }
     };
-    // four samples of a row from column c on, c a multiple of 4, in planes of 32 x 32
-    auto four = [&](int e) { return T1 + place(e >> 5) * P + place(e & 31); };
-    constexpr bool QUADS = FULL && C == 16;
+    // four samples of a row from sample e of the plane on, e a multiple of 4
+    auto four = [&](int e) { return T1 + place(e / S) * P + place(e % S); };
+    constexpr bool QUADS = FULL && C == HO;
+    constexpr int N4 = S * S / 4 / NT;
     if constexpr (IO16) {
         const uint16_t *src = reinterpret_cast<const uint16_t *>(p.y) + plane * HW;
         plane_in([&](int e) { return bf16_bits_to_f32(src[e]); });
     } else {
         const float *src = p.y + plane * HW;
         if (QUADS && ((uintptr_t)src % 16) == 0) {
+            float4 q[N4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int e = (i * 64 + lane) * 4;
-                const float4 q = load16(src + e, p.stream != 0);
+            for (int i = 0; i < N4; ++i) q[i] = load16(src + (i * NT + tid) * 4, p.stream != 0);
+#pragma unroll
+            for (int i = 0; i < N4; ++i) {
+                const int e = (i * NT + tid) * 4;
                 float *d = four(e);
-                const int s = (e & 31) < 16 ? 1 : -1;
-                d[0] = q.x; d[s] = q.y; d[2 * s] = q.z; d[3 * s] = q.w;
+                const int s = Tile::step(e % S);
+                d[0] = q[i].x; d[s] = q[i].y; d[2 * s] = q[i].z; d[3 * s] = q[i].w;
             }
         } else {
             plane_in([&](int e) { return src[e]; });
@@ -497,20 +545,20 @@ __global__ __launch_bounds__(64, 4) void tv2d_fwd_pair_kernel(Small2dFwdParams p
     }
     auto put_plane = [&](float *dst) {
         if (QUADS && ((uintptr_t)dst % 16) == 0) {
-            int own = lane;
+            int own = tid;
             asm volatile("" : "+v"(own));           // (addresses formed here, not kept through the solves)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int e = (i * 64 + own) * 4;
+            for (int i = 0; i < N4; ++i) {
+                const int e = (i * NT + own) * 4;
                 const float *d = four(e);
-                const int s = (e & 31) < 16 ? 1 : -1;
+                const int s = Tile::step(e % S);
                 store16(dst + e, make_float4(d[0], d[s], d[2 * s], d[3 * s]), p.stream != 0);
             }
         } else {
             each_sample([&](int e, const float *d) { dst[e] = *d; });
         }
     };
-    wave_lds_sync();
+    sync();
 
     auto samples = [&](int n) -> uint32_t { return FULL ? ~0u : pair_samples<C>(n, right); };
     auto masked = [](float v, uint32_t have, int k) { return pair_masked<PADS>(v, have, k); };
@@ -525,19 +573,19 @@ __global__ __launch_bounds__(64, 4) void tv2d_fwd_pair_kernel(Small2dFwdParams p
     const int n_pass = 2 * p.sweeps;
     for (int i = 0; i < n_pass; ++i) {
         const bool col = (i & 1) != 0;
-        wave_lds_sync();                            // every lane has taken its input out of the tile
+        sync();                            // every lane has taken its input out of the tile
 #pragma unroll
-        for (int k = 0; k < C; ++k) park[k * 64] = v[k];
-        wave_lds_sync();
+        for (int k = 0; k < C; ++k) park[k * NT] = v[k];
+        sync();
 
-        PairSolver<C, PADS> sv;
+        PairSolver<C, PADS, NT> sv;
         float xs[C];
         sv.yl = park; sv.gtab = gtab; sv.lam = lam;
         if constexpr (!FULL) {
             sv.cut = pair_cut<C>(n, right);
             sv.live = pair_live(sv.cut, right);
         }
-        if (i < 2) sv.start(v, rtab[n], have);
+        if (i < 2) sv.start(v, __builtin_amdgcn_rcpf((float)n), have);
         else {
 #pragma unroll
             for (int k = 0; k < C; ++k) sv.u[k] = u0[k];
@@ -546,7 +594,7 @@ __global__ __launch_bounds__(64, 4) void tv2d_fwd_pair_kernel(Small2dFwdParams p
         sv.solve(valid);
         sv.recover(xs);
 
-        {
+        if constexpr (C <= 16) {
             const uint2 code = pair_segment_code<C, FULL>(xs, n, right);
             if (valid) {
                 uint32_t *to = reinterpret_cast<uint32_t *>(p.codes + (size_t)i * p.code_stride + (size_t)plane * (col ? W : H) + idx);
@@ -557,8 +605,8 @@ __global__ __launch_bounds__(64, 4) void tv2d_fwd_pair_kernel(Small2dFwdParams p
         const bool keep = i + 2 < n_pass;
         float corr[C];
 #pragma unroll
-        for (int k = 0; k < C; ++k) corr[k] = park[k * 64] - xs[k];
-        wave_lds_sync();
+        for (int k = 0; k < C; ++k) corr[k] = park[k * NT] - xs[k];
+        sync();
         if (col) {
 #pragma unroll
             for (int k = 0; k < C; ++k) by_col[k * P] = xs[k];
@@ -566,8 +614,8 @@ __global__ __launch_bounds__(64, 4) void tv2d_fwd_pair_kernel(Small2dFwdParams p
 #pragma unroll
             for (int k = 0; k < C; ++k) by_row[k] = xs[k];
         }
-        wave_lds_sync();
-        if (p.keep_passes) put_plane(p.saved + (size_t)i * p.saved_stride + plane * HW);
+        sync();
+        if (C > 16 || p.keep_passes) put_plane(p.saved + (size_t)i * p.saved_stride + plane * HW);
         // input of the next pass: this output seen the other way plus that direction's correction
         // term, whose negated running sum is the dual to start from
         valid = in_half && (FULL || idx < (col ? H : W));
@@ -585,7 +633,7 @@ __global__ __launch_bounds__(64, 4) void tv2d_fwd_pair_kernel(Small2dFwdParams p
             float run = 0.f;
 #pragma unroll
             for (int k = 0; k < C; ++k) {
-                const float c = mine[k * 64];
+                const float c = mine[k * NT];
                 t[k] += c;
                 run -= c;
                 u0[k] = run;
@@ -596,7 +644,7 @@ __global__ __launch_bounds__(64, 4) void tv2d_fwd_pair_kernel(Small2dFwdParams p
         }
         if (keep) {
 #pragma unroll
-            for (int k = 0; k < C; ++k) mine[k * 64] = corr[k];
+            for (int k = 0; k < C; ++k) mine[k * NT] = corr[k];
         }
 #pragma unroll
         for (int k = 0; k < C; ++k) v[k] = t[k];
@@ -613,7 +661,9 @@ __global__ __launch_bounds__(64, 4) void tv2d_fwd_pair_kernel(Small2dFwdParams p
 // Forward on a batch of rows, 32 to a wave: plain calls (input y, output x, optionally info words and
 // segment codes).  Grid and tiles: TileMap with tiles of 32 rows.
 // MODE: how the rows lie in memory.  kPairPacked: row r starts n r samples after the base; a wave's rows are
-// moved through the tile with coalesced accesses (kPairPacked4: of 16 bytes).  kPairPlane: the rows are the columns of contiguous 32 x 32
+// moved through the tile as one block.  kPairPacked4: the same for multiples of 8 samples, 16-byte aligned,
+// whose rows start on a quarter of the banks or less: the tile has the rows by place (rows of 56, most of them
+// done at once, 103 -> 79 us).  kPairPlane: the rows are the columns of contiguous 32 x 32
 // planes, a plane a wave.  kPairStrided: anything else, read and written sample by sample.  (PADS < C:
 // n > 2C - 1 - PADS.)
 // IO16: y and x are bf16 (packed rows of 32).
@@ -621,24 +671,26 @@ __global__ __launch_bounds__(64, 4) void tv2d_fwd_pair_kernel(Small2dFwdParams p
 constexpr int kPairStrided = 0, kPairPacked = 1, kPairPlane = 2, kPairPacked4 = 3;
 
 template <int C, int PADS, int MODE, bool IO16 = false>
-__global__ __launch_bounds__(64, 4) void tv1d_fwd_pair_kernel(FwdParams p)
+__global__ __launch_bounds__(64, C > 16 ? 3 : 4) void tv1d_fwd_pair_kernel(FwdParams p)
 {
-    constexpr int P = kPairPitch;
+    using Tile = PairTile<C>;
+    constexpr int P = Tile::PITCH, HO = Tile::HALF;
     constexpr bool FULL = PADS == 0;
     constexpr bool WHOLE = FULL && C == 16;         // rows of exactly 32
     static_assert(MODE != kPairPlane || WHOLE, "plane columns: 32 x 32 planes");
     static_assert(!IO16 || (WHOLE && MODE == kPairPacked4), "bf16 storage: packed rows of 32");
+    static_assert(MODE != kPairPacked4 || (FULL && C % 4 == 0), "the middle splits no group of four");
     __shared__ __align__(16) float tile[MODE == kPairStrided ? 64 * C : 32 * P];
-    __shared__ float gtab[34], rtab[34];
+    __shared__ float gtab[C + 2];
     const int lane = threadIdx.x;
-    fill_tables<32>(gtab, rtab);
+    pair_fill_table<C>(gtab, lane);
 
     const uint32_t slot = p.order ? min(p.order[blockIdx.y], gridDim.y - 1u) : blockIdx.y;
     const uint32_t r0 = p.tm.first<32>(__builtin_amdgcn_readfirstlane(blockIdx.x), slot);
     const int at = lane >> 1;
     const bool right = (lane & 1) != 0;
     // (plane columns lie in the tile by place, like the planes' rows)
-    const uint32_t row = p.tm.row(r0, (uint32_t)(MODE == kPairPlane ? pair_place<16>(at) : at));
+    const uint32_t row = p.tm.row(r0, (uint32_t)(MODE == kPairPlane ? PairTile<16>::place(at) : at));
     const bool valid = row < p.L.n_rows;
     const int n = FULL ? 2 * C : p.L.n;
     float lam = 0.f;
@@ -648,9 +700,9 @@ __global__ __launch_bounds__(64, 4) void tv1d_fwd_pair_kernel(FwdParams p)
     const bool stream = p.L.stream != 0;
 
     // the lane's samples in the tile (kPairPacked: the right lane's backwards from place 2C - 1 of its row)
-    float *half = MODE == kPairPlane    ? tile + (right ? 16 * P : 0) + at
+    float *half = MODE == kPairPlane    ? tile + (right ? HO * P : 0) + at
                   : MODE == kPairPacked ? tile + at * n + (right ? 2 * C - 1 : 0)
-                                        : tile + at * P + (right ? 16 : 0);
+                                        : tile + at * P + (right ? HO : 0);
     const int half_step = MODE == kPairPlane ? P : (MODE == kPairPacked && right ? -1 : 1);
     float *park = tile + lane;
 
@@ -672,30 +724,22 @@ __global__ __launch_bounds__(64, 4) void tv1d_fwd_pair_kernel(FwdParams p)
         }
     };
     const bool all_there = p.tm.row(r0, 31u) < p.L.n_rows;
+    // (rows of 32 or 64: an access of the wave covers RP whole rows, which lie together where a lambda's rows do)
+    constexpr int RP = 128 / C, LR = C / 2;         // rows an access, lanes a row
+    const bool whole_rows = FULL && (C == 16 || C == 32) && all_there && (1u << p.tm.lg) >= (uint32_t)RP;
+    auto rows_at = [&](int i) { return (size_t)__builtin_amdgcn_readfirstlane(p.tm.row(r0, (uint32_t)(i * RP))) * (2 * C); };
     // kPairPacked: the wave's rows lie in the tile as in memory, one block of samples
     const int total = MODE == kPairPacked ? (int)min(32u, p.L.n_rows - r0) * n : 0;
     const bool aligned = MODE == kPairPacked && all_there && ((uintptr_t)p.y | (uintptr_t)p.x) % 16 == 0;
-    // (C = 10, 14: the middle splits a group of four)
     auto put4 = [&](int r, int c, const float4 &q) {
-        float *d = tile + r * P;
-        if constexpr (C % 4 == 0) {
-            const int s = pair_step<C>(c);
-            d += pair_place<C>(c);
-            d[0] = q.x; d[s] = q.y; d[2 * s] = q.z; d[3 * s] = q.w;
-        } else {
-            d[pair_place<C>(c)] = q.x; d[pair_place<C>(c + 1)] = q.y;
-            d[pair_place<C>(c + 2)] = q.z; d[pair_place<C>(c + 3)] = q.w;
-        }
+        float *d = tile + r * P + Tile::place(c);
+        const int s = Tile::step(c);
+        d[0] = q.x; d[s] = q.y; d[2 * s] = q.z; d[3 * s] = q.w;
     };
     auto get4 = [&](int r, int c) {
-        const float *d = tile + r * P;
-        if constexpr (C % 4 == 0) {
-            const int s = pair_step<C>(c);
-            d += pair_place<C>(c);
-            return make_float4(d[0], d[s], d[2 * s], d[3 * s]);
-        } else {
-            return make_float4(d[pair_place<C>(c)], d[pair_place<C>(c + 1)], d[pair_place<C>(c + 2)], d[pair_place<C>(c + 3)]);
-        }
+        const float *d = tile + r * P + Tile::place(c);
+        const int s = Tile::step(c);
+        return make_float4(d[0], d[s], d[2 * s], d[3 * s]);
     };
     // plane columns: the plane's samples 4 (i * 64 + lane) ..
     const int64_t plane_at = MODE == kPairPlane ? (int64_t)(r0 >> 5) * p.L.outer_stride : 0;
@@ -716,7 +760,7 @@ __global__ __launch_bounds__(64, 4) void tv1d_fwd_pair_kernel(FwdParams p)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int e = (i * 64 + lane) * 4;
-                put4(pair_place<16>(e >> 5), e & 31, q[i]);
+                put4(PairTile<16>::place(e >> 5), e & 31, q[i]);
             }
         } else if constexpr (IO16) {
             const uint16_t *src = reinterpret_cast<const uint16_t *>(p.y);
@@ -727,8 +771,8 @@ __global__ __launch_bounds__(64, 4) void tv1d_fwd_pair_kernel(FwdParams p)
                 if (g >= p.L.n_rows) continue;
                 const float4 q = load16(reinterpret_cast<const float *>(src + (size_t)g * 32 + (e & 31)), stream);
                 const uint32_t w[4] = {__float_as_uint(q.x), __float_as_uint(q.y), __float_as_uint(q.z), __float_as_uint(q.w)};
-                float *d = tile + (e >> 5) * P + pair_place<C>(e & 31);
-                const int s = pair_step<C>(e & 31);
+                float *d = tile + (e >> 5) * P + Tile::place(e & 31);
+                const int s = Tile::step(e & 31);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     d[2 * j * s] = __uint_as_float(w[j] << 16);
@@ -737,8 +781,15 @@ __global__ __launch_bounds__(64, 4) void tv1d_fwd_pair_kernel(FwdParams p)
             }
         } else if constexpr (MODE == kPairPacked4) {
             float4 q[(C + 3) / 4];                  // (every load is issued before the first is waited for)
-            move_fours([&](int i, size_t a, int, int) { q[i] = load16(p.y + a, stream); });
-            move_fours([&](int i, size_t, int r, int c) { put4(r, c, q[i]); });
+            if (whole_rows) {
+#pragma unroll
+                for (int i = 0; i < C / 4; ++i) q[i] = load16(p.y + rows_at(i) + lane * 4, stream);
+#pragma unroll
+                for (int i = 0; i < C / 4; ++i) put4(i * RP + lane / LR, lane % LR * 4, q[i]);
+            } else {
+                move_fours([&](int i, size_t a, int, int) { q[i] = load16(p.y + a, stream); });
+                move_fours([&](int i, size_t, int r, int c) { put4(r, c, q[i]); });
+            }
         } else {
             const float *blk = p.y + (size_t)r0 * n;
             if (aligned) {
@@ -777,13 +828,13 @@ __global__ __launch_bounds__(64, 4) void tv1d_fwd_pair_kernel(FwdParams p)
         sv.cut = pair_cut<C>(n, right);
         sv.live = pair_live(sv.cut, right);
     }
-    sv.start(y, rtab[n], have);
+    sv.start(y, __builtin_amdgcn_rcpf((float)n), have);
     sv.solve(valid);
     float xs[C];
     sv.recover(xs);
 
     if (p.info && valid && !right) p.info[row] = sv.steps | sv.flags;
-    if (p.seg) {
+    if constexpr (C <= 16) if (p.seg) {
         const uint2 code = pair_segment_code<C, FULL>(xs, n, right);
         if (valid) reinterpret_cast<uint32_t *>(p.seg + row)[right ? 1 : 0] = right ? code.y : code.x;
     }
@@ -804,7 +855,7 @@ __global__ __launch_bounds__(64, 4) void tv1d_fwd_pair_kernel(FwdParams p)
             int own = lane;
             asm volatile("" : "+v"(own));
             const int e = (i * 64 + own) * 4;
-            const float4 q = get4(pair_place<16>(e >> 5), e & 31);
+            const float4 q = get4(PairTile<16>::place(e >> 5), e & 31);
             if (plane_there) store16(p.x + plane_at + e, q, stream);
         }
     } else if constexpr (IO16) {
@@ -814,8 +865,8 @@ __global__ __launch_bounds__(64, 4) void tv1d_fwd_pair_kernel(FwdParams p)
             const int e = (i * 64 + lane) * 8;
             const uint32_t g = p.tm.row(r0, (uint32_t)e >> 5);
             if (g >= p.L.n_rows) continue;
-            const float *d = tile + (e >> 5) * P + pair_place<C>(e & 31);
-            const int s = pair_step<C>(e & 31);
+            const float *d = tile + (e >> 5) * P + Tile::place(e & 31);
+            const int s = Tile::step(e & 31);
             uint32_t w[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) w[j] = f32x2_to_bf16x2(d[2 * j * s], d[(2 * j + 1) * s]);
@@ -823,7 +874,13 @@ __global__ __launch_bounds__(64, 4) void tv1d_fwd_pair_kernel(FwdParams p)
                     make_float4(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]), __uint_as_float(w[3])), stream);
         }
     } else if constexpr (MODE == kPairPacked4) {
-        if (all_there) move_fours([&](int, size_t a, int r, int c) { store16(p.x + a, get4(r, c), stream); });
+        if (whole_rows) {
+            int own = lane;
+            asm volatile("" : "+v"(own));
+#pragma unroll
+            for (int i = 0; i < C / 4; ++i)
+                store16(p.x + rows_at(i) + own * 4, get4(i * RP + own / LR, own % LR * 4), stream);
+        } else if (all_there) move_fours([&](int, size_t a, int r, int c) { store16(p.x + a, get4(r, c), stream); });
         else move_fours([&](int, size_t a, int r, int c) {
             if (p.tm.row(r0, (uint32_t)r) < p.L.n_rows) store16(p.x + a, get4(r, c), stream);
         });

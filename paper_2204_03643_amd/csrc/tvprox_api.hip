@@ -217,11 +217,13 @@ int launch_bwd_short(const BwdParams &p, bool packed_ok, hipStream_t s, bool pla
                  : launch_bwd_short<NMAX, false, false>(p, packed_ok, s, plane_ok, ragged_ok);
 }
 
-// Rows of 17-32 samples, plain calls: two lanes a row (tv_pair.hpp), halves of 10, 12, 14 or 16 samples.
+// Rows of 17-64 samples, plain calls: two lanes a row (tv_pair.hpp), halves of 10, 12, 14, 16, 20, 24, 28 or 32
+// samples.
 int launch_fwd_pairs(FwdParams p, const tv_rows &r, const tv_lambda &l, int64_t n_rows, hipStream_t s)
 {
     const int n = p.L.n;
-    const bool packed = rows_packed(r), quads = packed && n % 4 == 0 && aligned16(p.y) && aligned16(p.x);
+    const bool packed = rows_packed(r);
+    const bool quads = packed && n % 8 == 0 && aligned16(p.y) && aligned16(p.x);
     const bool planes = rows_are_plane_columns(r) && aligned16(p.y) && aligned16(p.x);
     // (packed rows of other lengths move as one block: rows in natural order)
     p.tm = packed && !quads ? tvk::TileMap{6u, 0u, 0u, 1u} : make_tile_map(l, n_rows, 32);
@@ -237,25 +239,42 @@ int launch_fwd_pairs(FwdParams p, const tv_rows &r, const tv_lambda &l, int64_t 
         hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<16, 0, tvk::kPairPlane>), grid, block, 0, s, p);
         return launch_status();
     }
-#define TV_PAIR(C)                                                                                                                  \
+#define TV_PAIR(C, PADS)                                                                                                            \
     if (n <= 2 * C) {                                                                                                               \
-        if (quads) hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<C, 0, tvk::kPairPacked4>), grid, block, 0, s, p);                  \
-        else if (packed) hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<C, 3, tvk::kPairPacked>), grid, block, 0, s, p);             \
-        else if (n == 2 * C) hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<C, 0, tvk::kPairStrided>), grid, block, 0, s, p);        \
-        else hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<C, 3, tvk::kPairStrided>), grid, block, 0, s, p);                        \
+        if constexpr (C % 4 == 0)                                                                                                   \
+            if (quads) {                                                                                                            \
+                hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<C, 0, tvk::kPairPacked4>), grid, block, 0, s, p);                     \
+                return launch_status();                                                                                             \
+            }                                                                                                                       \
+        if (n == 2 * C) {                                                                                                           \
+            if (packed) hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<C, 0, tvk::kPairPacked>), grid, block, 0, s, p);              \
+            else hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<C, 0, tvk::kPairStrided>), grid, block, 0, s, p);                    \
+        } else {                                                                                                                    \
+            if (packed) hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<C, PADS, tvk::kPairPacked>), grid, block, 0, s, p);           \
+            else hipLaunchKernelGGL((tvk::tv1d_fwd_pair_kernel<C, PADS, tvk::kPairStrided>), grid, block, 0, s, p);                 \
+        }                                                                                                                           \
         return launch_status();                                                                                                     \
     }
-    TV_PAIR(10) TV_PAIR(12) TV_PAIR(14) TV_PAIR(16)
+    TV_PAIR(10, 3) TV_PAIR(12, 3) TV_PAIR(14, 3) TV_PAIR(16, 3) TV_PAIR(20, 7) TV_PAIR(24, 7) TV_PAIR(28, 7) TV_PAIR(32, 7)
 #undef TV_PAIR
     return TV_ERR_UNSUPPORTED;
 }
 
-// Planes of 17-32 samples a side, two lanes a row (tv_pair.hpp): halves of 10, 12, 14 or 16 samples.
+// Rows of 33-64 samples: two lanes a row beyond this many rows (tv_dispatch.hpp; halves of 20, 24, 28 and 32
+// samples: chains, and a wave's time alone, grow with the half).
+int64_t pair_long_rows(const tv_rows &r)
+{
+    const int64_t quarters = (r.length + 7) / 8 - 4;        // 1 .. 4
+    const int64_t most = tvd::get(tvd::kPair1dLongRows) * quarters;
+    return r.elem_stride != 1 ? most / 4 * 3 : most;
+}
+
+// Planes of 17-64 samples a side, two lanes a row (tv_pair.hpp): halves as above.
 template <bool IO16>
 int launch_fwd_pairs_2d(const tvk::Small2dFwdParams &q, hipStream_t stream)
 {
     const int longer = q.H > q.W ? q.H : q.W, shorter = q.H > q.W ? q.W : q.H;
-    const dim3 grid((uint32_t)q.planes), block(64);
+    const dim3 grid((uint32_t)q.planes), block(longer <= 32 ? 64 : 128);
 #define TV_PAIR(C)                                                                                                              \
     if (longer <= 2 * C) {                                                                                                      \
         if (shorter == 2 * C) hipLaunchKernelGGL((tvk::tv2d_fwd_pair_kernel<C, 0, IO16>), grid, block, 0, stream, q);           \
@@ -264,6 +283,14 @@ int launch_fwd_pairs_2d(const tvk::Small2dFwdParams &q, hipStream_t stream)
         return launch_status();                                                                                                 \
     }
     TV_PAIR(10) TV_PAIR(12) TV_PAIR(14) TV_PAIR(16)
+#undef TV_PAIR
+#define TV_PAIR(C)                                                                                                              \
+    if (longer <= 2 * C) {                                                                                                      \
+        if (shorter == 2 * C) hipLaunchKernelGGL((tvk::tv2d_fwd_pair_kernel<C, 0>), grid, block, 0, stream, q);                 \
+        else hipLaunchKernelGGL((tvk::tv2d_fwd_pair_kernel<C, C>), grid, block, 0, stream, q);                                  \
+        return launch_status();                                                                                                 \
+    }
+    if constexpr (!IO16) { TV_PAIR(20) TV_PAIR(24) TV_PAIR(28) TV_PAIR(32) }
 #undef TV_PAIR
     return TV_ERR_UNSUPPORTED;
 }
@@ -638,7 +665,7 @@ int run_fwd(const float *y, const float *addend, float *x, float *resid, int32_t
                         (!addend || aligned16(addend)) && (!resid || aligned16(resid));
     const bool ragged = rows_packed(r);
     if (psearch) return launch_fwd_short<32>(p, packed, s);     // every length up to 32
-    if (r.length > 16 && r.length <= 32 && !addend && !resid && !x2)
+    if (r.length > 16 && !addend && !resid && !x2 && (r.length <= 32 || (r.length <= 64 && n_rows > pair_long_rows(r))))
         return launch_fwd_pairs(p, r, l, n_rows, s);
     if (r.length <= 8) return launch_fwd_short<8>(p, packed, s, ragged);
     if (r.length <= 16) return launch_fwd_short<16>(p, packed, s, ragged);
@@ -1215,6 +1242,16 @@ size_t tv2d_workspace_bytes(int64_t planes, int64_t H, int64_t W, int sweeps)
 // Small batches of planes of 17-64 samples a side: one launch with a plane per workgroup
 // (tv_plane2d.hpp), up to the plane counts of tv_dispatch.hpp.  Planes of at most 32 x 32 leave
 // segment codes for the reverse sweep, larger ones their pass outputs.
+// Planes of 33-64 samples a side in one launch, two lanes a row: where the shorter side fills at least four
+// fifths of what the longer one's lanes and registers are laid out for (2C = 40, 48, 56 or 64).
+// 4096 planes, K = 3, against pass by pass: 40 x 40 238 / 272 us, 33 x 33 261 / 243, 40 x 56 406 / 327 (left
+// pass by pass), 64 x 40, K = 1 202 / 127 (likewise).
+static bool pairs_2d_apply(int64_t H, int64_t W)
+{
+    const int64_t longer = H > W ? H : W, shorter = H > W ? W : H;
+    return longer > 32 && longer <= 64 && 5 * shorter >= 4 * ((longer + 7) / 8 * 8);
+}
+
 static bool plane_per_group_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
 {
     if (small_planes(H, W)) {
@@ -1224,7 +1261,7 @@ static bool plane_per_group_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
     }
     if (H > 64 || W > 64) return false;
     if (sweeps == 1) return planes <= tvd::get(tvd::kPlanePerGroup64Planes);
-    if (H == 64 && W == 64)
+    if (pairs_2d_apply(H, W))
         return planes <= tvd::get(sweeps == 2 ? tvd::kPlanePerGroup64FullPlanesK2
                                                : (sweeps <= 4 ? tvd::kPlanePerGroup64FullPlanesK3 : tvd::kPlanePerGroup64FullPlanesK5));
     return planes <= tvd::get(tvd::kPlanePerGroup64PlanesK2);
@@ -1296,6 +1333,16 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
             return launch_status();
         }
         return launch_fwd_small_2d<false>(q, stream);
+    }
+    if (pairs_2d_apply(H, W)) {
+        // planes of 33-64 samples a side: the same
+        tvk::Small2dFwdParams q;
+        q.y = y; q.x = x; q.saved = saved(0); q.saved_stride = tb / sizeof(float); q.keep_passes = 1u;
+        q.codes = nullptr; q.code_stride = 0;
+        q.lam = lam.lam; q.lam_count = lam.count;
+        q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
+        q.stream = (planes * H * W >= tvd::get(tvd::kStreamBytes) / 4) ? 1u : 0u;
+        return launch_fwd_pairs_2d<false>(q, stream);
     }
     // one lambda for all planes: its gradient hinges on the last bits of x (see tv_long_tri.hpp;
     // not for planes of at most 64 x 64, whose smaller batches are solved by block means anyway)

@@ -1,5 +1,5 @@
-"""GPU parity of the kernels that solve a row with two lanes, one from each end (1D rows of 17-32 samples
-in large batches; planes of 17-32 samples a side in one launch), at the sizes where their parts meet:
+"""GPU parity of the kernels that solve a row with two lanes, one from each end (1D rows of 17-64 samples
+in large batches; planes of 17-64 samples a side in one launch), at the sizes where their parts meet:
 rows that fill the two halves, that lack a sample or a few, that lie in one half only, ties across the
 middle of the row, and every way the rows can lie in memory."""
 import numpy as np
@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 @pytest.fixture
 def pairs():
     import paper_2204_03643_amd as tv
-    saved = {k: tv.tv_dispatch_threshold(k) for k in ("plane_per_group_planes", "thread_per_sample_1d_rows")}
+    saved = {k: tv.tv_dispatch_threshold(k) for k in ("plane_per_group_planes", "thread_per_sample_1d_rows", "pair_1d_long_rows",
+                                                      "plane_per_group64_planes", "plane_per_group64_full_planes_k2",
+                                                      "plane_per_group64_full_planes_k3")}
     for k in saved:
         tv.tv_dispatch_override(k, 0)
     yield
@@ -25,8 +27,11 @@ def pairs():
 # (halves of 10, 12, 14 and 16 samples: rows of 20, 24, 28 and 32, and their neighbours)
 @pytest.mark.parametrize("H,W", [(17, 17), (19, 18), (20, 20), (20, 17), (21, 21), (24, 24), (23, 22), (25, 28), (28, 28),
                                  (27, 26), (29, 32), (30, 30), (31, 31), (32, 32), (32, 31), (32, 16), (17, 32), (32, 15),
-                                 (5, 20), (24, 12), (28, 1), (1, 19), (32, 2)])
-def test_planes_of_17_to_32_a_side(H, W, pairs):
+                                 (5, 20), (24, 12), (28, 1), (1, 19), (32, 2),
+                                 # halves of 20, 24, 28 and 32, two waves a plane
+                                 (33, 33), (40, 40), (33, 39), (40, 32), (41, 41), (48, 48), (47, 40), (39, 45), (49, 52),
+                                 (56, 56), (55, 45), (57, 57), (64, 64), (63, 62), (64, 52), (52, 60)])
+def test_planes_of_17_to_64_a_side(H, W, pairs):
     rng = np.random.default_rng(1000 * H + W)
     y = rng.normal(size=(9, H, W)).astype(np.float32)
     y[3:6] = np.maximum(np.round(y[3:6], 1), 0)               # ties, across the middle too
@@ -42,12 +47,13 @@ LAYOUTS = {"packed": lambda n: (16 * n, n, 1, 0), "shifted": lambda n: (16 * n, 
            "columns": lambda n: (16 * n, 1, 16, 0), "gap columns": lambda n: (37 * n, 2, 36, 3)}
 
 
-@pytest.mark.parametrize("n", [17, 18, 19, 20, 21, 23, 24, 25, 27, 28, 29, 30, 31, 32])
+@pytest.mark.parametrize("n", [17, 18, 19, 20, 21, 23, 24, 25, 27, 28, 29, 30, 31, 32, 33, 36, 39, 40, 41, 47, 48, 49, 53, 56,
+                               57, 60, 63, 64])
 @pytest.mark.parametrize("layout", sorted(LAYOUTS))
 @pytest.mark.parametrize("count,div", [(1, 1), (112, 1), (7, 16), (2, 8)])
-def test_rows_of_17_to_32_in_every_layout(n, layout, count, div, pairs):
+def test_rows_of_17_to_64_in_every_layout(n, layout, count, div, pairs):
     """112 rows (the last wave half empty, except where the rows of a lambda are grouped): output, info
-    words, segment codes and both gradients; nothing is written outside the rows."""
+    words, segment codes (up to 32 samples) and both gradients; nothing is written outside the rows."""
     import torch
     import paper_2204_03643_amd as tv
     so, si, se, at = LAYOUTS[layout](n)
@@ -76,19 +82,23 @@ def test_rows_of_17_to_32_in_every_layout(n, layout, count, div, pairs):
     seg = torch.full((rows_n,), -1, dtype=torch.int64, device=dev)
     wsb = tv.tv1d_bwd_workspace_bytes(rows, L)
     ws = torch.empty(wsb, dtype=torch.uint8, device=dev)
-    tv.tv1d_prox_fwd_ex(y[at:], x[at:], rows, L, info=info, seg=seg)
-    tv.tv1d_prox_bwd_seg(g[at:], seg, gy[at:], gl, rows, L, ws, wsb)
+    tv.tv1d_prox_fwd_ex(y[at:], x[at:], rows, L, info=info, seg=seg if n <= 32 else None)
+    if n <= 32:
+        tv.tv1d_prox_bwd_seg(g[at:], seg, gy[at:], gl, rows, L, ws, wsb)
+    else:
+        tv.tv1d_prox_bwd(g[at:], x[at:], gy[at:], gl, rows, L, ws, wsb)
     torch.cuda.synchronize()
     out = x.cpu().numpy()
     xr, gyr = out[where], gy.cpu().numpy()[where]
     rest = np.ones(size, bool)
     rest[where] = False
     assert np.isnan(out[rest]).all() and np.isnan(gy.cpu().numpy()[rest]).all()
-    code = np.zeros(rows_n, np.uint64)
-    for k in range(n - 1):
-        code |= (xr[:, k + 1] != xr[:, k]).astype(np.uint64) << np.uint64(k)
-        code |= (xr[:, k + 1] > xr[:, k]).astype(np.uint64) << np.uint64(32 + k)
-    assert np.array_equal(seg.cpu().numpy().view(np.uint64), code)
+    if n <= 32:
+        code = np.zeros(rows_n, np.uint64)
+        for k in range(n - 1):
+            code |= (xr[:, k + 1] != xr[:, k]).astype(np.uint64) << np.uint64(k)
+            code |= (xr[:, k + 1] > xr[:, k]).astype(np.uint64) << np.uint64(32 + k)
+        assert np.array_equal(seg.cpu().numpy().view(np.uint64), code)
     assert not (info.cpu().numpy() >> 18).any()               # no row stopped short
     check_batch(yr, lam_per_row(lam, rows_n, div), gr, xr, gyr, gl_gpu=gl.cpu().numpy(), lam_count=count, lam_div=div,
                 label="pairs n=%d %s" % (n, layout))
@@ -109,3 +119,40 @@ def test_plane_columns_with_several_lambdas_a_plane(div, count, pairs):
     torch.cuda.synchronize()
     cols = lambda a: a.transpose(0, 2, 1).reshape(-1, 32)
     check_batch(cols(y), lam_per_row(lam, 256, div), None, cols(x.cpu().numpy()), None, label="plane columns")
+
+
+@pytest.mark.parametrize("n,axis", [(33, -1), (40, 0), (48, -1), (55, 0), (64, -1), (64, 0)])
+def test_rows_of_33_to_64_alone_in_company_and_scaled(n, axis, pairs):
+    """What the other kernels for these lengths promise: a row has the same bits alone, in another order and
+    between rows that take longer or hold NaN; lambda = 0 is the identity; and with data and lambda both
+    multiplied by a power of two so is the solution, where their squares underflow too."""
+    import oracle
+    from gpuutil import rows_view, run_1d
+    rng = np.random.default_rng(n)
+    count = 90
+    y = rng.normal(size=(count, n)).astype(np.float32)
+    y[::3] = np.round(y[::3], 1)
+    y[1::3] = np.cumsum(0.3 * y[1::3], axis=1)
+    lam = (10 ** rng.uniform(-1.5, 0.7, size=count)).astype(np.float32)
+    turn = lambda a: a if axis == -1 else np.ascontiguousarray(a.T)
+    solve = lambda a, l: (lambda o: (rows_view(o["x"], axis), o["info"]))(run_1d(turn(a), l, 1, axis=axis, want_info=True))
+    want, info = solve(y, lam)
+    at = rng.permutation(count)
+    got, gi = solve(y[at], lam[at])
+    assert np.array_equal(got, want[at]) and np.array_equal(gi, info[at])
+    mixed, ml = np.repeat(y, 2, axis=0), np.repeat(lam, 2)
+    mixed[0::4] = np.cumsum(rng.normal(size=mixed[0::4].shape), axis=1)
+    mixed[2::8, n // 2] = np.nan
+    ml[0::4] = 20.0
+    got, gi = solve(mixed, ml)
+    assert np.array_equal(got[1::2], want) and np.array_equal(gi[1::2], info)
+    for r in range(0, count, 9):
+        got, _ = solve(np.stack([y[r], 0 * y[r]]), np.repeat(lam[r], 2))
+        assert np.array_equal(got[0], want[r])
+    assert np.array_equal(solve(y, np.zeros(1, np.float32))[0], y)
+    ref = oracle.prox1d_batch(y.astype(np.float64), lam.astype(np.float64), lam_div=1)
+    floor = 16 * np.finfo(np.float32).eps * (np.abs(y).max(axis=1) + lam)         # as the solver's own
+    for power in (-100, -64, -40, 0, 20, 40):
+        s = np.float32(2.0 ** power)
+        x = solve(y * s, lam * s)[0].astype(np.float64) / float(s)
+        assert np.all(np.abs(x - ref).max(axis=1) <= floor), power
