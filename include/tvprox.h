@@ -257,7 +257,9 @@ int tv1d_prox_bwd_seg_bf16(const uint16_t *g_up, const uint64_t *seg, uint16_t *
  * call then reads; it must be handed unchanged to tv2d_prox_bwd.  The forward call leaves
  * there what the backward call will read: the pass outputs, or, where planes of at most
  * 32 x 32 run all their passes in one launch, the codes alone (the pass outputs as well
- * after tv_dispatch_override("fused_keeps_passes", 1)).  x must not alias y.
+ * after tv_dispatch_override("fused_keeps_passes", 1)), or, on sides of 65-768 samples and from
+ * "chunk_codes_bytes" of pass outputs on, codes in their place (the pass outputs instead after the
+ * same override; the backward call finds out from the workspace).  x must not alias y.
  * From the second sweep on, the correction term a pass adds to its input is D^T u of the
  * same pass one sweep earlier (x = y - D^T u), and the pass starts its Newton iteration
  * from that dual.  Planes of at most 64 x 64 run all their passes in one launch where that is
@@ -275,7 +277,7 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
 /*
  * Reverse sweep through paper Alg. 1 (replaces autograd through the loop, paper
  * Sec. 3.2).  ws is the buffer tv2d_prox_fwd filled; its two scratch tensors are
- * overwritten, the saved pass outputs are only read.  Planes of at most 64 x 64 run the
+ * overwritten, the saved pass outputs or codes are only read.  Planes of at most 64 x 64 run the
  * whole sweep in one launch (small batches with a plane per workgroup, planes of at most
  * 32 x 32 and of 64 x 64 otherwise with a row per lane); which mapping the forward call used
  * does not matter.  grad_lam (lam.count floats,

@@ -140,6 +140,8 @@ struct FwdParams {
     float       *debug;     // debug_rows records of step_record_floats(L.n) floats
     uint32_t     debug_rows;
     uint32_t     flag_pitch;
+    uint32_t    *chunk_codes;  // 2D passes on sides of 65-768: optional, a chunk code per thread (tv_long.hpp) ...
+    uint32_t    *codes_tag;    // ... and, first pass of a call only: receives 1 where it writes codes, 0 where it does not
     Layout       L;
     TileMap      tm;       // row-per-lane kernels only
 };
@@ -149,6 +151,8 @@ struct BwdParams {
     const float *sub;      // optional: the averaged quantity is g - sub, and sub is added back
     const float *x;        // forward output (defines the segments) ...
     const uint2 *seg;      // ... or the segment code the forward pass wrote (row-per-lane kernels)
+    const uint32_t *chunk_codes;   // ... or, where *codes_tag is not 0, the chunk codes (2D, sides of 65-768)
+    const uint32_t *codes_tag;
     float       *gy;       // output
     float       *partial;  // optional: dL/dlam contributions, one per group of 1 << part_lg rows
     uint32_t     part_lg;  // row-per-lane kernels only; a group never spans two lambda slots

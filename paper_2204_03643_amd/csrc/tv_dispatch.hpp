@@ -35,6 +35,7 @@ enum {
     kPlanePerGroup64BwdRaggedPlanes,
     kPlanePerGroup64BwdRaggedPlanesK2,
     kFusedKeepsPasses,
+    kChunkCodesBytes,
     kThreadPerSampleWideRows,
     kThreadPerSample1dRows,
     kPair1dRows,
@@ -142,6 +143,17 @@ inline Threshold table[kCount] = {
     // tests set it to compare each pass with the oracle's).  Not writing them: 4096 planes of
     // 32 x 32, K = 1 / 4 / 10: 56 -> 52, 156 -> 149, 403 -> 385; 16 384 planes, K = 4: 560 -> 512.
     {"fused_keeps_passes", 0, "2D one-launch forward of planes of at most 32 x 32: 1 = also write every pass's output"},
+    // 2D pass by pass, sides of 65-768 samples: chunk codes instead of pass outputs (tv_long.hpp) where the
+    // 2K outputs and the two correction tensors take this many bytes or more, that is
+    // where they push one another out of the 256 MB last-level cache.  Forming the codes costs a forward pass
+    // some forty instructions a wave, which a call without a reverse sweep does not get back.  Pass outputs
+    // / codes, lambda 0.1 on images, forward, and forward + reverse sweep:
+    //   24 x 512 x 512, K = 10, one lambda (528 MB): 746 / 764, 1246 / 1156;  three lambdas: 646 / 654, 1132 / 1043
+    //   24 x 700 x 700, K = 3 (359 MB): 457 / 452, 762 / 700;  48 x 512 x 512, K = 4 (480 MB): 505 / 495, 839 / 776
+    //   512 x 100 x 100, K = 4 (196 MB): 285 / 290, 514 / 451;  512 x 128 x 128, K = 2 (193 MB): 189 / 188, 307 / 283
+    //   12 x 512 x 512, K = 3 (96 MB): 140 / 141, 233 / 221;  128 x 128 x 128, K = 4 (80 MB): 140 / 147, 234 / 226
+    // Below, the gain of the pair is a few percent and the loss of the lone forward call of the same size.
+    {"chunk_codes_bytes", (int64_t)160 << 20, "2D, sides of 65-768 samples: the forward call leaves codes, not pass outputs, from this many bytes of passes on"},
     // Rows of at most 32 samples on the long-row kernels (small 1D batches, see
     // thread_per_sample_1d_rows): 16 threads x 2 samples up to this many rows, 8 x 4 beyond
     // (8192 rows of 32 samples as 256 planes, ten passes each way: 204 -> 180 with 16 x 2).

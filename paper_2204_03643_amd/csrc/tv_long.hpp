@@ -35,6 +35,51 @@ __device__ __forceinline__ bool chunk_vec_ok(const void *base, int64_t off, int6
 
 typedef float tv_long_v4f __attribute__((ext_vector_type(4)));
 
+// Chunk codes: what the reverse sweep of a 2D call reads of a pass on sides of 65-768 samples, a word per
+// thread of the pass kernel.  Two bits a sample, sample k0 + i at 32 - 2C + 2i: x changes after it; x does not rise
+// there (duals past the row's end: anything).  An eighth of the bytes of x and no transpose, and the
+// passes then share two output tensors, which stay in the last-level cache, instead of filling 2K.
+template <int T, int C>
+constexpr bool chunk_coded() { return T <= 64 && C <= 16 && T * C > 64 && T * C <= 768; }
+
+template <int T, int C>
+__device__ __forceinline__ uint32_t chunk_code(const float (&xs)[C])
+{
+    const float xnext0 = __shfl_down(xs[0], 1, T);
+    // the sign of a difference, -1, 0 or 1, tells both in three instructions a sample, but not where
+    // infinities meet or beside NaN, which the sum shows
+    float sum = fabsf(xnext0);
+#pragma unroll
+    for (int i = 0; i < C; ++i) sum += fabsf(xs[i]);
+    uint32_t code = 0;
+    if (!__any(sum <= 3.0e38f ? 0 : 1)) {
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            const float d = ((i + 1 < C) ? xs[i + 1] : xnext0) - xs[i];
+            const int sign = min(max(__float_as_int(d), -1), 1);
+            code = __builtin_amdgcn_alignbit((uint32_t)sign, code, 2);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            const float xn = (i + 1 < C) ? xs[i + 1] : xnext0;
+            const uint32_t bits = (xn != xs[i] ? 1u : 0u) | (xn > xs[i] ? 0u : 2u);
+            code = __builtin_amdgcn_alignbit(bits, code, 2);
+        }
+    }
+    return code;
+}
+
+// Every other bit of v, the lowest first.
+__device__ __forceinline__ uint32_t even_bits(uint32_t v)
+{
+    v &= 0x55555555u;
+    v = (v | v >> 1) & 0x33333333u;
+    v = (v | v >> 2) & 0x0f0f0f0fu;
+    v = (v | v >> 4) & 0x00ff00ffu;
+    return (v | v >> 8) & 0x0000ffffu;
+}
+
 // stream: the tensor is far larger than the last-level cache and touched once per call;
 // non-temporal accesses keep such streams from evicting each other.
 template <int C>
@@ -306,6 +351,14 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>()))
             chunk_store<C>(p.resid, off, es, k0, n, rvalid, yl);
         }
     }
+    // (last, behind the stores that the wave waits for at its end anyway)
+    if constexpr (!DEBUG && chunk_coded<T, C>() && WARM <= 1) {
+        if (p.chunk_codes) {
+            const uint32_t code = chunk_code<T, C>(xs);
+            if (rvalid) p.chunk_codes[(size_t)row * T + t] = code;
+        }
+        if (p.codes_tag && blockIdx.x == 0 && tid == 0) *p.codes_tag = p.chunk_codes ? 1u : 0u;
+    }
     if (p.info && rvalid && t == 0) p.info[row] = info;
     if constexpr (DEBUG) {
         if (rec && t == 0) rec[2] = (float)info;
@@ -319,9 +372,11 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>()))
 // HAS_SUB: p.sub is given (the reverse sweep of the 2D operator).
 // Workgroups of 1024 threads ask for 8 waves per SIMD (at most 64 VGPRs), so that a CU holds two of
 // them and one's loads overlap the other's scans.
-template <int T, int C, int G, bool COLS, bool XPOSE = false, bool HAS_SUB = false>
+// CODES: where the forward pass left chunk codes (p.codes_tag says whether it did) they are read, not x.
+template <int T, int C, int G, bool COLS, bool XPOSE = false, bool HAS_SUB = false, bool CODES = false>
 __global__ __launch_bounds__(T *G, (T * G == 1024 && !COLS && !HAS_SUB) ? 8 : 1) void tv1d_bwd_long_kernel(BwdParams p)
 {
+    static_assert(!CODES || chunk_coded<T, C>(), "chunk codes are for rows inside one wave");
     static_assert(!XPOSE || (COLS && T <= 64), "the transposing variant is for strided rows inside one wave");
     constexpr bool MCOLS = COLS && !XPOSE;
     using Mp = LongMap<T, G, MCOLS>;
@@ -375,7 +430,23 @@ __global__ __launch_bounds__(T *G, (T * G == 1024 && !COLS && !HAS_SUB) ? 8 : 1)
     // duals of this chunk that lie inside the row (dual i sits behind sample k0 + i)
     const int nv = min(max(n - 1 - k0, 0), C);
     const uint32_t inrow = (1u << nv) - 1u;
-    {
+    bool coded = false;
+    if constexpr (CODES) coded = *p.codes_tag != 0u;
+    if (CODES && coded) {
+        const uint32_t code = rvalid ? p.chunk_codes[(size_t)row * T + t] : 0u;
+        if constexpr (XPOSE) {
+            float rg[C], rs[HAS_SUB ? C : 1];
+            fetch(p.g, rg);
+            if constexpr (HAS_SUB) fetch(p.sub, rs);
+            turn(rg, g);
+            if constexpr (HAS_SUB) turn(rs, sb);
+        } else {
+            chunk_load<C>(p.g, off, es, k0, n, rvalid, g, p.L.stream);
+            if constexpr (HAS_SUB) chunk_load<C>(p.sub, off, es, k0, n, rvalid, sb, p.L.stream);
+        }
+        jmask = even_bits(code >> (32 - 2 * C));
+        upmask = jmask & ~even_bits(code >> (33 - 2 * C));
+    } else {
         float x[C];
         if constexpr (XPOSE) {
             float rg[C], rx[C], rs[HAS_SUB ? C : 1];
@@ -506,6 +577,15 @@ inline hipError_t launch_bwd_long_t(const BwdParams &p, hipStream_t s)
 {
     const dim3 grid((p.L.n_rows + G - 1) / G), block(T * G);
     constexpr bool XP = COLS && T <= 64;
+    if constexpr (chunk_coded<T, C>()) {
+        if (p.chunk_codes) {
+            if (p.sub)
+                hipLaunchKernelGGL((tv1d_bwd_long_kernel<T, C, G, COLS, XP, true, true>), grid, block, 0, s, p);
+            else
+                hipLaunchKernelGGL((tv1d_bwd_long_kernel<T, C, G, COLS, XP, false, true>), grid, block, 0, s, p);
+            return hipGetLastError();
+        }
+    }
     if (p.sub)
         hipLaunchKernelGGL((tv1d_bwd_long_kernel<T, C, G, COLS, XP, true>), grid, block, 0, s, p);
     else
@@ -521,6 +601,13 @@ inline hipError_t launch_bwd_long_t(const BwdParams &p, hipStream_t s)
 // 769-1024 samples need 139 registers that way and are slower, 44 -> 48).  Backward 16: it is
 // bound by memory, and 8 adjacent columns are 32 bytes of every image row (24 images of
 // 512 x 512, K = 4 reverse sweep: 205 us with 16 rows, 232 with 8).
+// Threads of the mappings below per row of 65-768 samples (the same for rows and columns, and for the
+// elimination kernels of tv_long_tri.hpp): the words a row's chunk codes take.
+inline int chunk_threads(int64_t n)
+{
+    return n <= 96 ? 8 : n <= 192 ? 16 : n <= 384 ? 32 : 64;
+}
+
 #define TV_LONG_DISPATCH(FN, p, s, GX)                                                    \
     do {                                                                                  \
         const int n = (p).L.n;                                                            \

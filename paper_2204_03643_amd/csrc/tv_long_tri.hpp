@@ -533,6 +533,13 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, XPOSE, XPOSE>())
             chunk_store<C>(p.resid, off, es, k0, n, rvalid, y);
         }
     }
+    if constexpr (chunk_coded<T, C>()) {
+        if (p.chunk_codes) {
+            const uint32_t code = chunk_code<T, C>(xs);
+            if (rvalid) p.chunk_codes[(size_t)row * T + t] = code;
+        }
+        if (p.codes_tag && blockIdx.x == 0 && tid == 0) *p.codes_tag = p.chunk_codes ? 1u : 0u;
+    }
 #undef TV_EX
 #undef TV_PB
 #undef TV_LK

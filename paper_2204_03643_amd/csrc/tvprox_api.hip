@@ -624,7 +624,8 @@ int run_fwd_multilevel(FwdParams p, const tv_lambda &l, int64_t n_rows, const Ml
 int run_fwd(const float *y, const float *addend, float *x, float *resid, int32_t *info,
             uint2 *seg, uint32_t *order_ws, const tv_rows &r, const tv_lambda &l, int64_t n_rows,
             hipStream_t s, float *x2 = nullptr, bool warm = false, char *ml_ws = nullptr, bool io16 = false,
-            bool thread_per_sample = false, bool order_ready = false, bool psearch = false, bool tri = false)
+            bool thread_per_sample = false, bool order_ready = false, bool psearch = false, bool tri = false,
+            uint32_t *chunk_codes = nullptr, uint32_t *codes_tag = nullptr)
 {
     FwdParams p;
     p.y = y; p.addend = addend; p.x = x; p.x2 = x2; p.resid = resid; p.lam = l.lam; p.info = info;
@@ -636,6 +637,7 @@ int run_fwd(const float *y, const float *addend, float *x, float *resid, int32_t
     p.ml_flag = nullptr; p.flag_pitch = 1; p.ml_skip = 0;
     p.lam_scale = 1.0f;
     p.debug = nullptr; p.debug_rows = 0;
+    p.chunk_codes = chunk_codes; p.codes_tag = codes_tag;
     p.L = make_layout(r, l, n_rows);
     p.tm = make_tile_map(l, n_rows);
     // (a few thousand short rows at most: a few threads per row instead of a lane per row; the 2D
@@ -838,10 +840,12 @@ PartialShape partial_shape(const tv_rows &r, const tv_lambda &l, int64_t n_rows)
 // reduce_now = false: the dL/dlam terms stay in `partial` and the caller sums them later.
 int run_bwd(const float *g, const float *sub, const float *x, const uint2 *seg, float *gy,
             float *grad_lam, int accumulate, const tv_rows &r, const tv_lambda &l, int64_t n_rows,
-            float *partial, hipStream_t s, bool reduce_now = true, bool io16 = false)
+            float *partial, hipStream_t s, bool reduce_now = true, bool io16 = false,
+            const uint32_t *chunk_codes = nullptr, const uint32_t *codes_tag = nullptr)
 {
     BwdParams p;
     p.g = g; p.sub = sub; p.x = x; p.seg = seg; p.gy = gy;
+    p.chunk_codes = chunk_codes; p.codes_tag = codes_tag;
     p.io16 = io16 ? 1u : 0u;
     p.partial = grad_lam ? partial : nullptr;
     p.L = make_layout(r, l, n_rows);
@@ -1121,6 +1125,7 @@ int tv1d_prox_fwd_steps(const float *y, float *x, int32_t *info, float *record, 
     p.lam_scale = 1.0f;
     p.debug = record;
     p.debug_rows = (uint32_t)(record_rows < n_rows ? record_rows : n_rows);
+    p.chunk_codes = nullptr; p.codes_tag = nullptr;
     p.L = make_layout(rows, lam, n_rows);
     p.tm = tvk::TileMap{6u, 0u, 0u, 1u};
     if (rows.length <= 32) {
@@ -1239,6 +1244,31 @@ size_t tv2d_workspace_bytes(int64_t planes, int64_t H, int64_t W, int sweeps)
     return tb * (size_t)(2 * sweeps + 2) + (pb + cb) * (size_t)(2 * sweeps) + kSplitScratchBytes;
 }
 
+// Planes whose sides are both of 65-768 samples always go pass by pass, every row inside one wave, and keep
+// chunk codes (tv_long.hpp) instead of pass outputs unless fused_keeps_passes asks for those.  The codes of
+// the 2K passes, then the two output tensors that the passes alternate between, take the place of
+// the 2K pass outputs; whether they did is a word in the workspace's last bytes, beyond what the split
+// reductions use, since the threshold may be another one by the time of the backward call.
+struct ChunkCodes {
+    size_t    stride;     // bytes per pass; 0: these planes have none
+    uint32_t *tag;
+};
+
+static ChunkCodes chunk_codes_2d(char *base, int64_t planes, int64_t H, int64_t W, int sweeps, size_t tensor_bytes,
+                                 size_t ws_bytes)
+{
+    static_assert(kSplitScratchBytes >= 2 * (size_t)(kSplitMaxSlots - 1) * kSplitMax * sizeof(double) + 16,
+                  "the tag lies behind the split sums");
+    ChunkCodes cc = {0, (uint32_t *)(base + ws_bytes - 16)};
+    if (H <= 64 || W <= 64 || H > 768 || W > 768) return cc;
+    const size_t row_pass = (size_t)(planes * H) * (size_t)tvk::chunk_threads(W);
+    const size_t col_pass = (size_t)(planes * W) * (size_t)tvk::chunk_threads(H);
+    const size_t bytes = align16((row_pass > col_pass ? row_pass : col_pass) * sizeof(uint32_t));
+    // (a row of n samples has at most n / 6 words, so this holds but for rounding up to 16 bytes)
+    if (2 * (size_t)sweeps * bytes + (sweeps == 1 ? 1 : 2) * tensor_bytes <= 2 * (size_t)sweeps * tensor_bytes) cc.stride = bytes;
+    return cc;
+}
+
 // Small batches of planes of 17-64 samples a side: one launch with a plane per workgroup
 // (tv_plane2d.hpp), up to the plane counts of tv_dispatch.hpp.  Planes of at most 32 x 32 leave
 // segment codes for the reverse sweep, larger ones their pass outputs.
@@ -1349,20 +1379,29 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
     const int64_t longest = H > W ? H : W;
     const bool tri = lam.count == 1 && sweeps >= 3 && longest > 64 && longest <= 768 &&
                      longest <= tvd::get(tvd::kOneLambdaTriSide);
+    const ChunkCodes cc = chunk_codes_2d(base, planes, H, W, sweeps, tb, tv2d_workspace_bytes(planes, H, W, sweeps));
+    uint32_t *tag = cc.stride ? cc.tag : nullptr;
+    const bool lean = cc.stride && tvd::get(tvd::kFusedKeepsPasses) == 0 &&
+                      tb * (size_t)(2 * sweeps + 2) >= (size_t)tvd::get(tvd::kChunkCodesBytes);
+    char *outputs = base + 2 * (size_t)sweeps * cc.stride;               // (lean: the two tensors behind the codes)
+    auto pass_out = [&](int pass) { return lean ? (float *)(outputs + tb * (size_t)(pass & 1)) : saved(pass); };
+    auto pass_codes = [&](int pass) { return lean ? (uint32_t *)(base + cc.stride * (size_t)pass) : nullptr; };
     for (int k = 0; k < sweeps; ++k) {
         const bool last = (k == sweeps - 1);
-        const float *Yk = (k == 0) ? y : saved(2 * k - 1);
-        float *Z = saved(2 * k), *Yn = saved(2 * k + 1);
+        const float *Yk = (k == 0) ? y : pass_out(2 * k - 1);
+        float *Z = pass_out(2 * k), *Yn = (lean && last) ? x : pass_out(2 * k + 1);
         // Z = proxRows(Y + P);  P <- (Y + P) - Z      (P = 0 in the first sweep)
         // From the second sweep on, P = D^T u of the row pass one sweep earlier (x = y - D^T u),
         // and likewise Q for the columns: each pass starts from that dual.
         st = run_fwd(Yk, k == 0 ? nullptr : P, Z, last ? nullptr : P, nullptr, codes(2 * k), nullptr,
-                     rrow, lrow, planes * H, stream, nullptr, true, nullptr, false, false, false, false, tri);
+                     rrow, lrow, planes * H, stream, nullptr, true, nullptr, false, false, false, false, tri,
+                     pass_codes(2 * k), k == 0 ? tag : nullptr);
         if (st != TV_OK) return st;
         // Y' = proxCols(Z + Q);  Q <- (Z + Q) - Y'
-        // the last pass writes its output twice: where the reverse sweep will look for it, and to x
+        // the last pass writes its output twice where the reverse sweep will look for it: there, and to x
         st = run_fwd(Z, k == 0 ? nullptr : Q, Yn, last ? nullptr : Q, nullptr, codes(2 * k + 1), nullptr,
-                     rcol, lcol, planes * W, stream, last ? x : nullptr, true, nullptr, false, false, false, false, tri);
+                     rcol, lcol, planes * W, stream, (last && !lean) ? x : nullptr, true, nullptr, false, false, false,
+                     false, tri, pass_codes(2 * k + 1));
         if (st != TV_OK) return st;
     }
     return TV_OK;
@@ -1510,13 +1549,17 @@ int tv2d_prox_bwd(const float *g_up, float *grad_y, float *grad_lam, int64_t pla
         const tv_lambda lp = {lam.lam, lam.count, 1};
         return launch_reduce_lambda(partial(0), grad_lam, planes, lp, 0, stream);
     }
+    const ChunkCodes cc = chunk_codes_2d(base, planes, H, W, sweeps, tb, tv2d_workspace_bytes(planes, H, W, sweeps));
+    const uint32_t *tag = cc.stride ? cc.tag : nullptr;
+    auto pass_codes = [&](int pass) { return tag ? (const uint32_t *)(base + cc.stride * (size_t)pass) : nullptr; };
     for (int k = sweeps - 1; k >= 0; --k) {
         const bool first = (k == sweeps - 1);
         st = run_bwd(first ? g_up : Ab, first ? nullptr : Bb, cb ? nullptr : saved(2 * k + 1), codes(2 * k + 1),
-                     Bb, grad_lam, 0, rcol, lcol, planes * W, partial(2 * k + 1), stream, false);
+                     Bb, grad_lam, 0, rcol, lcol, planes * W, partial(2 * k + 1), stream, false, false,
+                     pass_codes(2 * k + 1), tag);
         if (st != TV_OK) return st;
         st = run_bwd(Bb, first ? nullptr : Ab, cb ? nullptr : saved(2 * k), codes(2 * k), k == 0 ? grad_y : Ab,
-                     grad_lam, 0, rrow, lrow, planes * H, partial(2 * k), stream, false);
+                     grad_lam, 0, rrow, lrow, planes * H, partial(2 * k), stream, false, false, pass_codes(2 * k), tag);
         if (st != TV_OK) return st;
     }
     if (grad_lam) {

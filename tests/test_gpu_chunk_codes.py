@@ -1,0 +1,59 @@
+"""2D calls on sides of 65-768 samples leave chunk codes for the reverse sweep instead of pass outputs."""
+import numpy as np
+import pytest
+
+from gpuutil import run_2d
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H,W,K,count", [
+    (65, 96, 1, 2), (97, 65, 2, 3), (128, 97, 3, 1), (129, 192, 2, 2), (256, 193, 1, 1), (193, 257, 4, 3),
+    (384, 385, 3, 1), (512, 512, 2, 2), (321, 481, 3, 3), (513, 768, 3, 1), (768, 513, 1, 3), (768, 65, 2, 1)])
+def test_codes_and_kept_passes_give_the_same_bits(H, W, K, count):
+    """Both ends of every thread mapping, rows and columns, block means and elimination (one lambda,
+    three sweeps), cold and warm passes: x, grad_y and grad_lam are bit for bit what the call gives when
+    it keeps its pass outputs, the reverse sweep telling the two apart by the workspace alone."""
+    import paper_2204_03643_amd as tv
+    rng = np.random.default_rng(H * 1000 + W)
+    y = (np.cumsum(rng.normal(scale=0.05, size=(3, H, W)), axis=-1) + rng.normal(scale=0.2, size=(3, H, W))).astype(np.float32)
+    y[1] = np.maximum(y[1], 0)                                  # ties
+    y[2, 5, 7:9] = np.inf                                       # equal infinities are no jump
+    g = rng.normal(size=y.shape).astype(np.float32)
+    lam = (10 ** rng.uniform(-2, 0, size=count)).astype(np.float32)
+    kept = run_2d(y, lam, K, g, keep_passes=True)
+    bytes_ = tv.tv_dispatch_threshold("chunk_codes_bytes")
+    tv.tv_dispatch_override("chunk_codes_bytes", 0)
+    try:
+        lean = run_2d(y, lam, K, g, keep_passes=False)
+    finally:
+        tv.tv_dispatch_override("chunk_codes_bytes", bytes_)
+    for k in ("x", "gy", "gl"):
+        assert np.array_equal(kept[k], lean[k], equal_nan=True), k
+    assert np.array_equal(kept["saved"][2 * K - 1], kept["x"], equal_nan=True)
+
+
+def test_reverse_sweep_twice_on_one_workspace():
+    """The reverse sweep only reads the codes: a second one on the same workspace gives the same bits
+    (63 lambdas: the reduction split over the most workgroups it has, beside the word that tells
+    codes from pass outputs)."""
+    import torch
+
+    import paper_2204_03643_amd as tv
+    planes, H, W, K = 63, 66, 70, 40
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    y, g = (torch.randn((planes, H, W), generator=gen, device="cuda") for _ in range(2))
+    lam = torch.full((planes,), 0.2, device="cuda")
+    L = tv.tv_lambda(lam.data_ptr(), planes, 1)
+    wsb = tv.tv2d_workspace_bytes(planes, H, W, K)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    x = torch.empty_like(y)
+    tv.tv2d_prox_fwd(y, x, planes, H, W, L, K, ws, wsb)
+    out = []
+    for _ in range(2):
+        gy, gl = torch.empty_like(y), torch.empty_like(lam)
+        tv.tv2d_prox_bwd(g, gy, gl, planes, H, W, L, K, ws, wsb)
+        out.append((gy, gl))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert bool(torch.isfinite(out[0][0]).all())
