@@ -279,7 +279,8 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
  * Sec. 3.2).  ws is the buffer tv2d_prox_fwd filled; its two scratch tensors are
  * overwritten, the saved pass outputs or codes are only read.  Planes of at most 64 x 64 run the
  * whole sweep in one launch (small batches with a plane per workgroup, planes of at most
- * 32 x 32 and of 64 x 64 otherwise with a row per lane); which mapping the forward call used
+ * 32 x 32 otherwise with a row per lane, larger ones that fill their square with two lanes a row);
+ * which mapping the forward call used
  * does not matter.  grad_lam (lam.count floats,
  * overwritten) may be NULL; it is one fp64 sum, in a fixed order, over the terms of all
  * passes.  grad_y must not alias g_up.

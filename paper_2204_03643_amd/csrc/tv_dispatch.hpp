@@ -125,10 +125,17 @@ inline Threshold table[kCount] = {
     //   32 x 32, K = 4:  64 planes 14 / 19,  256: 14 / 20,  512: 18 / 22,  768: 23 / 24,  896: 27 / 25;
     //            K = 10: 256 planes 23 / 38;  K = 1: 15 / 15 at every count up to 768 (launches);
     //   28 x 30, K = 2: 512 planes 14 / 21, 1024: 21 / 26;
-    //   64 x 64, K = 4:  64 planes 31 / 54,  256: 35 / 58,  512: 43 / 62,  640: 65 / 64;
-    //            K = 1: 256 planes 15 / 21,  512: 21 / 23,  640: 29 / 27.
+    // Planes of 33-64 samples a side against two lanes a row (tv2d_bwd_pair_kernel: four planes a CU at
+    // once, half the threads of this mapping):
+    //   64 x 64, K = 1: 256 planes 13 / 14,  512: 18 / 16,  640: 26 / 19, 2048:  61 /  42, 8192: 230 / 112;
+    //            K = 4: 256 planes 33 / 36,  512: 39 / 41,  640: 64 / 44, 1024:  75 /  48, 2048: 163 / 115, 4096: 310 / 180;
+    //   48 x 48, K = 2: 256 planes 15 / 17,  512: 21 / 19,  640: 29 / 20, 1024:  37 /  25, 8192: 252 / 132;
+    //   40 x 40, K = 4: 256 planes 22 / 24,  512: 30 / 26,  640: 47 / 29, 1024:  56 /  31, 4096: 189 / 108;
+    //   52 x 56, K = 4: 576 planes 53 / 42, 1024: 65 / 48, 2048: 121 / 112, 4096: 244 / 173;
+    //   64 x 60, K = 4: 640 planes 55 / 55, 1024: 67 / 63, 1536: 100 / 111, 2048: 144 / 153, 3072: 203 / 192, 4096: 268 / 246;
+    //   36 x 40, K = 1, against pass by pass from 1024 planes on: 1024: 24 / 18, 1536: 28 / 26, 2048: 33 / 37, 3072: 43 / 34.
     {"plane_per_group_bwd_planes", 768, "2D reverse sweep, planes of 17-32 a side: a plane per workgroup up to this many planes"},
-    {"plane_per_group64_bwd_planes", 512, "2D reverse sweep, planes of 64 x 64: a plane per workgroup up to this many planes"},
+    {"plane_per_group64_bwd_planes", 512, "2D reverse sweep, planes of 33-64 a side that two lanes a row can take over: a plane per workgroup up to this many planes (half as many again: sides beyond 56 that do not fill 64 x 64)"},
     // ... and against the pass-by-pass reverse sweep (2K launches), which is what other planes of
     // 33-64 samples a side get otherwise: 40 x 48, K = 1: 256 planes 14 / 20, 512: 18 / 22,
     // 1024: 29 / 28, 2048: 53 / 40; K = 3: 256 planes 22 / 44, 1024: 52 / 74, 2048: 95 / 108.

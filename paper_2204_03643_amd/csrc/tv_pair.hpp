@@ -900,4 +900,188 @@ __global__ __launch_bounds__(64, C > 16 ? 3 : 4) void tv1d_fwd_pair_kernel(FwdPa
     }
 }
 
+// ---------------------------------------------------------------------------------
+// Reverse sweep on planes of 33-64 samples a side in one launch, two lanes a row, two waves a plane.
+//
+// Bound by the chains of its segment sums: with a row per lane a plane is one wave, 1024 planes are one wave
+// per SIMD, and each walks 64 samples twice a pass (VALU busy a third of the time).  Halves make twice the
+// waves and chains of 32.  Both adjoint state tensors of the plane lie in LDS as PairTile has them; of
+// a pass's output a lane reads its half row one pass ahead, rows in 16-byte pieces, columns in rows of 32
+// neighbouring columns, and keeps a jump and a direction bit a sample.
+// Reverse sweep of 1024 planes of 64 x 64, K = 4, a row per lane / two lanes: 69 / 48 us, 8192 planes, K = 2: 290 / 180;
+// 1024 planes of 40 x 40, K = 4, a plane per workgroup / two lanes: 56 / 31.
+// W a multiple of 4, the saved outputs 16-byte aligned; at most 2C / 5 samples short of 2C.
+// ---------------------------------------------------------------------------------
+template <int C, bool FULL>
+__global__ __launch_bounds__(128, 2) void tv2d_bwd_pair_kernel(Small2dBwdParams p)
+{
+    static_assert(C > 16 && C <= 32 && C % 4 == 0, "planes of 33-64 samples a side");
+    using Tile = PairTile<C>;
+    constexpr int HO = Tile::HALF, P = Tile::PITCH, S = 2 * C, NT = 4 * HO;
+    __shared__ float A[2 * HO * P], B[2 * HO * P], rtab[S + 2], wave_term[2];
+    const int tid = threadIdx.x;
+    for (int i = tid; i <= S; i += NT) rtab[i] = i > 0 ? 1.0f / (float)i : 0.0f;
+    const int H = FULL ? S : p.H, W = FULL ? S : p.W, HW = H * W;
+    const int64_t plane = blockIdx.x;
+    const int at = tid >> 1;                        // the pair's row or column, by place
+    const bool right = (tid & 1) != 0;
+    const int idx = at < HO ? at : HO + S - 1 - at;
+    const bool in_half = (at & (HO - 1)) < C;
+    const bool cvalid = in_half && (FULL || idx < W), rvalid = in_half && (FULL || idx < H);
+    const int row_at = at * P + (right ? HO : 0);               // half row in a tile, step 1
+    const int col_at = (right ? HO : 0) * P + at;               // half column, step P
+
+    // memory <-> tile: sample e = tid, tid + NT, ... of the plane
+    auto each_sample = [&](auto &&f) {
+        int r = tid / W, c = tid - r * W;
+        const int dq = NT / W, dr = NT - dq * W;
+        for (int e = tid; e < HW; e += NT) {
+            f(e, Tile::place(r) * P + Tile::place(c));
+            r += dq; c += dr;
+            if (c >= W) { c -= W; r += 1; }
+        }
+    };
+    {
+        const float *src = p.g_up + plane * HW;
+        constexpr int N = (S * S + NT - 1) / NT;
+        float q[N];                                 // every load is issued before the first is waited for
+#pragma unroll
+        for (int i = 0; i < N; ++i) q[i] = i * NT + tid < HW ? src[i * NT + tid] : 0.f;
+        int r = tid / W, c = tid - r * W;
+        const int dq = NT / W, dr = NT - dq * W;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if (i * NT + tid < HW) A[Tile::place(r) * P + Tile::place(c)] = q[i];
+            r += dq; c += dr;
+            if (c >= W) { c -= W; r += 1; }
+        }
+    }
+
+    // The lane's half of its row or column of a pass's output, in the order of memory: samples 0 .. C-1, or
+    // C .. n-1 and beyond (lanes without a row, and samples past the end, read inside the plane all the same:
+    // no branch a load).
+    const int row_in = FULL ? idx : min(idx, H - 1), col_in = FULL ? idx : min(idx, W - 1);
+    auto fetch = [&](int pass, float (&xv)[C]) {
+        if (pass < 0) return;
+        const float *xs = p.saved + (size_t)pass * p.saved_stride + (size_t)plane * HW;
+        if (pass & 1) {
+            const int r0 = right ? C : 0;
+#pragma unroll
+            for (int r = 0; r < C; ++r) xv[r] = xs[(FULL ? r0 + r : min(r0 + r, H - 1)) * W + col_in];
+        } else {
+            const int c0 = right ? C : 0;
+#pragma unroll
+            for (int c = 0; c < C; c += 4) {
+                const float4 q = *reinterpret_cast<const float4 *>(xs + row_in * W + (FULL ? c0 + c : min(c0 + c, W - 4)));
+                xv[c] = q.x; xv[c + 1] = q.y; xv[c + 2] = q.z; xv[c + 3] = q.w;
+            }
+        }
+    };
+    // Jump and direction bits of the lane's local duals: bit i behind local sample i, towards the middle; up: x rises there,
+    // seen from the lane's end.  The sign of x[k] - x[k+1] says "rises", that of -|.| "differs".
+    auto bits_of = [&](const float (&xv)[C], uint32_t &jump, uint32_t &up) {
+        jump = 0; up = 0;
+#pragma unroll
+        for (int k = C - 2; k >= 0; --k) {
+            const float d = xv[k] - xv[k + 1];
+            up = __builtin_amdgcn_alignbit(up, __float_as_uint(d), 31);
+            jump = __builtin_amdgcn_alignbit(jump, __float_as_uint(0.0f - fabsf(d)), 31);
+        }
+        // (the right lane's duals the other way round: C - 1 bits turned; there x rises where it falls in memory)
+        const uint32_t turned_jump = __builtin_bitreverse32(jump) >> (33 - C);
+        const uint32_t turned_up = __builtin_bitreverse32(jump & ~up) >> (33 - C);
+        jump = right ? turned_jump : jump;
+        up = right ? turned_up : up;
+        const float near = right ? xv[0] : xv[C - 1];           // the sample at the middle
+        const float d = near - pair_other(near);
+        up |= (__float_as_uint(d) >> 31) << (C - 1);
+        jump |= (__float_as_uint(0.0f - fabsf(d)) >> 31) << (C - 1);
+    };
+    // Segment means of the pair's row of n samples in place; returns the lane's part of the row's dL/dlam term.
+    auto means = [&](float (&g)[C], uint32_t jump, uint32_t up, int n) -> float {
+        // local samples past the row's end, outermost (at most 2C / 5 of them: the shorter side fills four fifths)
+        const int pads = FULL ? 0 : (right ? S - n : 0);
+        if (!FULL && pads > 0) jump |= 1u << (pads - 1);
+        float s = 0.f;
+        int c4 = 0;
+        auto inverse = [&](int bytes) { return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(rtab) + bytes); };
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            s += g[k];
+            c4 += 4;
+            if (k < C - 1) {
+                g[k] = s * inverse(c4);
+                if (jump & (1u << k)) { s = 0.f; c4 = 0; }
+            }
+        }
+        const bool mid = (jump & (1u << (C - 1))) != 0u;
+        const float s2 = pair_other(s);
+        const int c2 = (int)pair_other((uint32_t)c4);
+        if (!mid) { s += s2; c4 += c2; }
+        float carry = s * inverse(c4), term = 0.f;
+        {
+            const float d = carry - pair_other(carry);          // (0 where the middle is no jump)
+            term = right ? 0.f : ((up & (1u << (C - 1))) ? d : -d);
+        }
+        g[C - 1] = carry;
+#pragma unroll
+        for (int k = C - 2; k >= 0; --k) {
+            const float inner = carry;
+            carry = (jump & (1u << k)) ? g[k] : carry;
+            g[k] = carry;
+            const float d = carry - inner;
+            if (FULL || k >= 2 * C / 5 || k >= pads) term += (up & (1u << k)) ? d : -d;
+        }
+        return term;
+    };
+    float glam = 0.f;
+    float v[C], xv[C];
+    fetch(2 * p.sweeps - 1, xv);
+    __syncthreads();
+    for (int k = p.sweeps - 1; k >= 0; --k) {
+        const bool first = (k == p.sweeps - 1);
+        uint32_t jump, up;
+        // ---- adjoint of the column pass: B <- C^T(A - B) + B  (B = 0 in the first reverse step)
+        bits_of(xv, jump, up);
+        fetch(2 * k, xv);
+        {
+            const float *a = A + col_at;
+            float *b = B + col_at;
+#pragma unroll
+            for (int r = 0; r < C; ++r) v[r] = first ? a[r * P] : a[r * P] - b[r * P];
+            const float t = means(v, jump, up, H);
+            if (cvalid) glam += t;
+#pragma unroll
+            for (int r = 0; r < C; ++r) b[r * P] = first ? v[r] : b[r * P] + v[r];
+        }
+        __syncthreads();
+        // ---- adjoint of the row pass: A <- R^T(B - A) + A  (without A in the first reverse step)
+        bits_of(xv, jump, up);
+        fetch(2 * k - 1, xv);
+        {
+            float *a = A + row_at;
+            const float *b = B + row_at;
+#pragma unroll
+            for (int c = 0; c < C; ++c) v[c] = first ? b[c] : b[c] - a[c];
+            const float t = means(v, jump, up, W);
+            if (rvalid) glam += t;
+#pragma unroll
+            for (int c = 0; c < C; ++c) a[c] = first ? v[c] : a[c] + v[c];
+        }
+        __syncthreads();
+    }
+
+    float *dst = p.gy + plane * HW;
+    each_sample([&](int e, int place) { dst[e] = A[place]; });
+    if (p.partial) {
+        // sum over the plane's lanes, in a fixed order
+        float s = glam;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) s += __shfl_xor(s, d);
+        if ((tid & 63) == 0) wave_term[tid >> 6] = s;
+        __syncthreads();
+        if (tid == 0) p.partial[plane] = wave_term[0] + wave_term[1];
+    }
+}
+
 }  // namespace tvk

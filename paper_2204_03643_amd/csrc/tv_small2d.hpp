@@ -69,18 +69,17 @@ struct Small2dBwdParams {
     uint32_t     stream;       // tensors too large to stay in cache: non-temporal accesses
 };                             // (IO16 kernels: g_up and gy point to bf16 bit patterns)
 
-// Bit k of a row's segment code: x = jump bits 0-31, y = direction bits 0-31, z and w = the same
-// for duals 32-62 (rows of more than 32 samples).
+// Bit k of a row's segment code: x = jump bits, y = direction bits.
 template <int K>
-__device__ __forceinline__ bool code_jump(const uint4 &c) { return ((K < 32 ? c.x : c.z) & (1u << (K & 31))) != 0u; }
+__device__ __forceinline__ bool code_jump(const uint2 &c) { return (c.x & (1u << K)) != 0u; }
 template <int K>
-__device__ __forceinline__ bool code_up(const uint4 &c) { return ((K < 32 ? c.y : c.w) & (1u << (K & 31))) != 0u; }
+__device__ __forceinline__ bool code_up(const uint2 &c) { return (c.y & (1u << K)) != 0u; }
 
 // Segment means of g[0 .. n-1] in place, segments given by the code's jump bits; returns the
 // row's dL/dlam term  sum over jumps k of sign(x[k+1] - x[k]) (mean_left - mean_right).
 // FULL: n = S at compile time.
 template <int S, bool FULL, int K = 0>
-__device__ __forceinline__ void small2d_means_up(float (&g)[S], const uint4 &code, int n, const float *rtab,
+__device__ __forceinline__ void small2d_means_up(float (&g)[S], const uint2 &code, int n, const float *rtab,
                                                  float &s, int &c4)
 {
     if constexpr (K < S) {
@@ -95,7 +94,7 @@ __device__ __forceinline__ void small2d_means_up(float (&g)[S], const uint4 &cod
     }
 }
 template <int S, bool FULL, int K = S - 1>
-__device__ __forceinline__ void small2d_means_down(float (&g)[S], const uint4 &code, int n, float &carry,
+__device__ __forceinline__ void small2d_means_down(float (&g)[S], const uint2 &code, int n, float &carry,
                                                    float &glam)
 {
     if constexpr (K >= 0) {
@@ -115,7 +114,7 @@ __device__ __forceinline__ void small2d_means_down(float (&g)[S], const uint4 &c
     }
 }
 template <int S, bool FULL>
-__device__ __forceinline__ float small2d_segment_means(float (&g)[S], const uint4 &code, int n, const float *rtab)
+__device__ __forceinline__ float small2d_segment_means(float (&g)[S], const uint2 &code, int n, const float *rtab)
 {
     float s = 0.f, carry = 0.f, glam = 0.f;
     int c4 = 0;
@@ -126,12 +125,10 @@ __device__ __forceinline__ float small2d_segment_means(float (&g)[S], const uint
     small2d_means_down<S, FULL>(g, code, n, carry, glam);
     return glam;
 }
-// S = 8, 16, 32 or 64: the side of the square a plane is padded to; a wave holds 64 / S planes,
-// one row or column per lane.  FULL: planes of exactly S x S.  S = 64: the segments of a pass are
-// read off its saved output (the forward kernels for rows of more than 32 samples write no codes).
-// FROM_X: the segments of a pass are read off its saved output instead of its codes.
+// S = 8, 16 or 32: the side of the square a plane is padded to; a wave holds 64 / S planes,
+// one row or column per lane.  FULL: planes of exactly S x S.
 // IO16: the upstream gradient and grad_y are bf16 in memory (fp32 in the tiles and in all arithmetic).
-template <int S, bool FULL, bool FROM_X = (S > 32), bool IO16 = false>
+template <int S, bool FULL, bool IO16 = false>
 __global__ __launch_bounds__(64) void tv2d_bwd_small_kernel(Small2dBwdParams p)
 {
     constexpr int P = S + 1;                        // tile pitch
@@ -181,57 +178,20 @@ __global__ __launch_bounds__(64) void tv2d_bwd_small_kernel(Small2dBwdParams p)
     // the segment code of a pass is fetched one pass ahead, so that its latency hides behind
     // the pass before
     const bool cvalid = pvalid && (FULL || idx < W), rvalid = pvalid && (FULL || idx < H);
-    auto fetch_code = [&](int pass) -> uint4 {
-        if (pass < 0) return make_uint4(0u, 0u, 0u, 0u);
+    auto fetch_code = [&](int pass) -> uint2 {
+        if (pass < 0) return make_uint2(0u, 0u);
         const bool col = (pass & 1) != 0;
-        if constexpr (!FROM_X) {
-            if (!(col ? cvalid : rvalid)) return make_uint4(0u, 0u, 0u, 0u);
-            const uint2 c = p.codes[(size_t)pass * p.code_stride + (size_t)plane * (col ? W : H) + idx];
-            return make_uint4(c.x, c.y, 0u, 0u);
-        } else {
-            // the lane's row or column of the pass's output, then one bit per neighbour pair
-            const float *xs = p.saved + (size_t)pass * p.saved_stride + (size_t)plane * HW;
-            float xv[S];
-            if (col) {
-#pragma unroll
-                for (int r = 0; r < S; ++r) xv[r] = (cvalid && (FULL || r < H)) ? xs[r * W + idx] : 0.f;
-            } else if (FULL && ((uintptr_t)xs % 16) == 0) {
-#pragma unroll
-                for (int c = 0; c < S; c += 4) {
-                    float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (rvalid) q = *reinterpret_cast<const float4 *>(xs + idx * S + c);
-                    xv[c] = q.x; xv[c + 1] = q.y; xv[c + 2] = q.z; xv[c + 3] = q.w;
-                }
-            } else {
-#pragma unroll
-                for (int c = 0; c < S; ++c) xv[c] = (rvalid && (FULL || c < W)) ? xs[idx * W + c] : 0.f;
-            }
-            // built from the highest dual of each word down, one shift-in per dual, so that dual k
-            // ends up at bit k & 31; the sign of x[k] - x[k+1] says "rises", that of -|.| "differs"
-            uint4 c = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-            for (int k = S - 2; k >= 32; --k) {
-                const float d = xv[k] - xv[k + 1];
-                c.w = __builtin_amdgcn_alignbit(c.w, __float_as_uint(d), 31);
-                c.z = __builtin_amdgcn_alignbit(c.z, __float_as_uint(0.0f - fabsf(d)), 31);
-            }
-#pragma unroll
-            for (int k = (S - 2 < 31 ? S - 2 : 31); k >= 0; --k) {
-                const float d = xv[k] - xv[k + 1];
-                c.y = __builtin_amdgcn_alignbit(c.y, __float_as_uint(d), 31);
-                c.x = __builtin_amdgcn_alignbit(c.x, __float_as_uint(0.0f - fabsf(d)), 31);
-            }
-            return c;
-        }
+        if (!(col ? cvalid : rvalid)) return make_uint2(0u, 0u);
+        return p.codes[(size_t)pass * p.code_stride + (size_t)plane * (col ? W : H) + idx];
     };
-    uint4 code_next = fetch_code(2 * p.sweeps - 1);
+    uint2 code_next = fetch_code(2 * p.sweeps - 1);
     for (int k = p.sweeps - 1; k >= 0; --k) {
         const bool first = (k == p.sweeps - 1);
         // ---- adjoint of the column pass: B <- C^T(A - B) + B  (B = 0 in the first reverse step);
         //      a lane holds column idx of its plane
         {
             const bool valid = cvalid;
-            const uint4 code = code_next;
+            const uint2 code = code_next;
             code_next = fetch_code(2 * k);
             const float *a = A + (h * S) * P + idx;
             float *b = B + (h * S) * P + idx;
@@ -259,7 +219,7 @@ __global__ __launch_bounds__(64) void tv2d_bwd_small_kernel(Small2dBwdParams p)
         //      a lane holds row idx of its plane
         {
             const bool valid = rvalid;
-            const uint4 code = code_next;
+            const uint2 code = code_next;
             code_next = fetch_code(2 * k - 1);
             float *a = A + (h * S + idx) * P;
             const float *b = B + (h * S + idx) * P;

@@ -295,6 +295,22 @@ int launch_fwd_pairs_2d(const tvk::Small2dFwdParams &q, hipStream_t stream)
     return TV_ERR_UNSUPPORTED;
 }
 
+// The reverse sweep on planes of 33-64 samples a side, two lanes a row.
+int launch_bwd_pairs_2d(const tvk::Small2dBwdParams &q, hipStream_t stream)
+{
+    const int longer = q.H > q.W ? q.H : q.W, shorter = q.H > q.W ? q.W : q.H;
+    const dim3 grid((uint32_t)q.planes), block(128);
+#define TV_PAIR(C)                                                                                                \
+    if (longer <= 2 * C) {                                                                                        \
+        if (shorter == 2 * C) hipLaunchKernelGGL((tvk::tv2d_bwd_pair_kernel<C, true>), grid, block, 0, stream, q); \
+        else hipLaunchKernelGGL((tvk::tv2d_bwd_pair_kernel<C, false>), grid, block, 0, stream, q);                 \
+        return launch_status();                                                                                   \
+    }
+    TV_PAIR(20) TV_PAIR(24) TV_PAIR(28) TV_PAIR(32)
+#undef TV_PAIR
+    return TV_ERR_UNSUPPORTED;
+}
+
 // ---- slot order for the grouped grid -----------------------------------------------
 //
 // A tile's cost is its largest Newton step count, which depends mostly on where the slot's
@@ -1282,6 +1298,19 @@ static bool pairs_2d_apply(int64_t H, int64_t W)
     return longer > 32 && longer <= 64 && 5 * shorter >= 4 * ((longer + 7) / 8 * 8);
 }
 
+// The reverse sweep of these, in one launch with two lanes a row (rows move in 16-byte pieces), beyond the
+// counts up to which a plane per workgroup is faster; the measurements are in tv_dispatch.hpp.  Planes that
+// do not fill their square pay for the samples past their ends: with one sweep, or with sides beyond 56,
+// they stay out where a second or third round of 1024 planes (four a CU) is mostly empty.
+static bool pairs_2d_bwd(int64_t planes, int64_t H, int64_t W, int sweeps)
+{
+    if (!pairs_2d_apply(H, W) || W % 4 != 0) return false;
+    const int64_t most = tvd::get(tvd::kPlanePerGroup64BwdPlanes), longer = H > W ? H : W;
+    if (H == W && H % 8 == 0) return planes > most;
+    if (longer <= 56 && sweeps >= 2) return planes > most;
+    return planes > (longer <= 56 ? most : most + most / 2) && (planes <= 1024 || planes >= 3072);
+}
+
 static bool plane_per_group_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
 {
     if (small_planes(H, W)) {
@@ -1466,7 +1495,7 @@ int tv2d_prox_bwd_bf16(const uint16_t *g_up, uint16_t *grad_y, float *grad_lam, 
     if (small_side(H, W) == 32 && planes <= tvd::get(tvd::kPlanePerGroupBwdPlanes))
         hipLaunchKernelGGL((tvk::tv2d_bwd_plane_kernel<16, 2, true>), dim3((uint32_t)planes), dim3(512), 0, stream, q);
     else
-        TV_SMALL2D_LAUNCH(tvk::tv2d_bwd_small_kernel, q, planes, H, W, stream, false, true);
+        TV_SMALL2D_LAUNCH(tvk::tv2d_bwd_small_kernel, q, planes, H, W, stream, true);
     if (launch_status() != TV_OK) return TV_ERR_HIP;
     if (!grad_lam) return TV_OK;
     const tv_lambda lp = {lam.lam, lam.count, 1};
@@ -1510,9 +1539,8 @@ int tv2d_prox_bwd(const float *g_up, float *grad_y, float *grad_lam, int64_t pla
     // Ybar and Pbar coincide from the second reverse step on, so two tensors carry the state.
     if ((cb && small_side(H, W) == 32 && planes <= tvd::get(tvd::kPlanePerGroupBwdPlanes)) ||
         (!cb && H <= 64 && W <= 64 &&
-         planes <= tvd::get((H == 64 && W == 64) ? tvd::kPlanePerGroup64BwdPlanes
-                                                 : (sweeps == 1 ? tvd::kPlanePerGroup64BwdRaggedPlanes
-                                                                : tvd::kPlanePerGroup64BwdRaggedPlanesK2)))) {
+         !pairs_2d_bwd(planes, H, W, sweeps) &&
+         planes <= tvd::get(sweeps == 1 ? tvd::kPlanePerGroup64BwdRaggedPlanes : tvd::kPlanePerGroup64BwdRaggedPlanesK2))) {
         // a small batch of planes of 17-64 samples a side: one launch, a plane per workgroup
         tvk::Small2dBwdParams q;
         q.g_up = g_up; q.gy = grad_y; q.codes = codes(0); q.code_stride = cb / sizeof(uint2);
@@ -1528,22 +1556,28 @@ int tv2d_prox_bwd(const float *g_up, float *grad_y, float *grad_lam, int64_t pla
         const tv_lambda lp = {lam.lam, lam.count, 1};
         return launch_reduce_lambda(partial(0), grad_lam, planes, lp, 0, stream);
     }
-    if (cb || (H == 64 && W == 64)) {
-        // planes of at most 32 x 32, or of 64 x 64: the whole reverse sweep in one launch, state
-        // resident in LDS (up to 32 x 32 the segments come from the codes, at 64 x 64 from the saved
-        // pass outputs; other planes of 33-64 samples a side are faster pass by pass: 40 x 40,
-        // K = 1, 44 us against 116)
+    if (!cb && pairs_2d_bwd(planes, H, W, sweeps)) {
+        // planes of 33-64 samples a side: the same, two lanes a row
+        tvk::Small2dBwdParams q;
+        q.g_up = g_up; q.gy = grad_y; q.codes = nullptr; q.code_stride = 0;
+        q.saved = saved(0); q.saved_stride = tb / sizeof(float);
+        q.partial = grad_lam ? partial(0) : nullptr;
+        q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
+        q.stream = 0u;
+        st = launch_bwd_pairs_2d(q, stream);
+        if (st != TV_OK || !grad_lam) return st;
+        const tv_lambda lp = {lam.lam, lam.count, 1};
+        return launch_reduce_lambda(partial(0), grad_lam, planes, lp, 0, stream);
+    }
+    if (cb) {
+        // planes of at most 32 x 32: the whole reverse sweep in one launch, state resident in LDS
         tvk::Small2dBwdParams q;
         q.g_up = g_up; q.gy = grad_y; q.codes = codes(0); q.code_stride = cb / sizeof(uint2);
         q.saved = saved(0); q.saved_stride = tb / sizeof(float);
         q.partial = grad_lam ? partial(0) : nullptr;
         q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
         q.stream = (planes * H * W >= tvd::get(tvd::kStreamBytes) / 4) ? 1u : 0u;
-        if (cb) {
-            TV_SMALL2D_LAUNCH(tvk::tv2d_bwd_small_kernel, q, planes, H, W, stream);
-        } else {
-            hipLaunchKernelGGL((tvk::tv2d_bwd_small_kernel<64, true>), dim3((uint32_t)planes), dim3(64), 0, stream, q);
-        }
+        TV_SMALL2D_LAUNCH(tvk::tv2d_bwd_small_kernel, q, planes, H, W, stream);
         if (launch_status() != TV_OK) return TV_ERR_HIP;
         if (!grad_lam) return TV_OK;
         const tv_lambda lp = {lam.lam, lam.count, 1};

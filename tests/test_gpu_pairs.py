@@ -156,3 +156,23 @@ def test_rows_of_33_to_64_alone_in_company_and_scaled(n, axis, pairs):
         s = np.float32(2.0 ** power)
         x = solve(y * s, lam * s)[0].astype(np.float64) / float(s)
         assert np.all(np.abs(x - ref).max(axis=1) <= floor), power
+
+
+@pytest.mark.parametrize("H,W", [(40, 40), (33, 36), (33, 40), (39, 40), (41, 44), (39, 48), (48, 40), (48, 48), (49, 52),
+                                 (45, 56), (56, 56), (57, 60), (52, 64), (64, 52), (63, 64), (64, 64)])
+@pytest.mark.parametrize("K", [1, 3])
+def test_reverse_sweep_of_planes_of_33_to_64(H, W, K):
+    """The one-launch reverse sweep with two lanes a row, both ends of every half length and the most samples
+    past a row's end, against the oracle."""
+    import paper_2204_03643_amd as tv
+    rng = np.random.default_rng(H * 100 + W + K)
+    y = np.maximum(rng.normal(size=(5, H, W)), -0.3).astype(np.float32)
+    g = rng.normal(size=y.shape).astype(np.float32)
+    lam = np.array([0.02, 0.3, 1.5], np.float32)
+    most = tv.tv_dispatch_threshold("plane_per_group64_bwd_planes")
+    tv.tv_dispatch_override("plane_per_group64_bwd_planes", 0)
+    try:
+        out = run_2d(y, lam, K, g)
+    finally:
+        tv.tv_dispatch_override("plane_per_group64_bwd_planes", most)
+    check_2d(y, lam, K, g, out, "reverse pairs %dx%d" % (H, W))
