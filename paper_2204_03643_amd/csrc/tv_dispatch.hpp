@@ -40,6 +40,7 @@ enum {
     kThreadPerSample1dRows,
     kPair1dRows,
     kPair1dLongRows,
+    kWavePerRowRows,
     kOneLambdaTriSide,
     kMlMinLength,
     kMlCoarsest,
@@ -193,6 +194,16 @@ inline Threshold table[kCount] = {
     //   56 samples, 32 768 rows  14 /  15,  19 /  23,  131 072:  32 /  28,  46 /  42,  524 288: 110 /  79, 158 / 113
     //   64 samples, 65 536 rows  20 /  21,  28 /  30,  131 072:  32 /  35,  46 /  50,  524 288: 117 /  99, 165 / 144
     {"pair_1d_long_rows", 24576, "1D rows of 33-64 samples: two lanes a row beyond this many rows x 1, 2, 3, 4 (up to 40, 48, 56, 64 samples; three quarters of it: strided rows)"},
+    // 1D calls on unit-stride rows of 65-256 samples: 32 threads (up to 128 samples) or 64 per row, four samples
+    // each, instead of 8-32 threads with 8 or 12.  Few waves are bound by their chains, which follow the samples
+    // per thread; many by their instructions, of which the scans across more threads take more.  Forward, N(0, 1)
+    // with lambda 1, 8 or 12 samples per thread / four:
+    //    65 samples,   64 rows 13.3 /  7.5, 1024: 16.3 / 8.7, 8192: 17.3 / 12.4, 16 384: 20.2 / 18.8, 32 768: 26.1 / 29.3
+    //   128 samples,   64 rows 10.0 /  7.6, 1024: 11.1 / 9.3, 8192: 13.8 / 12.6, 12 288: 17.3 / 16.1, 16 384: 18.0 / 19.3
+    //   160 samples,   64 rows 14.5 /  7.7, 1024: 14.9 / 8.3, 4096: 15.8 / 12.2
+    //   192 samples, 6144 rows 17.2 / 15.0, 8192: 18.4 / 18.4, 12 288: 21.0 / 23.7
+    //   256 samples,   64 rows  9.6 /  7.0, 1024: 12.0 / 8.9, 4096: 14.9 / 12.1, 6144: 15.2 / 15.5, 12 288: 22.5 / 24.1
+    {"wave_per_row_rows", 6144, "1D calls on unit-stride rows of 65-256 samples: four samples a thread up to this many rows (half as many again: up to 128 samples)"},
     // 2D pass by pass with ONE lambda for all planes and three sweeps or more: sides up to this many
     // samples (768 at most, and beyond 64) are solved by tridiagonal elimination (tv_long_tri.hpp), not
     // by block means.  The slower one of the two is kept here for the sake of one number, the

@@ -659,6 +659,18 @@ inline hipError_t launch_fwd_long(const FwdParams &p, hipStream_t s)
     TV_LONG_DISPATCH(launch_fwd_long_t, p, s, 8);
 }
 
+// Small batches of unit-stride rows of 65-256 samples (wave_per_row_rows in tv_dispatch.hpp): four samples per
+// thread instead of eight or twelve, cold start.  A lone wave per SIMD is bound by its chains, which follow
+// the samples per thread.
+inline hipError_t launch_fwd_long_few(const FwdParams &p, hipStream_t s)
+{
+    if (p.L.n <= 128)
+        hipLaunchKernelGGL((tv1d_fwd_long_kernel<32, 4, 2, false, false, 0>), dim3((p.L.n_rows + 1) / 2), dim3(64), 0, s, p);
+    else
+        hipLaunchKernelGGL((tv1d_fwd_long_kernel<64, 4, 1, false, false, 0>), dim3(p.L.n_rows), dim3(64), 0, s, p);
+    return hipGetLastError();
+}
+
 // The forward launch with step records (cold start, unit-stride rows): one mapping of each kind
 // -- rows inside a wave (wave-level fences, scans inside the wave), and a workgroup per
 // row with 256 and with 1024 threads (workgroup barriers, the waves' totals through LDS).

@@ -699,6 +699,9 @@ int run_fwd(const float *y, const float *addend, float *x, float *resid, int32_t
         if (pl.row_floats > 0 && rows_packed(r) && (x_end <= y || y_end <= x))
             return run_fwd_multilevel(p, l, n_rows, pl, nullptr, s);
     }
+    if (!warm && !addend && r.elem_stride == 1 && r.length > 64 && r.length <= 256 &&
+        n_rows <= tvd::get(tvd::kWavePerRowRows) / 2 * (r.length <= 128 ? 3 : 2))
+        return tvk::launch_fwd_long_few(p, s) == hipSuccess ? TV_OK : TV_ERR_HIP;
     // long rows that start cold after all (in place, with gaps between them, strided): the cold
     // start with two candidates, which does not run into the step cap when lambda is of the
     // order of the row's lam_max
