@@ -390,9 +390,9 @@ def dispatch_probe(dev) -> int:
         case(name, "at_threshold_%dx%d_k%d" % (S, S, K), lambda: two_d(n, S, S, K), 0, "a plane per workgroup", "pass by pass")
         case(name, "beyond_%dx%d_k%d" % (S, S, K), lambda: two_d(n + n // 4, S, S, K), big, "pass by pass", "a plane per workgroup")
     for name, H, W, K, other in (("plane_per_group_bwd_planes", 32, 32, 4, "a row per lane"),
-                                 ("plane_per_group64_bwd_planes", 64, 64, 4, "a row per lane"),
-                                 ("plane_per_group64_bwd_ragged_planes", 40, 48, 1, "pass by pass"),
-                                 ("plane_per_group64_bwd_ragged_planes_k2", 40, 48, 3, "pass by pass")):
+                                 ("plane_per_group64_bwd_planes", 64, 64, 4, "two lanes a row"),
+                                 ("plane_per_group64_bwd_ragged_planes", 40, 46, 1, "pass by pass"),
+                                 ("plane_per_group64_bwd_ragged_planes_k2", 40, 46, 3, "pass by pass")):
         n = defaults[name]
         case(name, "at_threshold_k%d" % K, lambda: two_d(n, H, W, K), 0, "reverse sweep: a plane per workgroup",
              "reverse sweep: " + other)
