@@ -352,7 +352,7 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>()))
         }
     }
     // (last, behind the stores that the wave waits for at its end anyway)
-    if constexpr (!DEBUG && chunk_coded<T, C>() && WARM <= 1) {
+    if constexpr (!DEBUG && chunk_coded<T, C>() && WARM <= 2) {
         if (p.chunk_codes) {
             const uint32_t code = chunk_code<T, C>(xs);
             if (rvalid) p.chunk_codes[(size_t)row * T + t] = code;

@@ -621,6 +621,7 @@ int run_fwd_multilevel(FwdParams p, const tv_lambda &l, int64_t n_rows, const Ml
         c.L = make_layout(rc, l, n_rows);
         c.y = yl(lv); c.addend = nullptr; c.x = nullptr; c.x2 = nullptr; c.resid = nullptr;
         c.info = nullptr; c.seg = nullptr; c.order = nullptr;
+        c.chunk_codes = nullptr; c.codes_tag = nullptr;      // the fine level alone leaves these
         c.dual_out = ul(lv); c.dual_pitch = (int32_t)pitch(lv);
         c.ml_flag = flag; c.flag_pitch = flag_pitch; c.ml_skip = 1;
         c.lam_scale = scale;

@@ -57,3 +57,41 @@ def test_reverse_sweep_twice_on_one_workspace():
         out.append((gy, gl))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
     assert bool(torch.isfinite(out[0][0]).all())
+
+
+@pytest.fixture
+def overrides():
+    import paper_2204_03643_amd as tv
+    saved = {}
+
+    def set_to(**values):
+        for name, value in values.items():
+            saved.setdefault(name, tv.tv_dispatch_threshold(name))
+            tv.tv_dispatch_override(name, value)
+    yield set_to
+    for name, value in saved.items():
+        tv.tv_dispatch_override(name, value)
+
+
+def _kept_and_codes(y, lam, K, g, overrides):
+    """The call with its pass outputs kept, and with codes in their place."""
+    kept = run_2d(y, lam, K, g, keep_passes=True)
+    overrides(chunk_codes_bytes=0)
+    return kept, run_2d(y, lam, K, g, keep_passes=False)
+
+
+@pytest.mark.parametrize("H,W,K,count", [(70, 65, 1, 2), (80, 130, 2, 3), (66, 300, 3, 1), (100, 768, 2, 2)])
+@pytest.mark.parametrize("coarsest", [4096, 64])
+def test_codes_behind_a_multilevel_first_pass(H, W, K, count, coarsest, overrides):
+    """With the multilevel start asked for on these sides, the first pass is several launches, of which the
+    last one alone leaves codes and the word that tells codes from pass outputs (one level, and several)."""
+    from parity import check_2d
+    rng = np.random.default_rng(H + W)
+    y = np.cumsum(rng.normal(scale=0.1, size=(3, H, W)), axis=-1).astype(np.float32)
+    g = rng.normal(size=y.shape).astype(np.float32)
+    lam = (10 ** rng.uniform(-0.5, 0.5, size=count)).astype(np.float32)
+    overrides(ml_min_length=65, ml_coarsest=coarsest, one_lambda_tri_side=0)
+    kept, lean = _kept_and_codes(y, lam, K, g, overrides)
+    check_2d(y, lam, K, g, kept, "multilevel first pass %dx%d" % (H, W))
+    for k in ("x", "gy", "gl"):
+        assert np.array_equal(kept[k], lean[k]), k
