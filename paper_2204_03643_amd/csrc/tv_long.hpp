@@ -36,36 +36,36 @@ __device__ __forceinline__ bool chunk_vec_ok(const void *base, int64_t off, int6
 typedef float tv_long_v4f __attribute__((ext_vector_type(4)));
 
 // Chunk codes: what the reverse sweep of a 2D call reads of a pass on sides of 65-768 samples, a word per
-// thread of the pass kernel.  Two bits a sample, sample k0 + i at 32 - 2C + 2i: x changes after it; x does not rise
-// there (duals past the row's end: anything).  An eighth of the bytes of x and no transpose, and the
+// thread of the pass kernel.  Two bits a sample, sample k0 + i at 2i: x changes after it; x rises there (duals
+// past the row's end: anything).  An eighth of the bytes of x and no transpose, and the
 // passes then share two output tensors, which stay in the last-level cache, instead of filling 2K.
 template <int T, int C>
 constexpr bool chunk_coded() { return T <= 64 && C <= 16 && T * C > 64 && T * C <= 768; }
+
+// code <- 2 code + (a differs from b), 2 code + (a is greater): a comparison and an addition that takes it as its
+// carry.  (The comparisons themselves, as where the segments are read off x: the bits of a difference call -0
+// beside +0 a fall, and say nothing next to an infinity.)
+__device__ __forceinline__ uint32_t shift_in_differs(uint32_t code, float a, float b)
+{
+    asm("v_cmp_neq_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(code) : "v"(a), "v"(b) : "vcc");
+    return code;
+}
+__device__ __forceinline__ uint32_t shift_in_greater(uint32_t code, float a, float b)
+{
+    asm("v_cmp_gt_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(code) : "v"(a), "v"(b) : "vcc");
+    return code;
+}
 
 template <int T, int C>
 __device__ __forceinline__ uint32_t chunk_code(const float (&xs)[C])
 {
     const float xnext0 = __shfl_down(xs[0], 1, T);
-    // the sign of a difference, -1, 0 or 1, tells both in three instructions a sample, but not where
-    // infinities meet or beside NaN, which the sum shows
-    float sum = fabsf(xnext0);
-#pragma unroll
-    for (int i = 0; i < C; ++i) sum += fabsf(xs[i]);
     uint32_t code = 0;
-    if (!__any(sum <= 3.0e38f ? 0 : 1)) {
 #pragma unroll
-        for (int i = 0; i < C; ++i) {
-            const float d = ((i + 1 < C) ? xs[i + 1] : xnext0) - xs[i];
-            const int sign = min(max(__float_as_int(d), -1), 1);
-            code = __builtin_amdgcn_alignbit((uint32_t)sign, code, 2);
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < C; ++i) {
-            const float xn = (i + 1 < C) ? xs[i + 1] : xnext0;
-            const uint32_t bits = (xn != xs[i] ? 1u : 0u) | (xn > xs[i] ? 0u : 2u);
-            code = __builtin_amdgcn_alignbit(bits, code, 2);
-        }
+    for (int i = C - 1; i >= 0; --i) {
+        const float xn = (i + 1 < C) ? xs[i + 1] : xnext0;
+        code = shift_in_greater(code, xn, xs[i]);
+        code = shift_in_differs(code, xn, xs[i]);
     }
     return code;
 }
@@ -444,8 +444,8 @@ __global__ __launch_bounds__(T *G, (T * G == 1024 && !COLS && !HAS_SUB) ? 8 : 1)
             chunk_load<C>(p.g, off, es, k0, n, rvalid, g, p.L.stream);
             if constexpr (HAS_SUB) chunk_load<C>(p.sub, off, es, k0, n, rvalid, sb, p.L.stream);
         }
-        jmask = even_bits(code >> (32 - 2 * C));
-        upmask = jmask & ~even_bits(code >> (33 - 2 * C));
+        jmask = even_bits(code);
+        upmask = even_bits(code >> 1);
     } else {
         float x[C];
         if constexpr (XPOSE) {

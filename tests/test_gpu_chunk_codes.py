@@ -80,6 +80,21 @@ def _kept_and_codes(y, lam, K, g, overrides):
     return kept, run_2d(y, lam, K, g, keep_passes=False)
 
 
+@pytest.mark.parametrize("H,W,K,count", [(65, 97, 3, 1), (130, 96, 3, 1), (200, 260, 3, 1), (400, 70, 3, 1), (65, 97, 2, 3), (300, 130, 1, 1)])
+@pytest.mark.parametrize("value", [0.0, -1.0])
+def test_zeros_of_both_signs_are_no_jump(H, W, K, count, value, overrides):
+    """lambda = 0 leaves a masked image as it is, zeros of both signs included: no code may call -0 beside
+    +0 a jump, by elimination (one lambda, three sweeps) or by block means."""
+    rng = np.random.default_rng(H + W)
+    y = rng.normal(size=(3, H, W)).astype(np.float32)
+    y = np.where(np.abs(y) < 0.8, np.where(rng.random(y.shape) < 0.5, np.float32(0), np.float32(-0.0)), y).astype(np.float32)
+    g = rng.normal(size=y.shape).astype(np.float32)
+    kept, lean = _kept_and_codes(y, np.full(count, value, np.float32), K, g, overrides)
+    assert np.array_equal(kept["x"], y)
+    for k in ("x", "gy", "gl"):
+        assert np.array_equal(kept[k], lean[k]), k
+
+
 @pytest.mark.parametrize("H,W,K,count", [(70, 65, 1, 2), (80, 130, 2, 3), (66, 300, 3, 1), (100, 768, 2, 2)])
 @pytest.mark.parametrize("coarsest", [4096, 64])
 def test_codes_behind_a_multilevel_first_pass(H, W, K, count, coarsest, overrides):
