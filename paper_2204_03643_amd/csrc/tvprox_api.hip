@@ -1064,7 +1064,7 @@ int tv_dispatch_override(const char *name, int64_t value)
     if (!name || value < 0) return TV_ERR_SHAPE;
     for (int i = 0; i < tvd::kCount; ++i)
         if (strcmp(name, tvd::table[i].name) == 0) {
-            tvd::table[i].value = value;
+            tvd::set(i, value);
             return TV_OK;
         }
     return TV_ERR_UNSUPPORTED;
@@ -1588,7 +1588,8 @@ int tv2d_prox_bwd(const float *g_up, float *grad_y, float *grad_lam, int64_t pla
         return launch_reduce_lambda(partial(0), grad_lam, planes, lp, 0, stream);
     }
     const ChunkCodes cc = chunk_codes_2d(base, planes, H, W, sweeps, tb, tv2d_workspace_bytes(planes, H, W, sweeps));
-    const uint32_t *tag = cc.stride ? cc.tag : nullptr;
+    const bool codes_or_passes = cc.stride && tb * (size_t)(2 * sweeps + 2) >= (size_t)tvd::chunk_codes_lowest;
+    const uint32_t *tag = codes_or_passes ? cc.tag : nullptr;
     auto pass_codes = [&](int pass) { return tag ? (const uint32_t *)(base + cc.stride * (size_t)pass) : nullptr; };
     for (int k = sweeps - 1; k >= 0; --k) {
         const bool first = (k == sweeps - 1);

@@ -110,3 +110,31 @@ def test_codes_behind_a_multilevel_first_pass(H, W, K, count, coarsest, override
     check_2d(y, lam, K, g, kept, "multilevel first pass %dx%d" % (H, W))
     for k in ("x", "gy", "gl"):
         assert np.array_equal(kept[k], lean[k]), k
+
+
+@pytest.mark.parametrize("H,W,K,count", [(65, 97, 2, 3), (192, 130, 3, 1), (260, 384, 1, 2), (513, 768, 2, 3)])
+def test_threshold_moved_between_forward_and_reverse(H, W, K, count, overrides):
+    """The reverse sweep expects what a forward call leaves at its own moment, and gives the same bits when it
+    finds the other."""
+    import torch
+
+    import paper_2204_03643_amd as tv
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(H)
+    y, g = (torch.randn((3, H, W), generator=gen, device="cuda") for _ in range(2))
+    lam = torch.full((count,), 0.3, device="cuda")
+    L = tv.tv_lambda(lam.data_ptr(), count, 1)
+    wsb = tv.tv2d_workspace_bytes(3, H, W, K)
+    out = []
+    for at_forward in (0, 1 << 40):
+        for at_reverse in (0, 1 << 40):
+            ws = torch.full((wsb,), 0xff, dtype=torch.uint8, device="cuda")
+            x, gy, gl = torch.empty_like(y), torch.empty_like(y), torch.empty_like(lam)
+            overrides(chunk_codes_bytes=at_forward)
+            tv.tv2d_prox_fwd(y, x, 3, H, W, L, K, ws, wsb)
+            overrides(chunk_codes_bytes=at_reverse)
+            tv.tv2d_prox_bwd(g, gy, gl, 3, H, W, L, K, ws, wsb)
+            out.append((x, gy, gl))
+    for other in out[1:]:
+        for a, b in zip(out[0], other):
+            assert torch.equal(a, b)
