@@ -68,11 +68,18 @@ inline Threshold table[kCount] = {
     // waves per SIMD) against pass by pass.  N(0, 1), lambda 10^U(-1.3, 0), forward:
     //   32 x 32, K = 1: 4096 planes 33 / 53,  8192: 59 / 71, 65 536: 393 / 429;  K = 2: 65 536 planes 696 / 864;
     //   28 x 28, K = 1: 16 384 planes 98 / 111, 65 536: 348 / 392;  20 x 20, K = 1: 16 384 planes 61 / 76.
-    // The one launch wins at every count: the values mean "always".
-    {"fused32_full_planes", (int64_t)1 << 40, "2D planes of 32 x 32, one sweep: all passes in one launch up to this many planes"},
-    {"fused32_full_planes_k2", (int64_t)1 << 40, "... two sweeps"},
+    // So for planes that fill, or nearly fill, their square the one launch wins at every count, and with two sweeps or
+    // more it does for every plane: the first three values mean "always".
+    {"fused32_full_planes", (int64_t)1 << 40, "2D planes of 17-32 a side, the shorter at least 15/16 of the longer, one sweep: all passes in one launch up to this many planes"},
+    {"fused32_full_planes_k2", (int64_t)1 << 40, "2D planes of 32 x 32, two sweeps: one launch up to this many planes"},
     {"fused32_full_planes_k3", (int64_t)1 << 40, "... three sweeps or more"},
-    {"fused32_ragged_planes", (int64_t)1 << 40, "2D planes of 17-32 a side other than 32 x 32, one sweep: one launch up to this many planes"},
+    // Other planes leave lanes idle, a wave being a plane whatever it holds, and with one sweep there is
+    // little to save.  K = 1, one launch / pass by pass, and / pass by pass with a row per lane:
+    //   20 000 planes:  1 x 32: 83 / 22 / 28,  8 x 32: 112 / 41 / 49,  32 x 16: 146 / 66 / 83,  10 x 20: 75 / - / 68,  20 x 28: 0.87 of it;
+    //   12 288 planes: 24 x 32 0.93 / 1.24 of it, 20 x 28 0.95 / 1.42, 16 x 20 0.69 / 1.81, 1 x 32 0.34 / 1.33;
+    //   80 000 planes:  1 x 32: 295 / 44 / 47,  16 x 24: 0.47 / 0.98 of it,  20 x 32: 0.76 / 0.80.
+    // (The line is where it was with a row per lane; for the thinnest planes it could lie lower.)
+    {"fused32_ragged_planes", 12288, "2D planes with a longer side of 17-32 and a shorter below 15/16 of it (or below 17), one sweep: one launch up to this many planes"},
     // 2D, planes of 9-16 samples a side, single sweep, forward + backward, one launch against pass
     // by pass: 16 x 16, 24 576 planes 67 / 73, 49 152: 101 / 107, 98 304: 178 / 180, 262 144: 445 / 500;
     // 14 x 14, 49 152 planes 111 / 118, 262 144: 507 / 579 (the value means "always").

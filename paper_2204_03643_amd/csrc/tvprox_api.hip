@@ -1332,12 +1332,15 @@ static bool plane_per_group_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
 
 // Whether all passes of the forward call on planes of at most 32 x 32 go in one launch: the plane counts,
 // and the measurements behind them, are in tv_dispatch.hpp; planes of at most 8 x 8 are always better off so.
-static bool fused_fwd_applies(int side, bool full, int64_t planes, int sweeps)
+static bool fused_fwd_applies(int64_t H, int64_t W, int64_t planes, int sweeps)
 {
+    const int side = small_side(H, W);
     if (side == 32) {
-        if (!full) return sweeps >= 2 || planes <= tvd::get(tvd::kFused32RaggedPlanes);
-        return planes <= tvd::get(sweeps == 1 ? tvd::kFused32FullPlanes
-                                              : (sweeps == 2 ? tvd::kFused32FullPlanesK2 : tvd::kFused32FullPlanesK3));
+        const int64_t longer = H > W ? H : W, shorter = H > W ? W : H;
+        const bool near_square = shorter > 16 && 16 * shorter >= 15 * longer;
+        if (sweeps == 1) return planes <= tvd::get(near_square ? tvd::kFused32FullPlanes : tvd::kFused32RaggedPlanes);
+        if (shorter < 32) return true;
+        return planes <= tvd::get(sweeps == 2 ? tvd::kFused32FullPlanesK2 : tvd::kFused32FullPlanesK3);
     }
     if (side == 16) return sweeps >= 2 || planes <= tvd::get(tvd::kFused16OneSweepPlanes);
     return true;
@@ -1381,7 +1384,7 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
         else hipLaunchKernelGGL((tvk::tv2d_fwd_plane_kernel<8, 8>), grid, dim3(512), 0, stream, q);
         return launch_status();
     }
-    if (cb && fused_fwd_applies(small_side(H, W), H == small_side(H, W) && W == H, planes, sweeps)) {
+    if (cb && fused_fwd_applies(H, W, planes, sweeps)) {
         // planes of at most 32 x 32: all passes in one launch, the planes resident in LDS
         tvk::Small2dFwdParams q;
         q.y = y; q.x = x; q.saved = saved(0); q.saved_stride = tb / sizeof(float); q.keep_passes = tvd::get(tvd::kFusedKeepsPasses) != 0 ? 1u : 0u;

@@ -1,0 +1,41 @@
+"""Calls on either side of the dispatch rules that look at a plane's shape or at how rows lie, forced onto small
+batches through the thresholds, against the oracle."""
+import numpy as np
+import pytest
+
+from gpuutil import run_2d
+from parity import check_2d
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def overrides():
+    import paper_2204_03643_amd as tv
+    saved = tv.tv_dispatch_thresholds()
+
+    def set_to(**values):
+        for name, value in values.items():
+            tv.tv_dispatch_override(name, value)
+    yield set_to
+    for name, value in saved.items():
+        tv.tv_dispatch_override(name, value)
+
+
+def _planes(shape):
+    rng = np.random.default_rng(shape[0] * 10000 + shape[1] * 100 + shape[2])
+    y = rng.normal(size=shape).astype(np.float32)
+    y[1::3] = np.maximum(np.round(y[1::3], 1), 0)
+    return y, (10 ** rng.uniform(-2, 0.3, size=3)).astype(np.float32), rng.normal(size=shape).astype(np.float32)
+
+
+@pytest.mark.parametrize("one_launch", [False, True])
+@pytest.mark.parametrize("shape", [(70, 1, 17), (33, 4, 32), (40, 32, 3), (21, 16, 17), (9, 32, 16), (12, 15, 32), (10, 20, 28),
+                                   (7, 17, 18), (5, 30, 32), (6, 29, 32)])
+def test_one_sweep_on_planes_of_at_most_32(shape, one_launch, overrides):
+    """One sweep in one launch and pass by pass: thin planes, planes that nearly fill their square (30 x 32) and the
+    next that do not (29 x 32)."""
+    value = (1 << 40) if one_launch else 0
+    overrides(plane_per_group_planes=0, fused32_ragged_planes=value, fused32_full_planes=value)
+    y, lam, g = _planes(shape)
+    check_2d(y, lam, 1, g, run_2d(y, lam, 1, g), "%s one launch: %s" % (shape, one_launch))
