@@ -102,7 +102,12 @@ inline Threshold table[kCount] = {
     //            K = 4: 768 planes 41 / 41, 49 / 55,  1024: 49 / 41, 59 / 55;
     //   20 x 30, K = 4: 1024 planes 46 / 51, 54 / 60, 1280: 57 / 58, 68 / 70.
     // (With two sweeps or more the library takes a third more planes than the value says.)
-    {"plane_per_group_planes", 768, "2D planes of 17-32 a side: one launch, a plane per workgroup, up to this many planes"},
+    // Planes with one side of 29-32 that are no squares take three quarters more: two lanes a row lie in halves of
+    // 16 and leave what the shorter side lacks idle.  This kernel / two lanes a row:
+    //   1 x 32, K = 1: 800 planes 11 / 15, 1200: 14 / 15, 1536: 16 / 17;  8 x 32: 800: 16 / 18, 1000: 17 / 18, 1300: 22 / 23;
+    //   32 x 16: 800 planes 20 / 23, 1200: 24 / 25;  K = 4: 1000: 47 / 53, 1200: 0.96 of it, 1536: 1.07 of it;
+    //   20 x 32: 1000 planes 21 / 23, 1300: 1.04 of it;  28 x 32, K = 4: 1000: 0.91 of it, 1200: 0.95, 1536: 1.11.
+    {"plane_per_group_planes", 768, "2D planes of 17-32 a side: one launch, a plane per workgroup, up to this many planes (a third more: two sweeps and more; three quarters more: one side of 29-32, no square)"},
     //   64 x 64, K = 1:  512 planes  47 /  50,  768:  67 /  60, 1024:  78 /  73, 1536: 109 / 94;
     //   48 x 48, K = 1:  512 planes  35 /  38,  768:  55 /  54, 1024:  64 /  57.
     {"plane_per_group64_planes", 512, "2D planes of 33-64 a side, one sweep: one launch, a plane per workgroup, up to this many planes"},

@@ -1318,9 +1318,10 @@ static bool pairs_2d_bwd(int64_t planes, int64_t H, int64_t W, int sweeps)
 static bool plane_per_group_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
 {
     if (small_planes(H, W)) {
-        // (from two sweeps on a third more)
+        // (from two sweeps on a third more; planes of 29-32 on one side only, three quarters more)
         const int64_t most = tvd::get(tvd::kPlanePerGroupPlanes);
-        return small_side(H, W) == 32 && planes <= (sweeps == 1 ? most : most + most / 3);
+        const bool oblong = H != W && (H > 28 || W > 28);
+        return small_side(H, W) == 32 && planes <= most + (oblong ? 3 * (most / 4) : sweeps == 1 ? 0 : most / 3);
     }
     if (H > 64 || W > 64) return false;
     if (sweeps == 1) return planes <= tvd::get(tvd::kPlanePerGroup64Planes);
