@@ -30,6 +30,8 @@ enum {
     kPlanePerGroup64FullPlanesK2,
     kPlanePerGroup64FullPlanesK3,
     kPlanePerGroup64FullPlanesK5,
+    kPair2dPlanes,
+    kPair2dManyPlanes,
     kPlanePerGroupBwdPlanes,
     kPlanePerGroup64BwdPlanes,
     kPlanePerGroup64BwdRaggedPlanes,
@@ -117,19 +119,29 @@ inline Threshold table[kCount] = {
     //            K = 4: 1280 planes 0.93 0.99, 1536: 0.97 1.01, 2048: 1.05 1.07;
     //   64 x 40, K = 3: 1280 planes 0.93 0.99, 1536: 0.96 1.01, 2048: 1.04 1.06.
     {"plane_per_group64_planes_k2", 1280, "... two sweeps or more, planes smaller than 64 x 64"},
-    // Planes whose shorter side fills four fifths of 40, 48, 56 or 64 (pairs_2d_apply) go in one launch with two
-    // lanes a row beyond these counts (two waves a plane, four planes a CU: up to 1024 planes cost what one
-    // plane a CU costs, where this kernel pays a second round beyond 512).  This kernel / two lanes, N(0, 1),
-    // lambda 0.3 and 10^U(-1.3, 0), forward:
-    //   64 x 64, K = 2: 512 planes  46 /  57,  61 /  85,  640:  70 /  58,  88 /  81;
-    //            K = 4: 512 planes  78 /  97, 101 / 135,  640: 118 / 101, 150 / 136, 1024: 146 / 103, 187 / 138;
-    //            K = 8: 512 planes 135 / 169, 180 / 240,  640: 206 / 171, 258 / 235;
-    //   48 x 48, K = 4: 512 planes  69 /  79,  86 / 101,  640: 105 /  79, 131 / 102;
-    //   40 x 36, K = 4: 512 planes  62 /  81,  74 /  98,  640:  94 /  81, 114 /  98;
-    //   56 x 52, K = 4: 640 planes 109 / 117, 137 / 150,  896: 134 / 118, 170 / 155.
-    {"plane_per_group64_full_planes_k2", 512, "... planes that two lanes a row take over, two sweeps"},
-    {"plane_per_group64_full_planes_k3", 512, "... three or four sweeps"},
-    {"plane_per_group64_full_planes_k5", 512, "... five sweeps or more"},
+    // Planes whose shorter side fills four fifths of 40, 48, 56 or 64 (pairs_2d_apply), forward in one launch with two
+    // lanes a row.  N(0, 1), lambda 10^U(-1.3, 0), time of the best other mapping (a plane per workgroup up to 512 planes
+    // with one sweep and 1280 with more, pass by pass beyond) over the time with two lanes a row:
+    //   squares, K = 4:     520 planes  600   1024  1100  1536  2048  4096  16 384
+    //      40 x 40             1.13     1.32  1.63  1.24  1.25  1.27  1.19  1.15
+    //      56 x 56             1.02     1.06  1.36  1.02  1.14  1.14  1.10  1.15
+    //      64 x 64             0.95     1.11  1.37  1.01  1.09  1.31  1.22  1.31     (K = 6, 520 planes: 0.92)
+    //   K = 2: 56 x 56, 1300-3150 planes 0.92-0.96, 4200: 1.06; 64 x 64, 1300-2100: 0.96, 3000: 1.09.
+    //   K = 1: 40 x 40, 768 planes 1.16, 1024: 1.24, otherwise 0.88-1.04;  64 x 64, 512: 0.81, 1024: 1.07, 1100: 0.85.
+    {"plane_per_group64_full_planes_k2", 560, "... planes of 40 x 40, 48 x 48, 56 x 56 and 64 x 64, two sweeps; two lanes a row beyond"},
+    {"plane_per_group64_full_planes_k3", 560, "... three or four sweeps"},
+    {"plane_per_group64_full_planes_k5", 560, "... five sweeps or more"},
+    //   others, K = 4:      600 planes  768   1024  1200  1536  2100  4096  16 384
+    //      36 x 36             1.08     1.19  1.38  1.27  1.05  1.06  0.99  0.96
+    //      44 x 48             1.01     1.09  1.25  1.22  1.02  1.01  0.99  1.03
+    //      48 x 40 (660: 1.05)          1.06        1.18        1.03  0.98  0.95     (K = 2: 0.89-0.95 from 2100 on)
+    //      52 x 56             0.86     0.96  1.10  0.83  0.90   -    0.89  0.93
+    //      60 x 60             0.75     0.90  0.97  0.75  0.91   -    0.92  0.96     (K = 1: 0.6-0.75)
+    //      45 x 45             1.00     1.10  1.17  1.14  1.11  1.14  1.14  1.18     (K = 2: 0.95-1.09)
+    //      50 x 50             0.95     0.95  1.08  0.83  0.97  1.00  0.99  1.12
+    //      63 x 63             0.81     0.92  0.99  0.78  1.12  1.15  1.28  1.27     (K = 3, 57 x 58: 4200 0.91-0.96, 5200 1.02)
+    {"pair_2d_planes", 704, "2D planes of 33-48 a side that fill four fifths of 40 or 48: two lanes a row beyond this many planes, up to plane_per_group64_planes_k2 (one sweep: squares of 40 and 48, up to 1024)"},
+    {"pair_2d_many_planes", 5000, "2D planes of 33-64 a side with rows of no multiple of four samples: two lanes a row from this many planes on (6 sweeps; 4 on sides beyond 48, 3 beyond 56); squares of 56 and 64, two sweeps"},
     // 2D reverse sweep of small batches with a plane per workgroup (tv_plane2d.hpp): both adjoint
     // state tensors of the plane in LDS, 16 x 2 or 8 x 8 threads x samples per row, the segment
     // sums across a row's threads by row shifts.  Against the row-per-lane one-launch kernel (a

@@ -1289,17 +1289,34 @@ static ChunkCodes chunk_codes_2d(char *base, int64_t planes, int64_t H, int64_t 
     return cc;
 }
 
-// Small batches of planes of 17-64 samples a side: one launch with a plane per workgroup
-// (tv_plane2d.hpp), up to the plane counts of tv_dispatch.hpp.  Planes of at most 32 x 32 leave
-// segment codes for the reverse sweep, larger ones their pass outputs.
-// Planes of 33-64 samples a side in one launch, two lanes a row: where the shorter side fills at least four
-// fifths of what the longer one's lanes and registers are laid out for (2C = 40, 48, 56 or 64).
-// 4096 planes, K = 3, against pass by pass: 40 x 40 238 / 272 us, 33 x 33 261 / 243, 40 x 56 406 / 327 (left
-// pass by pass), 64 x 40, K = 1 202 / 127 (likewise).
+// Planes of 33-64 samples a side that the kernels with two lanes a row take in one launch: those whose shorter
+// side fills at least four fifths of what the longer one's lanes and registers are laid out for (2C = 40, 48,
+// 56 or 64).  4096 planes, K = 3, against pass by pass: 40 x 56 406 / 327 us, 64 x 40, K = 1 202 / 127.
 static bool pairs_2d_apply(int64_t H, int64_t W)
 {
     const int64_t longer = H > W ? H : W, shorter = H > W ? W : H;
     return longer > 32 && longer <= 64 && 5 * shorter >= 4 * ((longer + 7) / 8 * 8);
+}
+
+// The forward call on these.  Time goes in rounds of 1024 planes (two waves a plane, four planes a CU), and what a
+// plane lacks of its square is worked on all the same, so there are three ranges (measurements: tv_dispatch.hpp):
+// squares with two sweeps or more; sides of at most 48 in the first round, where the other choice is a plane
+// per workgroup at its second or third plane a CU; and large batches whose rows start on no 16-byte boundary,
+// which the pass-by-pass kernels read word by word, from a number of sweeps on.
+static bool pairs_2d_fwd(int64_t planes, int64_t H, int64_t W, int sweeps)
+{
+    if (!pairs_2d_apply(H, W)) return false;
+    const int64_t longer = H > W ? H : W, many = tvd::get(tvd::kPair2dManyPlanes);
+    const int64_t group_most = tvd::get(tvd::kPlanePerGroup64PlanesK2);
+    const bool square = H == W && H % 8 == 0;
+    if (square && sweeps >= 2) {
+        const int64_t most = tvd::get(sweeps == 2 ? tvd::kPlanePerGroup64FullPlanesK2
+                                                  : (sweeps <= 4 ? tvd::kPlanePerGroup64FullPlanesK3 : tvd::kPlanePerGroup64FullPlanesK5));
+        return planes > most && (sweeps >= 3 || longer <= 48 || planes <= group_most || planes >= many);
+    }
+    const int64_t first_round = sweeps >= 2 ? group_most : (square ? 1024 : 0);
+    if (longer <= 48 && planes > tvd::get(tvd::kPair2dPlanes) && planes <= first_round) return true;
+    return W % 4 != 0 && planes >= many && sweeps >= (longer <= 48 ? 6 : longer <= 56 ? 4 : 3);
 }
 
 // The reverse sweep of these, in one launch with two lanes a row (rows move in 16-byte pieces), beyond the
@@ -1315,6 +1332,9 @@ static bool pairs_2d_bwd(int64_t planes, int64_t H, int64_t W, int sweeps)
     return planes > (longer <= 56 ? most : most + most / 2) && (planes <= 1024 || planes >= 3072);
 }
 
+// Small batches of planes of 17-64 samples a side: one launch with a plane per workgroup
+// (tv_plane2d.hpp), up to the plane counts of tv_dispatch.hpp.  Planes of at most 32 x 32 leave
+// segment codes for the reverse sweep, larger ones their pass outputs.
 static bool plane_per_group_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
 {
     if (small_planes(H, W)) {
@@ -1323,12 +1343,8 @@ static bool plane_per_group_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
         const bool oblong = H != W && (H > 28 || W > 28);
         return small_side(H, W) == 32 && planes <= most + (oblong ? 3 * (most / 4) : sweeps == 1 ? 0 : most / 3);
     }
-    if (H > 64 || W > 64) return false;
-    if (sweeps == 1) return planes <= tvd::get(tvd::kPlanePerGroup64Planes);
-    if (pairs_2d_apply(H, W))
-        return planes <= tvd::get(sweeps == 2 ? tvd::kPlanePerGroup64FullPlanesK2
-                                               : (sweeps <= 4 ? tvd::kPlanePerGroup64FullPlanesK3 : tvd::kPlanePerGroup64FullPlanesK5));
-    return planes <= tvd::get(tvd::kPlanePerGroup64PlanesK2);
+    if (H > 64 || W > 64 || pairs_2d_fwd(planes, H, W, sweeps)) return false;
+    return planes <= tvd::get(sweeps == 1 ? tvd::kPlanePerGroup64Planes : tvd::kPlanePerGroup64PlanesK2);
 }
 
 // Whether all passes of the forward call on planes of at most 32 x 32 go in one launch: the plane counts,
@@ -1401,7 +1417,7 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
         }
         return launch_fwd_small_2d<false>(q, stream);
     }
-    if (pairs_2d_apply(H, W)) {
+    if (pairs_2d_fwd(planes, H, W, sweeps)) {
         // planes of 33-64 samples a side: the same
         tvk::Small2dFwdParams q;
         q.y = y; q.x = x; q.saved = saved(0); q.saved_stride = tb / sizeof(float); q.keep_passes = 1u;

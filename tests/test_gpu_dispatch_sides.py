@@ -39,3 +39,21 @@ def test_one_sweep_on_planes_of_at_most_32(shape, one_launch, overrides):
     overrides(plane_per_group_planes=0, fused32_ragged_planes=value, fused32_full_planes=value)
     y, lam, g = _planes(shape)
     check_2d(y, lam, 1, g, run_2d(y, lam, 1, g), "%s one launch: %s" % (shape, one_launch))
+
+
+@pytest.mark.parametrize("shape,K", [((3, 40, 40), 1), ((3, 36, 44), 2), ((2, 48, 41), 1), ((2, 56, 56), 2), ((2, 52, 56), 2),
+                                     ((2, 55, 50), 4), ((2, 64, 64), 2), ((2, 63, 63), 3), ((2, 60, 64), 3)])
+def test_planes_of_33_to_64(shape, K, overrides):
+    """Planes that two lanes a row can take: by the rule that gives them to that kernel, and to the others."""
+    big = 1 << 40
+    y, lam, g = _planes(shape)
+    outs = []
+    for group, pairs in ((big, 0), (big, big), (0, big)):       # two lanes a row, a plane per workgroup, pass by pass
+        overrides(plane_per_group64_planes=group, plane_per_group64_planes_k2=group, plane_per_group64_full_planes_k2=pairs,
+                  plane_per_group64_full_planes_k3=pairs, pair_2d_planes=pairs, pair_2d_many_planes=pairs)
+        out = run_2d(y, lam, K, g)
+        check_2d(y, lam, K, g, out, "%s K=%d group %d pairs %d" % (shape, K, group > 0, pairs == 0))
+        outs.append(out["x"])
+    # every mapping solves the same problems to rounding
+    for x in outs[1:]:
+        assert np.abs(x - outs[0]).max() <= 2e-5 * (1 + np.abs(y).max())

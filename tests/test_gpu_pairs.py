@@ -16,7 +16,7 @@ def pairs():
     import paper_2204_03643_amd as tv
     saved = {k: tv.tv_dispatch_threshold(k) for k in ("plane_per_group_planes", "thread_per_sample_1d_rows", "pair_1d_long_rows",
                                                       "plane_per_group64_planes", "plane_per_group64_full_planes_k2",
-                                                      "plane_per_group64_full_planes_k3")}
+                                                      "plane_per_group64_full_planes_k3", "pair_2d_planes", "pair_2d_many_planes")}
     for k in saved:
         tv.tv_dispatch_override(k, 0)
     yield
