@@ -208,8 +208,8 @@ inline Threshold table[kCount] = {
     //   28 samples, 32 768 rows 11.8 / 12.3, 40 960: 13.2 / 12.9;                      columns, 24 576: 12.9 / 12.5
     //   32 samples, 32 768 rows 12.3 / 15.7, 49 152: 15.4 / 16.1 (lambda 0.3: 11.5 / 11.0); columns, 32 768: 13.5 / 14.8
     {"pair_1d_rows", 40960, "1D rows of 17-32 samples: two lanes a row beyond this many rows x (n - 12) / 20 (three quarters of it: strided rows)"},
-    // 1D calls on rows of 33-64 samples: beyond this many rows, times 1, 2, 3, 4 for rows of up to 40, 48, 56, 64
-    // samples (and three quarters of that for strided rows), two lanes a row instead of eight threads with
+    // 1D calls on rows of 33-64 samples: beyond this many rows, times 1, 2, 3, 8 for rows of up to 40, 48, 56, 64
+    // samples, two lanes a row instead of eight threads with
     // 8 or 12 samples each: an elimination takes half the instructions of sums over blocks that cross
     // threads, but a wave holds 32 rows and the longer halves chains of 32.  N(0, 1), lambda 0.3 / 1, forward,
     // eight threads / two lanes:
@@ -217,7 +217,12 @@ inline Threshold table[kCount] = {
     //   48 samples, 32 768 rows  13 /  13,  18 /  19,  131 072:  32 /  25,  46 /  37,  524 288: 105 /  69, 152 /  98
     //   56 samples, 32 768 rows  14 /  15,  19 /  23,  131 072:  32 /  28,  46 /  42,  524 288: 110 /  79, 158 / 113
     //   64 samples, 65 536 rows  20 /  21,  28 /  30,  131 072:  32 /  35,  46 /  50,  524 288: 117 /  99, 165 / 144
-    {"pair_1d_long_rows", 24576, "1D rows of 33-64 samples: two lanes a row beyond this many rows x 1, 2, 3, 4 (up to 40, 48, 56, 64 samples; three quarters of it: strided rows)"},
+    //   60 samples, random walks, lambda 2, the ratio of the two: 98 304 rows 0.92, 131 072: 0.84, 196 608: 0.96, 262 144: 0.99,
+    //   524 288: 1.06; its columns 98 304: 1.00, 131 072: 0.91, 196 608: 1.03
+    // Unit-stride rows with 3 samples between them, the ratio at 131 072 rows for lambda 0.3 / 1 / walks: 33 samples
+    // 0.91 / 1.07 / 1.17, 40: 1.15 / 1.38 / 1.51, 44: 0.84 / 0.95 / 0.99, 52: 0.75 / 0.81 / 0.87, 64: 0.59 / 0.68 / 0.69, and no better with
+    // more rows: not beyond 40 samples.
+    {"pair_1d_long_rows", 24576, "1D rows of 33-64 samples: two lanes a row beyond this many rows x 1, 2, 3, 8 (up to 40, 48, 56, 64 samples; beyond 40 not where rows lie apart)"},
     // 1D calls on unit-stride rows of 65-256 samples: 32 threads (up to 128 samples) or 64 per row, four samples
     // each, instead of 8-32 threads with 8 or 12.  Few waves are bound by their chains, which follow the samples
     // per thread; many by their instructions, of which the scans across more threads take more.  Forward, N(0, 1)

@@ -261,12 +261,13 @@ int launch_fwd_pairs(FwdParams p, const tv_rows &r, const tv_lambda &l, int64_t 
 }
 
 // Rows of 33-64 samples: two lanes a row beyond this many rows (tv_dispatch.hpp; halves of 20, 24, 28 and 32
-// samples: chains, and a wave's time alone, grow with the half).
+// samples: chains, and a wave's time alone, grow with the half).  Unit-stride rows with gaps between them are read
+// sample by sample, a row a lane, and beyond 40 samples that costs what the elimination saves.
 int64_t pair_long_rows(const tv_rows &r)
 {
-    const int64_t quarters = (r.length + 7) / 8 - 4;        // 1 .. 4
-    const int64_t most = tvd::get(tvd::kPair1dLongRows) * quarters;
-    return r.elem_stride != 1 ? most / 4 * 3 : most;
+    if (r.length > 40 && r.elem_stride == 1 && !rows_packed(r)) return INT64_MAX;
+    const int64_t factor = r.length <= 40 ? 1 : r.length <= 48 ? 2 : r.length <= 56 ? 3 : 8;
+    return tvd::get(tvd::kPair1dLongRows) * factor;
 }
 
 // Planes of 17-64 samples a side, two lanes a row (tv_pair.hpp): halves as above.

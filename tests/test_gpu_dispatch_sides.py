@@ -3,8 +3,8 @@ batches through the thresholds, against the oracle."""
 import numpy as np
 import pytest
 
-from gpuutil import run_2d
-from parity import check_2d
+from gpuutil import lam_per_row, run_2d
+from parity import check_2d, check_batch
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +57,26 @@ def test_planes_of_33_to_64(shape, K, overrides):
     # every mapping solves the same problems to rounding
     for x in outs[1:]:
         assert np.abs(x - outs[0]).max() <= 2e-5 * (1 + np.abs(y).max())
+
+
+@pytest.mark.parametrize("value", [0, 1 << 40])
+@pytest.mark.parametrize("n", [33, 40, 41, 57, 64])
+def test_rows_that_lie_apart(n, value, overrides):
+    """Unit-stride rows with gaps between them, on both sides of the length and of the count from which two lanes
+    hold such a row; the gaps stay as they were."""
+    import torch
+
+    import paper_2204_03643_amd as tv
+    overrides(pair_1d_long_rows=value)
+    rng = np.random.default_rng(n)
+    y = rng.normal(size=(70, n)).astype(np.float32)
+    y[::3] = np.round(y[::3], 1)
+    lam = (10 ** rng.uniform(-2, 0.7, size=5)).astype(np.float32)
+    spread = np.full((70, n + 3), np.nan, np.float32)
+    spread[:, :n] = y
+    yt, lt = torch.from_numpy(spread).cuda(), torch.from_numpy(lam).cuda()
+    x = torch.full_like(yt, 7.0)
+    tv.tv1d_prox_fwd(yt, x, tv.tv_rows(1, 70 * (n + 3), 70, n + 3, n, 1), tv.tv_lambda(lt.data_ptr(), 5, 2))
+    out = x.cpu().numpy()
+    assert (out[:, n:] == 7.0).all()
+    check_batch(y, lam_per_row(lam, 70, 2), None, out[:, :n], None, label="rows of %d apart" % n)
