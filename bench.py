@@ -377,18 +377,31 @@ def dispatch_probe(dev) -> int:
     for K in (1, 4):
         most = n if K == 1 else n + n // 3      # (a third more with several sweeps)
         case("plane_per_group_planes", "at_threshold_k%d" % K, lambda: two_d(most, 32, 32, K), 0,
-             "a plane per workgroup", "the row-per-lane kernels")
+             "a plane per workgroup", "two lanes a row")
         case("plane_per_group_planes", "beyond_k%d" % K, lambda: two_d(most + most // 4, 32, 32, K), big,
-             "the row-per-lane kernels", "a plane per workgroup")
+             "two lanes a row", "a plane per workgroup")
     case("plane_per_group_planes", "at_a_fifth_k4", lambda: two_d(n // 5, 32, 32, 4), 0,
-         "a plane per workgroup", "the row-per-lane kernels")
-    for name, S, K in (("plane_per_group64_planes", 64, 1), ("plane_per_group64_planes_k2", 48, 2),
-                       ("plane_per_group64_planes_k2", 48, 4), ("plane_per_group64_full_planes_k2", 64, 2),
-                       ("plane_per_group64_full_planes_k3", 64, 3), ("plane_per_group64_full_planes_k3", 64, 4),
-                       ("plane_per_group64_full_planes_k5", 64, 5), ("plane_per_group64_full_planes_k5", 64, 8)):
+         "a plane per workgroup", "two lanes a row")
+    most = n + 3 * (n // 4)                     # (three quarters more: one side of 29-32, no square)
+    case("plane_per_group_planes", "at_threshold_8x32_k1", lambda: two_d(most, 8, 32, 1), 0, "a plane per workgroup", "two lanes a row")
+    case("plane_per_group_planes", "beyond_8x32_k1", lambda: two_d(most + most // 4, 8, 32, 1), big, "two lanes a row",
+         "a plane per workgroup")
+    for name, H, W, K, beyond in (("plane_per_group64_planes", 64, 64, 1, "pass by pass"),
+                                  ("plane_per_group64_planes_k2", 40, 64, 2, "pass by pass"),
+                                  ("plane_per_group64_planes_k2", 40, 64, 4, "pass by pass"),
+                                  ("plane_per_group64_full_planes_k2", 64, 64, 2, "two lanes a row"),
+                                  ("plane_per_group64_full_planes_k3", 64, 64, 3, "two lanes a row"),
+                                  ("plane_per_group64_full_planes_k3", 64, 64, 4, "two lanes a row"),
+                                  ("plane_per_group64_full_planes_k5", 64, 64, 5, "two lanes a row"),
+                                  ("plane_per_group64_full_planes_k5", 64, 64, 8, "two lanes a row"),
+                                  ("pair_2d_planes", 44, 48, 3, "two lanes a row")):
         n = defaults[name]
-        case(name, "at_threshold_%dx%d_k%d" % (S, S, K), lambda: two_d(n, S, S, K), 0, "a plane per workgroup", "pass by pass")
-        case(name, "beyond_%dx%d_k%d" % (S, S, K), lambda: two_d(n + n // 4, S, S, K), big, "pass by pass", "a plane per workgroup")
+        case(name, "at_threshold_%dx%d_k%d" % (H, W, K), lambda: two_d(n, H, W, K), 0, "a plane per workgroup", beyond)
+        case(name, "beyond_%dx%d_k%d" % (H, W, K), lambda: two_d(n + n // 4, H, W, K), big, beyond, "a plane per workgroup")
+    n = defaults["pair_2d_many_planes"]
+    for H, W, K in ((57, 58, 3), (50, 50, 4), (33, 33, 6)):
+        case("pair_2d_many_planes", "at_threshold_%dx%d_k%d" % (H, W, K), lambda: two_d(n, H, W, K), big, "two lanes a row", "pass by pass")
+        case("pair_2d_many_planes", "below_%dx%d_k%d" % (H, W, K), lambda: two_d(n - n // 4, H, W, K), 0, "pass by pass", "two lanes a row")
     for name, H, W, K, other in (("plane_per_group_bwd_planes", 32, 32, 4, "a row per lane"),
                                  ("plane_per_group64_bwd_planes", 64, 64, 4, "two lanes a row"),
                                  ("plane_per_group64_bwd_ragged_planes", 40, 46, 1, "pass by pass"),
@@ -407,10 +420,10 @@ def dispatch_probe(dev) -> int:
         case(name, "beyond_k%d" % K, lambda: two_d(n + n // 4, 32, 32, K), big, "pass by pass", "one launch")
     n = defaults["fused32_ragged_planes"]
     if n > (1 << 20):               # "always", as above
-        case("fused32_ragged_planes", "at_65536_planes_k1", lambda: two_d(65536, 28, 28, 1), 0, "one launch", "pass by pass")
+        case("fused32_ragged_planes", "at_65536_planes_k1", lambda: two_d(65536, 20, 28, 1), 0, "one launch", "pass by pass")
     else:
-        case("fused32_ragged_planes", "at_threshold_k1", lambda: two_d(n, 28, 28, 1), 0, "one launch", "pass by pass")
-        case("fused32_ragged_planes", "beyond_k1", lambda: two_d(n + n // 4, 28, 28, 1), big, "pass by pass", "one launch")
+        case("fused32_ragged_planes", "at_threshold_k1", lambda: two_d(n, 20, 28, 1), 0, "one launch", "pass by pass")
+        case("fused32_ragged_planes", "beyond_k1", lambda: two_d(n + n // 4, 20, 28, 1), big, "pass by pass", "one launch")
     n = defaults["fused16_one_sweep_planes"]
     if n > (1 << 20):               # "always", as above
         case("fused16_one_sweep_planes", "at_262144_planes_k1", lambda: two_d(262144, 16, 16, 1), 0, "one launch", "pass by pass")
@@ -440,6 +453,22 @@ def dispatch_probe(dev) -> int:
          big, "two lanes per row", "16 threads per row")
     case("pair_1d_rows", "at_a_quarter", lambda: one_d((n // (128 * 128), 128, 32, 32), 128, 32, False), 0,
          "16 threads per row", "two lanes per row")
+    for length, factor in ((48, 2), (60, 8)):
+        n = defaults["pair_1d_long_rows"] * factor
+        case("pair_1d_long_rows", "at_threshold_%d" % length, lambda: one_d((n // 128, 128, length), 128, 1, False), 0,
+             "8 threads per row", "two lanes per row")
+        case("pair_1d_long_rows", "beyond_%d" % length, lambda: one_d((n // 128 + n // 512, 128, length), 128, 1, False), big,
+             "two lanes per row", "8 threads per row")
+    n = defaults["wave_per_row_rows"]
+    for length, most in ((128, n + n // 2), (256, n)):
+        case("wave_per_row_rows", "at_threshold_%d" % length, lambda: one_d((most // 64, 64, length), 64, 1, False), 0,
+             "4 samples per thread", "8 or 12")
+        case("wave_per_row_rows", "beyond_%d" % length, lambda: one_d((most // 64 + most // 256, 64, length), 64, 1, False), big,
+             "8 or 12 samples per thread", "4")
+    # what the forward call leaves its reverse sweep: 160 MB are 19 planes of 512 x 512 with three sweeps
+    n = defaults["chunk_codes_bytes"] // (512 * 512 * 4 * 8) + 1
+    case("chunk_codes_bytes", "at_threshold_512x512_k3", lambda: two_d(n, 512, 512, 3), big, "codes", "pass outputs")
+    case("chunk_codes_bytes", "below_512x512_k3", lambda: two_d(n - n // 4, 512, 512, 3), 0, "pass outputs", "codes")
     # a tensor of exactly stream_bytes bytes: rows of 32 samples in 128 lambda slots
     nb = max(2, defaults["stream_bytes"] // (128 * 32 * 32 * 4))
     case("stream_bytes", "at_threshold", lambda: one_d((nb, 128, 32, 32), 128, 32, False), big,
@@ -707,7 +736,7 @@ def main() -> int:
     bwd_gbs = bwd_seg_bytes / (bwd_ms * 1e-3) / 1e9
     moved_bytes = fwd_bytes + 8 * n_rows + bwd_seg_bytes  # what the timed pair moves (codes written and read)
     traffic = None
-    tpath = os.path.join(ROOT, "profiles", "traffic_tv1d_fwd_short_config3.json")
+    tpath = os.path.join(ROOT, "profiles", "traffic_tv1d_fwd_config3.json")
     if os.path.exists(tpath):
         with open(tpath) as f:
             traffic = json.load(f).get("traffic_bytes_per_launch")
@@ -715,12 +744,13 @@ def main() -> int:
     # vector-ALU view of the forward kernel: a SIMD retires one wave64 VALU instruction per 4
     # cycles; 256 CUs x 4 SIMDs at 2.4 GHz.  Instruction count from the committed counter run.
     alu = None
-    vpath = os.path.join(ROOT, "profiles", "valu_tv1d_fwd_short_config3.json")
+    vpath = os.path.join(ROOT, "profiles", "valu_tv1d_fwd_config3.json")
     if os.path.exists(vpath):
         with open(vpath) as f:
-            valu = json.load(f).get("sq_insts_valu")
+            counted = json.load(f)
+        valu = counted["sq_insts_valu"]
         peak_ips = 256 * 4 * 2.4e9 / 4.0
-        alu = {"kernel": "tv1d_fwd_short_kernel<32>", "valu_wave_instructions_per_launch": valu,
+        alu = {"kernel": counted["kernel"], "valu_wave_instructions_per_launch": valu,
                "achieved_per_s": valu / (ker_ms * 1e-3), "peak_per_s": peak_ips,
                "frac": valu / (ker_ms * 1e-3) / peak_ips}
 
@@ -758,7 +788,7 @@ def main() -> int:
         "moved_frac_of_hbm_peak": moved_bytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS,
         "effective_gbs_fwd_bwd": (fwd_bytes + bwd_bytes) / (ms_per_step * 1e-3) / 1e9,
         "effective_frac_of_hbm_peak": (fwd_bytes + bwd_bytes) / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS,
-        "roofline": {"kernel": "tv1d_fwd_short_kernel<32>", "bound": "hbm", "achieved": fwd_gbs,
+        "roofline": {"kernel": "tv1d_fwd_pair_kernel<16, 0, 3>", "bound": "hbm", "achieved": fwd_gbs,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": fwd_gbs / HBM_PEAK_GBS,
                      "traffic": traffic, "launch_us": ker_ms * 1e3,
                      "launch_us_median": float(np.median(k_all)) * 1e3,
