@@ -158,6 +158,69 @@ def test_rows_of_33_to_64_alone_in_company_and_scaled(n, axis, pairs):
         assert np.all(np.abs(x - ref).max(axis=1) <= floor), power
 
 
+@pytest.mark.parametrize("n,axis", [(17, -1), (20, 0), (23, -1), (28, 0), (31, -1), (32, -1), (32, 0)])
+def test_rows_of_17_to_32_alone_and_in_company(n, axis, pairs):
+    """Rows of 17-32 samples on two lanes: a row has the same bits, info word and segment code alone, in another
+    order and between rows that take longer, hold a NaN or an infinity; lambda = 0 is the identity."""
+    from gpuutil import rows_view, run_1d
+    rng = np.random.default_rng(n + 100 * (axis + 1))
+    count = 90
+    y = rng.normal(size=(count, n)).astype(np.float32)
+    y[::3] = np.round(y[::3], 1)
+    y[1::3] = np.cumsum(0.3 * y[1::3], axis=1)
+    lam = (10 ** rng.uniform(-1.5, 0.7, size=count)).astype(np.float32)
+    turn = lambda a: a if axis == -1 else np.ascontiguousarray(a.T)
+
+    def solve(a, l):
+        info = run_1d(turn(a), l, 1, axis=axis, want_info=True)
+        seg = run_1d(turn(a), l, 1, axis=axis, use_seg=True)
+        assert np.array_equal(info["x"], seg["x"], equal_nan=True)
+        return rows_view(info["x"], axis), info["info"], seg["seg"]
+
+    want = solve(y, lam)
+    at = rng.permutation(count)
+    for got, ref in zip(solve(y[at], lam[at]), want):
+        assert np.array_equal(got, ref[at])
+    mixed, ml = np.repeat(y, 2, axis=0), np.repeat(lam, 2)
+    mixed[0::4] = np.cumsum(rng.normal(size=mixed[0::4].shape), axis=1)
+    mixed[2::8, n // 2] = np.nan
+    mixed[6::8, n // 3] = np.inf
+    ml[0::4] = 20.0
+    got = solve(mixed, ml)
+    for a, ref in zip(got, want):
+        assert np.array_equal(a[1::2], ref)
+    assert np.isnan(got[0][2::8, n // 2]).all() and not np.isfinite(got[0][6::8, n // 3]).any()
+    for r in range(0, count, 9):
+        alone = solve(np.stack([y[r], 0 * y[r]]), np.repeat(lam[r], 2))
+        for a, ref in zip(alone, want):
+            assert np.array_equal(a[0], ref[r])
+    assert np.array_equal(solve(y, np.zeros(1, np.float32))[0], y)
+
+
+@pytest.mark.parametrize("H,W", [(17, 20), (24, 24), (29, 32), (32, 32), (40, 40), (63, 63)])
+def test_planes_alone_and_in_company(H, W, pairs):
+    """Planes on two lanes a row: a plane has the same bits, gradients too, alone, in another order and beside a
+    plane with a NaN."""
+    rng = np.random.default_rng(H * 100 + W)
+    y = np.maximum(rng.normal(size=(9, H, W)), -0.3).astype(np.float32)
+    g = rng.normal(size=y.shape).astype(np.float32)
+    lam = (10 ** rng.uniform(-1.5, 0.5, size=9)).astype(np.float32)
+    want = run_2d(y, lam, 3, g)
+    at = rng.permutation(9)
+    got = run_2d(y[at], lam[at], 3, g[at])
+    for k in ("x", "gy", "gl"):
+        assert np.array_equal(got[k], want[k][at]), k
+    alone = run_2d(y[4:5], lam[4:5], 3, g[4:5])
+    spoilt = y.copy()
+    spoilt[3, H // 2, W // 2] = np.nan
+    beside = run_2d(spoilt, lam, 3, g)
+    rest = np.arange(9) != 3
+    for k in ("x", "gy", "gl"):
+        assert np.array_equal(alone[k][0], want[k][4]), k
+        assert np.array_equal(beside[k][rest], want[k][rest]), k
+    assert np.isnan(beside["x"][3, H // 2, W // 2])
+
+
 @pytest.mark.parametrize("H,W", [(40, 40), (33, 36), (33, 40), (39, 40), (41, 44), (39, 48), (48, 40), (48, 48), (49, 52),
                                  (45, 56), (56, 56), (57, 60), (52, 64), (64, 52), (63, 64), (64, 64)])
 @pytest.mark.parametrize("K", [1, 3])
