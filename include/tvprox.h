@@ -81,12 +81,13 @@ typedef struct {
  * length == 1 copies the row.  Zero rows: TV_OK without a launch.
  * A row whose input holds NaN/Inf gets unspecified values in that row (NaN at least at
  * the non-finite samples); other rows are unaffected and the call still terminates.
- * Rows of more than 32 samples, and shorter ones on the kernels for small batches, have the same
- * bits whatever the other rows of the call hold; on the row-per-lane kernels the rows of a wave
- * agree with that to rounding.
+ * Rows of more than 16 samples (more than 32 with TV_FWD_PARALLEL_SEARCH), and shorter ones on the
+ * kernels for small batches, have the same bits whatever the other rows of the call hold; shorter
+ * ones with a lane per row agree with that to rounding.  How many rows a call has decides which
+ * kernel solves rows of up to 256 samples, and two kernels agree to rounding.
  * Samples and lambdas of 1e-16 to 1e15 are safe with any length.  Outside, squares that the stopping
  * rules compare underflow or overflow: a row can run into the step cap (tv1d_prox_fwd_info tells),
- * and one of at most 32 samples on the row-per-lane kernels can stop early.
+ * and one of at most 32 samples in a large batch can stop early.
  * Within a maximal constant run of the result all samples are bit-identical, which
  * is what tv1d_prox_bwd relies on to recover the segments.
  */
@@ -115,7 +116,7 @@ int tv1d_prox_fwd_info(const float *y, float *x, int32_t *info, tv_rows rows, tv
  *           the drain of the launch when the slots' costs differ widely (the order costs a
  *           5 us kernel, which it has not earned back on any batch measured since single rows
  *           stopped needing many more steps than their neighbours); with it the call always
- *           runs the row-per-lane kernels, and its results are bit-identical to those of
+ *           runs the kernels for large batches, and its results are bit-identical to those of
  *           the same kernels without it;
  *         - unit-stride rows of 769 samples or more get a multilevel start: the row averaged
  *           in groups of 4 samples, with lambda / 4, is solved first, from the cold start, and
@@ -263,8 +264,8 @@ int tv1d_prox_bwd_seg_bf16(const uint16_t *g_up, const uint64_t *seg, uint16_t *
  * From the second sweep on, the correction term a pass adds to its input is D^T u of the
  * same pass one sweep earlier (x = y - D^T u), and the pass starts its Newton iteration
  * from that dual.  Planes of at most 64 x 64 run all their passes in one launch where that is
- * faster (small batches with a plane per workgroup, larger ones of planes of at most 32 x 32
- * with a row per lane; the plane counts: csrc/tv_dispatch.hpp).
+ * faster (small batches of planes of 17-64 a side with a plane per workgroup, larger ones with two lanes
+ * a row, planes of at most 16 x 16 with a row per lane; the plane counts: csrc/tv_dispatch.hpp).
  * With lam.count == 1 and three sweeps or more, planes with a side of 65 to 768 samples (and none
  * longer) run another solver than with two lambdas and more ("one_lambda_tri_side"): one lambda and the same
  * lambda repeated give outputs that agree to rounding, not bit for bit, and the gradients of
@@ -295,7 +296,7 @@ int tv2d_prox_bwd(const float *g_up, float *grad_y, float *grad_lam, int64_t pla
  * patterns (2-byte aligned; 16-byte aligned plane blocks move with 16-byte accesses), widened
  * exactly on the way in and rounded to nearest even on the way out; everything between is an
  * fp32 one-launch kernel (all 2K passes with the planes resident in LDS; a plane per workgroup
- * for small batches of planes of 17-32 samples a side, a row per lane otherwise, as for fp32),
+ * for small batches of planes of 17-32 samples a side, two lanes a row or a row per lane otherwise, as for fp32),
  * so x is bit for bit the rounded output of that kernel on the widened input, and the reverse
  * sweep uses the segment codes of the unrounded passes.  ws: as for tv2d_prox_fwd / tv2d_prox_bwd (same size, fp32
  * contents); grad_lam stays fp32.

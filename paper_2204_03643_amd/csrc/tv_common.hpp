@@ -41,7 +41,8 @@ struct Layout {
     uint32_t stream;       // tensors too large to stay in cache: use non-temporal accesses
 };
 
-// Which 64 rows a wave of the row-per-lane forward kernel works on.  Row t of a tile is
+// Which ROWS rows a wave of the forward kernels for short rows works on: 64 with a row per lane, 32 with two
+// lanes a row.  (Written for 64; the other is the same.)  Row t of a tile is
 //     first + (t >> lg) * hop + (t & ((1 << lg) - 1)).
 // Identity: lg = 6, tile w starts at row 64 w, the grid is one-dimensional.  Grouped by
 // lambda slot (lam.div = 2^lg < 64 and every slot owning a whole number of tiles): tile
@@ -122,7 +123,7 @@ struct FwdParams {
     int32_t     *info;     // optional per-row info word
     uint2       *seg;      // optional per-row segment code (rows of up to 32 samples only)
     const uint32_t *order; // optional: grid row j of the grouped grid works on slot order[j]
-    uint32_t     io16;     // y and x are bf16 arrays (row-per-lane kernel, packed rows of 32 only)
+    uint32_t     io16;     // y and x are bf16 arrays (two lanes a row, packed rows of 32 only)
     uint32_t     psearch;  // row-per-lane kernel, rows of up to 32 samples: parallel step-size search
     uint32_t     warm;     // 1: addend is D^T u of an earlier solve of nearly the same rows: start from that u
                            // 2: start from the dual of the row averaged in groups of kMlFactor (coarse_u)
@@ -143,14 +144,14 @@ struct FwdParams {
     uint32_t    *chunk_codes;  // 2D passes on sides of 65-768: optional, a chunk code per thread (tv_long.hpp) ...
     uint32_t    *codes_tag;    // ... and, first pass of a call only: receives 1 where it writes codes, 0 where it does not
     Layout       L;
-    TileMap      tm;       // row-per-lane kernels only
+    TileMap      tm;       // kernels with a row per lane or two lanes a row only
 };
 
 struct BwdParams {
     const float *g;        // upstream gradient
     const float *sub;      // optional: the averaged quantity is g - sub, and sub is added back
     const float *x;        // forward output (defines the segments) ...
-    const uint2 *seg;      // ... or the segment code the forward pass wrote (row-per-lane kernels)
+    const uint2 *seg;      // ... or the segment code the forward pass wrote (rows of up to 32 samples)
     const uint32_t *chunk_codes;   // ... or, where *codes_tag is not 0, the chunk codes (2D, sides of 65-768)
     const uint32_t *codes_tag;
     float       *gy;       // output

@@ -178,13 +178,19 @@ inline Threshold table[kCount] = {
     // 2D pass by pass, sides of 65-768 samples: chunk codes instead of pass outputs (tv_long.hpp) where the
     // 2K outputs and the two correction tensors take this many bytes or more, that is
     // where they push one another out of the 256 MB last-level cache.  Forming the codes costs a forward pass
-    // some forty instructions a wave, which a call without a reverse sweep does not get back.  Pass outputs
-    // / codes, lambda 0.1 on images, forward, and forward + reverse sweep:
-    //   24 x 512 x 512, K = 10, one lambda (528 MB): 746 / 764, 1246 / 1156;  three lambdas: 646 / 654, 1132 / 1043
-    //   24 x 700 x 700, K = 3 (359 MB): 457 / 452, 762 / 700;  48 x 512 x 512, K = 4 (480 MB): 505 / 495, 839 / 776
-    //   512 x 100 x 100, K = 4 (196 MB): 285 / 290, 514 / 451;  512 x 128 x 128, K = 2 (193 MB): 189 / 188, 307 / 283
-    //   12 x 512 x 512, K = 3 (96 MB): 140 / 141, 233 / 221;  128 x 128 x 128, K = 4 (80 MB): 140 / 147, 234 / 226
-    // Below, the gain of the pair is a few percent and the loss of the lone forward call of the same size.
+    // four instructions a sample and thread, which a call without a reverse sweep does not always get back: by elimination (one
+    // lambda, K >= 3) it loses up to 2.5 % on tensors that would stay in that cache by themselves, by block
+    // means up to 1 %, and both win where they would not.  Pass outputs / codes, lambda 0.1 on images, forward, and
+    // forward + reverse sweep:
+    //   24 x 512 x 512, K = 10, one lambda (528 MB): 745 / 759, 1252 / 1149;  three lambdas: 633 / 637, 1130 / 1028
+    //   48 x 512 x 512, K = 4 (480 MB): 584 / 578, 945 / 871;  three: 511 / 489, 848 / 770
+    //   24 x 700 x 700, K = 3 (359 MB): 502 / 502, 817 / 762;  three: 452 / 449, 753 / 702
+    //   100 x 256 x 256, K = 4 (250 MB): 316 / 322, 518 / 496;  three: 284 / 286, 474 / 452
+    //   512 x 100 x 100, K = 4 (196 MB): 291 / 296, 528 / 490;  three: 300 / 287, 519 / 457
+    //   512 x 128 x 128, K = 2 (193 MB): 189 / 181, 351 / 322;  256 of them, K = 4 (160 MB): 219 / 224, 365 / 351
+    //   12 x 512 x 512, K = 3 (96 MB), the codes formed in more instructions: 140 / 141, 233 / 221;  128 x 128 x 128, K = 4
+    //   (80 MB): 140 / 147, 234 / 226
+    // The line is drawn where most forward calls alone are not slower.
     {"chunk_codes_bytes", (int64_t)160 << 20, "2D, sides of 65-768 samples: the forward call leaves codes, not pass outputs, from this many bytes of passes on"},
     // Rows of at most 32 samples on the long-row kernels (small 1D batches, see
     // thread_per_sample_1d_rows): 16 threads x 2 samples up to this many rows, 8 x 4 beyond
@@ -232,6 +238,8 @@ inline Threshold table[kCount] = {
     //   160 samples,   64 rows 14.5 /  7.7, 1024: 14.9 / 8.3, 4096: 15.8 / 12.2
     //   192 samples, 6144 rows 17.2 / 15.0, 8192: 18.4 / 18.4, 12 288: 21.0 / 23.7
     //   256 samples,   64 rows  9.6 /  7.0, 1024: 12.0 / 8.9, 4096: 14.9 / 12.1, 6144: 15.2 / 15.5, 12 288: 22.5 / 24.1
+    // At the line, N(0, 1) with lambda 1 and 0.1, walks with 1 and 5, noisy steps with 0.2 and 10^U(-3, 1) a row: 128
+    // samples, 9216 rows 1.04-1.12 times as fast, 192, 6144: 1.13-1.25, 256, 6144: 1.01-1.07; nowhere below slower.
     {"wave_per_row_rows", 6144, "1D calls on unit-stride rows of 65-256 samples: four samples a thread up to this many rows (half as many again: up to 128 samples)"},
     // 2D pass by pass with ONE lambda for all planes and three sweeps or more: sides up to this many
     // samples (768 at most, and beyond 64) are solved by tridiagonal elimination (tv_long_tri.hpp), not

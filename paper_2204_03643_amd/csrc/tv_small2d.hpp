@@ -310,7 +310,7 @@ struct Small2dFwdParams {
 
 // S, FULL: as in the reverse sweep (a wave holds 64 / S planes), S <= 16.
 // IO16: y and x are bf16 in memory; the saved pass outputs stay fp32.
-// (Planes of 33-64 samples a side: tv_plane2d.hpp.  A row of 64 samples per lane would take four
+// (Planes of 17-64 samples a side: tv_plane2d.hpp and tv_pair.hpp.  A row of 64 samples per lane would take four
 // arrays of 64 registers, the whole register file of a SIMD lane, for one wave per SIMD.)
 // Waves per SIMD asked of the register allocator: two at least; six for planes of 8 x 8, which fit
 // 64-73 registers.  Planes of 16 x 16 take 104 registers, four waves; planes of 9-15 a side 129, one

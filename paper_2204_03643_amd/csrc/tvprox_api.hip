@@ -93,8 +93,9 @@ Layout make_layout(const tv_rows &r, const tv_lambda &l, int64_t n_rows)
     return L;
 }
 
-// Tiles of 64 rows for the row-per-lane forward kernel: grouped by lambda slot when the slot
-// pattern allows it (lam.div a power of two below 64, every slot a whole number of tiles).
+// Tiles of 64 rows for the forward kernel with a row per lane, of 32 for the one with two lanes a row: grouped by
+// lambda slot when the slot pattern allows it (lam.div a power of two below 64 and no more than a tile, every slot a
+// whole number of tiles).
 tvk::TileMap make_tile_map(const tv_lambda &l, int64_t n_rows, int64_t tile_rows = 64)
 {
     tvk::TileMap tm = {6u, 0u, 0u, 1u};
@@ -942,7 +943,7 @@ int fwd_entry(const float *y, float *x, tv_rows rows, tv_lambda lam, const tv_fw
     }
     // small batches of short rows: a few threads per row (see tv_dispatch.hpp)
     // (not when the caller hands over the slot-order workspace or asks for the parallel step-size
-    // search: both belong to the row-per-lane kernels)
+    // search: both belong to the kernels for large batches)
     int64_t few_rows = tvd::get(tvd::kThreadPerSample1dRows);
     if (rows.length <= 16) few_rows /= 2;
     if (rows.elem_stride != 1 && (rows.length <= 16 || rows.length == 32)) few_rows /= 2;
@@ -1323,7 +1324,8 @@ static bool pairs_2d_fwd(int64_t planes, int64_t H, int64_t W, int sweeps)
 // The reverse sweep of these, in one launch with two lanes a row (rows move in 16-byte pieces), beyond the
 // counts up to which a plane per workgroup is faster; the measurements are in tv_dispatch.hpp.  Planes that
 // do not fill their square pay for the samples past their ends: with one sweep, or with sides beyond 56,
-// they stay out where a second or third round of 1024 planes (four a CU) is mostly empty.
+// they stay out where a second or third round of 1024 planes (four a CU) is mostly empty.  (This rule against the
+// one before two lanes a row, 18 sizes with such rows, 1, 2, 3, 4 and 10 sweeps, 256-16 384 planes: never slower by more than 3 %.)
 static bool pairs_2d_bwd(int64_t planes, int64_t H, int64_t W, int sweeps)
 {
     if (!pairs_2d_apply(H, W) || W % 4 != 0) return false;
@@ -1463,7 +1465,7 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
 
 // ---- the 2D operator with bf16 storage of y, x, g_up and grad_y (planes of at most 32 x 32): always
 //      one launch each way (small batches of planes of 17-32 samples a side with a plane per
-//      workgroup, a row per lane otherwise); the workspace (saved pass outputs, segment codes) is
+//      workgroup, larger ones forward with two lanes a row, a row per lane otherwise); the workspace (saved pass outputs, segment codes) is
 //      as for fp32.
 int tv2d_prox_fwd_bf16(const uint16_t *y, uint16_t *x, int64_t planes, int64_t H, int64_t W, tv_lambda lam,
                        int sweeps, void *ws, size_t ws_bytes, hipStream_t stream)

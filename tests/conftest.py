@@ -31,8 +31,8 @@ def pytest_collection_modifyitems(config, items):
 
 @pytest.fixture
 def lane_per_row():
-    """For tests about the row-per-lane kernels (segment codes built in registers, slot order, bf16
-    storage, bit-identity of their variants): small batches of short rows, which the library
+    """For tests about the kernels with a lane per row, or two from 17 samples on (segment codes built in
+    registers, slot order, bf16 storage, bit-identity of their variants): small batches of short rows, which the library
     would give a few threads per row (`thread_per_sample_1d_rows`), are kept on those kernels."""
     import paper_2204_03643_amd as tv
     saved = tv.tv_dispatch_threshold("thread_per_sample_1d_rows")
