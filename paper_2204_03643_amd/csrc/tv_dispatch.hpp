@@ -178,19 +178,19 @@ inline Threshold table[kCount] = {
     // 2D pass by pass, sides of 65-768 samples: chunk codes instead of pass outputs (tv_long.hpp) where the
     // 2K outputs and the two correction tensors take this many bytes or more, that is
     // where they push one another out of the 256 MB last-level cache.  Forming the codes costs a forward pass
-    // four instructions a sample and thread, which a call without a reverse sweep does not always get back: by elimination (one
-    // lambda, K >= 3) it loses up to 2.5 % on tensors that would stay in that cache by themselves, by block
-    // means up to 1 %, and both win where they would not.  Pass outputs / codes, lambda 0.1 on images, forward, and
-    // forward + reverse sweep:
-    //   24 x 512 x 512, K = 10, one lambda (528 MB): 745 / 759, 1252 / 1149;  three lambdas: 633 / 637, 1130 / 1028
-    //   48 x 512 x 512, K = 4 (480 MB): 584 / 578, 945 / 871;  three: 511 / 489, 848 / 770
-    //   24 x 700 x 700, K = 3 (359 MB): 502 / 502, 817 / 762;  three: 452 / 449, 753 / 702
-    //   100 x 256 x 256, K = 4 (250 MB): 316 / 322, 518 / 496;  three: 284 / 286, 474 / 452
-    //   512 x 100 x 100, K = 4 (196 MB): 291 / 296, 528 / 490;  three: 300 / 287, 519 / 457
-    //   512 x 128 x 128, K = 2 (193 MB): 189 / 181, 351 / 322;  256 of them, K = 4 (160 MB): 219 / 224, 365 / 351
+    // four instructions a sample and thread, which a call without a reverse sweep does not always get back: it loses up
+    // to 3 % on tensors that would stay in that cache by themselves, and wins where they would not.  Pass outputs /
+    // codes, lambda 0.1 on images, forward, and forward + reverse sweep:
+    //   24 x 512 x 512, K = 10, one lambda (528 MB): 696 / 710, 1197 / 1098;  three lambdas: 607 / 611, 1092 / 995
+    //   48 x 512 x 512, K = 4 (480 MB): 553 / 537, 904 / 831;  three: 484 / 463, 814 / 744
+    //   24 x 700 x 700, K = 3 (359 MB): 471 / 467, 794 / 725;  three: 434 / 428, 747 / 680
+    //   100 x 256 x 256, K = 4 (250 MB): 295 / 298, 505 / 470;  three: 276 / 278, 474 / 439
+    //   24 x 512 x 512, K = 4 (240 MB): 309 / 313, 513 / 473;  three: 268 / 270, 465 / 425
+    //   512 x 100 x 100, K = 4 (196 MB): 275 / 279, 546 / 472;  three: 272 / 277, 513 / 446
+    //   512 x 128 x 128, K = 2 (193 MB): 176 / 176, 340 / 316;  256 of them, K = 4 (160 MB): 205 / 210, 355 / 336
     //   12 x 512 x 512, K = 3 (96 MB), the codes formed in more instructions: 140 / 141, 233 / 221;  128 x 128 x 128, K = 4
     //   (80 MB): 140 / 147, 234 / 226
-    // The line is drawn where most forward calls alone are not slower.
+    // The line is drawn where the pair gains two to five times what the forward call alone can lose.
     {"chunk_codes_bytes", (int64_t)160 << 20, "2D, sides of 65-768 samples: the forward call leaves codes, not pass outputs, from this many bytes of passes on"},
     // Rows of at most 32 samples on the long-row kernels (small 1D batches, see
     // thread_per_sample_1d_rows): 16 threads x 2 samples up to this many rows, 8 x 4 beyond

@@ -42,31 +42,35 @@ typedef float tv_long_v4f __attribute__((ext_vector_type(4)));
 template <int T, int C>
 constexpr bool chunk_coded() { return T <= 64 && C <= 16 && T * C > 64 && T * C <= 768; }
 
-// code <- 2 code + (a differs from b), 2 code + (a is greater): a comparison and an addition that takes it as its
-// carry.  (The comparisons themselves, as where the segments are read off x: the bits of a difference call -0
-// beside +0 a fall, and say nothing next to an infinity.)
-__device__ __forceinline__ uint32_t shift_in_differs(uint32_t code, float a, float b)
+// code <- 16 code + 8 (x2 > x1) + 4 (x2 != x1) + 2 (x1 > x0) + (x1 != x0): a comparison a bit and an addition that takes
+// it as its carry.  (The comparisons themselves, as where the segments are read off x: the bits of a difference
+// call -0 beside +0 a fall, and say nothing next to an infinity.)
+// A carry may be read in the third instruction after the comparison that writes it at the earliest, and nothing but
+// the order of the block sees to that: the compiler puts no waits inside.  So four comparisons come before the four
+// additions, which also spares the two idle slots a bit that it would put between each two of its own.
+__device__ __forceinline__ uint32_t shift_in_two(uint32_t code, float x0, float x1, float x2)
 {
-    asm("v_cmp_neq_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(code) : "v"(a), "v"(b) : "vcc");
-    return code;
-}
-__device__ __forceinline__ uint32_t shift_in_greater(uint32_t code, float a, float b)
-{
-    asm("v_cmp_gt_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(code) : "v"(a), "v"(b) : "vcc");
+    uint64_t c0, c1, c2;
+    asm("v_cmp_gt_f32 %1, %6, %5\n\t"
+        "v_cmp_neq_f32 %2, %6, %5\n\t"
+        "v_cmp_gt_f32 %3, %5, %4\n\t"
+        "v_cmp_neq_f32 vcc, %5, %4\n\t"
+        "v_addc_co_u32 %0, %1, %0, %0, %1\n\t"
+        "v_addc_co_u32 %0, %2, %0, %0, %2\n\t"
+        "v_addc_co_u32 %0, %3, %0, %0, %3\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, vcc"
+        : "+v"(code), "=&s"(c0), "=&s"(c1), "=&s"(c2) : "v"(x0), "v"(x1), "v"(x2) : "vcc");
     return code;
 }
 
 template <int T, int C>
 __device__ __forceinline__ uint32_t chunk_code(const float (&xs)[C])
 {
+    static_assert(C % 2 == 0, "two samples at a time");
     const float xnext0 = __shfl_down(xs[0], 1, T);
     uint32_t code = 0;
 #pragma unroll
-    for (int i = C - 1; i >= 0; --i) {
-        const float xn = (i + 1 < C) ? xs[i + 1] : xnext0;
-        code = shift_in_greater(code, xn, xs[i]);
-        code = shift_in_differs(code, xn, xs[i]);
-    }
+    for (int i = C - 2; i >= 0; i -= 2) code = shift_in_two(code, xs[i], xs[i + 1], (i + 2 < C) ? xs[i + 2] : xnext0);
     return code;
 }
 
