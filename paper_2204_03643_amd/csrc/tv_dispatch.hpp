@@ -190,7 +190,7 @@ inline Threshold table[kCount] = {
     //   512 x 128 x 128, K = 2 (193 MB): 176 / 176, 340 / 316;  256 of them, K = 4 (160 MB): 205 / 210, 355 / 336
     //   12 x 512 x 512, K = 3 (96 MB), the codes formed in more instructions: 140 / 141, 233 / 221;  128 x 128 x 128, K = 4
     //   (80 MB): 140 / 147, 234 / 226
-    // The line is drawn where the pair gains two to five times what the forward call alone can lose.
+    // The line is drawn where the pair gains at least three times what the forward call alone can lose.
     {"chunk_codes_bytes", (int64_t)160 << 20, "2D, sides of 65-768 samples: the forward call leaves codes, not pass outputs, from this many bytes of passes on"},
     // Rows of at most 32 samples on the long-row kernels (small 1D batches, see
     // thread_per_sample_1d_rows): 16 threads x 2 samples up to this many rows, 8 x 4 beyond
