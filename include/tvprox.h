@@ -218,8 +218,8 @@ int tv1d_prox_bwd_noalloc(const float *g_up, const float *x, float *grad_y, floa
  * tv1d_prox_fwd / tv1d_prox_bwd on the same batch.  (Which kernels a forward call runs
  * depends on the batch: up to tv_dispatch_threshold("thread_per_sample_1d_rows") rows of at
  * most 32 samples (half as many rows of at most 16 and columns of 32, a quarter as many columns of
- * at most 16; of 17-32 samples n, no more than (n - 12) / 20 of "pair_1d_rows", columns three quarters
- * of that) get sixteen or eight threads per row, larger batches two lanes per row (17-32 samples) or
+ * at most 16; of 17-32 samples, rounded up to a multiple m of four, no more than (m - 12) / 20 of
+ * "pair_1d_rows", columns three quarters of that, rows of 29-32 that lie apart twice that) get sixteen or eight threads per row, larger batches two lanes per row (17-32 samples) or
  * one; they agree to rounding, not bit for bit.)
  *   seg: device pointer, 8-byte aligned, one uint64 per row in row order
  *        (entry o * n_inner + i for the row at o * outer_stride + i * inner_stride);

@@ -204,16 +204,25 @@ inline Threshold table[kCount] = {
     // that again: 24 576 columns of 12 14.1 / 13.4, N(0, 1) 0.93 of it, 40 960: 17.6 / 12.9.
     // Rows of 17-32 samples: up to this many (columns of 32: half), and not beyond pair_1d_rows.
     {"thread_per_sample_1d_rows", 81920, "1D rows of at most 32 samples: a few threads per row up to this many rows (half of it: rows of at most 16, columns of 32; a quarter: columns of at most 16)"},
-    // 1D calls on rows of 17-32 samples: beyond this many rows, times (n - 12) / 20 for rows of n, and
-    // three quarters of that for strided rows, two lanes a row (tv_pair.hpp) instead of sixteen threads.
-    // The sixteen threads take about the same time for any n, the pairs' chains grow with it.  N(0, 1),
-    // lambda 1, forward, sixteen threads / two lanes:
-    //   17 samples,  8192 rows  7.2 /  8.7, 16 384:  8.6 /  9.0, 24 576: 10.6 /  9.4;  columns, 16 384:  9.3 /  9.0
-    //   20 samples, 16 384 rows  8.8 /  9.1, 24 576: 10.2 /  9.3;                      columns, 16 384:  9.2 /  9.7
-    //   24 samples, 24 576 rows 10.8 / 10.5, 32 768: 11.6 / 10.7;                      columns, 24 576: 12.2 / 10.7
-    //   28 samples, 32 768 rows 11.8 / 12.3, 40 960: 13.2 / 12.9;                      columns, 24 576: 12.9 / 12.5
-    //   32 samples, 32 768 rows 12.3 / 15.7, 49 152: 15.4 / 16.1 (lambda 0.3: 11.5 / 11.0); columns, 32 768: 13.5 / 14.8
-    {"pair_1d_rows", 40960, "1D rows of 17-32 samples: two lanes a row beyond this many rows x (n - 12) / 20 (three quarters of it: strided rows)"},
+    // 1D calls on rows of 17-32 samples: beyond this many rows, times (m - 12) / 20 for rows of n samples with m the next
+    // multiple of four, two lanes a row (tv_pair.hpp) instead of sixteen threads.  The sixteen threads take about
+    // the same time for any n; the pairs' chains are half of m long, padding included.  Three quarters of that for strided
+    // rows, whose sixteen threads' accesses are the worse ones; twice that for rows of 29-32 that lie apart, which the pairs read
+    // sample by sample, a row a lane.  Forward, sixteen threads / two lanes, back to back; N(0, 1) with lambda 1, with 0.3,
+    // walks with 2, and N(0, 1) with 64 lambdas of 10^U(-3, 1):
+    //   17 samples, 15 300 rows  8.6 /  9.1,  7.2 /  7.2,  9.6 /  8.5,  8.2 /  8.1;  columns, 12 800  8.4 / 8.5, 7.2 / 7.6, 7.4 / 8.2, 8.0 / 8.0
+    //   20 samples, 16 300 rows  9.0 /  9.1,  7.1 /  7.3, 10.0 /  9.0,  8.8 /  8.1;  columns, 12 200  8.5 / 9.4, 7.3 / 7.3, 7.5 / 7.7, 8.3 / 8.8
+    //   21 samples, 18 400 rows  9.8 / 10.3,  7.8 /  8.7, 11.1 / 10.5, 10.0 / 10.2;  27 600 11.2 / 10.6, 9.0 / 8.9, 12.7 / 10.5, 10.9 / 10.1
+    //   24 samples, 24 500 rows 10.8 / 10.8,  7.9 /  7.5, 11.5 / 10.9, 10.0 /  9.8;  columns, 18 400 10.7 / 10.6, 8.3 / 7.5, 9.3 / 9.5, 11.0 / 9.7
+    //   25 samples, 26 600 rows 11.9 / 12.8,  9.0 /  9.8, 12.9 / 12.6, 11.0 / 11.7;  33 200 13.1 / 12.9, 9.8 / 9.9, 14.6 / 12.7, 12.1 / 11.8
+    //   28 samples, 32 700 rows 11.9 / 12.3,  8.9 /  9.0, 13.4 / 13.5, 11.4 / 11.1;  columns, 24 500 13.0 / 11.9, 10.0 / 8.3, 10.9 / 11.0, 12.9 / 10.7
+    //   31 samples, 38 900 rows 14.0 / 15.6, 10.5 / 10.4, 15.6 / 16.5, 13.6 / 13.7;  columns, 29 100 13.3 / 15.1, 10.3 / 10.6, 11.7 / 11.7, 14.0 / 13.5
+    //   32 samples, 40 900 rows 14.2 / 15.8, 10.0 /  9.8, 15.1 / 15.0, 13.2 / 13.7;  columns, 30 700 13.9 / 15.1, 10.5 / 10.2, 11.6 / 12.6, 14.3 / 12.8
+    //   with 3 samples between them: 29 samples, 52 200 rows 15.9 / 19.4, 11.6 / 16.4, 18.3 / 19.4, 15.5 / 16.9;
+    //   32 samples, 40 900 rows 14.5 / 15.9, 10.9 / 12.3, 15.8 / 16.7, 13.6 / 13.5;  81 900: 22.1 / 20.3, 16.2 / 18.1, 25.4 / 21.5, 22.1 / 18.8
+    // (Packed rows of 29-32 that start off a 16-byte boundary are read word by word and would do better with a line half as high
+    // again, but which kernel runs does not depend on where a caller's buffers lie.)
+    {"pair_1d_rows", 40960, "1D rows of 17-32 samples: two lanes a row beyond this many rows x (m - 12) / 20, m the length rounded up to a multiple of four (three quarters of it: strided rows; twice: rows of 29-32 that lie apart)"},
     // 1D calls on rows of 33-64 samples: beyond this many rows, times 1, 2, 3, 8 for rows of up to 40, 48, 56, 64
     // samples, two lanes a row instead of eight threads with
     // 8 or 12 samples each: an elimination takes half the instructions of sums over blocks that cross

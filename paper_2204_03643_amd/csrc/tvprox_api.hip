@@ -261,6 +261,15 @@ int launch_fwd_pairs(FwdParams p, const tv_rows &r, const tv_lambda &l, int64_t 
     return TV_ERR_UNSUPPORTED;
 }
 
+// Rows of 17-32 samples: two lanes a row beyond this many rows (tv_dispatch.hpp; halves of 10, 12, 14 and 16 samples).
+int64_t pair_rows(const tv_rows &r)
+{
+    const int64_t padded = (r.length + 3) / 4 * 4;
+    const int64_t most = tvd::get(tvd::kPair1dRows) * (padded - 12) / 20;
+    if (r.elem_stride != 1) return most / 4 * 3;
+    return padded == 32 && !rows_packed(r) ? 2 * most : most;
+}
+
 // Rows of 33-64 samples: two lanes a row beyond this many rows (tv_dispatch.hpp; halves of 20, 24, 28 and 32
 // samples: chains, and a wave's time alone, grow with the half).  Unit-stride rows with gaps between them are read
 // sample by sample, a row a lane, and beyond 40 samples that costs what the elimination saves.
@@ -948,8 +957,7 @@ int fwd_entry(const float *y, float *x, tv_rows rows, tv_lambda lam, const tv_fw
     if (rows.length <= 16) few_rows /= 2;
     if (rows.elem_stride != 1 && (rows.length <= 16 || rows.length == 32)) few_rows /= 2;
     if (rows.length > 16 && rows.length <= 32) {        // (beyond that two lanes a row)
-        int64_t most = tvd::get(tvd::kPair1dRows) * (rows.length - 12) / 20;
-        if (rows.elem_stride != 1) most = most / 4 * 3;
+        int64_t most = pair_rows(rows);
         if (few_rows > most) few_rows = most;
     }
     const bool few = n_rows <= few_rows && !e.ws && !(e.flags & TV_FWD_PARALLEL_SEARCH);

@@ -80,3 +80,36 @@ def test_rows_that_lie_apart(n, value, overrides):
     out = x.cpu().numpy()
     assert (out[:, n:] == 7.0).all()
     check_batch(y, lam_per_row(lam, 70, 2), None, out[:, :n], None, label="rows of %d apart" % n)
+
+
+@pytest.mark.parametrize("n,layout,line", [(17, "packed", 160), (20, "packed", 160), (21, "packed", 240), (29, "packed", 400),
+                                           (32, "packed", 400), (17, "columns", 120), (31, "columns", 300), (28, "apart", 320),
+                                           (29, "apart", 800), (32, "apart", 800)])
+def test_line_of_two_lanes_a_row(n, layout, line, overrides):
+    """Rows of 17-32 samples at and beyond the count from which two lanes hold a row (pair_1d_rows at 400): the bits are those
+    of the mapping that the count asks for, and either mapping's are the oracle's."""
+    import torch
+
+    import paper_2204_03643_amd as tv
+    rng = np.random.default_rng(n)
+    for count in (line, line + 1):
+        y = rng.normal(size=(count, n)).astype(np.float32)
+        lam = torch.full((1,), 0.7, device="cuda")
+        if layout == "columns":
+            yt, rows = torch.from_numpy(np.ascontiguousarray(y.T)).cuda(), tv.tv_rows(1, count * n, count, 1, n, count)
+        else:
+            pitch = n + (3 if layout == "apart" else 0)
+            spread = np.zeros((count, pitch), np.float32)
+            spread[:, :n] = y
+            yt, rows = torch.from_numpy(spread).cuda(), tv.tv_rows(1, count * pitch, count, pitch, n, 1)
+        outs = {}
+        for value in (0, 400, 1 << 40):
+            overrides(pair_1d_rows=value)
+            x = torch.zeros_like(yt)
+            tv.tv1d_prox_fwd(yt, x, rows, tv.tv_lambda(lam.data_ptr(), 1, 1))
+            outs[value] = x.cpu().numpy()
+            got = outs[value].T if layout == "columns" else outs[value][:, :n]
+            check_batch(y, np.full(count, 0.7, np.float32), None, np.ascontiguousarray(got), None,
+                        label="%s rows of %d, pair_1d_rows %d" % (layout, n, value))
+        assert not np.array_equal(outs[0], outs[1 << 40])
+        assert np.array_equal(outs[400], outs[1 << 40] if count == line else outs[0])
