@@ -5,9 +5,6 @@
 
 namespace tvk {
 
-// A thread's C contiguous samples k0 .. k0 + C - 1 of a row (zero past the end).  With unit
-// stride and 16-byte alignment they move as float4: a wave then touches every cache line of
-// its 64 * C samples C / 4 times instead of C times.
 // Which group of G rows a workgroup of a strided launch works on.  Workgroups go to the 8 XCDs
 // round-robin in launch order, and each XCD has its own L2.  The G adjacent columns of a
 // workgroup are 4 G bytes of every image row, a part of a 128-byte line (half of it for G = 16);
@@ -26,14 +23,19 @@ __device__ __forceinline__ uint32_t xcd_grouped(uint32_t b, uint32_t n_groups)
     return base + SH * x + s;
 }
 
+// A thread's C contiguous samples k0 .. k0 + C - 1 of a row (zero past the end) move four at a time where the
+// samples lie side by side: a wave then touches every cache line of its 64 * C samples C / 4 times instead of C
+// times.  Global memory takes 16-byte accesses at any address that is a multiple of four, which is all that
+// the rows of an odd length have; the type says so.  (Word by word, as such rows moved before: 8M samples in rows of 127 / 481 / 3001 / 16 001,
+// backward 43 / 37 / 50 / 95 us, now 21 / 23 / 23 / 36; forward 61 / 69 / 106 / 189, now 55 / 66 / 96 / 149.  Rows on
+// 16-byte boundaries take the same time as with a type that asks for one.)
 template <int C>
-__device__ __forceinline__ bool chunk_vec_ok(const void *base, int64_t off, int64_t es, int k0)
+__device__ __forceinline__ bool chunk_vec_ok(const void *base, int64_t es)
 {
-    return C % 4 == 0 && es == 1 && (((uintptr_t)base >> 2) + (uint64_t)(off + k0)) % 4 == 0 &&
-           ((uintptr_t)base & 3u) == 0;
+    return C % 4 == 0 && es == 1 && ((uintptr_t)base & 3u) == 0;
 }
 
-typedef float tv_long_v4f __attribute__((ext_vector_type(4)));
+typedef float tv_long_v4f __attribute__((ext_vector_type(4), aligned(4)));
 
 // Chunk codes: what the reverse sweep of a 2D call reads of a pass on sides of 65-768 samples, a word per
 // thread of the pass kernel.  Two bits a sample, sample k0 + i at 2i: x changes after it; x rises there (duals
@@ -90,7 +92,7 @@ template <int C>
 __device__ __forceinline__ void chunk_load(const float *__restrict__ base, int64_t off, int64_t es,
                                            int k0, int n, bool rvalid, float (&v)[C], bool stream = false)
 {
-    if (rvalid && chunk_vec_ok<C>(base, off, es, k0)) {
+    if (rvalid && chunk_vec_ok<C>(base, es)) {
 #pragma unroll
         for (int i = 0; i < C; i += 4) {
             if (k0 + i + 3 < n) {
@@ -114,7 +116,7 @@ __device__ __forceinline__ void chunk_store(float *__restrict__ base, int64_t of
                                             int n, bool rvalid, const float (&v)[C], bool stream = false)
 {
     if (!rvalid) return;
-    if (chunk_vec_ok<C>(base, off, es, k0)) {
+    if (chunk_vec_ok<C>(base, es)) {
 #pragma unroll
         for (int i = 0; i < C; i += 4) {
             if (k0 + i + 3 < n) {
