@@ -96,6 +96,10 @@ constexpr float kWarmSnap = 1.0f + 1.0f / 4096.0f;
 
 // Multilevel start of long rows: a level averages groups of this many samples of the level below.
 constexpr int kMlFactor = 4;
+// Rows whose lambda is at least this many times the mean |y[k+1] - y[k]| take it (2, 4, 8: every kind of row slower;
+// 0.125: 1-2 % slower), judged on this many groups from the row's start.
+constexpr float kMlLambdaRatio = 0.5f;
+constexpr int kMlProbeGroups = 512;
 
 // Step record of one row, written by the DEBUG variants of the forward kernels for the first
 // debug_rows rows of a call (a test instrument: it lets a test check one Newton step, paper
@@ -127,6 +131,7 @@ struct FwdParams {
     uint32_t     psearch;  // row-per-lane kernel, rows of up to 32 samples: parallel step-size search
     uint32_t     warm;     // 1: addend is D^T u of an earlier solve of nearly the same rows: start from that u
                            // 2: start from the dual of the row averaged in groups of kMlFactor (coarse_u)
+                           // 4: the launch on those averages, which it forms itself from rows of fine_n samples; it decides ml_flag
     // long-row kernels only (multilevel start; the three pitches sit where the pointers' alignment
     // left holes, so that they cost no kernel argument space):
     int32_t      dual_pitch;   // floats between the rows of dual_out
@@ -134,13 +139,14 @@ struct FwdParams {
     int32_t      coarse_n;
     int32_t      coarse_pitch;
     float       *dual_out; // optional: receives the final dual, L.n per row (entry n - 1 is 0)
-    const uint32_t *ml_flag; // optional, per row (flag_pitch words apart): 0 = this row takes no part in the multilevel start
+    uint32_t    *ml_flag;  // optional, per row (flag_pitch words apart): 0 = this row takes no part in the multilevel start
     uint32_t     ml_skip;  // rows with ml_flag == 0 are not solved at all (the launch is a coarse level)
     float        lam_scale; // lambda of this launch = lam[slot] * lam_scale (1 / kMlFactor per level)
     // step record (kernel variants with DEBUG only; see StepRecord):
     float       *debug;     // debug_rows records of step_record_floats(L.n) floats
     uint32_t     debug_rows;
     uint32_t     flag_pitch;
+    int32_t      fine_n;    // warm == 4: samples of the rows that y holds (L.n: the groups of a row)
     uint32_t    *chunk_codes;  // 2D passes on sides of 65-768: optional, a chunk code per thread (tv_long.hpp) ...
     uint32_t    *codes_tag;    // ... and, first pass of a call only: receives 1 where it writes codes, 0 where it does not
     Layout       L;

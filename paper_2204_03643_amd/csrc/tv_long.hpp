@@ -177,6 +177,7 @@ struct LongSmemBwd {
 // WARM = 2 (unit-stride rows, C a multiple of kMlFactor): rows flagged in p.ml_flag start from
 // the dual of the same row averaged in groups of kMlFactor samples (p.coarse_u), which a launch
 // on the averaged rows with lambda / kMlFactor left behind (p.dual_out of that launch).
+// WARM = 4: that launch, cold, where it forms the averages itself (average_groups); it leaves nothing but the duals.
 // DEBUG: the first p.debug_rows rows leave a step record in p.debug (see step_record_floats).
 
 // Waves per SIMD that the forward kernel asks the register allocator for (the second argument
@@ -201,6 +202,71 @@ constexpr int fwd_waves_per_simd()
     if (C == 16 && T * G <= 256) return 4;
     return 1;
 }
+
+// The multilevel start's first look at a row (WARM = 4): whether lambda is large enough against the variation of its
+// first kMlProbeGroups groups of kMlFactor samples for the start to pay (p.ml_flag), and if so the means of all its groups, the
+// thread's chunk of them in y.  Threads read neighbouring groups, 16 bytes each, and the means change
+// hands through the room in LDS where the solver parks its input.  Every thread of the workgroup calls; false: the row takes no part.
+// (As a kernel of its own, this read the rows and wrote the means for the coarse launch to read.
+// Forward, 4096 rows of 16 384: 685 -> 648 us; 2999 of 3001: 96 -> 86; 8M samples in rows of 1001 / 2048 / 4096 / 8001:
+// 83 -> 70, 80 -> 74, 92 -> 89, 110 -> 99.)
+template <int T, int C, int G>
+__device__ __forceinline__ bool average_groups(const FwdParams &p, uint32_t row, int64_t off, bool rvalid,
+                                               RowSmem<T, C, G, false> &sm, int j, int t, float (&y)[C])
+{
+    using Mp = LongMap<T, G, false>;
+    static_assert(kMlFactor == 4 && RowSmem<T, C, G, false>::PARK, "groups of 16 bytes; the parked input's room");
+    static_assert(Mp::PRIVATE || G == 1, "a row that stays out must not leave others of its workgroup behind");
+    constexpr int PROBE = kMlProbeGroups / T < C ? kMlProbeGroups / T : C;      // groups of a thread that are judged
+    const int n = p.L.n, n_in = p.fine_n;
+    const float *src = p.y + off;
+    float *means = reinterpret_cast<float *>(sm.y);
+    tv_long_v4f q[C];
+    auto load = [&](int i, bool go) {                           // group i T + t, zero past the end of the row
+        const int k = (i * T + t) * kMlFactor;
+        q[i] = tv_long_v4f{0.f, 0.f, 0.f, 0.f};
+        if (go && k + 3 < n_in) q[i] = *reinterpret_cast<const tv_long_v4f *>(src + k);
+        else if (go && k < n_in) {
+            q[i].x = src[k];
+            if (k + 1 < n_in) q[i].y = src[k + 1];
+            if (k + 2 < n_in) q[i].z = src[k + 2];
+        }
+    };
+    auto put = [&](int i) {
+        const int g = i * T + t, e = g % C;
+        const int have = min(n_in - g * kMlFactor, kMlFactor);
+        float sum = 0.f;
+        sum += q[i].x; sum += q[i].y; sum += q[i].z; sum += q[i].w;
+        const float mean = have == kMlFactor ? sum * (1.f / kMlFactor) : sum / (float)max(have, 1);
+        means[((e >> 2) * (T * G) + j * T + g / C) * 4 + (e & 3)] = g < n ? mean : 0.f;
+    };
+#pragma unroll
+    for (int i = 0; i < PROBE; ++i) load(i, rvalid);
+    float var[1] = {0.f};
+#pragma unroll
+    for (int i = 0; i < PROBE; ++i) {
+        const int k = (i * T + t) * kMlFactor;
+        if (k + 1 < n_in) var[0] += fabsf(q[i].y - q[i].x);
+        if (k + 2 < n_in) var[0] += fabsf(q[i].z - q[i].y);
+        if (k + 3 < n_in) var[0] += fabsf(q[i].w - q[i].z);
+        put(i);
+    }
+    row_sum<T, G, false, 1>(var, sm.red, j, (int)threadIdx.x);
+    // differences counted: kMlFactor - 1 of every kMlFactor neighbouring pairs of the probed samples
+    const int last = min(kMlProbeGroups * kMlFactor, n_in);
+    const float pairs = (float)(last - 1) * (float)(kMlFactor - 1) / (float)kMlFactor;
+    const bool flagged = rvalid && load_lambda(p.lam, p.L, row) * pairs >= kMlLambdaRatio * var[0];
+    if (rvalid && t == 0) p.ml_flag[(size_t)row * p.flag_pitch] = flagged ? 1u : 0u;
+    if (!__any(flagged)) return false;          // (rows that span waves: the same in all of them)
+#pragma unroll
+    for (int i = PROBE; i < C; ++i) load(i, flagged);
+#pragma unroll
+    for (int i = PROBE; i < C; ++i) put(i);
+    Mp::sync();
+    sm.fetch((int)threadIdx.x, y, y);
+    return flagged;
+}
+
 template <int T, int C, int G, bool COLS, bool XPOSE = false, int WARM = 0, bool DEBUG = false>
 __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>())) void tv1d_fwd_long_kernel(FwdParams p)
 {
@@ -219,7 +285,7 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>()))
     const uint32_t row = group * G + j;
     bool rvalid = row < p.L.n_rows;
     bool from_coarse = false;
-    if (p.ml_flag && rvalid) {
+    if (WARM != 4 && p.ml_flag && rvalid) {
         const bool flagged = p.ml_flag[(size_t)row * p.flag_pitch] != 0;
         if (p.ml_skip) rvalid = flagged;            // a coarse level: only rows that asked for it
         else from_coarse = WARM == 2 && flagged;
@@ -244,7 +310,10 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>()))
     constexpr bool warm = WARM == 1;
     float u[C];
     float wsum = 0.f;                                  // negated sum of the chunk's addend
-    if constexpr (XPOSE) {
+    if constexpr (WARM == 4) {
+        rvalid = average_groups<T, C, G>(p, row, off, rvalid, sm, j, t, y);
+        if (!__any(rvalid)) return;
+    } else if constexpr (XPOSE) {
         // every global load is issued before the first trip through the tile
         const bool xvalid = xrow < p.L.n_rows;
         float ry[C], ra[C];
@@ -308,10 +377,10 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>()))
     // 256 / 512, lambda = 0.1 on images: 42 / 42 -> 38 / 40), not where it starts from a good dual
     // (workload 4, K = 10, warm passes with them: 700 -> 740 us; rows of 900 from the coarse level:
     // 120 -> 123).  Rows that span waves would need one more exchange through a barrier for them.
-    constexpr bool POLISH = Mp::PRIVATE && (WARM == 0 || WARM == 3);
-    constexpr bool DUAL = !COLS && (WARM == 0 || WARM == 2);
+    constexpr bool POLISH = Mp::PRIVATE && (WARM == 0 || WARM == 3 || WARM == 4);
+    constexpr bool DUAL = !COLS && (WARM == 0 || WARM == 2 || WARM == 4);
     float xs[C];
-    const int info = row_solve<T, C, G, MCOLS, WARM, POLISH, DEBUG, DUAL>(y, u, wsum, lam, n, j, t, rvalid, sm, cu,
+    const int info = row_solve<T, C, G, MCOLS, WARM == 4 ? 0 : WARM, POLISH, DEBUG, DUAL>(y, u, wsum, lam, n, j, t, rvalid, sm, cu,
                                                                    p.coarse_n, rec, xs);
 
     // (rows of at most 32 samples, small batches: the segment code comes from the registers; a kernel
@@ -322,7 +391,8 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>()))
             if (rvalid && t == 0) p.seg[row] = code;
         }
     }
-    if (DUAL && p.dual_out) chunk_store<C>(p.dual_out, (int64_t)row * p.dual_pitch, 1, k0, n, rvalid, u);
+    if (DUAL && (WARM == 4 || p.dual_out)) chunk_store<C>(p.dual_out, (int64_t)row * p.dual_pitch, 1, k0, n, rvalid, u);
+    if constexpr (WARM == 4) return;
 
     if constexpr (XPOSE) {
         // a wave writes only its own row of the tile; the barrier then hands the tile over
@@ -663,6 +733,31 @@ inline int chunk_threads(int64_t n)
 inline hipError_t launch_fwd_long(const FwdParams &p, hipStream_t s)
 {
     TV_LONG_DISPATCH(launch_fwd_long_t, p, s, 8);
+}
+
+// The coarse level that forms its averages itself, for the lengths that ml_min_length's default leaves it
+// (193 groups and more), in the mappings of TV_LONG_DISPATCH.
+inline bool averages_itself(int64_t groups) { return groups > 192 && groups <= 4096; }
+
+template <int T, int C, int G>
+inline hipError_t launch_fwd_averaged_t(const FwdParams &p, hipStream_t s)
+{
+    hipLaunchKernelGGL((tv1d_fwd_long_kernel<T, C, G, false, false, 4>), dim3((p.L.n_rows + G - 1) / G), dim3(T * G), 0, s, p);
+    return hipGetLastError();
+}
+
+inline hipError_t launch_fwd_averaged(const FwdParams &p, hipStream_t s)
+{
+    const int n = p.L.n;
+    if (n <= 256) return launch_fwd_averaged_t<32, 8, 8>(p, s);
+    if (n <= 384) return launch_fwd_averaged_t<32, 12, 8>(p, s);
+    if (n <= 512) return launch_fwd_averaged_t<64, 8, 4>(p, s);
+    if (n <= 768) return launch_fwd_averaged_t<64, 12, 4>(p, s);
+    if (n <= 1024) return launch_fwd_averaged_t<64, 16, 4>(p, s);
+    if (n <= 1536) return launch_fwd_averaged_t<128, 12, 1>(p, s);
+    if (n <= 2048) return launch_fwd_averaged_t<256, 8, 1>(p, s);
+    if (n <= 3072) return launch_fwd_averaged_t<256, 12, 1>(p, s);
+    return launch_fwd_averaged_t<256, 16, 1>(p, s);
 }
 
 // Small batches of unit-stride rows of 65-256 samples (wave_per_row_rows in tv_dispatch.hpp): four samples per

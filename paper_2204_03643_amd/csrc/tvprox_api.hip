@@ -492,8 +492,6 @@ bool order_applies(const tvk::TileMap &tm)
 // Rows whose lambda is small against their variation converge in a few steps anyway and are
 // left out (ml_flag = 0): they start cold at the fine level and are skipped at the others.
 constexpr int kMlMaxLevels = 8;                // (where it starts and ends: tv_dispatch.hpp)
-constexpr float kMlLambdaRatio = 0.5f;     // multilevel start when lambda >= ratio * mean |y[k+1] - y[k]| (2, 4, 8: every kind of row slower; 0.125: 1-2 % slower)
-constexpr int kMlProbeGroups = 512;        // ... judged on the row's first 2048 samples
 
 struct MlPlan {
     int levels;                       // coarse levels 1 .. levels (0 = the row itself)
@@ -564,7 +562,7 @@ __global__ __launch_bounds__(256) void ml_average_kernel(const float *__restrict
         // out of the multilevel start needs no averages
         __shared__ float red[256];
         __shared__ uint32_t decision;
-        const int probe = n_out < kMlProbeGroups ? n_out : kMlProbeGroups;
+        const int probe = n_out < tvk::kMlProbeGroups ? n_out : tvk::kMlProbeGroups;
         float var = 0.f;
         for (int j = threadIdx.x; j < probe; j += 256) {
             float v[F];
@@ -584,7 +582,7 @@ __global__ __launch_bounds__(256) void ml_average_kernel(const float *__restrict
             const int last = probe * F < n_in ? probe * F : n_in;
             const float pairs = (float)(last - 1) * (float)(F - 1) / (float)F;
             const float l = tvk::load_lambda(lam, L, row);
-            decision = (l * pairs >= kMlLambdaRatio * red[0]) ? 1u : 0u;
+            decision = (l * pairs >= tvk::kMlLambdaRatio * red[0]) ? 1u : 0u;
             flag[0] = decision;
         }
         __syncthreads();
@@ -617,6 +615,23 @@ int run_fwd_multilevel(FwdParams p, const tv_lambda &l, int64_t n_rows, const Ml
     auto yl = [&](int lv) { return in_rows ? p.x + pl.row_y_off[lv] : (float *)(ws + pl.y_off[lv]); };
     auto ul = [&](int lv) { return in_rows ? p.x + pl.row_u_off[lv] : (float *)(ws + pl.u_off[lv]); };
     auto pitch = [&](int lv) { return in_rows ? n0 : pl.n[lv]; };      // floats between consecutive rows of a level
+    auto fine_level = [&]() {
+        p.warm = 2; p.coarse_u = ul(1); p.coarse_n = (int32_t)pl.n[1]; p.coarse_pitch = (int32_t)pitch(1);
+        p.ml_flag = flag; p.flag_pitch = flag_pitch; p.ml_skip = 0;
+        return tvk::launch_fwd_long(p, s) == hipSuccess ? TV_OK : TV_ERR_HIP;
+    };
+    if (pl.levels == 1 && tvk::averages_itself(pl.n[1])) {
+        // one level, as is usual: its launch reads the rows themselves
+        FwdParams c = p;
+        c.L.n = (int32_t)pl.n[1]; c.fine_n = (int32_t)n0;
+        c.x = nullptr; c.x2 = nullptr; c.resid = nullptr; c.info = nullptr;
+        c.chunk_codes = nullptr; c.codes_tag = nullptr;
+        c.dual_out = ul(1); c.dual_pitch = (int32_t)pitch(1);
+        c.ml_flag = flag; c.flag_pitch = flag_pitch;
+        c.lam_scale = 1.0f / (float)tvk::kMlFactor;
+        c.warm = 4u;
+        return tvk::launch_fwd_averaged(c, s) == hipSuccess ? fine_level() : TV_ERR_HIP;
+    }
     const dim3 grid((uint32_t)n_rows), block(256);
     hipLaunchKernelGGL(ml_average_kernel<true>, grid, block, 0, s, p.y, yl(1), flag, l.lam, p.L,
                        (int32_t)pl.n[0], (int32_t)pl.n[1], (int64_t)0, pitch(1), flag_pitch);
@@ -642,9 +657,7 @@ int run_fwd_multilevel(FwdParams p, const tv_lambda &l, int64_t n_rows, const Ml
         c.coarse_pitch = lv == pl.levels ? 0 : (int32_t)pitch(lv + 1);
         if (tvk::launch_fwd_long(c, s) != hipSuccess) return TV_ERR_HIP;
     }
-    p.warm = 2; p.coarse_u = ul(1); p.coarse_n = (int32_t)pl.n[1]; p.coarse_pitch = (int32_t)pitch(1);
-    p.ml_flag = flag; p.flag_pitch = flag_pitch; p.ml_skip = 0;
-    return tvk::launch_fwd_long(p, s) == hipSuccess ? TV_OK : TV_ERR_HIP;
+    return fine_level();
 }
 
 // ---- dispatch ---------------------------------------------------------------------
@@ -662,7 +675,7 @@ int run_fwd(const float *y, const float *addend, float *x, float *resid, int32_t
     p.psearch = psearch ? 1u : 0u;
     p.warm = (warm && addend) ? 1u : 0u;
     p.coarse_u = nullptr; p.coarse_n = 0; p.coarse_pitch = 0; p.dual_out = nullptr; p.dual_pitch = 0;
-    p.ml_flag = nullptr; p.flag_pitch = 1; p.ml_skip = 0;
+    p.ml_flag = nullptr; p.flag_pitch = 1; p.ml_skip = 0; p.fine_n = 0;
     p.lam_scale = 1.0f;
     p.debug = nullptr; p.debug_rows = 0;
     p.chunk_codes = chunk_codes; p.codes_tag = codes_tag;
@@ -1151,7 +1164,7 @@ int tv1d_prox_fwd_steps(const float *y, float *x, int32_t *info, float *record, 
     p.y = y; p.addend = nullptr; p.x = x; p.x2 = nullptr; p.resid = nullptr; p.lam = lam.lam; p.info = info;
     p.seg = nullptr; p.order = nullptr; p.io16 = 0; p.psearch = 0; p.warm = 0;
     p.coarse_u = nullptr; p.coarse_n = 0; p.coarse_pitch = 0; p.dual_out = nullptr; p.dual_pitch = 0;
-    p.ml_flag = nullptr; p.flag_pitch = 1; p.ml_skip = 0;
+    p.ml_flag = nullptr; p.flag_pitch = 1; p.ml_skip = 0; p.fine_n = 0;
     p.lam_scale = 1.0f;
     p.debug = record;
     p.debug_rows = (uint32_t)(record_rows < n_rows ? record_rows : n_rows);
