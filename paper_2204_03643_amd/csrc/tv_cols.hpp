@@ -1,0 +1,247 @@
+// Backward kernel for strided rows (the columns of images) of 33-1024 samples: nothing is transposed.
+#pragma once
+#include "tv_long.hpp"
+
+namespace tvk {
+
+// Which group of columns a workgroup works on: runs of 1 << lg neighbouring groups on one XCD (see xcd_grouped), which has
+// its own L2.
+__device__ __forceinline__ uint32_t xcd_together(uint32_t b, uint32_t n_groups, uint32_t lg)
+{
+    const uint32_t base = b & ~((8u << lg) - 1u);
+    if (base + (8u << lg) > n_groups) return b;     // the ragged end keeps the launch order
+    return base + ((b & 7u) << lg) + ((b >> 3) & ((1u << lg) - 1u));
+}
+
+// s / n to an ulp: what the reciprocal's last bit takes is given back.
+__device__ __forceinline__ float mean_of(float s, float n)
+{
+    const float r = __builtin_amdgcn_rcpf(n), m = s * r;
+    return fmaf(fmaf(-m, n, s), r, m);
+}
+
+// T threads a column with C contiguous samples each, G adjacent columns a workgroup, thread = t * G + column: every load and
+// store of a wave covers 4 G contiguous bytes of 64 / G image rows, and a thread's samples stay in its registers from
+// the load to the store.  Between the threads of a column travel only the pieces of the segments that cross from one
+// chunk to the next (paper Eq. 5-6 as segment averaging): the sum and count of a chunk's samples up to its
+// first jump and behind its last one.  They lie in LDS as [t][column]; with columns and threads exchanged (T
+// neighbouring lanes take the T pieces of one column) a segmented sum over lanes and one fetch of a mean from the
+// lane where a segment ends turn them into the two means that each chunk needs: that of the segment open at its
+// start and that of the one open at its end.
+// Bound by memory: 24 planes of 512 x 512, backward, 21.7 -> 14.8 us (75 MB at 5.1 TB/s); with its lambda sum the call takes
+// 26.6 -> 19.1 us, and on 8M samples in planes of 33 / 64 / 100 / 200 / 481 / 900 a side 124 / 69 / 65 / 44 / 44 / 47 ->
+// 26 / 21 / 23 / 27 / 28 / 31.  (Before, every tensor crossed an LDS tile that turned columns into rows and back.)
+// Error against 64 bits, thirty calls: grad_y 6.3e-8 -> 4.8e-8, dL/dlam 3.1e-7 -> 2.6e-7.
+// G: 32 columns, a line, where that leaves workgroups of at most 512 threads, 16 beyond (512 a side, with sub: 18.5 us, with 32
+// columns 21.6; 768, no sub, 64 threads of 12 samples 19.8, 32 threads of 24 and 32 columns 23.8).
+// HAS_SUB: p.sub is given (the reverse sweep of the 2D operator).  CODES: where the forward pass left chunk codes
+// (p.codes_tag says whether it did) they are read, not x: CW words of C / CW samples a thread, in the forward kernel's
+// order (word t of its row).
+template <int T, int C, int G, int CW, bool HAS_SUB, bool CODES>
+__global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
+{
+    static_assert(T <= 64 && C <= 32 && C % CW == 0 && G <= 64, "a column's threads inside one wave when exchanged");
+    using Rw = RowWave<T, G, false>;
+    constexpr int P = G + 1;                     // (both [t][column] accesses are then free of bank conflicts)
+    __shared__ float first[T * P], last[T * P];  // sums of the pieces, then the two means
+    __shared__ uint32_t sizes[T * P];            // their counts and whether the chunk holds a jump, then dL/dlam terms
+    const int tid = threadIdx.x;
+    const int col = tid % G, t = tid / G;
+    const uint32_t group = xcd_together(blockIdx.x, gridDim.x, p.near_lg);
+    const uint32_t row = group * G + col;
+    const bool rvalid = row < p.L.n_rows;
+    const uint32_t arow = rvalid ? row : p.L.n_rows - 1u;      // (what is read for a column that does not exist)
+    const int n = p.L.n, k0 = t * C;
+    const int64_t es = p.L.elem_stride;
+    const int64_t at0 = row_offset(p.L, arow) + (int64_t)k0 * es;
+    const bool whole = k0 + C <= n;
+    auto fetch = [&](const float *__restrict__ src, float (&v)[C]) {
+        const float *at = src + at0;
+        if (whole) {
+#pragma unroll
+            for (int i = 0; i < C; ++i) v[i] = at[i * es];
+        } else {
+#pragma unroll
+            for (int i = 0; i < C; ++i) v[i] = k0 + i < n ? at[i * es] : 0.f;
+        }
+    };
+
+    float g[C], sb[HAS_SUB ? C : 1];
+    uint32_t jmask = 0, upmask = 0;
+    // duals of this chunk that lie inside the row (dual i sits behind sample k0 + i)
+    const int nv = min(max(n - 1 - k0, 0), C);
+    const uint32_t inrow = nv == 32 ? ~0u : (1u << nv) - 1u;
+    bool coded = false;
+    if constexpr (CODES) coded = *p.codes_tag != 0u;
+    fetch(p.g, g);
+    if constexpr (HAS_SUB) fetch(p.sub, sb);
+    if (CODES && coded) {
+        const uint32_t *words = p.chunk_codes + ((size_t)arow * T + t) * CW;
+#pragma unroll
+        for (int w = 0; w < CW; ++w) {
+            const uint32_t code = words[w];
+            jmask |= even_bits(code) << (w * (C / CW));
+            upmask |= even_bits(code >> 1) << (w * (C / CW));
+        }
+    } else {
+        float x[C];
+        fetch(p.x, x);
+        const float xnext0 = k0 + C < n ? p.x[at0 + C * es] : 0.f;
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            const float xn = (i + 1 < C) ? x[i + 1] : xnext0;
+            if (xn != x[i]) jmask |= 1u << i;
+            if (xn > x[i]) upmask |= 1u << i;
+        }
+    }
+    const uint32_t gmask = jmask & inrow;      // jumps that count for dL/dlam
+    jmask |= ~inrow;                           // (the end of the row ends a segment; samples past it are their own)
+    if constexpr (HAS_SUB) {
+#pragma unroll
+        for (int i = 0; i < C; ++i) g[i] -= sb[i];
+    }
+#define TV_JUMP(i) ((jmask >> (i)) & 1u)
+    const uint32_t jumps = C == 32 ? jmask : jmask & ((1u << (C & 31)) - 1u);
+    {
+        float head_s = 0.f, tail_s = 0.f;
+        bool any = false;
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            if (!any) head_s += g[i];
+            tail_s += g[i];
+            if (TV_JUMP(i)) { any = true; tail_s = 0.f; }
+        }
+        const uint32_t head_n = any ? (uint32_t)__builtin_ctz(jumps | 0x80000000u) + 1u : (uint32_t)C;
+        const uint32_t tail_n = any ? (uint32_t)(C - 32 + __builtin_clz(jumps | 1u)) : (uint32_t)C;
+        first[t * P + col] = head_s;
+        last[t * P + col] = tail_s;
+        sizes[t * P + col] = head_n | tail_n << 8 | (any ? 1u << 16 : 0u);
+    }
+    __syncthreads();
+    {
+        const int at = (tid % T) * P + tid / T;
+        const float head_s = first[at], tail_s = last[at];
+        const uint32_t sz = sizes[at];
+        const float head_n = (float)(sz & 0xffu), tail_n = (float)(sz >> 8 & 0xffu);
+        const bool closed = (sz >> 16) != 0u;
+        const Rw rw(tid % T);
+        const uint64_t cmask = lanes_with(closed);
+        const int L = rw.last_before(cmask);
+        const int apart = rw.lane - L;
+        float left_s = rw.prev(rw.open_sum(tail_s, closed ? 0 : apart));
+        float left_n = Rw::at(tail_n, L) + (float)(apart * C - C);
+        if (rw.tw == 0) { left_s = 0.f; left_n = 0.f; }
+        // the lane in which a segment ends knows its mean; the others fetch it (the last one always holds an end)
+        const float head_m = mean_of(left_s + head_s, left_n + head_n);
+        const float tail_m = Rw::at(head_m, rw.first_after(cmask));
+        first[at] = closed ? head_m : tail_m;
+        last[at] = tail_m;
+    }
+    __syncthreads();
+    const float head_m = first[t * P + col], tail_m = last[t * P + col];
+    double gl = 0.0;                             // (64 bits from here on: a slot's terms cancel)
+    {
+        float s = 0.f, c = 0.f;
+        bool any = false;
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            s += g[i]; c += 1.f;
+            if (TV_JUMP(i)) { g[i] = any ? mean_of(s, c) : head_m; s = 0.f; c = 0.f; any = true; }
+        }
+        float carry = tail_m;
+#pragma unroll
+        for (int i = C - 1; i >= 0; --i) {
+            const float behind = carry;
+            if (TV_JUMP(i)) carry = g[i];
+            g[i] = carry;
+            if ((gmask >> i) & 1u) gl += (double)(((upmask >> i) & 1u) ? carry - behind : behind - carry);
+        }
+    }
+    if constexpr (HAS_SUB) {
+#pragma unroll
+        for (int i = 0; i < C; ++i) g[i] += sb[i];
+    }
+    if (rvalid) {
+        float *at = p.gy + at0;
+        if (whole) {
+#pragma unroll
+            for (int i = 0; i < C; ++i) at[i * es] = g[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < C; ++i)
+                if (k0 + i < n) at[i * es] = g[i];
+        }
+    }
+#undef TV_JUMP
+    if (p.partial) {
+        float *terms = reinterpret_cast<float *>(sizes);
+        terms[t * P + col] = rvalid ? (float)gl : 0.f;
+        __syncthreads();
+        if (tid < G) {
+            double sum = 0.0;
+#pragma unroll 8
+            for (int q = 0; q < T; ++q) sum += (double)terms[q * P + tid];
+            // neighbouring columns that share a slot leave as one term, in two floats
+            for (uint32_t d = 0; d < p.part_lg; ++d) sum += __shfl_xor(sum, 1 << d);
+            if (rvalid && (tid & ((1 << p.part_lg) - 1)) == 0) {
+                const float hi = (float)sum;
+                if (p.part_lg) *reinterpret_cast<float2 *>(p.partial + 2 * (size_t)(row >> p.part_lg)) = make_float2(hi, (float)(sum - (double)hi));
+                else p.partial[row] = hi;
+            }
+        }
+    }
+}
+
+// Runs of neighbouring groups on one XCD: a 128-byte line at least.  Where image rows are no whole number of
+// lines every group shares one with each of its neighbours, in every image row: runs of 512 columns there, or as many as
+// leave three rounds of eight runs.  (8M samples, runs of 32 / 128 / 512 columns: 33 a side 32.0 / 22.6 / 21.0 us, 200
+// 28.7 / 24.5 / 22.6, 481 32.6 / 26.0 / 23.6, 900 30.1 / 24.6 / 23.0; whole lines, 512 a side, 18.7 / 18.7 / 18.2, a third fewer
+// images 14.8 / 15.5 / 15.7.)
+template <int G>
+inline uint32_t bwd_cols_near_lg(const BwdParams &p, uint32_t groups)
+{
+    const bool lines = p.L.elem_stride % 32 == 0 && p.L.n_inner % 32 == 0 && ((uintptr_t)p.g | (uintptr_t)p.gy) % 128 == 0;
+    uint32_t lg = 0;
+    while ((G << lg) < (lines ? 32 : 512) && (48u << lg) <= groups) ++lg;
+    return lg;
+}
+
+// Strided rows that go this way; and the columns of a workgroup, whose dL/dlam terms can leave as one.
+inline bool bwd_cols_apply(int64_t n, int64_t elem_stride) { return n > 32 && n <= 1024 && elem_stride != 1; }
+inline int bwd_cols_group_lg(int64_t n) { return n <= 256 ? 5 : 4; }
+
+template <int T, int C, int CW>
+inline hipError_t launch_bwd_cols_t(BwdParams p, hipStream_t s)
+{
+    constexpr int G = T <= 16 ? 32 : 16;
+    const dim3 grid((p.L.n_rows + G - 1) / G), block(T * G);
+    p.near_lg = bwd_cols_near_lg<G>(p, grid.x);
+    if constexpr (CW > 0) {
+        if (p.chunk_codes) {
+            if (p.sub) hipLaunchKernelGGL((tv1d_bwd_cols_kernel<T, C, G, CW, true, true>), grid, block, 0, s, p);
+            else hipLaunchKernelGGL((tv1d_bwd_cols_kernel<T, C, G, CW, false, true>), grid, block, 0, s, p);
+            return hipGetLastError();
+        }
+    }
+    if (p.sub) hipLaunchKernelGGL((tv1d_bwd_cols_kernel<T, C, G, 1, true, false>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((tv1d_bwd_cols_kernel<T, C, G, 1, false, false>), grid, block, 0, s, p);
+    return hipGetLastError();
+}
+
+// CW: the words of chunk_threads(n) that a thread's C samples are, 0 where there are none.
+inline hipError_t launch_bwd_cols(const BwdParams &p, hipStream_t s)
+{
+    const int n = p.L.n;
+    if (n <= 64) return launch_bwd_cols_t<4, 16, 0>(p, s);
+    if (n <= 96) return launch_bwd_cols_t<8, 12, 1>(p, s);
+    if (n <= 128) return launch_bwd_cols_t<8, 16, 2>(p, s);
+    if (n <= 192) return launch_bwd_cols_t<16, 12, 1>(p, s);
+    if (n <= 256) return launch_bwd_cols_t<16, 16, 2>(p, s);
+    if (n <= 384) return launch_bwd_cols_t<32, 12, 1>(p, s);
+    if (n <= 512) return launch_bwd_cols_t<32, 16, 2>(p, s);
+    if (n <= 768) return launch_bwd_cols_t<64, 12, 1>(p, s);
+    // (with sub 64 threads of 16 samples take 72 registers, and a CU holds one workgroup: 900 a side 36 us against 32)
+    return p.sub ? launch_bwd_cols_t<32, 32, 0>(p, s) : launch_bwd_cols_t<64, 16, 0>(p, s);
+}
+
+}  // namespace tvk

@@ -162,7 +162,8 @@ struct BwdParams {
     const uint32_t *codes_tag;
     float       *gy;       // output
     float       *partial;  // optional: dL/dlam contributions, one per group of 1 << part_lg rows
-    uint32_t     part_lg;  // row-per-lane kernels only; a group never spans two lambda slots
+    uint32_t     part_lg;  // row-per-lane and column kernels only; a group never spans two lambda slots
+    uint32_t     near_lg;  // column kernels only: log2 of the neighbouring groups of columns that an XCD takes
     uint32_t     io16;     // g and gy are bf16 arrays (row-per-lane kernel with codes, packed rows of 32 only)
     Layout       L;
 };

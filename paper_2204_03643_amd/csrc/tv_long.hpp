@@ -444,21 +444,17 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>()))
 // ---------------------------------------------------------------------------------
 // Backward (paper Eq. 5-6 as segment averaging), one row per T threads.
 // ---------------------------------------------------------------------------------
-// XPOSE: as in the forward kernel (strided rows through an LDS tile, one row per wave).
+// Unit-stride rows, and strided ones of more than 1024 samples (shorter ones: tv_cols.hpp).
 // HAS_SUB: p.sub is given (the reverse sweep of the 2D operator).
 // Workgroups of 1024 threads ask for 8 waves per SIMD (at most 64 VGPRs), so that a CU holds two of
 // them and one's loads overlap the other's scans.
 // CODES: where the forward pass left chunk codes (p.codes_tag says whether it did) they are read, not x.
-template <int T, int C, int G, bool COLS, bool XPOSE = false, bool HAS_SUB = false, bool CODES = false>
+template <int T, int C, int G, bool COLS, bool HAS_SUB = false, bool CODES = false>
 __global__ __launch_bounds__(T *G, (T * G == 1024 && !COLS && !HAS_SUB) ? 8 : 1) void tv1d_bwd_long_kernel(BwdParams p)
 {
     static_assert(!CODES || chunk_coded<T, C>(), "chunk codes are for rows inside one wave");
-    static_assert(!XPOSE || (COLS && T <= 64), "the transposing variant is for strided rows inside one wave");
-    constexpr bool MCOLS = COLS && !XPOSE;
-    using Mp = LongMap<T, G, MCOLS>;
-    __shared__ LongSmemBwd<T, C, G, MCOLS> sm;
-    constexpr int TILE_PITCH = xpose_tile_pitch<T, C, G>();
-    __shared__ float tile[XPOSE ? G * TILE_PITCH : 1];
+    using Mp = LongMap<T, G, COLS>;
+    __shared__ LongSmemBwd<T, C, G, COLS> sm;
     const int tid = threadIdx.x;
     const int j = Mp::row_of(tid), t = Mp::t_of(tid);
 #define TV_EX(q, tt) sm.ex[q][j][(tt) + 1]
@@ -474,31 +470,6 @@ __global__ __launch_bounds__(T *G, (T * G == 1024 && !COLS && !HAS_SUB) ? 8 : 1)
     const int64_t off = rvalid ? row_offset(p.L, row) : 0;
     const int64_t es = p.L.elem_stride;
 
-    // transposing variant: thread tid moves samples k = tid / G, tid / G + T, ... of row tid % G
-    const int xj = tid % G, xk0 = tid / G;
-    const uint32_t xrow = group * G + xj;
-    const bool xvalid = XPOSE && xrow < p.L.n_rows;
-    const int64_t xoff = xvalid ? row_offset(p.L, xrow) : 0;
-    // every global load is issued before the first trip through the tile
-    auto fetch = [&](const float *__restrict__ src, float (&raw)[C]) {
-#pragma unroll
-        for (int i = 0; i < C; ++i) {
-            const int k = xk0 + i * T;
-            raw[i] = (xvalid && k < n) ? src[xoff + (int64_t)k * es] : 0.f;
-        }
-    };
-    auto turn = [&](const float (&raw)[C], float (&dst)[C]) {
-#pragma unroll
-        for (int i = 0; i < C; ++i) {
-            const int k = xk0 + i * T;
-            tile[xj * TILE_PITCH + k + k / C] = raw[i];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < C; ++i) dst[i] = tile[j * TILE_PITCH + t * (C + 1) + i];
-        __syncthreads();
-    };
-
     // g becomes the averaged quantity, then the segment means, then the output; of x only two
     // bits per sample are kept (is there a jump behind it, and does x rise there)
     float g[C], sb[HAS_SUB ? C : 1];
@@ -510,33 +481,15 @@ __global__ __launch_bounds__(T *G, (T * G == 1024 && !COLS && !HAS_SUB) ? 8 : 1)
     if constexpr (CODES) coded = *p.codes_tag != 0u;
     if (CODES && coded) {
         const uint32_t code = rvalid ? p.chunk_codes[(size_t)row * T + t] : 0u;
-        if constexpr (XPOSE) {
-            float rg[C], rs[HAS_SUB ? C : 1];
-            fetch(p.g, rg);
-            if constexpr (HAS_SUB) fetch(p.sub, rs);
-            turn(rg, g);
-            if constexpr (HAS_SUB) turn(rs, sb);
-        } else {
-            chunk_load<C>(p.g, off, es, k0, n, rvalid, g, p.L.stream);
-            if constexpr (HAS_SUB) chunk_load<C>(p.sub, off, es, k0, n, rvalid, sb, p.L.stream);
-        }
+        chunk_load<C>(p.g, off, es, k0, n, rvalid, g, p.L.stream);
+        if constexpr (HAS_SUB) chunk_load<C>(p.sub, off, es, k0, n, rvalid, sb, p.L.stream);
         jmask = even_bits(code);
         upmask = even_bits(code >> 1);
     } else {
         float x[C];
-        if constexpr (XPOSE) {
-            float rg[C], rx[C], rs[HAS_SUB ? C : 1];
-            fetch(p.g, rg);
-            fetch(p.x, rx);
-            if constexpr (HAS_SUB) fetch(p.sub, rs);
-            turn(rg, g);
-            turn(rx, x);
-            if constexpr (HAS_SUB) turn(rs, sb);
-        } else {
-            chunk_load<C>(p.x, off, es, k0, n, rvalid, x, p.L.stream);
-            chunk_load<C>(p.g, off, es, k0, n, rvalid, g, p.L.stream);
-            if constexpr (HAS_SUB) chunk_load<C>(p.sub, off, es, k0, n, rvalid, sb, p.L.stream);
-        }
+        chunk_load<C>(p.x, off, es, k0, n, rvalid, x, p.L.stream);
+        chunk_load<C>(p.g, off, es, k0, n, rvalid, g, p.L.stream);
+        if constexpr (HAS_SUB) chunk_load<C>(p.sub, off, es, k0, n, rvalid, sb, p.L.stream);
         TV_EX(0, t) = x[0];
         Mp::sync();
         const float xnext0 = TV_EX(0, t + 1);
@@ -567,8 +520,8 @@ __global__ __launch_bounds__(T *G, (T * G == 1024 && !COLS && !HAS_SUB) ? 8 : 1)
         if (TV_JUMP(i)) { any = true; tail_s = 0.f; tail_n = 0.f; }
     }
     float ls, ln, rs, rn;
-    seg_scan<T, G, MCOLS, +1, true>(any, tail_s, tail_n, sm.buf, j, t, ls, ln);   // open part on the left
-    seg_scan<T, G, MCOLS, -1, true>(any, head_s, head_n, sm.buf, j, t, rs, rn);   // open part on the right
+    seg_scan<T, G, COLS, +1, true>(any, tail_s, tail_n, sm.buf, j, t, ls, ln);   // open part on the left
+    seg_scan<T, G, COLS, -1, true>(any, head_s, head_n, sm.buf, j, t, rs, rn);   // open part on the right
 
     // per-sample means: forward pass accumulates, backward pass broadcasts
     float (&mean)[C] = g;
@@ -607,17 +560,9 @@ __global__ __launch_bounds__(T *G, (T * G == 1024 && !COLS && !HAS_SUB) ? 8 : 1)
 #pragma unroll
         for (int i = 0; i < C; ++i) mean[i] += sb[i];
     }
-    if constexpr (XPOSE) {
-#pragma unroll
-        for (int i = 0; i < C; ++i) tile[j * TILE_PITCH + t * (C + 1) + i] = mean[i];
-        __syncthreads();
-        for (int k = xk0; k < T * C; k += T)
-            if (xvalid && k < n) p.gy[xoff + (int64_t)k * es] = tile[xj * TILE_PITCH + k + k / C];
-    } else {
-        chunk_store<C>(p.gy, off, es, k0, n, rvalid, mean, p.L.stream);
-    }
+    chunk_store<C>(p.gy, off, es, k0, n, rvalid, mean, p.L.stream);
     if (p.partial) {
-        row_sum<T, G, MCOLS, 1>(gl, sm.red, j, tid);
+        row_sum<T, G, COLS, 1>(gl, sm.red, j, tid);
         if (rvalid && t == 0) p.partial[row] = gl[0];
     }
 #undef TV_EX
@@ -652,31 +597,22 @@ template <int T, int C, int G, bool COLS>
 inline hipError_t launch_bwd_long_t(const BwdParams &p, hipStream_t s)
 {
     const dim3 grid((p.L.n_rows + G - 1) / G), block(T * G);
-    constexpr bool XP = COLS && T <= 64;
     if constexpr (chunk_coded<T, C>()) {
         if (p.chunk_codes) {
             if (p.sub)
-                hipLaunchKernelGGL((tv1d_bwd_long_kernel<T, C, G, COLS, XP, true, true>), grid, block, 0, s, p);
+                hipLaunchKernelGGL((tv1d_bwd_long_kernel<T, C, G, COLS, true, true>), grid, block, 0, s, p);
             else
-                hipLaunchKernelGGL((tv1d_bwd_long_kernel<T, C, G, COLS, XP, false, true>), grid, block, 0, s, p);
+                hipLaunchKernelGGL((tv1d_bwd_long_kernel<T, C, G, COLS, false, true>), grid, block, 0, s, p);
             return hipGetLastError();
         }
     }
     if (p.sub)
-        hipLaunchKernelGGL((tv1d_bwd_long_kernel<T, C, G, COLS, XP, true>), grid, block, 0, s, p);
+        hipLaunchKernelGGL((tv1d_bwd_long_kernel<T, C, G, COLS, true>), grid, block, 0, s, p);
     else
-        hipLaunchKernelGGL((tv1d_bwd_long_kernel<T, C, G, COLS, XP, false>), grid, block, 0, s, p);
+        hipLaunchKernelGGL((tv1d_bwd_long_kernel<T, C, G, COLS, false>), grid, block, 0, s, p);
     return hipGetLastError();
 }
 
-// GX: strided rows of 193-768 samples per workgroup of the transposing kernels.  Forward 8: a
-// workgroup of 512 threads (at most 128 registers each) leaves room for a second one on the CU,
-// whose loads and transposes then overlap the first one's solve (with 16 rows, 1024 threads, a CU
-// holds one workgroup and every phase waits for the slowest wave; 24 images of 512 x 512: column
-// pass 61 -> 57 us, K = 4 forward 313 -> 295; 12 of 768 x 768: 48 -> 42, 372 -> 344; columns of
-// 769-1024 samples need 139 registers that way and are slower, 44 -> 48).  Backward 16: it is
-// bound by memory, and 8 adjacent columns are 32 bytes of every image row (24 images of
-// 512 x 512, K = 4 reverse sweep: 205 us with 16 rows, 232 with 8).
 // Threads of the mappings below per row of 65-768 samples (the same for rows and columns, and for the
 // elimination kernels of tv_long_tri.hpp): the words a row's chunk codes take.
 inline int chunk_threads(int64_t n)
@@ -684,33 +620,9 @@ inline int chunk_threads(int64_t n)
     return n <= 96 ? 8 : n <= 192 ? 16 : n <= 384 ? 32 : 64;
 }
 
-#define TV_LONG_DISPATCH(FN, p, s, GX)                                                    \
+// Unit-stride rows of more than 32 samples.
+#define TV_LONG_ROWS(FN, n, p, s)                                                         \
     do {                                                                                  \
-        const int n = (p).L.n;                                                            \
-        const bool cols = (p).L.elem_stride != 1;                                         \
-        const int64_t wide = tvd::get(tvd::kThreadPerSampleWideRows);                     \
-        if (cols) {                                                                       \
-            if (n <= 32 && (int64_t)(p).L.n_rows <= wide) return FN<16, 2, 16, true>(p, s);        \
-            if (n <= 32) return FN<8, 4, 16, true>(p, s);                                 \
-            if (n <= 64) return FN<8, 8, 16, true>(p, s);                                 \
-            if (n <= 96) return FN<8, 12, 16, true>(p, s);                                \
-            if (n <= 128) return FN<16, 8, 16, true>(p, s);                               \
-            if (n <= 192) return FN<16, 12, 16, true>(p, s);                              \
-            if (n <= 256) return FN<32, 8, GX, true>(p, s);                               \
-            if (n <= 384) return FN<32, 12, GX, true>(p, s);                              \
-            if (n <= 512) return FN<64, 8, GX, true>(p, s);                               \
-            if (n <= 768) return FN<64, 12, GX, true>(p, s);                              \
-            if (n <= 1024) return FN<64, 16, 16, true>(p, s);                             \
-            if (n <= 1536) return FN<128, 12, 8, true>(p, s);                             \
-            if (n <= 2048) return FN<128, 16, 8, true>(p, s);                             \
-            if (n <= 3072) return FN<256, 12, 4, true>(p, s);                             \
-            if (n <= 4096) return FN<256, 16, 4, true>(p, s);                             \
-            if (n <= 8192) return FN<1024, 8, 1, true>(p, s);                             \
-            if (n <= 12288) return FN<1024, 12, 1, true>(p, s);                           \
-            return FN<1024, 16, 1, true>(p, s);                                           \
-        }                                                                                 \
-        if (n <= 32 && (int64_t)(p).L.n_rows <= wide) return FN<16, 2, 16, false>(p, s);           \
-        if (n <= 32) return FN<8, 4, 32, false>(p, s);                                    \
         if (n <= 64) return FN<8, 8, 32, false>(p, s);                                    \
         if (n <= 96) return FN<8, 12, 32, false>(p, s);                                   \
         if (n <= 128) return FN<16, 8, 16, false>(p, s);                                  \
@@ -730,13 +642,47 @@ inline int chunk_threads(int64_t n)
         return FN<1024, 16, 1, false>(p, s);                                              \
     } while (0)
 
+// Strided rows of more than 1024 samples.
+#define TV_LONG_COLS(FN, n, p, s)                                                         \
+    do {                                                                                  \
+        if (n <= 1536) return FN<128, 12, 8, true>(p, s);                                 \
+        if (n <= 2048) return FN<128, 16, 8, true>(p, s);                                 \
+        if (n <= 3072) return FN<256, 12, 4, true>(p, s);                                 \
+        if (n <= 4096) return FN<256, 16, 4, true>(p, s);                                 \
+        if (n <= 8192) return FN<1024, 8, 1, true>(p, s);                                 \
+        if (n <= 12288) return FN<1024, 12, 1, true>(p, s);                               \
+        return FN<1024, 16, 1, true>(p, s);                                               \
+    } while (0)
+
 inline hipError_t launch_fwd_long(const FwdParams &p, hipStream_t s)
 {
-    TV_LONG_DISPATCH(launch_fwd_long_t, p, s, 8);
+    const int n = p.L.n;
+    const bool wide = (int64_t)p.L.n_rows <= tvd::get(tvd::kThreadPerSampleWideRows);
+    if (p.L.elem_stride == 1) {
+        if (n <= 32) return wide ? launch_fwd_long_t<16, 2, 16, false>(p, s) : launch_fwd_long_t<8, 4, 32, false>(p, s);
+        TV_LONG_ROWS(launch_fwd_long_t, n, p, s);
+    }
+    // through an LDS tile up to 1024 samples.  Rows a workgroup, of 193-768 samples: 8.  A
+    // workgroup of 512 threads (at most 128 registers each) leaves room for a second one on the CU,
+    // whose loads and transposes then overlap the first one's solve (with 16 rows, 1024 threads, a CU
+    // holds one workgroup and every phase waits for the slowest wave; 24 images of 512 x 512: column
+    // pass 61 -> 57 us, K = 4 forward 313 -> 295; 12 of 768 x 768: 48 -> 42, 372 -> 344; columns of
+    // 769-1024 samples need 139 registers that way and are slower, 44 -> 48).
+    if (n <= 32) return wide ? launch_fwd_long_t<16, 2, 16, true>(p, s) : launch_fwd_long_t<8, 4, 16, true>(p, s);
+    if (n <= 64) return launch_fwd_long_t<8, 8, 16, true>(p, s);
+    if (n <= 96) return launch_fwd_long_t<8, 12, 16, true>(p, s);
+    if (n <= 128) return launch_fwd_long_t<16, 8, 16, true>(p, s);
+    if (n <= 192) return launch_fwd_long_t<16, 12, 16, true>(p, s);
+    if (n <= 256) return launch_fwd_long_t<32, 8, 8, true>(p, s);
+    if (n <= 384) return launch_fwd_long_t<32, 12, 8, true>(p, s);
+    if (n <= 512) return launch_fwd_long_t<64, 8, 8, true>(p, s);
+    if (n <= 768) return launch_fwd_long_t<64, 12, 8, true>(p, s);
+    if (n <= 1024) return launch_fwd_long_t<64, 16, 16, true>(p, s);
+    TV_LONG_COLS(launch_fwd_long_t, n, p, s);
 }
 
 // The coarse level that forms its averages itself, for the lengths that ml_min_length's default leaves it
-// (193 groups and more), in the mappings of TV_LONG_DISPATCH.
+// (193 groups and more), in the mappings of TV_LONG_ROWS.
 inline bool averages_itself(int64_t groups) { return groups > 192 && groups <= 4096; }
 
 template <int T, int C, int G>
@@ -792,7 +738,9 @@ inline hipError_t launch_fwd_long_debug(const FwdParams &p, hipStream_t s)
 
 inline hipError_t launch_bwd_long(const BwdParams &p, hipStream_t s)
 {
-    TV_LONG_DISPATCH(launch_bwd_long_t, p, s, 16);
+    const int n = p.L.n;
+    if (p.L.elem_stride == 1) TV_LONG_ROWS(launch_bwd_long_t, n, p, s);
+    TV_LONG_COLS(launch_bwd_long_t, n, p, s);
 }
 
 }  // namespace tvk

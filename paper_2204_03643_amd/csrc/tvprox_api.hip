@@ -8,6 +8,7 @@
 #include <mutex>
 #include <string.h>
 
+#include "tv_cols.hpp"
 #include "tv_common.hpp"
 #include "tv_dispatch.hpp"
 #include "tv_long.hpp"
@@ -860,9 +861,9 @@ int launch_reduce_lambda(const float *partial, float *grad_lam, int64_t n_rows, 
     return launch_status();
 }
 
-// Row-per-lane kernels add up the dL/dlam terms of neighbouring rows that share a slot before
-// they leave the wave: groups of 1 << lg rows, the largest power of two (at most 64) dividing
-// div.  What is left for the reduction kernel: red_rows values, red_div of them per slot visit.
+// Row-per-lane kernels, and those of strided rows of 33-1024 samples, add up the dL/dlam terms of neighbouring rows that
+// share a slot before they leave the workgroup: groups of 1 << lg rows, the largest power of two (at most 64, or the
+// columns of a workgroup) dividing div.  (The column kernels leave a group's sum in two floats.)  What is left for the reduction kernel: red_rows values, red_div of them per slot visit.
 struct PartialShape {
     uint32_t lg;
     int64_t  red_rows, red_div;
@@ -871,12 +872,15 @@ struct PartialShape {
 PartialShape partial_shape(const tv_rows &r, const tv_lambda &l, int64_t n_rows)
 {
     PartialShape ps = {0, n_rows, l.div};
-    if (r.length <= 32) {
-        uint32_t lg = 0;
-        while (lg < 6 && (l.count == 1 || l.div % ((int64_t)2 << lg) == 0)) ++lg;
+    const bool cols = tvk::bwd_cols_apply(r.length, r.elem_stride);
+    const uint32_t most = r.length <= 32 ? 6u : cols ? (uint32_t)tvk::bwd_cols_group_lg(r.length) : 0u;
+    uint32_t lg = 0;
+    while (lg < most && (l.count == 1 || l.div % ((int64_t)2 << lg) == 0)) ++lg;
+    if (most) {
+        const int64_t floats = cols && lg ? 2 : 1;              // (room for one a row is room for two a group of two)
         ps.lg = lg;
-        ps.red_rows = (n_rows + ((int64_t)1 << lg) - 1) >> lg;
-        ps.red_div = l.count == 1 ? 1 : l.div >> lg;
+        ps.red_rows = ((n_rows + ((int64_t)1 << lg) - 1) >> lg) * floats;
+        ps.red_div = l.count == 1 ? 1 : (l.div >> lg) * floats;
     }
     return ps;
 }
@@ -891,6 +895,7 @@ int run_bwd(const float *g, const float *sub, const float *x, const uint2 *seg, 
     p.g = g; p.sub = sub; p.x = x; p.seg = seg; p.gy = gy;
     p.chunk_codes = chunk_codes; p.codes_tag = codes_tag;
     p.io16 = io16 ? 1u : 0u;
+    p.near_lg = 0;
     p.partial = grad_lam ? partial : nullptr;
     p.L = make_layout(r, l, n_rows);
     const bool packed = rows_packed(r) && aligned16(g) && (!x || aligned16(x)) && aligned16(gy) &&
@@ -907,6 +912,7 @@ int run_bwd(const float *g, const float *sub, const float *x, const uint2 *seg, 
                             aligned16(gy) && (!sub || aligned16(sub));
         st = launch_bwd_short<32>(p, packed, s, planes, ragged);
     }
+    else if (tvk::bwd_cols_apply(r.length, r.elem_stride)) st = tvk::launch_bwd_cols(p, s) == hipSuccess ? TV_OK : TV_ERR_HIP;
     else st = tvk::launch_bwd_long(p, s) == hipSuccess ? TV_OK : TV_ERR_HIP;
     if (st != TV_OK) return st;
     if (grad_lam && reduce_now) {

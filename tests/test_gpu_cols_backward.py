@@ -1,0 +1,55 @@
+"""Backward along columns of 33-1024 samples, at the edges of the thread mappings, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -24
+
+
+def _piecewise(rng, P, n, W):
+    """Segments from one sample to whole columns, and ties of neighbouring levels."""
+    p = 10 ** rng.uniform(-3.5, 0.1, size=(P, 1, W))
+    at = rng.random((P, n, W)) < p
+    ids = np.cumsum(at, axis=1)
+    level = rng.integers(-3, 4, size=(P, n + 1, W)).astype(np.float32)
+    return np.take_along_axis(level, ids, axis=1)
+
+
+@pytest.mark.parametrize("slots", ["one", "plane", "column"])
+@pytest.mark.parametrize("n", [33, 63, 64, 65, 96, 97, 128, 129, 192, 193, 256, 257, 384, 385, 512, 513, 768, 769, 1024])
+def test_columns(n, slots):
+    import torch
+
+    import paper_2204_03643_amd as tv
+
+    P, W, dev = 3, 37, torch.device("cuda:0")      # (groups of columns that span planes, and a last one partly filled)
+    rng = np.random.default_rng(n)
+    x = _piecewise(rng, P, n, W)
+    g = rng.normal(size=x.shape).astype(np.float32)
+    count, div = {"one": (1, 1), "plane": (P, W), "column": (P * W, 1)}[slots]
+    xt, gt = torch.from_numpy(x).to(dev), torch.from_numpy(g).to(dev)
+    lam = torch.ones(count, device=dev)
+    rows, L = tv.rows_along(x.shape, 1), tv.tv_lambda(lam.data_ptr(), count, div)
+    room = torch.full((x.size + 64,), float("nan"), device=dev)
+    gy, gl = room[32:32 + x.size], torch.full((count,), float("nan"), device=dev)
+    wsb = tv.tv1d_bwd_workspace_bytes(rows, L)
+    ws = torch.full((max(16, wsb),), 0xff, dtype=torch.uint8, device=dev)
+    tv.tv1d_prox_bwd(gt, xt, gy, gl, rows, L, ws, wsb)
+    torch.cuda.synchronize()
+    assert torch.isnan(room[:32]).all() and torch.isnan(room[32 + x.size:]).all()
+    want, wl = oracle.prox1d_bwd_batch(g, x, lam_count=count, axis=1, lam_div=div)
+    # a mean: at most 2 x 32 additions inside a chunk, 7 across chunks and a reciprocal (2), each half an ulp of a sum
+    # of at most count * max|g|
+    mean_err = 73 * EPS * np.abs(g).max()
+    assert np.abs(gy.cpu().numpy().reshape(x.shape) - want).max() <= mean_err
+    # a slot: two means a jump, and at most 32 + 64 + 5 additions of what they leave
+    jump = np.diff(x, axis=1) != 0
+    terms = (np.abs(np.diff(want, axis=1)) * jump).sum(1).reshape(-1)
+    jumps = jump.sum(1).reshape(-1)
+    slot = (np.arange(P * W) // div) % count
+    bound = np.zeros(count)
+    np.add.at(bound, slot, 2 * jumps * mean_err + 102 * EPS * terms)
+    assert (np.abs(gl.cpu().numpy() - wl) <= bound + EPS * np.abs(wl)).all()
