@@ -399,9 +399,9 @@ def dispatch_probe(dev) -> int:
         case(name, "at_threshold_%dx%d_k%d" % (H, W, K), lambda: two_d(n, H, W, K), 0, "a plane per workgroup", beyond)
         case(name, "beyond_%dx%d_k%d" % (H, W, K), lambda: two_d(n + n // 4, H, W, K), big, beyond, "a plane per workgroup")
     n = defaults["pair_2d_many_planes"]
-    for H, W, K in ((57, 58, 3), (50, 50, 4), (33, 33, 6)):
-        case("pair_2d_many_planes", "at_threshold_%dx%d_k%d" % (H, W, K), lambda: two_d(n, H, W, K), big, "two lanes a row", "pass by pass")
-        case("pair_2d_many_planes", "below_%dx%d_k%d" % (H, W, K), lambda: two_d(n - n // 4, H, W, K), 0, "pass by pass", "two lanes a row")
+    for H, W, K in ((57, 58, 3), (60, 60, 2)):
+        case("pair_2d_many_planes", "at_threshold_%dx%d_k%d" % (H, W, K), lambda: two_d(n, H, W, K), 0, "a plane per workgroup", "two lanes a row")
+        case("pair_2d_many_planes", "beyond_%dx%d_k%d" % (H, W, K), lambda: two_d(n + n // 4, H, W, K), big, "two lanes a row", "pass by pass")
     for name, H, W, K, other in (("plane_per_group_bwd_planes", 32, 32, 4, "a row per lane"),
                                  ("plane_per_group64_bwd_planes", 64, 64, 4, "two lanes a row"),
                                  ("plane_per_group64_bwd_ragged_planes", 40, 46, 1, "pass by pass"),

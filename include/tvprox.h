@@ -258,8 +258,9 @@ int tv1d_prox_bwd_seg_bf16(const uint16_t *g_up, const uint64_t *seg, uint16_t *
  * call then reads; it must be handed unchanged to tv2d_prox_bwd.  The forward call leaves
  * there what the backward call will read: the pass outputs, or, where planes of at most
  * 32 x 32 run all their passes in one launch, the codes alone (the pass outputs as well
- * after tv_dispatch_override("fused_keeps_passes", 1)), or, on sides of 65-768 samples and from
- * "chunk_codes_bytes" of pass outputs on, codes in their place (the pass outputs instead after the
+ * after tv_dispatch_override("fused_keeps_passes", 1)), or codes in their place: where planes with both
+ * sides of 33-64 samples run all their passes in one launch, and on sides of 65-768 samples from
+ * "chunk_codes_bytes" of pass outputs on (the pass outputs instead after the
  * same override; the backward call finds out from the workspace).  x must not alias y.
  * From the second sweep on, the correction term a pass adds to its input is D^T u of the
  * same pass one sweep earlier (x = y - D^T u), and the pass starts its Newton iteration

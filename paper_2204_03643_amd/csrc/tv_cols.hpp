@@ -36,7 +36,7 @@ __device__ __forceinline__ float mean_of(float s, float n)
 // columns 21.6; 768, no sub, 64 threads of 12 samples 19.8, 32 threads of 24 and 32 columns 23.8).
 // HAS_SUB: p.sub is given (the reverse sweep of the 2D operator).  CODES: where the forward pass left chunk codes
 // (p.codes_tag says whether it did) they are read, not x: CW words of C / CW samples a thread, in the forward kernel's
-// order (word t of its row).
+// order (word t of its row); row masks where columns have 33-64 samples.
 template <int T, int C, int G, int CW, bool HAS_SUB, bool CODES>
 __global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
 {
@@ -72,16 +72,20 @@ __global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
     const int nv = min(max(n - 1 - k0, 0), C);
     const uint32_t inrow = nv == 32 ? ~0u : (1u << nv) - 1u;
     bool coded = false;
-    if constexpr (CODES) coded = *p.codes_tag != 0u;
+    if constexpr (CODES) coded = *p.codes_tag == 1u;
     fetch(p.g, g);
     if constexpr (HAS_SUB) fetch(p.sub, sb);
     if (CODES && coded) {
-        const uint32_t *words = p.chunk_codes + ((size_t)arow * T + t) * CW;
+        if constexpr (row_masked<T, C>()) {
+            mask_bits<C>(p.chunk_codes, arow, k0, jmask, upmask);
+        } else {
+            const uint32_t *words = p.chunk_codes + ((size_t)arow * T + t) * CW;
 #pragma unroll
-        for (int w = 0; w < CW; ++w) {
-            const uint32_t code = words[w];
-            jmask |= even_bits(code) << (w * (C / CW));
-            upmask |= even_bits(code >> 1) << (w * (C / CW));
+            for (int w = 0; w < CW; ++w) {
+                const uint32_t code = words[w];
+                jmask |= even_bits(code) << (w * (C / CW));
+                upmask |= even_bits(code >> 1) << (w * (C / CW));
+            }
         }
     } else {
         float x[C];
@@ -228,11 +232,11 @@ inline hipError_t launch_bwd_cols_t(BwdParams p, hipStream_t s)
     return hipGetLastError();
 }
 
-// CW: the words of chunk_threads(n) that a thread's C samples are, 0 where there are none.
+// CW: the words of chunk_threads(n) that a thread's C samples are (1 where it reads a row mask), 0 where there are none.
 inline hipError_t launch_bwd_cols(const BwdParams &p, hipStream_t s)
 {
     const int n = p.L.n;
-    if (n <= 64) return launch_bwd_cols_t<4, 16, 0>(p, s);
+    if (n <= 64) return launch_bwd_cols_t<4, 16, 1>(p, s);
     if (n <= 96) return launch_bwd_cols_t<8, 12, 1>(p, s);
     if (n <= 128) return launch_bwd_cols_t<8, 16, 2>(p, s);
     if (n <= 192) return launch_bwd_cols_t<16, 12, 1>(p, s);

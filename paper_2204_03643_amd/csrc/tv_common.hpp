@@ -158,7 +158,7 @@ struct BwdParams {
     const float *sub;      // optional: the averaged quantity is g - sub, and sub is added back
     const float *x;        // forward output (defines the segments) ...
     const uint2 *seg;      // ... or the segment code the forward pass wrote (rows of up to 32 samples)
-    const uint32_t *chunk_codes;   // ... or, where *codes_tag is not 0, the chunk codes (2D, sides of 65-768)
+    const uint32_t *chunk_codes;   // ... or, where *codes_tag is 1, the chunk codes (2D, sides of 65-768) or row masks (33-64)
     const uint32_t *codes_tag;
     float       *gy;       // output
     float       *partial;  // optional: dL/dlam contributions, one per group of 1 << part_lg rows

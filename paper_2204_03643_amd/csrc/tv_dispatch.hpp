@@ -112,6 +112,7 @@ inline Threshold table[kCount] = {
     {"plane_per_group_planes", 768, "2D planes of 17-32 a side: one launch, a plane per workgroup, up to this many planes (a third more: two sweeps and more; three quarters more: one side of 29-32, no square)"},
     //   64 x 64, K = 1:  512 planes  47 /  50,  768:  67 /  60, 1024:  78 /  73, 1536: 109 / 94;
     //   48 x 48, K = 1:  512 planes  35 /  38,  768:  55 /  54, 1024:  64 /  57.
+    // (With row masks, forward + reverse sweep: 600 planes of 45 x 45 59 / 57, 560 of 64 x 64 57 / 61.)
     {"plane_per_group64_planes", 512, "2D planes of 33-64 a side, one sweep: one launch, a plane per workgroup, up to this many planes"},
     // Several sweeps, forward + reverse sweep, ratio of this kernel to pass by pass on post-ReLU
     // maps and on N(0, 1) data:
@@ -120,28 +121,27 @@ inline Threshold table[kCount] = {
     //   64 x 40, K = 3: 1280 planes 0.93 0.99, 1536: 0.96 1.01, 2048: 1.04 1.06.
     {"plane_per_group64_planes_k2", 1280, "... two sweeps or more, planes smaller than 64 x 64"},
     // Planes whose shorter side fills four fifths of 40, 48, 56 or 64 (pairs_2d_apply), forward in one launch with two
-    // lanes a row.  N(0, 1), lambda 10^U(-1.3, 0), time of the best other mapping (a plane per workgroup up to 512 planes
-    // with one sweep and 1280 with more, pass by pass beyond) over the time with two lanes a row:
-    //   squares, K = 4:     520 planes  600   1024  1100  1536  2048  4096  16 384
-    //      40 x 40             1.13     1.32  1.63  1.24  1.25  1.27  1.19  1.15
-    //      56 x 56             1.02     1.06  1.36  1.02  1.14  1.14  1.10  1.15
-    //      64 x 64             0.95     1.11  1.37  1.01  1.09  1.31  1.22  1.31     (K = 6, 520 planes: 0.92)
-    //   K = 2: 56 x 56, 1300-3150 planes 0.92-0.96, 4200: 1.06; 64 x 64, 1300-2100: 0.96, 3000: 1.09.
-    //   K = 1: 40 x 40, 768 planes 1.16, 1024: 1.24, otherwise 0.88-1.04;  64 x 64, 512: 0.81, 1024: 1.07, 1100: 0.85.
+    // lanes a row, both leaving row masks.  N(0, 1), lambda 10^U(-1.3, 0), forward, two lanes a row / a plane per workgroup /
+    // pass by pass, us:
+    //   K = 2       560 planes    800           1000          1300           2048           4096
+    //      33 x 33   55  48  58    55  67  63    55  74  66    70  92  78    102 136 102    166 252 156
+    //      40 x 40   46  54  65    46  73  74    46  81  79    72 103  89     91 149 117    161 278 190
+    //      44 x 48   68  56  66    68  83  73    68  91  82    86 110  98    130 162 126    215 298 214
+    //      50 x 50   80  58  73    80  81  84    81  96  92   126 114 109    154 166 150    271 311 260
+    //      56 x 56   64  63  74    65  82  87    72  98  99   105 118 115    132 174 158    232 322 290
+    //      60 x 60   97  61  78    99  87  88   110 104 106   149 124 126    185 179 170    321 333 325
+    //      64 x 64   76  62  83    77  86  96    79 103 104   118 125 122    149 183 172    260 339 311
+    //   K = 10: 36 x 36, 800 planes 194 252 288, 4096: 629 995 722;  47 x 47 237 283 340, 777 1111 1038;
+    //      52 x 56 278 295 364, 1300: 441 424 491, 4096: 1003 1163 1127;  63 x 63 330 306 430, 504 441 620, 1150 1229 1666;
+    //      64 x 64 274 310 400, 428 444 515, 995 1227 1406.
+    // (Where pass by pass is level at K = 2, its reverse sweep, which reads pass outputs, takes half as long again.)
+    //   K = 1: 800 planes 40 x 40 27 43 35, 56 x 56 40 49 44, 64 x 64 46 54 50, 44 x 48 41 47 38, 60 x 60 60 52 46; 1300: 40 59 42,
+    //      60 71 59, 67 74 64.
     {"plane_per_group64_full_planes_k2", 560, "... planes of 40 x 40, 48 x 48, 56 x 56 and 64 x 64, two sweeps; two lanes a row beyond"},
     {"plane_per_group64_full_planes_k3", 560, "... three or four sweeps"},
     {"plane_per_group64_full_planes_k5", 560, "... five sweeps or more"},
-    //   others, K = 4:      600 planes  768   1024  1200  1536  2100  4096  16 384
-    //      36 x 36             1.08     1.19  1.38  1.27  1.05  1.06  0.99  0.96
-    //      44 x 48             1.01     1.09  1.25  1.22  1.02  1.01  0.99  1.03
-    //      48 x 40 (660: 1.05)          1.06        1.18        1.03  0.98  0.95     (K = 2: 0.89-0.95 from 2100 on)
-    //      52 x 56             0.86     0.96  1.10  0.83  0.90   -    0.89  0.93
-    //      60 x 60             0.75     0.90  0.97  0.75  0.91   -    0.92  0.96     (K = 1: 0.6-0.75)
-    //      45 x 45             1.00     1.10  1.17  1.14  1.11  1.14  1.14  1.18     (K = 2: 0.95-1.09)
-    //      50 x 50             0.95     0.95  1.08  0.83  0.97  1.00  0.99  1.12
-    //      63 x 63             0.81     0.92  0.99  0.78  1.12  1.15  1.28  1.27     (K = 3, 57 x 58: 4200 0.91-0.96, 5200 1.02)
-    {"pair_2d_planes", 704, "2D planes of 33-48 a side that fill four fifths of 40 or 48: two lanes a row beyond this many planes, up to plane_per_group64_planes_k2 (one sweep: squares of 40 and 48, up to 1024)"},
-    {"pair_2d_many_planes", 5000, "2D planes of 33-64 a side with rows of no multiple of four samples: two lanes a row from this many planes on (6 sweeps; 4 on sides beyond 48, 3 beyond 56); squares of 56 and 64, two sweeps"},
+    {"pair_2d_planes", 704, "2D planes of 33-56 a side that fill four fifths of 40, 48 or 56: two lanes a row beyond this many planes (sides beyond 48: not from 1025 to plane_per_group64_planes_k2; one sweep: squares of 40, 48, 56 and 64, up to 1024)"},
+    {"pair_2d_many_planes", 2048, "2D planes of 57-64 a side that fill four fifths of 64, no squares, two sweeps or more: two lanes a row beyond this many planes"},
     // 2D reverse sweep of small batches with a plane per workgroup (tv_plane2d.hpp): both adjoint
     // state tensors of the plane in LDS, 16 x 2 or 8 x 8 threads x samples per row, the segment
     // sums across a row's threads by row shifts.  Against the row-per-lane one-launch kernel (a
@@ -158,9 +158,17 @@ inline Threshold table[kCount] = {
     //   40 x 40, K = 4: 256 planes 22 / 24,  512: 30 / 26,  640: 47 / 29, 1024:  56 /  31, 4096: 189 / 108;
     //   52 x 56, K = 4: 576 planes 53 / 42, 1024: 65 / 48, 2048: 121 / 112, 4096: 244 / 173;
     //   64 x 60, K = 4: 640 planes 55 / 55, 1024: 67 / 63, 1536: 100 / 111, 2048: 144 / 153, 3072: 203 / 192, 4096: 268 / 246;
-    //   36 x 40, K = 1, against pass by pass from 1024 planes on: 1024: 24 / 18, 1536: 28 / 26, 2048: 33 / 37, 3072: 43 / 34.
+    //   36 x 40, K = 1, against pass by pass from 1024 planes on: 1024: 24 / 18, 1536: 28 / 26, 2048: 33 / 37, 3072: 43 / 34;
+    //   rows of no multiple of four samples: 33 x 33, 4096 planes 39 / 42, 47 x 47: 59 / 55, 63 x 63: 106 / 78; 6200: 49 / 56, 92 / 74, 158 / 115.
+    // From row masks, K = 10, this mapping / two lanes a row:
+    //      560 planes  800       1000      1300        2048        3000        4096
+    //   36 x 36  75 / 60  94 / 63   94 / 63  135 / 118  176 / 159  247 / 170  327 / 261
+    //   47 x 47  76 / 72  94 / 74   95 / 75  139 / 142  182 / 190  254 / 207  334 / 306
+    //   52 x 56  77 / 82  96 / 86   98 / 86  140 / 161  188 / 210  258 / 240  341 / 356
+    //   60 x 60  79 / 94  96 / 96   99 / 100 141 / 182  186 / 244  262 / 271  349 / 412
+    //   64 x 64  80 / 83  98 / 87  100 / 89  142 / 162  194 / 239  267 / 240  356 / 378
     {"plane_per_group_bwd_planes", 768, "2D reverse sweep, planes of 17-32 a side: a plane per workgroup up to this many planes"},
-    {"plane_per_group64_bwd_planes", 512, "2D reverse sweep, planes of 33-64 a side that two lanes a row can take over: a plane per workgroup up to this many planes (half as many again: sides beyond 56 that do not fill 64 x 64)"},
+    {"plane_per_group64_bwd_planes", 512, "2D reverse sweep, planes of 33-64 a side that two lanes a row can take over: a plane per workgroup up to this many planes (half as many again: pass outputs, sides beyond 56 that do not fill 64 x 64; row masks, sides beyond 48: see pairs_2d_bwd)"},
     // ... and against the pass-by-pass reverse sweep (2K launches), which is what other planes of
     // 33-64 samples a side get otherwise: 40 x 48, K = 1: 256 planes 14 / 20, 512: 18 / 22,
     // 1024: 29 / 28, 2048: 53 / 40; K = 3: 256 planes 22 / 44, 1024: 52 / 74, 2048: 95 / 108.

@@ -44,6 +44,20 @@ typedef float tv_long_v4f __attribute__((ext_vector_type(4), aligned(4)));
 template <int T, int C>
 constexpr bool chunk_coded() { return T <= 64 && C <= 16 && T * C > 64 && T * C <= 768; }
 
+// Rows of 33-64 samples, a thread's samples a part of a row mask (tv_small2d.hpp).
+template <int T, int C>
+constexpr bool row_masked() { return T * C == 64; }
+
+// The bits of samples k0 .. k0 + C - 1 in a row mask's jumps and rises.
+template <int C>
+__device__ __forceinline__ void mask_bits(const uint32_t *__restrict__ masks, size_t row, int k0, uint32_t &jump, uint32_t &up)
+{
+    const uint4 m = *reinterpret_cast<const uint4 *>(masks + row * 4);
+    constexpr uint32_t low = (1u << C) - 1u;                // (C divides 32: a chunk lies in one word)
+    jump = ((k0 < 32 ? m.x : m.y) >> (k0 & 31)) & low;
+    up = ((k0 < 32 ? m.z : m.w) >> (k0 & 31)) & low;
+}
+
 // code <- 16 code + 8 (x2 > x1) + 4 (x2 != x1) + 2 (x1 > x0) + (x1 != x0): a comparison a bit and an addition that takes
 // it as its carry.  (The comparisons themselves, as where the segments are read off x: the bits of a difference
 // call -0 beside +0 a fall, and say nothing next to an infinity.)
@@ -281,6 +295,9 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>()))
     const int tid = threadIdx.x;
     const int j = Mp::row_of(tid), t = Mp::t_of(tid);
 
+    if constexpr (!DEBUG && !COLS && row_masked<T, C>() && WARM != 1) {
+        if (blockIdx.x == 0 && tid == 0 && p.codes_tag) *p.codes_tag = 0u;     // (pass by pass, such sides leave no masks)
+    }
     const uint32_t group = COLS ? xcd_grouped<G>(blockIdx.x, gridDim.x) : blockIdx.x;
     const uint32_t row = group * G + j;
     bool rvalid = row < p.L.n_rows;
@@ -452,7 +469,7 @@ __global__ __launch_bounds__(T *G, (fwd_waves_per_simd<T, C, G, COLS, XPOSE>()))
 template <int T, int C, int G, bool COLS, bool HAS_SUB = false, bool CODES = false>
 __global__ __launch_bounds__(T *G, (T * G == 1024 && !COLS && !HAS_SUB) ? 8 : 1) void tv1d_bwd_long_kernel(BwdParams p)
 {
-    static_assert(!CODES || chunk_coded<T, C>(), "chunk codes are for rows inside one wave");
+    static_assert(!CODES || chunk_coded<T, C>() || row_masked<T, C>(), "chunk codes are for rows inside one wave");
     using Mp = LongMap<T, G, COLS>;
     __shared__ LongSmemBwd<T, C, G, COLS> sm;
     const int tid = threadIdx.x;
@@ -478,13 +495,17 @@ __global__ __launch_bounds__(T *G, (T * G == 1024 && !COLS && !HAS_SUB) ? 8 : 1)
     const int nv = min(max(n - 1 - k0, 0), C);
     const uint32_t inrow = (1u << nv) - 1u;
     bool coded = false;
-    if constexpr (CODES) coded = *p.codes_tag != 0u;
+    if constexpr (CODES) coded = *p.codes_tag == 1u;
     if (CODES && coded) {
-        const uint32_t code = rvalid ? p.chunk_codes[(size_t)row * T + t] : 0u;
+        const uint32_t code = !row_masked<T, C>() && rvalid ? p.chunk_codes[(size_t)row * T + t] : 0u;
         chunk_load<C>(p.g, off, es, k0, n, rvalid, g, p.L.stream);
         if constexpr (HAS_SUB) chunk_load<C>(p.sub, off, es, k0, n, rvalid, sb, p.L.stream);
-        jmask = even_bits(code);
-        upmask = even_bits(code >> 1);
+        if constexpr (row_masked<T, C>()) {
+            if (rvalid) mask_bits<C>(p.chunk_codes, row, k0, jmask, upmask);
+        } else {
+            jmask = even_bits(code);
+            upmask = even_bits(code >> 1);
+        }
     } else {
         float x[C];
         chunk_load<C>(p.x, off, es, k0, n, rvalid, x, p.L.stream);
@@ -597,7 +618,7 @@ template <int T, int C, int G, bool COLS>
 inline hipError_t launch_bwd_long_t(const BwdParams &p, hipStream_t s)
 {
     const dim3 grid((p.L.n_rows + G - 1) / G), block(T * G);
-    if constexpr (chunk_coded<T, C>()) {
+    if constexpr (chunk_coded<T, C>() || row_masked<T, C>()) {
         if (p.chunk_codes) {
             if (p.sub)
                 hipLaunchKernelGGL((tv1d_bwd_long_kernel<T, C, G, COLS, true, true>), grid, block, 0, s, p);

@@ -412,6 +412,33 @@ __device__ __forceinline__ uint2 pair_segment_code(const float (&xs)[C], int n, 
     return make_uint2(jm, rises);
 }
 
+// The half of a pair's row mask (tv_small2d.hpp) that the lane leaves: the left lane the jumps, the right one the rises.
+template <int C, bool FULL>
+__device__ __forceinline__ uint2 pair_row_mask(const float (&xs)[C], int n, bool right)
+{
+    uint32_t jump, rises;                       // local duals, as in pair_segment_code
+    {
+        const float d = xs[C - 1] - pair_other(xs[C - 1]);
+        rises = __float_as_uint(d) >> 31;
+        jump = __float_as_uint(0.0f - fabsf(d)) >> 31;
+    }
+#pragma unroll
+    for (int k = C - 2; k >= 0; --k) {
+        const float d = xs[k] - xs[k + 1];
+        rises = __builtin_amdgcn_alignbit(rises, __float_as_uint(d), 31);
+        jump = __builtin_amdgcn_alignbit(jump, __float_as_uint(0.0f - fabsf(d)), 31);
+    }
+    // left: duals 0 .. C-1 as they are.  Right: its duals 0 .. C-2 are 2C-2 .. C of the row, which rises where the lane falls
+    const uint32_t turned_jump = __builtin_bitreverse32(jump) >> (33 - C);
+    const uint32_t turned_rises = __builtin_bitreverse32(jump & ~rises) >> (33 - C);
+    jump = right ? turned_jump : jump;
+    rises = right ? turned_rises : rises;
+    const uint32_t other = pair_other(right ? jump : rises);
+    uint64_t mask = right ? other | (uint64_t)rises << C : jump | (uint64_t)other << C;
+    if (!FULL) mask &= (1ull << (n - 1)) - 1ull;
+    return make_uint2((uint32_t)mask, (uint32_t)(mask >> 32));
+}
+
 // The tile in LDS: samples 0 .. C-1 of a row in order, the others from the row's end, HALF places on, so
 // that either lane of a pair finds its half at offsets known at compile time.  With HALF = 16 the 16 rows
 // that half a wave works on cover 16 banks, and their other halves the other 16.  (HALF = 32: two by two
@@ -466,7 +493,8 @@ __device__ __forceinline__ uint32_t pair_live(int cut, bool right)
 // between passes through one LDS tile, whose rows and columns both lie as PairTile has them.  As in
 // tv2d_fwd_small_kernel the tile also parks the solver's input, and the correction term that is not in
 // use lives in a lane-private LDS column.  Planes of at most 32 x 32 leave segment codes for the reverse
-// sweep, larger ones their pass outputs.
+// sweep, larger ones row masks (1024 planes of 64 x 64, K = 4, forward + reverse sweep 186 -> 177 us,
+// 2000 of 47 x 47, K = 3, 307 -> 265) or, where those are asked for, their pass outputs.
 // Registers: four waves a SIMD up to 32 x 32 (a fifth, at 96 registers, spills and is 10 % slower), two beyond,
 // where LDS holds no more (33 KB a plane).
 // ---------------------------------------------------------------------------------
@@ -600,6 +628,9 @@ __global__ __launch_bounds__(C > 16 ? 128 : 64, C > 16 ? 2 : 4) void tv2d_fwd_pa
                 uint32_t *to = reinterpret_cast<uint32_t *>(p.codes + (size_t)i * p.code_stride + (size_t)plane * (col ? W : H) + idx);
                 to[right ? 1 : 0] = right ? code.y : code.x;
             }
+        } else if (p.codes) {
+            const uint2 mask = pair_row_mask<C, FULL>(xs, n, right);
+            if (valid) p.codes[(size_t)i * p.code_stride + ((size_t)plane * (col ? W : H) + idx) * 2 + (right ? 1 : 0)] = mask;
         }
 
         const bool keep = i + 2 < n_pass;
@@ -615,7 +646,7 @@ __global__ __launch_bounds__(C > 16 ? 128 : 64, C > 16 ? 2 : 4) void tv2d_fwd_pa
             for (int k = 0; k < C; ++k) by_row[k] = xs[k];
         }
         sync();
-        if (C > 16 || p.keep_passes) put_plane(p.saved + (size_t)i * p.saved_stride + plane * HW);
+        if (C > 16 ? p.codes == nullptr : p.keep_passes != 0u) put_plane(p.saved + (size_t)i * p.saved_stride + plane * HW);
         // input of the next pass: this output seen the other way plus that direction's correction
         // term, whose negated running sum is the dual to start from
         valid = in_half && (FULL || idx < (col ? H : W));
@@ -655,6 +686,7 @@ __global__ __launch_bounds__(C > 16 ? 128 : 64, C > 16 ? 2 : 4) void tv2d_fwd_pa
     } else {
         put_plane(p.x + plane * HW);
     }
+    if (C > 16 && p.tag && blockIdx.x == 0 && tid == 0) *p.tag = p.codes ? 1u : 0u;
 }
 
 // ---------------------------------------------------------------------------------
@@ -684,6 +716,8 @@ __global__ __launch_bounds__(64, C > 16 ? 3 : 4) void tv1d_fwd_pair_kernel(FwdPa
     __shared__ float gtab[C + 2];
     const int lane = threadIdx.x;
     pair_fill_table<C>(gtab, lane);
+    // (the row pass of a 2D call with one sweep on sides of 33-64: this route leaves no masks)
+    if (C > 16 && p.codes_tag && blockIdx.x == 0 && blockIdx.y == 0 && lane == 0) *p.codes_tag = 0u;
 
     const uint32_t slot = p.order ? min(p.order[blockIdx.y], gridDim.y - 1u) : blockIdx.y;
     const uint32_t r0 = p.tm.first<32>(__builtin_amdgcn_readfirstlane(blockIdx.x), slot);
@@ -908,9 +942,10 @@ __global__ __launch_bounds__(64, C > 16 ? 3 : 4) void tv1d_fwd_pair_kernel(FwdPa
 // waves and chains of 32.  Both adjoint state tensors of the plane lie in LDS as PairTile has them; of
 // a pass's output a lane reads its half row one pass ahead, rows in 16-byte pieces, columns in rows of 32
 // neighbouring columns, and keeps a jump and a direction bit a sample.
+// Row masks in place of pass outputs (p.tag): 1024 planes of 64 x 64, K = 4, 49.7 -> 43.4 us, 1000 of 50 x 50, K = 10, 97 -> 86.
 // Reverse sweep of 1024 planes of 64 x 64, K = 4, a row per lane / two lanes: 69 / 48 us, 8192 planes, K = 2: 290 / 180;
 // 1024 planes of 40 x 40, K = 4, a plane per workgroup / two lanes: 56 / 31.
-// W a multiple of 4, the saved outputs 16-byte aligned; at most 2C / 5 samples short of 2C.
+// At most 2C / 5 samples short of 2C.
 // ---------------------------------------------------------------------------------
 template <int C, bool FULL>
 __global__ __launch_bounds__(128, 2) void tv2d_bwd_pair_kernel(Small2dBwdParams p)
@@ -961,8 +996,16 @@ __global__ __launch_bounds__(128, 2) void tv2d_bwd_pair_kernel(Small2dBwdParams 
     // C .. n-1 and beyond (lanes without a row, and samples past the end, read inside the plane all the same:
     // no branch a load).
     const int row_in = FULL ? idx : min(idx, H - 1), col_in = FULL ? idx : min(idx, W - 1);
+    // Or, where the forward call left row masks, the row's mask.
+    const bool coded = p.tag && *p.tag == 1u;
+    uint4 mask = make_uint4(0u, 0u, 0u, 0u);
     auto fetch = [&](int pass, float (&xv)[C]) {
         if (pass < 0) return;
+        if (coded) {
+            const size_t row = (size_t)plane * ((pass & 1) ? W : H) + ((pass & 1) ? col_in : row_in);
+            mask = *reinterpret_cast<const uint4 *>(p.codes + (size_t)pass * p.code_stride + row * 2);
+            return;
+        }
         const float *xs = p.saved + (size_t)pass * p.saved_stride + (size_t)plane * HW;
         if (pass & 1) {
             const int r0 = right ? C : 0;
@@ -970,16 +1013,31 @@ __global__ __launch_bounds__(128, 2) void tv2d_bwd_pair_kernel(Small2dBwdParams 
             for (int r = 0; r < C; ++r) xv[r] = xs[(FULL ? r0 + r : min(r0 + r, H - 1)) * W + col_in];
         } else {
             const int c0 = right ? C : 0;
+            const float *from = xs + row_in * W;
+            if (FULL || W % 4 == 0) {
 #pragma unroll
-            for (int c = 0; c < C; c += 4) {
-                const float4 q = *reinterpret_cast<const float4 *>(xs + row_in * W + (FULL ? c0 + c : min(c0 + c, W - 4)));
-                xv[c] = q.x; xv[c + 1] = q.y; xv[c + 2] = q.z; xv[c + 3] = q.w;
+                for (int c = 0; c < C; c += 4) {
+                    const float4 q = *reinterpret_cast<const float4 *>(from + (FULL ? c0 + c : min(c0 + c, W - 4)));
+                    xv[c] = q.x; xv[c + 1] = q.y; xv[c + 2] = q.z; xv[c + 3] = q.w;
+                }
+            } else {
+#pragma unroll
+                for (int c = 0; c < C; ++c) xv[c] = from[min(c0 + c, W - 1)];
             }
         }
     };
     // Jump and direction bits of the lane's local duals: bit i behind local sample i, towards the middle; up: x rises there,
     // seen from the lane's end.  The sign of x[k] - x[k+1] says "rises", that of -|.| "differs".
     auto bits_of = [&](const float (&xv)[C], uint32_t &jump, uint32_t &up) {
+        if (coded) {
+            const uint64_t j = mask64(mask.x, mask.y), u = mask64(mask.z, mask.w);
+            const uint32_t middle = (uint32_t)(j >> (C - 1)) & 1u;
+            const uint32_t rj = (uint32_t)(j >> C), ru = (uint32_t)(u >> C);
+            constexpr uint32_t half = C == 32 ? ~0u : (1u << (C & 31)) - 1u;
+            jump = right ? __builtin_bitreverse32(rj) >> (33 - C) | middle << (C - 1) : (uint32_t)j & half;
+            up = right ? __builtin_bitreverse32(rj & ~ru) >> (33 - C) : (uint32_t)u & half;
+            return;
+        }
         jump = 0; up = 0;
 #pragma unroll
         for (int k = C - 2; k >= 0; --k) {

@@ -22,8 +22,9 @@
 namespace tvk {
 
 // T threads per row, C samples per thread: planes of at most S x S, S = T * C (16 x 2: up to
-// 32 x 32, with segment codes for the reverse sweep; 8 x 8: up to 64 x 64, whose reverse sweep
-// reads the saved pass outputs).  One plane per workgroup of S * T = 512 threads.
+// 32 x 32, with segment codes for the reverse sweep; 8 x 8: up to 64 x 64, with row masks where both sides are
+// longer than 32 and the passes are not asked for, pass outputs otherwise).  With masks, 256 planes of
+// 64 x 64, K = 4: forward 73 -> 68 us, reverse sweep 33 -> 20.  One plane per workgroup of S * T = 512 threads.
 // (32 x 32 with 8 threads x 4 samples, 256 threads: 256 planes, K = 4, 52 us against 38 with
 // 16 x 2, whose chains are shorter; from 1500 planes on 8 x 4 is 5-10 % ahead, where the
 // row-per-lane kernels take over anyway.)
@@ -103,10 +104,28 @@ __global__ __launch_bounds__(T * T * C, C <= 4 ? 8 : 4) void tv2d_fwd_plane_kern
             const uint2 code = row_segment_code<T, C>(xs, n, t);
             if (valid && t == 0)
                 p.codes[(size_t)i * p.code_stride + (size_t)plane * rows + j] = code;
+        } else if (p.codes) {
+            // row masks, a byte of eight samples a thread
+            static_assert(S <= 32 || C == 8, "");
+            const float xnext0 = from_right<T, 1>(xs[0], t);
+            uint32_t jm = 0, up = 0;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const float xn = (c + 1 < C) ? xs[c + 1] : xnext0;
+                if (k0 + c < n - 1) {
+                    if (xn != xs[c]) jm |= 1u << c;
+                    if (xn > xs[c]) up |= 1u << c;
+                }
+            }
+            if (valid) {
+                uint8_t *to = reinterpret_cast<uint8_t *>(p.codes + (size_t)i * p.code_stride + ((size_t)plane * rows + j) * 2);
+                to[t] = (uint8_t)jm;
+                to[8 + t] = (uint8_t)up;
+            }
         }
         __syncthreads();
         // (planes of at most 32 x 32: the reverse sweep reads the codes written above)
-        if (S > 32 || p.keep_passes) {
+        if (S > 32 ? p.codes == nullptr : p.keep_passes != 0u) {
             put_plane(p.saved + (size_t)i * p.saved_stride + plane * HW);
             if (i + 1 < n_pass) __syncthreads();      // the next pass writes into the tile
         }
@@ -117,6 +136,7 @@ __global__ __launch_bounds__(T * T * C, C <= 4 ? 8 : 4) void tv2d_fwd_plane_kern
     } else {
         put_plane(p.x + plane * HW);
     }
+    if (S > 32 && p.tag && blockIdx.x == 0 && tid == 0) *p.tag = p.codes ? 1u : 0u;
 }
 
 // ---------------------------------------------------------------------------------
@@ -205,7 +225,7 @@ __device__ __forceinline__ float lanes_segment_means(float (&g)[C], uint32_t jm,
 }
 
 // T, C as in the forward kernel.  Planes of at most 32 x 32 read the segments of a pass from its
-// 8-byte codes, larger ones from its saved output.  p.partial gets one dL/dlam term per plane.
+// 8-byte codes, larger ones from their row masks (where p.tag says so) or its saved output.  p.partial gets one dL/dlam term per plane.
 // IO16: the upstream gradient and grad_y are bf16 in memory.
 template <int T, int C, bool IO16 = false>
 __global__ __launch_bounds__(T * T * C, C <= 4 ? 8 : 4) void tv2d_bwd_plane_kernel(Small2dBwdParams p)
@@ -227,6 +247,7 @@ __global__ __launch_bounds__(T * T * C, C <= 4 ? 8 : 4) void tv2d_bwd_plane_kern
 
     // Segments of pass `pass` for the thread's chunk of its row (row pass) or column (column
     // pass); fetched one pass ahead, so that the latency hides behind the pass before.
+    const bool coded = S > 32 && p.tag && *p.tag == 1u;
     auto fetch = [&](int pass, uint32_t &jm, uint32_t &up) {
         jm = 0u; up = 0u;
         if (pass < 0) return;
@@ -238,6 +259,12 @@ __global__ __launch_bounds__(T * T * C, C <= 4 ? 8 : 4) void tv2d_bwd_plane_kern
                 const uint2 c = p.codes[(size_t)pass * p.code_stride + (size_t)plane * rows + j];
                 jm = (c.x >> k0) & ((1u << C) - 1u);
                 up = (c.y >> k0) & ((1u << C) - 1u);
+            }
+        } else if (coded) {
+            if (valid) {
+                const uint8_t *from = reinterpret_cast<const uint8_t *>(p.codes + (size_t)pass * p.code_stride + ((size_t)plane * rows + j) * 2);
+                jm = from[t];
+                up = from[8 + t];
             }
         } else {
             const float *xs = p.saved + (size_t)pass * p.saved_stride + (size_t)plane * HW;

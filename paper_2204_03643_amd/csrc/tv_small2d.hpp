@@ -62,12 +62,18 @@ struct Small2dBwdParams {
     float       *gy;
     const uint2 *codes;        // pass i (row pass of sweep k: 2k, column pass: 2k + 1) at codes + i * code_stride
     size_t       code_stride;  // in uint2
-    const float *saved;        // planes of 33-64 samples a side have no codes: the output of pass i,
-    size_t       saved_stride; // at saved + i * saved_stride (floats), is read instead
+    const uint32_t *tag;       // planes of 33-64 samples a side: optional; where it holds 1 the codes are row masks (below) ...
+    const float *saved;        // ... and otherwise the output of pass i, at saved + i * saved_stride (floats), is read instead
+    size_t       saved_stride;
     float       *partial;      // optional: one dL/dlam term per plane (all passes summed)
     int32_t      planes, H, W, sweeps;
     uint32_t     stream;       // tensors too large to stay in cache: non-temporal accesses
 };                             // (IO16 kernels: g_up and gy point to bf16 bit patterns)
+
+// Row masks: what the reverse sweep reads of a pass on planes with both sides of 33-64 samples, 16 bytes a row where its output
+// takes 132-256.  Bit k of .x (low) and .y (high): the row jumps behind sample k < n - 1; of .z and .w: it rises
+// there.
+__device__ __forceinline__ uint64_t mask64(uint32_t lo, uint32_t hi) { return (uint64_t)hi << 32 | lo; }
 
 // Bit k of a row's segment code: x = jump bits, y = direction bits.
 template <int K>
@@ -300,8 +306,9 @@ struct Small2dFwdParams {
     float       *saved;        // output of pass i at saved + i * saved_stride (floats)
     size_t       saved_stride;
     uint32_t     keep_passes;  // planes of at most 32 x 32: 0 = write the codes only, not the pass outputs
-    uint2       *codes;        // as in Small2dBwdParams
+    uint2       *codes;        // as in Small2dBwdParams (sides of 33-64: null where the pass outputs are kept)
     size_t       code_stride;
+    uint32_t    *tag;          // sides of 33-64: receives whether codes were written
     const float *lam;          // plane p uses lam[p % lam_count]
     int64_t      lam_count;
     int32_t      planes, H, W, sweeps;

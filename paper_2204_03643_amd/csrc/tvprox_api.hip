@@ -1318,6 +1318,17 @@ static ChunkCodes chunk_codes_2d(char *base, int64_t planes, int64_t H, int64_t 
     return cc;
 }
 
+// Planes with both sides of 33-64 samples: the one-launch forward kernels leave row masks (tv_small2d.hpp) in place of pass
+// outputs, from the start of the workspace on (16 bytes a row where a pass output has 33 floats at least), unless
+// fused_keeps_passes asks for those; the word at the same place as above says which it is.  Pass by pass,
+// such planes leave pass outputs.
+static bool row_masks_2d(int64_t H, int64_t W) { return H > 32 && W > 32 && H <= 64 && W <= 64; }
+static size_t row_mask_bytes_2d(int64_t planes, int64_t H, int64_t W) { return (size_t)(planes * (H > W ? H : W)) * 16; }
+static uint32_t *row_mask_tag(char *base, int64_t planes, int64_t H, int64_t W, int sweeps)
+{
+    return (uint32_t *)(base + tv2d_workspace_bytes(planes, H, W, sweeps) - 16);
+}
+
 // Planes of 33-64 samples a side that the kernels with two lanes a row take in one launch: those whose shorter
 // side fills at least four fifths of what the longer one's lanes and registers are laid out for (2C = 40, 48,
 // 56 or 64).  4096 planes, K = 3, against pass by pass: 40 x 56 406 / 327 us, 64 x 40, K = 1 202 / 127.
@@ -1328,37 +1339,42 @@ static bool pairs_2d_apply(int64_t H, int64_t W)
 }
 
 // The forward call on these.  Time goes in rounds of 1024 planes (two waves a plane, four planes a CU), and what a
-// plane lacks of its square is worked on all the same, so there are three ranges (measurements: tv_dispatch.hpp):
-// squares with two sweeps or more; sides of at most 48 in the first round, where the other choice is a plane
-// per workgroup at its second or third plane a CU; and large batches whose rows start on no 16-byte boundary,
-// which the pass-by-pass kernels read word by word, from a number of sweeps on.
+// plane lacks of its square is worked on all the same, so an early second round is left to the other kernel where
+// that is much (measurements: tv_dispatch.hpp).  One sweep: squares in the first round.
 static bool pairs_2d_fwd(int64_t planes, int64_t H, int64_t W, int sweeps)
 {
     if (!pairs_2d_apply(H, W)) return false;
-    const int64_t longer = H > W ? H : W, many = tvd::get(tvd::kPair2dManyPlanes);
-    const int64_t group_most = tvd::get(tvd::kPlanePerGroup64PlanesK2);
-    const bool square = H == W && H % 8 == 0;
-    if (square && sweeps >= 2) {
-        const int64_t most = tvd::get(sweeps == 2 ? tvd::kPlanePerGroup64FullPlanesK2
-                                                  : (sweeps <= 4 ? tvd::kPlanePerGroup64FullPlanesK3 : tvd::kPlanePerGroup64FullPlanesK5));
-        return planes > most && (sweeps >= 3 || longer <= 48 || planes <= group_most || planes >= many);
-    }
-    const int64_t first_round = sweeps >= 2 ? group_most : (square ? 1024 : 0);
-    if (longer <= 48 && planes > tvd::get(tvd::kPair2dPlanes) && planes <= first_round) return true;
-    return W % 4 != 0 && planes >= many && sweeps >= (longer <= 48 ? 6 : longer <= 56 ? 4 : 3);
+    const int64_t longer = H > W ? H : W, group_most = tvd::get(tvd::kPlanePerGroup64PlanesK2);
+    const bool square = H == W && H % 8 == 0, beyond = planes > tvd::get(tvd::kPair2dPlanes);
+    if (sweeps == 1) return beyond && planes <= 1024 && square;
+    if (square)
+        return planes > tvd::get(sweeps == 2 ? tvd::kPlanePerGroup64FullPlanesK2
+                                             : (sweeps <= 4 ? tvd::kPlanePerGroup64FullPlanesK3 : tvd::kPlanePerGroup64FullPlanesK5));
+    if (!row_masks_2d(H, W)) return beyond && planes <= group_most;         // (one side of 32: pass outputs, not masks)
+    if (longer <= 48) return beyond;
+    if (longer <= 56) return beyond && (planes <= 1024 || planes > group_most);
+    return planes > tvd::get(tvd::kPair2dManyPlanes);
 }
 
-// The reverse sweep of these, in one launch with two lanes a row (rows move in 16-byte pieces), beyond the
-// counts up to which a plane per workgroup is faster; the measurements are in tv_dispatch.hpp.  Planes that
-// do not fill their square pay for the samples past their ends: with one sweep, or with sides beyond 56,
-// they stay out where a second or third round of 1024 planes (four a CU) is mostly empty.  (This rule against the
-// one before two lanes a row, 18 sizes with such rows, 1, 2, 3, 4 and 10 sweeps, 256-16 384 planes: never slower by more than 3 %.)
-static bool pairs_2d_bwd(int64_t planes, int64_t H, int64_t W, int sweeps)
+// The reverse sweep of these, in one launch with two lanes a row, beyond the counts up to which a plane per workgroup is
+// faster; the measurements are in tv_dispatch.hpp.  masks: the forward call is one that leaves row masks; the
+// plane per workgroup then reads next to nothing, and what a plane lacks of its square or a late round of it lacks of
+// 1024 planes decides.  With pass outputs, planes that do not fill their square stay out, with one sweep or sides beyond 56,
+// where a second or third round is mostly empty, and with one sweep and ragged rows where they fill less than four
+// fifths of it.
+static bool pairs_2d_bwd(int64_t planes, int64_t H, int64_t W, int sweeps, bool masks)
 {
-    if (!pairs_2d_apply(H, W) || W % 4 != 0) return false;
-    const int64_t most = tvd::get(tvd::kPlanePerGroup64BwdPlanes), longer = H > W ? H : W;
-    if (H == W && H % 8 == 0) return planes > most;
+    if (!pairs_2d_apply(H, W)) return false;
+    const int64_t most = tvd::get(tvd::kPlanePerGroup64BwdPlanes), longer = H > W ? H : W, side = (longer + 7) / 8 * 8;
+    const bool square = H == W && H % 8 == 0;
+    if (masks) {
+        if (longer <= 48) return planes > most;
+        if (longer > 56 && !square) return false;
+        return planes > most + (longer <= 56 ? most / 4 : 3 * (most / 8)) && (planes <= 1024 || planes > 2048);
+    }
+    if (square) return planes > most;
     if (longer <= 56 && sweeps >= 2) return planes > most;
+    if (sweeps == 1 && W % 4 != 0 && 5 * H * W < 4 * side * side) return false;
     return planes > (longer <= 56 ? most : most + most / 2) && (planes <= 1024 || planes >= 3072);
 }
 
@@ -1374,7 +1390,17 @@ static bool plane_per_group_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
         return small_side(H, W) == 32 && planes <= most + (oblong ? 3 * (most / 4) : sweeps == 1 ? 0 : most / 3);
     }
     if (H > 64 || W > 64 || pairs_2d_fwd(planes, H, W, sweeps)) return false;
-    return planes <= tvd::get(sweeps == 1 ? tvd::kPlanePerGroup64Planes : tvd::kPlanePerGroup64PlanesK2);
+    const int64_t most = tvd::get(sweeps == 1 ? tvd::kPlanePerGroup64Planes : tvd::kPlanePerGroup64PlanesK2);
+    // (up to where two lanes a row take over from it: the others would pay a launch a pass)
+    const bool far = sweeps >= 2 && pairs_2d_apply(H, W) && row_masks_2d(H, W) && (H > 56 || W > 56);
+    return planes <= (far ? most + 3 * (most / 5) : most);
+}
+
+// Whether a forward call on such planes leaves row masks.
+static bool leaves_row_masks_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
+{
+    return row_masks_2d(H, W) && tvd::get(tvd::kFusedKeepsPasses) == 0 &&
+           (plane_per_group_2d(planes, H, W, sweeps) || pairs_2d_fwd(planes, H, W, sweeps));
 }
 
 // Whether all passes of the forward call on planes of at most 32 x 32 go in one launch: the plane counts,
@@ -1418,11 +1444,16 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
     const tv_lambda lrow = {lam.lam, lam.count, H};
     const tv_lambda lcol = {lam.lam, lam.count, W};
 
+    const bool masks = row_masks_2d(H, W);
+    uint2 *mask_codes = masks && tvd::get(tvd::kFusedKeepsPasses) == 0 ? (uint2 *)base : nullptr;
+    const size_t mask_stride = row_mask_bytes_2d(planes, H, W) / sizeof(uint2);
+    uint32_t *mask_tag = masks ? row_mask_tag(base, planes, H, W, sweeps) : nullptr;
     if (plane_per_group_2d(planes, H, W, sweeps)) {
         // a small batch of planes of 17-64 samples a side: one launch, a plane per workgroup
         tvk::Small2dFwdParams q;
         q.y = y; q.x = x; q.saved = saved(0); q.saved_stride = tb / sizeof(float); q.keep_passes = tvd::get(tvd::kFusedKeepsPasses) != 0 ? 1u : 0u;
-        q.codes = codes(0); q.code_stride = cb / sizeof(uint2);
+        q.codes = codes(0); q.code_stride = cb / sizeof(uint2); q.tag = nullptr;
+        if (masks) { q.codes = mask_codes; q.code_stride = mask_stride; q.tag = mask_tag; }
         q.lam = lam.lam; q.lam_count = lam.count;
         q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
         q.stream = 0u;
@@ -1435,7 +1466,7 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
         // planes of at most 32 x 32: all passes in one launch, the planes resident in LDS
         tvk::Small2dFwdParams q;
         q.y = y; q.x = x; q.saved = saved(0); q.saved_stride = tb / sizeof(float); q.keep_passes = tvd::get(tvd::kFusedKeepsPasses) != 0 ? 1u : 0u;
-        q.codes = codes(0); q.code_stride = cb / sizeof(uint2);
+        q.codes = codes(0); q.code_stride = cb / sizeof(uint2); q.tag = nullptr;
         q.lam = lam.lam; q.lam_count = lam.count;
         q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
         q.stream = (planes * H * W >= tvd::get(tvd::kStreamBytes) / 4) ? 1u : 0u;
@@ -1451,7 +1482,7 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
         // planes of 33-64 samples a side: the same
         tvk::Small2dFwdParams q;
         q.y = y; q.x = x; q.saved = saved(0); q.saved_stride = tb / sizeof(float); q.keep_passes = 1u;
-        q.codes = nullptr; q.code_stride = 0;
+        q.codes = mask_codes; q.code_stride = mask_stride; q.tag = mask_tag;
         q.lam = lam.lam; q.lam_count = lam.count;
         q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
         q.stream = (planes * H * W >= tvd::get(tvd::kStreamBytes) / 4) ? 1u : 0u;
@@ -1463,7 +1494,7 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
     const bool tri = lam.count == 1 && sweeps >= 3 && longest > 64 && longest <= 768 &&
                      longest <= tvd::get(tvd::kOneLambdaTriSide);
     const ChunkCodes cc = chunk_codes_2d(base, planes, H, W, sweeps, tb, tv2d_workspace_bytes(planes, H, W, sweeps));
-    uint32_t *tag = cc.stride ? cc.tag : nullptr;
+    uint32_t *tag = cc.stride ? cc.tag : mask_tag;
     const bool lean = cc.stride && tvd::get(tvd::kFusedKeepsPasses) == 0 &&
                       tb * (size_t)(2 * sweeps + 2) >= (size_t)tvd::get(tvd::kChunkCodesBytes);
     char *outputs = base + 2 * (size_t)sweeps * cc.stride;               // (lean: the two tensors behind the codes)
@@ -1512,7 +1543,7 @@ int tv2d_prox_fwd_bf16(const uint16_t *y, uint16_t *x, int64_t planes, int64_t H
     q.y = reinterpret_cast<const float *>(y); q.x = reinterpret_cast<float *>(x);
     q.saved = (float *)base; q.saved_stride = tb / sizeof(float); q.keep_passes = tvd::get(tvd::kFusedKeepsPasses) != 0 ? 1u : 0u;
     q.codes = (uint2 *)(base + tb * (size_t)(2 * sweeps + 2) + pb * (size_t)(2 * sweeps));
-    q.code_stride = cb / sizeof(uint2);
+    q.code_stride = cb / sizeof(uint2); q.tag = nullptr;
     q.lam = lam.lam; q.lam_count = lam.count;
     q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
     q.stream = (planes * H * W >= tvd::get(tvd::kStreamBytes) / 4) ? 1u : 0u;
@@ -1541,7 +1572,7 @@ int tv2d_prox_bwd_bf16(const uint16_t *g_up, uint16_t *grad_y, float *grad_lam, 
     tvk::Small2dBwdParams q;
     q.g_up = reinterpret_cast<const float *>(g_up); q.gy = reinterpret_cast<float *>(grad_y);
     q.codes = (const uint2 *)(base + tb * (size_t)(2 * sweeps + 2) + pb * (size_t)(2 * sweeps));
-    q.code_stride = cb / sizeof(uint2);
+    q.code_stride = cb / sizeof(uint2); q.tag = nullptr;
     q.saved = (const float *)base; q.saved_stride = tb / sizeof(float);
     q.partial = grad_lam ? partial : nullptr;
     q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
@@ -1591,13 +1622,19 @@ int tv2d_prox_bwd(const float *g_up, float *grad_y, float *grad_lam, int64_t pla
     //   Bbar = Qbar' + C^T(Ybar' - Qbar'),   Qbar = Bbar,
     //   Abar = Pbar' + R^T(Bbar - Pbar'),    Ybar = Pbar = Abar.
     // Ybar and Pbar coincide from the second reverse step on, so two tensors carry the state.
+    // (which of the two the workspace holds is found out on the device; what a forward call would leave now picks the mapping)
+    const bool masks = row_masks_2d(H, W), expect_masks = leaves_row_masks_2d(planes, H, W, sweeps);
+    const uint2 *mask_codes = masks ? (const uint2 *)base : nullptr;
+    const size_t mask_stride = row_mask_bytes_2d(planes, H, W) / sizeof(uint2);
+    const uint32_t *mask_tag = masks ? row_mask_tag(base, planes, H, W, sweeps) : nullptr;
     if ((cb && small_side(H, W) == 32 && planes <= tvd::get(tvd::kPlanePerGroupBwdPlanes)) ||
         (!cb && H <= 64 && W <= 64 &&
-         !pairs_2d_bwd(planes, H, W, sweeps) &&
-         planes <= tvd::get(sweeps == 1 ? tvd::kPlanePerGroup64BwdRaggedPlanes : tvd::kPlanePerGroup64BwdRaggedPlanesK2))) {
+         !pairs_2d_bwd(planes, H, W, sweeps, expect_masks) &&
+         (expect_masks || planes <= tvd::get(sweeps == 1 ? tvd::kPlanePerGroup64BwdRaggedPlanes : tvd::kPlanePerGroup64BwdRaggedPlanesK2)))) {
         // a small batch of planes of 17-64 samples a side: one launch, a plane per workgroup
         tvk::Small2dBwdParams q;
-        q.g_up = g_up; q.gy = grad_y; q.codes = codes(0); q.code_stride = cb / sizeof(uint2);
+        q.g_up = g_up; q.gy = grad_y; q.codes = codes(0); q.code_stride = cb / sizeof(uint2); q.tag = nullptr;
+        if (masks) { q.codes = mask_codes; q.code_stride = mask_stride; q.tag = mask_tag; }
         q.saved = saved(0); q.saved_stride = tb / sizeof(float);
         q.partial = grad_lam ? partial(0) : nullptr;
         q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
@@ -1610,10 +1647,10 @@ int tv2d_prox_bwd(const float *g_up, float *grad_y, float *grad_lam, int64_t pla
         const tv_lambda lp = {lam.lam, lam.count, 1};
         return launch_reduce_lambda(partial(0), grad_lam, planes, lp, 0, stream);
     }
-    if (!cb && pairs_2d_bwd(planes, H, W, sweeps)) {
+    if (!cb && pairs_2d_bwd(planes, H, W, sweeps, expect_masks)) {
         // planes of 33-64 samples a side: the same, two lanes a row
         tvk::Small2dBwdParams q;
-        q.g_up = g_up; q.gy = grad_y; q.codes = nullptr; q.code_stride = 0;
+        q.g_up = g_up; q.gy = grad_y; q.codes = mask_codes; q.code_stride = mask_stride; q.tag = mask_tag;
         q.saved = saved(0); q.saved_stride = tb / sizeof(float);
         q.partial = grad_lam ? partial(0) : nullptr;
         q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
@@ -1626,7 +1663,7 @@ int tv2d_prox_bwd(const float *g_up, float *grad_y, float *grad_lam, int64_t pla
     if (cb) {
         // planes of at most 32 x 32: the whole reverse sweep in one launch, state resident in LDS
         tvk::Small2dBwdParams q;
-        q.g_up = g_up; q.gy = grad_y; q.codes = codes(0); q.code_stride = cb / sizeof(uint2);
+        q.g_up = g_up; q.gy = grad_y; q.codes = codes(0); q.code_stride = cb / sizeof(uint2); q.tag = nullptr;
         q.saved = saved(0); q.saved_stride = tb / sizeof(float);
         q.partial = grad_lam ? partial(0) : nullptr;
         q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
@@ -1639,8 +1676,9 @@ int tv2d_prox_bwd(const float *g_up, float *grad_y, float *grad_lam, int64_t pla
     }
     const ChunkCodes cc = chunk_codes_2d(base, planes, H, W, sweeps, tb, tv2d_workspace_bytes(planes, H, W, sweeps));
     const bool codes_or_passes = cc.stride && tb * (size_t)(2 * sweeps + 2) >= (size_t)tvd::chunk_codes_lowest;
-    const uint32_t *tag = codes_or_passes ? cc.tag : nullptr;
-    auto pass_codes = [&](int pass) { return tag ? (const uint32_t *)(base + cc.stride * (size_t)pass) : nullptr; };
+    const uint32_t *tag = codes_or_passes ? cc.tag : mask_tag;
+    const size_t code_bytes = masks ? mask_stride * sizeof(uint2) : cc.stride;
+    auto pass_codes = [&](int pass) { return tag ? (const uint32_t *)(base + code_bytes * (size_t)pass) : nullptr; };
     for (int k = sweeps - 1; k >= 0; --k) {
         const bool first = (k == sweeps - 1);
         st = run_bwd(first ? g_up : Ab, first ? nullptr : Bb, cb ? nullptr : saved(2 * k + 1), codes(2 * k + 1),

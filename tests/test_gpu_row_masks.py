@@ -1,0 +1,85 @@
+"""Planes with both sides of 33-64 samples: the reverse sweep from row masks has the bits it has from pass outputs, whichever
+mappings wrote and read them, and finds out by itself which of the two a workspace holds."""
+import itertools
+
+import numpy as np
+import pytest
+
+from gpuutil import run_2d
+
+pytestmark = pytest.mark.gpu
+
+KNOBS = ("plane_per_group64_planes", "plane_per_group64_planes_k2", "plane_per_group64_full_planes_k2",
+         "plane_per_group64_full_planes_k3", "plane_per_group64_full_planes_k5", "pair_2d_planes", "pair_2d_many_planes",
+         "plane_per_group64_bwd_planes", "plane_per_group64_bwd_ragged_planes", "plane_per_group64_bwd_ragged_planes_k2",
+         "fused_keeps_passes")
+
+
+@pytest.fixture
+def overrides():
+    import paper_2204_03643_amd as tv
+    saved = {k: tv.tv_dispatch_threshold(k) for k in KNOBS}
+
+    def set_to(**values):
+        for name, value in values.items():
+            tv.tv_dispatch_override(name, value)
+    yield set_to
+    for name, value in saved.items():
+        tv.tv_dispatch_override(name, value)
+
+
+def _case(H, W, n=5):
+    rng = np.random.default_rng(100 * H + W)
+    y = np.round(rng.normal(size=(n, H, W)), 1).astype(np.float32)
+    return y, (10 ** rng.uniform(-2, 0.5, size=3)).astype(np.float32), rng.normal(size=y.shape).astype(np.float32)
+
+
+SIDES = [(33, 33), (33, 40), (40, 40), (41, 48), (47, 41), (48, 48), (49, 55), (56, 56), (57, 64), (63, 58), (64, 64)]
+
+
+@pytest.mark.parametrize("mapping", ["pairs", "planes"])
+@pytest.mark.parametrize("H,W", SIDES + [(33, 64), (64, 36)])
+def test_masks_and_passes(H, W, mapping, overrides):
+    big = 1 << 40
+    pairs, group = (0, big) if mapping == "pairs" else (big, big)
+    overrides(plane_per_group64_planes=group, plane_per_group64_planes_k2=group, plane_per_group64_full_planes_k2=pairs,
+              plane_per_group64_full_planes_k3=pairs, pair_2d_planes=pairs, pair_2d_many_planes=pairs)
+    y, lam, g = _case(H, W)
+    for K in (1, 2, 3):
+        kept = run_2d(y, lam, K, g, keep_passes=True)
+        lean = run_2d(y, lam, K, g, keep_passes=False)
+        for k in ("x", "gy", "gl"):
+            assert np.isfinite(kept[k]).all()
+            if k == "x":
+                assert np.array_equal(kept[k], lean[k]), (K, k)
+            else:                               # (the mapping of the reverse sweep may be another one)
+                assert np.abs(kept[k] - lean[k]).max() <= 2e-5 * (1 + np.abs(kept[k]).max()), (K, k)
+
+
+@pytest.mark.parametrize("H,W", SIDES)
+def test_every_writer_with_every_reader(H, W, overrides):
+    import torch
+
+    import paper_2204_03643_amd as tv
+    big, K = 1 << 40, 2
+    y, lam, g = _case(H, W, 3)
+    yt, lt, gt = (torch.from_numpy(a).cuda() for a in (y, lam, g))
+    L = tv.tv_lambda(lt.data_ptr(), 3, 1)
+    wsb = tv.tv2d_workspace_bytes(3, H, W, K)
+    ws = torch.full((wsb,), 0xff, dtype=torch.uint8, device="cuda")     # one workspace for all: nothing stale may be believed
+    first = {}
+    for writer, keep, reader in itertools.product(("pairs", "planes", "passes"), (0, 1), ("pairs", "planes", "passes")):
+        group, pairs = {"pairs": (big, 0), "planes": (big, big), "passes": (0, big)}[writer]
+        overrides(fused_keeps_passes=keep, plane_per_group64_planes_k2=group, plane_per_group64_full_planes_k2=pairs,
+                  pair_2d_planes=pairs, pair_2d_many_planes=pairs)
+        x, gy, gl = torch.empty_like(yt), torch.empty_like(yt), torch.empty_like(lt)
+        tv.tv2d_prox_fwd(yt, x, 3, H, W, L, K, ws, wsb)
+        # another route by the time of the reverse sweep, so that it looks for the other thing
+        overrides(fused_keeps_passes=1, plane_per_group64_bwd_planes=0 if reader == "pairs" else big,
+                  plane_per_group64_bwd_ragged_planes_k2=big if reader == "planes" else 0)
+        tv.tv2d_prox_bwd(gt, gy, gl, 3, H, W, L, K, ws, wsb)
+        want = first.setdefault(writer, (x, gy, gl))
+        assert torch.equal(x, want[0])
+        for a, b in zip((gy, gl), want[1:]):
+            assert torch.isfinite(a).all()
+            assert (a - b).abs().max() <= 2e-5 * (1 + b.abs().max()), (writer, keep, reader)
