@@ -36,11 +36,11 @@ __device__ __forceinline__ float mean_of(float s, float n)
 // columns 21.6; 768, no sub, 64 threads of 12 samples 19.8, 32 threads of 24 and 32 columns 23.8).
 // HAS_SUB: p.sub is given (the reverse sweep of the 2D operator).  CODES: where the forward pass left chunk codes
 // (p.codes_tag says whether it did) they are read, not x: CW words of C / CW samples a thread, in the forward kernel's
-// order (word t of its row); row masks where columns have 33-64 samples.
+// order (word t of its row); CW = -2: a word for two threads; row masks where columns have 33-64 samples.
 template <int T, int C, int G, int CW, bool HAS_SUB, bool CODES>
 __global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
 {
-    static_assert(T <= 64 && C <= 32 && C % CW == 0 && G <= 64, "a column's threads inside one wave when exchanged");
+    static_assert(T <= 64 && C <= 32 && (CW == -2 || C % CW == 0) && G <= 64, "a column's threads inside one wave when exchanged");
     using Rw = RowWave<T, G, false>;
     constexpr int P = G + 1;                     // (both [t][column] accesses are then free of bank conflicts)
     __shared__ float first[T * P], last[T * P];  // sums of the pieces, then the two means
@@ -78,6 +78,10 @@ __global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
     if (CODES && coded) {
         if constexpr (row_masked<T, C>()) {
             mask_bits<C>(p.chunk_codes, arow, k0, jmask, upmask);
+        } else if constexpr (CW == -2) {
+            const uint32_t code = p.chunk_codes[(size_t)arow * (T / 2) + t / 2] >> (t & 1) * 2 * C;
+            jmask = even_bits(code) & ((1u << C) - 1u);
+            upmask = even_bits(code >> 1) & ((1u << C) - 1u);
         } else {
             const uint32_t *words = p.chunk_codes + ((size_t)arow * T + t) * CW;
 #pragma unroll
@@ -212,15 +216,15 @@ inline uint32_t bwd_cols_near_lg(const BwdParams &p, uint32_t groups)
 
 // Strided rows that go this way; and the columns of a workgroup, whose dL/dlam terms can leave as one.
 inline bool bwd_cols_apply(int64_t n, int64_t elem_stride) { return n > 32 && n <= 1024 && elem_stride != 1; }
-inline int bwd_cols_group_lg(int64_t n) { return n <= 256 ? 5 : 4; }
+// (16 of them at least, 32 in larger calls on shorter columns; groups of 16 leave as one in both.)
+constexpr int kBwdColsGroupLg = 4;
 
-template <int T, int C, int CW>
+template <int T, int C, int CW, int G = (T <= 16 ? 32 : 16)>
 inline hipError_t launch_bwd_cols_t(BwdParams p, hipStream_t s)
 {
-    constexpr int G = T <= 16 ? 32 : 16;
     const dim3 grid((p.L.n_rows + G - 1) / G), block(T * G);
     p.near_lg = bwd_cols_near_lg<G>(p, grid.x);
-    if constexpr (CW > 0) {
+    if constexpr (CW != 0) {
         if (p.chunk_codes) {
             if (p.sub) hipLaunchKernelGGL((tv1d_bwd_cols_kernel<T, C, G, CW, true, true>), grid, block, 0, s, p);
             else hipLaunchKernelGGL((tv1d_bwd_cols_kernel<T, C, G, CW, false, true>), grid, block, 0, s, p);
@@ -232,10 +236,20 @@ inline hipError_t launch_bwd_cols_t(BwdParams p, hipStream_t s)
     return hipGetLastError();
 }
 
-// CW: the words of chunk_threads(n) that a thread's C samples are (1 where it reads a row mask), 0 where there are none.
+// CW: the words of chunk_threads(n) that a thread's C samples are (1 where it reads a row mask, -2 for half a word), 0 where there are none.
 inline hipError_t launch_bwd_cols(const BwdParams &p, hipStream_t s)
 {
     const int n = p.L.n;
+    // Few columns: half the samples a thread and groups of 16, for shorter chains and more workgroups (3 planes of
+    // 166 x 200 6.0 -> 4.8 us, with sub 6.5 -> 5.1; 20 of 128 x 128 4.9 -> 4.1; 120 of 120 x 120, 14 400 columns, 7.4 -> 6.7;
+    // 40 of 256 x 256 8.1 -> 7.5).
+    if (p.L.n_rows <= 16384) {
+        if (n <= 64) return launch_bwd_cols_t<16, 4, 1, 16>(p, s);
+        if (n <= 96) return launch_bwd_cols_t<16, 6, -2, 16>(p, s);
+        if (n <= 128) return launch_bwd_cols_t<16, 8, 1, 16>(p, s);
+        if (n <= 192) return launch_bwd_cols_t<32, 6, -2, 16>(p, s);
+        if (n <= 256) return launch_bwd_cols_t<32, 8, 1, 16>(p, s);
+    }
     if (n <= 64) return launch_bwd_cols_t<4, 16, 1>(p, s);
     if (n <= 96) return launch_bwd_cols_t<8, 12, 1>(p, s);
     if (n <= 128) return launch_bwd_cols_t<8, 16, 2>(p, s);

@@ -873,7 +873,7 @@ PartialShape partial_shape(const tv_rows &r, const tv_lambda &l, int64_t n_rows)
 {
     PartialShape ps = {0, n_rows, l.div};
     const bool cols = tvk::bwd_cols_apply(r.length, r.elem_stride);
-    const uint32_t most = r.length <= 32 ? 6u : cols ? (uint32_t)tvk::bwd_cols_group_lg(r.length) : 0u;
+    const uint32_t most = r.length <= 32 ? 6u : cols ? (uint32_t)tvk::kBwdColsGroupLg : 0u;
     uint32_t lg = 0;
     while (lg < most && (l.count == 1 || l.div % ((int64_t)2 << lg) == 0)) ++lg;
     if (most) {
