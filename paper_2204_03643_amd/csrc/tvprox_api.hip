@@ -735,57 +735,64 @@ int run_fwd(const float *y, const float *addend, float *x, float *resid, int32_t
     return tvk::launch_fwd_long(p, s) == hipSuccess ? TV_OK : TV_ERR_HIP;
 }
 
-// Sums the per-row dL/dlam contributions of every slot: one workgroup per slot, fp64
-// accumulation in a fixed order (deterministic).  Four independent loads are kept in
-// flight per thread; the walk over the slot's rows needs no division.  `batches` arrays of the
+// Sums the per-row dL/dlam contributions of every slot: T threads a slot (a workgroup of its own from 256 on), fp64
+// accumulation in a fixed order (deterministic).  The threads are chosen such that a slot takes the time of one
+// trip to memory or a few (1024 planes, 64 slots: 16 threads a slot take 5 us less than one that waits for each load), and
+// several independent loads are kept in flight; the walk over the slot's rows needs no division.  `batches` arrays of the
 // same shape, `batch_stride` floats apart, are summed together (the passes of a 2D reverse
 // sweep).  With few slots and many batches the work of a slot is split over gridDim.y
 // workgroups (workgroup j takes batches j, j + gridDim.y, ...), each leaving its fp64 sum in
 // `split_out[slot * gridDim.y + j]` for sum_splits_kernel.
-template <int kReduceThreads>
-__global__ __launch_bounds__(kReduceThreads) void reduce_lambda_kernel(
+template <int T>
+__global__ __launch_bounds__(T < 256 ? 256 : T) void reduce_lambda_kernel(
     const float *__restrict__ partial, float *__restrict__ grad_lam, uint32_t n_rows,
     uint32_t count, uint32_t div, int accumulate, uint32_t batches, uint64_t batch_stride,
     double *__restrict__ split_out)
 {
-    __shared__ double red[kReduceThreads];
-    const uint32_t slot = blockIdx.x;
+    constexpr int SLOTS = T < 256 ? 256 / T : 1, LOADS = T < 256 ? 2 : 4, WAVES = T / 64;
+    const uint32_t slot = blockIdx.x * SLOTS + threadIdx.x / T, t = threadIdx.x % T;
     // rows of this slot: r = (q*count + slot)*div + i,  i < div,  q = 0, 1, ...
     // thread t visits the pairs (q, i) with q*div + i = t, t + T, t + 2T, ...
-    const uint32_t dq = kReduceThreads / div, di = kReduceThreads - dq * div;
-    const uint64_t stride = (uint64_t)count * div;
-    const uint64_t base = (uint64_t)slot * div;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    const uint32_t dq = T / div, di = T - dq * div;
+    const uint64_t stride = (uint64_t)count * div, hop = dq * stride;
+    double acc[LOADS] = {};
     partial += blockIdx.y * batch_stride;
     for (uint32_t b = blockIdx.y; b < batches; b += gridDim.y, partial += gridDim.y * batch_stride) {
-        uint32_t q = threadIdx.x / div, i = threadIdx.x - q * div;
-        bool more = true;
+        const uint32_t q = t / div;
+        uint32_t i = t - q * div;
+        uint64_t g0 = q * stride + (uint64_t)slot * div;            // where the group of row i starts
+        bool more = slot < count;
         while (more) {
-            float v[4];
+            float v[LOADS];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                // group starts grow with q: once a group starts past the end, nothing follows
-                const uint64_t g0 = q * stride + base;
+            for (int j = 0; j < LOADS; ++j) {
+                // group starts grow: once a group starts past the end, nothing follows
                 more = more && (g0 < n_rows);
                 v[j] = (more && g0 + i < n_rows) ? partial[g0 + i] : 0.f;
-                q += dq; i += di;
-                if (i >= div) { i -= div; q += 1; }
+                g0 += hop; i += di;
+                if (i >= div) { i -= div; g0 += stride; }
             }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[j] += (double)v[j];
+            for (int j = 0; j < LOADS; ++j) acc[j] += (double)v[j];
         }
     }
-    red[threadIdx.x] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-    __syncthreads();
-    for (int w = kReduceThreads / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    double sum = acc[0] + acc[1];
+    if constexpr (LOADS == 4) sum += acc[2] + acc[3];
+#pragma unroll
+    for (int d = 1; d < T && d < 64; d <<= 1) sum += __shfl_xor(sum, d);
+    if constexpr (WAVES > 1) {
+        __shared__ double red[WAVES];
+        if ((t & 63) == 0) red[t >> 6] = sum;
         __syncthreads();
+        sum = 0.0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) sum += red[w];
     }
-    if (threadIdx.x == 0) {
+    if (t == 0 && slot < count) {
         if (split_out) {
-            split_out[slot * gridDim.y + blockIdx.y] = red[0];
+            split_out[slot * gridDim.y + blockIdx.y] = sum;
         } else {
-            const float v = (float)red[0];
+            const float v = (float)sum;
             grad_lam[slot] = accumulate ? grad_lam[slot] + v : v;
         }
     }
@@ -805,22 +812,6 @@ __global__ __launch_bounds__(64) void sum_splits_kernel(const double *__restrict
     grad_lam[slot] = (float)acc;
 }
 
-// Slots that own only a handful of rows (e.g. one lambda per row): one thread per slot.
-__global__ __launch_bounds__(256) void reduce_lambda_small_kernel(
-    const float *__restrict__ partial, float *__restrict__ grad_lam, uint32_t n_rows,
-    uint32_t count, uint32_t div, int accumulate, uint32_t batches, uint64_t batch_stride)
-{
-    const uint32_t slot = blockIdx.x * 256 + threadIdx.x;
-    if (slot >= count) return;
-    const uint64_t stride = (uint64_t)count * div;
-    double acc = 0.0;
-    for (uint32_t b = 0; b < batches; ++b, partial += batch_stride)
-        for (uint64_t g0 = (uint64_t)slot * div; g0 < n_rows; g0 += stride)
-            for (uint32_t i = 0; i < div && g0 + i < n_rows; ++i) acc += (double)partial[g0 + i];
-    const float v = (float)acc;
-    grad_lam[slot] = accumulate ? grad_lam[slot] + v : v;
-}
-
 // The split reduction applies below this many slots (more slots fill the chip by themselves) ...
 constexpr uint32_t kSplitMaxSlots = 64;
 // ... and uses at most this many workgroups per slot and direction.
@@ -833,8 +824,7 @@ uint32_t reduce_splits(int64_t count, int sweeps)
     return (uint32_t)sweeps < kSplitMax ? (uint32_t)sweeps : kSplitMax;
 }
 
-// splits > 1: workgroup (slot, j) leaves its fp64 sum in split_out[slot * splits + j]; the rows of
-// a slot must then be many enough for the workgroup-per-slot kernel.
+// splits > 1: workgroup (slot, j) leaves its fp64 sum in split_out[slot * splits + j].
 int launch_reduce_lambda(const float *partial, float *grad_lam, int64_t n_rows, const tv_lambda &l,
                          int accumulate, hipStream_t s, uint32_t batches = 1, uint64_t batch_stride = 0,
                          uint32_t splits = 1, double *split_out = nullptr)
@@ -842,22 +832,17 @@ int launch_reduce_lambda(const float *partial, float *grad_lam, int64_t n_rows, 
     const uint32_t count = (uint32_t)l.count, div = (uint32_t)l.div, nr = (uint32_t)n_rows;
     const uint64_t groups = ((uint64_t)nr + div - 1) / div;
     const uint64_t rows_per_slot = ((groups + count - 1) / count) * div * ((batches + splits - 1) / splits);
-    if (splits > 1) {
-        if (rows_per_slot <= 2048)
-            hipLaunchKernelGGL(reduce_lambda_kernel<256>, dim3(count, splits), dim3(256), 0, s, partial,
-                               grad_lam, nr, count, div, accumulate, batches, batch_stride, split_out);
-        else
-            hipLaunchKernelGGL(reduce_lambda_kernel<1024>, dim3(count, splits), dim3(1024), 0, s, partial,
-                               grad_lam, nr, count, div, accumulate, batches, batch_stride, split_out);
-    } else if (rows_per_slot <= 32)
-        hipLaunchKernelGGL(reduce_lambda_small_kernel, dim3((count + 255) / 256), dim3(256), 0, s,
-                           partial, grad_lam, nr, count, div, accumulate, batches, batch_stride);
-    else if (rows_per_slot <= 2048)
-        hipLaunchKernelGGL(reduce_lambda_kernel<256>, dim3(count), dim3(256), 0, s, partial, grad_lam,
-                           nr, count, div, accumulate, batches, batch_stride, (double *)nullptr);
-    else
-        hipLaunchKernelGGL(reduce_lambda_kernel<1024>, dim3(count), dim3(1024), 0, s, partial,
-                           grad_lam, nr, count, div, accumulate, batches, batch_stride, (double *)nullptr);
+    // (threads that a slot's terms keep busy for one trip to memory)
+#define TV_REDUCE(T)                                                                                                             \
+    hipLaunchKernelGGL(reduce_lambda_kernel<T>, dim3(T < 256 ? (count + 256 / T - 1) / (256 / T) : count, splits), dim3(T < 256 ? 256 : T), \
+                       0, s, partial, grad_lam, nr, count, div, accumulate, batches, batch_stride, splits > 1 ? split_out : (double *)nullptr)
+    if (rows_per_slot <= 2) TV_REDUCE(1);
+    else if (rows_per_slot <= 8) TV_REDUCE(4);
+    else if (rows_per_slot <= 32) TV_REDUCE(16);
+    else if (rows_per_slot <= 128) TV_REDUCE(64);
+    else if (rows_per_slot <= 2048) TV_REDUCE(256);
+    else TV_REDUCE(1024);
+#undef TV_REDUCE
     return launch_status();
 }
 
@@ -896,12 +881,15 @@ int run_bwd(const float *g, const float *sub, const float *x, const uint2 *seg, 
     p.chunk_codes = chunk_codes; p.codes_tag = codes_tag;
     p.io16 = io16 ? 1u : 0u;
     p.near_lg = 0;
-    p.partial = grad_lam ? partial : nullptr;
+    const PartialShape ps = partial_shape(r, l, n_rows);
+    // a lambda for every row: its term is the gradient, and nothing is left to sum (64 rows of 256, backward
+    // call: 6.0 -> 3.5 us; 250 315 of 16: 11.5 -> 8.6)
+    const bool direct = grad_lam && reduce_now && !accumulate && ps.lg == 0 && l.div == 1 && l.count == n_rows;
+    p.partial = !grad_lam ? nullptr : direct ? grad_lam : partial;
     p.L = make_layout(r, l, n_rows);
     const bool packed = rows_packed(r) && aligned16(g) && (!x || aligned16(x)) && aligned16(gy) &&
                         (!sub || aligned16(sub));
     int st;
-    const PartialShape ps = partial_shape(r, l, n_rows);
     p.part_lg = grad_lam ? ps.lg : 0;
     const int64_t red_rows = ps.red_rows, red_div = ps.red_div;
     const bool ragged = rows_packed(r);
@@ -915,7 +903,7 @@ int run_bwd(const float *g, const float *sub, const float *x, const uint2 *seg, 
     else if (tvk::bwd_cols_apply(r.length, r.elem_stride)) st = tvk::launch_bwd_cols(p, s) == hipSuccess ? TV_OK : TV_ERR_HIP;
     else st = tvk::launch_bwd_long(p, s) == hipSuccess ? TV_OK : TV_ERR_HIP;
     if (st != TV_OK) return st;
-    if (grad_lam && reduce_now) {
+    if (grad_lam && reduce_now && !direct) {
         tv_lambda lr = l;
         lr.div = red_div;
         st = launch_reduce_lambda(partial, grad_lam, red_rows, lr, accumulate, s);
@@ -1574,7 +1562,7 @@ int tv2d_prox_bwd_bf16(const uint16_t *g_up, uint16_t *grad_y, float *grad_lam, 
     q.codes = (const uint2 *)(base + tb * (size_t)(2 * sweeps + 2) + pb * (size_t)(2 * sweeps));
     q.code_stride = cb / sizeof(uint2); q.tag = nullptr;
     q.saved = (const float *)base; q.saved_stride = tb / sizeof(float);
-    q.partial = grad_lam ? partial : nullptr;
+    q.partial = !grad_lam ? nullptr : lam.count == planes ? grad_lam : partial;        // (a lambda a plane: the terms are the gradient)
     q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
     q.stream = (planes * H * W >= tvd::get(tvd::kStreamBytes) / 4) ? 1u : 0u;
     if (small_side(H, W) == 32 && planes <= tvd::get(tvd::kPlanePerGroupBwdPlanes))
@@ -1582,7 +1570,7 @@ int tv2d_prox_bwd_bf16(const uint16_t *g_up, uint16_t *grad_y, float *grad_lam, 
     else
         TV_SMALL2D_LAUNCH(tvk::tv2d_bwd_small_kernel, q, planes, H, W, stream, true);
     if (launch_status() != TV_OK) return TV_ERR_HIP;
-    if (!grad_lam) return TV_OK;
+    if (!grad_lam || lam.count == planes) return TV_OK;
     const tv_lambda lp = {lam.lam, lam.count, 1};
     return launch_reduce_lambda(partial, grad_lam, planes, lp, 0, stream);
 }
@@ -1627,6 +1615,12 @@ int tv2d_prox_bwd(const float *g_up, float *grad_y, float *grad_lam, int64_t pla
     const uint2 *mask_codes = masks ? (const uint2 *)base : nullptr;
     const size_t mask_stride = row_mask_bytes_2d(planes, H, W) / sizeof(uint2);
     const uint32_t *mask_tag = masks ? row_mask_tag(base, planes, H, W, sweeps) : nullptr;
+    // one launch: a term a plane, which is the gradient where every plane has a lambda of its own
+    float *terms = !grad_lam ? nullptr : lam.count == planes ? grad_lam : partial(0);
+    auto sum_planes = [&]() {
+        if (terms == grad_lam) return (int)TV_OK;
+        return launch_reduce_lambda(terms, grad_lam, planes, tv_lambda{lam.lam, lam.count, 1}, 0, stream);
+    };
     if ((cb && small_side(H, W) == 32 && planes <= tvd::get(tvd::kPlanePerGroupBwdPlanes)) ||
         (!cb && H <= 64 && W <= 64 &&
          !pairs_2d_bwd(planes, H, W, sweeps, expect_masks) &&
@@ -1636,43 +1630,35 @@ int tv2d_prox_bwd(const float *g_up, float *grad_y, float *grad_lam, int64_t pla
         q.g_up = g_up; q.gy = grad_y; q.codes = codes(0); q.code_stride = cb / sizeof(uint2); q.tag = nullptr;
         if (masks) { q.codes = mask_codes; q.code_stride = mask_stride; q.tag = mask_tag; }
         q.saved = saved(0); q.saved_stride = tb / sizeof(float);
-        q.partial = grad_lam ? partial(0) : nullptr;
+        q.partial = terms;
         q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
         q.stream = 0u;
         const dim3 grid((uint32_t)planes);
         if (cb) hipLaunchKernelGGL((tvk::tv2d_bwd_plane_kernel<16, 2>), grid, dim3(512), 0, stream, q);
         else hipLaunchKernelGGL((tvk::tv2d_bwd_plane_kernel<8, 8>), grid, dim3(512), 0, stream, q);
-        if (launch_status() != TV_OK) return TV_ERR_HIP;
-        if (!grad_lam) return TV_OK;
-        const tv_lambda lp = {lam.lam, lam.count, 1};
-        return launch_reduce_lambda(partial(0), grad_lam, planes, lp, 0, stream);
+        return launch_status() == TV_OK ? sum_planes() : TV_ERR_HIP;
     }
     if (!cb && pairs_2d_bwd(planes, H, W, sweeps, expect_masks)) {
         // planes of 33-64 samples a side: the same, two lanes a row
         tvk::Small2dBwdParams q;
         q.g_up = g_up; q.gy = grad_y; q.codes = mask_codes; q.code_stride = mask_stride; q.tag = mask_tag;
         q.saved = saved(0); q.saved_stride = tb / sizeof(float);
-        q.partial = grad_lam ? partial(0) : nullptr;
+        q.partial = terms;
         q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
         q.stream = 0u;
         st = launch_bwd_pairs_2d(q, stream);
-        if (st != TV_OK || !grad_lam) return st;
-        const tv_lambda lp = {lam.lam, lam.count, 1};
-        return launch_reduce_lambda(partial(0), grad_lam, planes, lp, 0, stream);
+        return st == TV_OK ? sum_planes() : st;
     }
     if (cb) {
         // planes of at most 32 x 32: the whole reverse sweep in one launch, state resident in LDS
         tvk::Small2dBwdParams q;
         q.g_up = g_up; q.gy = grad_y; q.codes = codes(0); q.code_stride = cb / sizeof(uint2); q.tag = nullptr;
         q.saved = saved(0); q.saved_stride = tb / sizeof(float);
-        q.partial = grad_lam ? partial(0) : nullptr;
+        q.partial = terms;
         q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
         q.stream = (planes * H * W >= tvd::get(tvd::kStreamBytes) / 4) ? 1u : 0u;
         TV_SMALL2D_LAUNCH(tvk::tv2d_bwd_small_kernel, q, planes, H, W, stream);
-        if (launch_status() != TV_OK) return TV_ERR_HIP;
-        if (!grad_lam) return TV_OK;
-        const tv_lambda lp = {lam.lam, lam.count, 1};
-        return launch_reduce_lambda(partial(0), grad_lam, planes, lp, 0, stream);
+        return launch_status() == TV_OK ? sum_planes() : TV_ERR_HIP;
     }
     const ChunkCodes cc = chunk_codes_2d(base, planes, H, W, sweeps, tb, tv2d_workspace_bytes(planes, H, W, sweeps));
     const bool codes_or_passes = cc.stride && tb * (size_t)(2 * sweeps + 2) >= (size_t)tvd::chunk_codes_lowest;
