@@ -1,0 +1,56 @@
+"""TVLayer takes the SoftPlus of its parameter into its Function: same bits as with the SoftPlus outside, for the gradient
+of a gradient too."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("mode,shape,dtype", [("2d", (2, 6, 20, 24), "float32"), ("2d", (2, 6, 30, 30), "bfloat16"), ("2d", (1, 6, 70, 90), "float32"),
+                                              ("rows", (2, 6, 5, 32), "float32"), ("rows", (2, 6, 5, 300), "float32"), ("cols", (2, 6, 90, 7), "float32")])
+@pytest.mark.parametrize("shared", [False, True])
+def test_same_bits_as_outside(mode, shape, dtype, shared):
+    import torch
+
+    from paper_2204_03643_amd.layer import TVLayer
+
+    class Outside(TVLayer):
+        def lambdas(self):
+            return torch.nn.functional.softplus(self.raw_lambda)
+
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    y = torch.randn(shape, generator=gen, device="cuda").to(getattr(torch, dtype)).requires_grad_(True)
+    g = torch.randn(shape, generator=gen, device="cuda").to(y.dtype)
+    out = []
+    for kind in (TVLayer, Outside):
+        layer = kind(6, mode=mode, shared_lambda=shared, sweeps=2).cuda()
+        with torch.no_grad():
+            layer.raw_lambda.copy_(torch.linspace(-2, 25, layer.raw_lambda.numel()))      # (beyond 20 SoftPlus is the identity)
+        x = layer(y)
+        gy, gr = torch.autograd.grad(x, [y, layer.raw_lambda], g, create_graph=True)
+        second, = torch.autograd.grad(gr.sum(), [layer.raw_lambda])
+        frozen = torch.autograd.grad(layer.requires_grad_(False)(y), [y], g)[0]
+        out.append((x, gy, gr, second, frozen))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+
+
+def test_an_instance_with_lambdas_of_its_own():
+    import torch
+
+    from paper_2204_03643_amd.layer import TVLayer
+    y = torch.randn(1, 3, 16, 16, device="cuda")
+    layer = TVLayer(3).cuda()
+    layer.lambdas = lambda: torch.zeros(3, device="cuda")
+    assert torch.equal(layer(y), y)
+
+
+def test_calls_go_to_the_current_stream():
+    import torch
+
+    import paper_2204_03643_amd as tv
+    from paper_2204_03643_amd import binding
+    side = torch.cuda.Stream()
+    assert binding._stream(None) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert binding._stream(None) == side.cuda_stream
+    assert binding._stream(side) == side.cuda_stream and tv.lib() is not None
