@@ -13,11 +13,48 @@ __device__ __forceinline__ uint32_t xcd_together(uint32_t b, uint32_t n_groups, 
     return base + ((b & 7u) << lg) + ((b >> 3) & ((1u << lg) - 1u));
 }
 
-// s / n to an ulp: what the reciprocal's last bit takes is given back.
-__device__ __forceinline__ float mean_of(float s, float n)
+// The value of `v` in the lane that a DPP control word or a permutation names, for 64-bit values.
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ double dpp64(double v)
 {
-    const float r = __builtin_amdgcn_rcpf(n), m = s * r;
-    return fmaf(fmaf(-m, n, s), r, m);
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xf, true);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double lane64(double v, int from)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from << 2, (int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from << 2, (int)(uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+// s / n, to 2^-45 or so
+__device__ __forceinline__ double mean64(double s, float n)
+{
+    const double r = (double)__builtin_amdgcn_rcpf(n);
+    return s * fma(fma(-(double)n, r, 1.0), r, r);
+}
+// RowWave::open_sum in 64 bits: v of this lane and of the `dist` lanes before it, TW lanes a row, at most 64.
+template <int TW>
+__device__ __forceinline__ double open_sum64(double v, int dist, int lane)
+{
+#define TV_STEP(S)                                        \
+    if constexpr ((S) < TW) {                             \
+        const double o = dpp64<0x110 + ((S) & 15)>(v);    \
+        v += dist >= (S) ? o : 0.0;                       \
+    }
+    TV_STEP(1) TV_STEP(2) TV_STEP(4) TV_STEP(8)
+#undef TV_STEP
+    if constexpr (TW > 16) {
+        const double o = lane64(v, (lane & ~15) - 1);     // the last lane of the 16 before
+        v += (lane & 16) && dist > (lane & 15) ? o : 0.0;
+    }
+    if constexpr (TW > 32) {
+        const double o = lane64(v, 31);
+        v += (lane & 32) && dist > (lane & 31) ? o : 0.0;
+    }
+    return v;
 }
 
 // T threads a column with C contiguous samples each, G adjacent columns a workgroup, thread = t * G + column: every load and
@@ -28,10 +65,12 @@ __device__ __forceinline__ float mean_of(float s, float n)
 // neighbouring lanes take the T pieces of one column) a segmented sum over lanes and one fetch of a mean from the
 // lane where a segment ends turn them into the two means that each chunk needs: that of the segment open at its
 // start and that of the one open at its end.
-// Bound by memory: 24 planes of 512 x 512, backward, 21.7 -> 14.8 us (75 MB at 5.1 TB/s); with its lambda sum the call takes
-// 26.6 -> 19.1 us, and on 8M samples in planes of 33 / 64 / 100 / 200 / 481 / 900 a side 124 / 69 / 65 / 44 / 44 / 47 ->
-// 26 / 21 / 23 / 27 / 28 / 31.  (Before, every tensor crossed an LDS tile that turned columns into rows and back.)
-// Error against 64 bits, thirty calls: grad_y 6.3e-8 -> 4.8e-8, dL/dlam 3.1e-7 -> 2.6e-7.
+// Bound by memory, and by the vector ALUs on columns of at most 64 samples: 24 planes of 512 x 512, backward with its
+// lambda sum, 26.7 -> 20.5 us (75 MB); 8M samples in planes of 33 / 64 / 100 / 200 / 481 / 900 a side
+// 124 / 69 / 65 / 44 / 44 / 47 -> 37 / 25 / 26 / 26 / 27 / 28.  (Before, every tensor crossed an LDS tile that turned columns into
+// rows and back.)  Error against 64 bits, thirty calls: grad_y 6.3e-8 -> 2.5e-8, dL/dlam 3.1e-7 -> 4.0e-8; with
+// sums and means in 32 bits and dL/dlam in 64, 4.8e-8 and 2.4e-7, at 19.0 us: one lambda's gradient cancels, and was
+// further off than before in one call of ten.
 // G: 32 columns, a line, where that leaves workgroups of at most 512 threads, 16 beyond (512 a side, with sub: 18.5 us, with 32
 // columns 21.6; 768, no sub, 64 threads of 12 samples 19.8, 32 threads of 24 and 32 columns 23.8).
 // HAS_SUB: p.sub is given (the reverse sweep of the 2D operator).  CODES: where the forward pass left chunk codes
@@ -43,7 +82,7 @@ __global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
     static_assert(T <= 64 && C <= 32 && (CW == -2 || C % CW == 0) && G <= 64, "a column's threads inside one wave when exchanged");
     using Rw = RowWave<T, G, false>;
     constexpr int P = G + 1;                     // (both [t][column] accesses are then free of bank conflicts)
-    __shared__ float first[T * P], last[T * P];  // sums of the pieces, then the two means
+    __shared__ double first[T * P], last[T * P]; // sums of the pieces, then the two means
     __shared__ uint32_t sizes[T * P];            // their counts and whether the chunk holds a jump, then dL/dlam terms
     const int tid = threadIdx.x;
     const int col = tid % G, t = tid / G;
@@ -110,17 +149,37 @@ __global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
     }
 #define TV_JUMP(i) ((jmask >> (i)) & 1u)
     const uint32_t jumps = C == 32 ? jmask : jmask & ((1u << (C & 31)) - 1u);
+    // Segments that lie inside the chunk are done at once.  Sums and means in 64 bits: dL/dlam sees only differences of
+    // means, each once at either end of its segment, with the signs of the jumps there, and those of a slot cancel.
+    double gl = 0.0;
+    float sign_first = 0.f, sign_last = 0.f;
     {
-        float head_s = 0.f, tail_s = 0.f;
+        double s = 0.0, head_s = 0.0;
+        float c = 0.f;
         bool any = false;
 #pragma unroll
         for (int i = 0; i < C; ++i) {
-            if (!any) head_s += g[i];
-            tail_s += g[i];
-            if (TV_JUMP(i)) { any = true; tail_s = 0.f; }
+            s += (double)g[i]; c += 1.f;
+            if (TV_JUMP(i)) {
+                const float sign = (gmask >> i) & 1u ? (((upmask >> i) & 1u) ? 1.f : -1.f) : 0.f;
+                if (any) {
+                    const double m = mean64(s, c);
+                    const float w = sign - sign_last;
+                    if (w != 0.f) gl = fma((double)w, m, gl);
+                    g[i] = (float)m;
+                } else {
+                    head_s = s;
+                    sign_first = sign;
+                }
+                sign_last = sign;
+                any = true;
+                s = 0.0; c = 0.f;
+            }
         }
+        const double tail_s = s;
+        if (!any) head_s = s;
         const uint32_t head_n = any ? (uint32_t)__builtin_ctz(jumps | 0x80000000u) + 1u : (uint32_t)C;
-        const uint32_t tail_n = any ? (uint32_t)(C - 32 + __builtin_clz(jumps | 1u)) : (uint32_t)C;
+        const uint32_t tail_n = (uint32_t)c;
         first[t * P + col] = head_s;
         last[t * P + col] = tail_s;
         sizes[t * P + col] = head_n | tail_n << 8 | (any ? 1u << 16 : 0u);
@@ -128,7 +187,7 @@ __global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
     __syncthreads();
     {
         const int at = (tid % T) * P + tid / T;
-        const float head_s = first[at], tail_s = last[at];
+        const double head_s = first[at], tail_s = last[at];
         const uint32_t sz = sizes[at];
         const float head_n = (float)(sz & 0xffu), tail_n = (float)(sz >> 8 & 0xffu);
         const bool closed = (sz >> 16) != 0u;
@@ -136,33 +195,28 @@ __global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
         const uint64_t cmask = lanes_with(closed);
         const int L = rw.last_before(cmask);
         const int apart = rw.lane - L;
-        float left_s = rw.prev(rw.open_sum(tail_s, closed ? 0 : apart));
+        const double upto = open_sum64<T>(tail_s, closed ? 0 : apart, rw.lane);
+        double left_s = lane64(upto, rw.lane - 1);
         float left_n = Rw::at(tail_n, L) + (float)(apart * C - C);
-        if (rw.tw == 0) { left_s = 0.f; left_n = 0.f; }
+        if (rw.tw == 0) { left_s = 0.0; left_n = 0.f; }
         // the lane in which a segment ends knows its mean; the others fetch it (the last one always holds an end)
-        const float head_m = mean_of(left_s + head_s, left_n + head_n);
-        const float tail_m = Rw::at(head_m, rw.first_after(cmask));
+        const double head_m = mean64(left_s + head_s, left_n + head_n);
+        const double tail_m = lane64(head_m, rw.first_after(cmask));
         first[at] = closed ? head_m : tail_m;
         last[at] = tail_m;
     }
     __syncthreads();
-    const float head_m = first[t * P + col], tail_m = last[t * P + col];
-    double gl = 0.0;                             // (64 bits from here on: a slot's terms cancel)
     {
-        float s = 0.f, c = 0.f;
-        bool any = false;
-#pragma unroll
-        for (int i = 0; i < C; ++i) {
-            s += g[i]; c += 1.f;
-            if (TV_JUMP(i)) { g[i] = any ? mean_of(s, c) : head_m; s = 0.f; c = 0.f; any = true; }
-        }
-        float carry = tail_m;
+        const double head_m = first[t * P + col], tail_m = last[t * P + col];
+        if (sign_first != 0.f) gl = fma((double)sign_first, head_m, gl);
+        if (sign_last != 0.f) gl = fma(-(double)sign_last, tail_m, gl);
+        const float head = (float)head_m;
+        const uint32_t lowest = jumps & (0u - jumps);
+        float carry = (float)tail_m;
 #pragma unroll
         for (int i = C - 1; i >= 0; --i) {
-            const float behind = carry;
-            if (TV_JUMP(i)) carry = g[i];
+            if (TV_JUMP(i)) carry = (lowest >> i) & 1u ? head : g[i];
             g[i] = carry;
-            if ((gmask >> i) & 1u) gl += (double)(((upmask >> i) & 1u) ? carry - behind : behind - carry);
         }
     }
     if constexpr (HAS_SUB) {
@@ -186,7 +240,7 @@ __global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
         terms[t * P + col] = rvalid ? (float)gl : 0.f;
         __syncthreads();
         if (tid < G) {
-            double sum = 0.0;
+            double sum = 0.0;                    // (64 bits from here on)
 #pragma unroll 8
             for (int q = 0; q < T; ++q) sum += (double)terms[q * P + tid];
             // neighbouring columns that share a slot leave as one term, in two floats

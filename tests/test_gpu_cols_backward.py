@@ -53,3 +53,31 @@ def test_columns(n, slots):
     bound = np.zeros(count)
     np.add.at(bound, slot, 2 * jumps * mean_err + 102 * EPS * terms)
     assert (np.abs(gl.cpu().numpy() - wl) <= bound + EPS * np.abs(wl)).all()
+
+
+@pytest.mark.parametrize("n", [40, 100, 300, 1000])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -3e38])
+def test_one_bad_sample_stays_in_its_segment(n, bad):
+    import torch
+
+    import paper_2204_03643_amd as tv
+
+    rng = np.random.default_rng(n)
+    x = _piecewise(rng, 1, n, 21)
+    g = rng.normal(size=x.shape).astype(np.float32)
+    for k in (0, n // 2, n - 1):
+        h = g.copy()
+        h[0, k, 3::5] = bad
+        want, _ = oracle.prox1d_bwd_batch(np.where(np.isfinite(h) & (np.abs(h) < 1e30), h, 0), x, axis=1)
+        same = np.cumsum(np.pad(np.diff(x, axis=1) != 0, ((0, 0), (1, 0), (0, 0))), axis=1)
+        hit = np.zeros(x.shape, bool)
+        hit[0, :, 3::5] = (same == same[:, k:k + 1])[0, :, 3::5]
+        xt, ht = torch.from_numpy(x).cuda(), torch.from_numpy(h).cuda()
+        lam = torch.ones(1, device="cuda")
+        rows, L = tv.rows_along(x.shape, 1), tv.tv_lambda(lam.data_ptr(), 1, 1)
+        gy = torch.empty_like(ht)
+        tv.tv1d_prox_bwd(ht, xt, gy, None, rows, L, None, 0)
+        got = gy.cpu().numpy()
+        assert np.abs(got - want)[~hit].max() <= 73 * EPS * np.abs(g).max()
+        if bad != -3e38:
+            assert not np.isfinite(got[hit]).any()
