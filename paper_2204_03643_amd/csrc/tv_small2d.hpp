@@ -62,12 +62,12 @@ struct Small2dBwdParams {
     float       *gy;
     const uint2 *codes;        // pass i (row pass of sweep k: 2k, column pass: 2k + 1) at codes + i * code_stride
     size_t       code_stride;  // in uint2
-    const uint32_t *tag;       // planes of 33-64 samples a side: optional; where it holds 1 the codes are row masks (below) ...
-    const float *saved;        // ... and otherwise the output of pass i, at saved + i * saved_stride (floats), is read instead
-    size_t       saved_stride;
+    const float *saved;        // planes of 33-64 samples a side (unless tag says that codes are there): the output of pass i,
+    size_t       saved_stride; // at saved + i * saved_stride (floats), is read instead
     float       *partial;      // optional: one dL/dlam term per plane (all passes summed)
     int32_t      planes, H, W, sweeps;
     uint32_t     stream;       // tensors too large to stay in cache: non-temporal accesses
+    const uint32_t *tag;       // sides of 33-64: optional; holds 1 where the codes are row masks (below)
 };                             // (IO16 kernels: g_up and gy point to bf16 bit patterns)
 
 // Row masks: what the reverse sweep reads of a pass on planes with both sides of 33-64 samples, 16 bytes a row where its output
@@ -308,11 +308,11 @@ struct Small2dFwdParams {
     uint32_t     keep_passes;  // planes of at most 32 x 32: 0 = write the codes only, not the pass outputs
     uint2       *codes;        // as in Small2dBwdParams (sides of 33-64: null where the pass outputs are kept)
     size_t       code_stride;
-    uint32_t    *tag;          // sides of 33-64: receives whether codes were written
     const float *lam;          // plane p uses lam[p % lam_count]
     int64_t      lam_count;
     int32_t      planes, H, W, sweeps;
     uint32_t     stream;
+    uint32_t    *tag;          // sides of 33-64: receives whether codes were written
 };
 
 // S, FULL: as in the reverse sweep (a wave holds 64 / S planes), S <= 16.
