@@ -30,30 +30,13 @@ def _check_input(x: torch.Tensor, what: str, bf16_ok: bool = False) -> torch.Ten
     return x.contiguous()
 
 
-def _lambda_grad(ctx, gl, raw):
-    """The gradient of a Function's second argument from that of the lambdas."""
-    if gl is None:
-        return None
-    gl = gl.reshape(ctx.lam_shape)
-    # (an op of its own, so that a second derivative finds the SoftPlus as it would outside)
-    return gl if raw is None else torch.ops.aten.softplus_backward.default(gl, raw, 1, 20)
-
-
-# With soft, the second argument of the Functions is the parameter whose SoftPlus is lambda: as a
-# node of its own in the graph, that SoftPlus took 17 of the 76 us that a small layer's forward and
-# backward pass takes on the host.
-
-
 class _Prox1d(torch.autograd.Function):
     """x = prox along `axis` of a contiguous tensor; lam[(row // lam_div) % lam.numel()] per row."""
 
     @staticmethod
-    def forward(ctx, y, lam, axis, lam_div, soft):
+    def forward(ctx, y, lam, axis, lam_div):
         y = _check_input(y, "tv prox 1d", bf16_ok=True)
         ctx.lam_shape = lam.shape                  # the gradient goes back in the caller's shape
-        raw = (lam,) if soft else ()
-        if soft:
-            lam = torch.nn.functional.softplus(lam)
         lam = _check_input(lam, "tv prox 1d (lambda)").reshape(-1)
         rows = _b.rows_along(tuple(y.shape), axis)
         ctx.bf16 = y.dtype == torch.bfloat16
@@ -75,16 +58,16 @@ class _Prox1d(torch.autograd.Function):
             _b.tv1d_prox_fwd_ex(y, x, rows, L, seg=seg, ws=ws if wsb else None, ws_bytes=wsb)
         ctx.rows, ctx.lam_count, ctx.lam_div = rows, lam.numel(), int(lam_div)
         if seg is not None:
-            ctx.save_for_backward(seg, lam, *raw)
+            ctx.save_for_backward(seg, lam)
             ctx.has_seg = True
         else:
-            ctx.save_for_backward(x, lam, *raw)
+            ctx.save_for_backward(x, lam)
             ctx.has_seg = False
         return x
 
     @staticmethod
     def backward(ctx, g):
-        saved, lam, *raw = ctx.saved_tensors
+        saved, lam = ctx.saved_tensors
         g = _check_input(g, "tv prox 1d (gradient)", bf16_ok=ctx.bf16)
         if ctx.bf16 and g.dtype != torch.bfloat16:
             g = g.to(torch.bfloat16)
@@ -101,19 +84,16 @@ class _Prox1d(torch.autograd.Function):
             _b.tv1d_prox_bwd_seg(g, saved, gy, gl, rows, L, ws, wsb)
         else:
             _b.tv1d_prox_bwd(g, saved, gy, gl, rows, L, ws, wsb)
-        return gy, _lambda_grad(ctx, gl, *(raw or (None,))), None, None, None
+        return gy, (gl.reshape(ctx.lam_shape) if want_lam else None), None, None
 
 
 class _Prox2d(torch.autograd.Function):
     """x = 2D prox of the trailing two axes; plane p uses lam[p % lam.numel()]."""
 
     @staticmethod
-    def forward(ctx, y, lam, sweeps, soft):
+    def forward(ctx, y, lam, sweeps):
         y = _check_input(y, "tv prox 2d", bf16_ok=True)
         ctx.lam_shape = lam.shape                  # the gradient goes back in the caller's shape
-        raw = (lam,) if soft else ()
-        if soft:
-            lam = torch.nn.functional.softplus(lam)
         lam = _check_input(lam, "tv prox 2d (lambda)").reshape(-1)
         H, W = int(y.shape[-2]), int(y.shape[-1])
         ctx.bf16 = y.dtype == torch.bfloat16
@@ -126,12 +106,12 @@ class _Prox2d(torch.autograd.Function):
         x = torch.empty_like(y)
         (_b.tv2d_prox_fwd_bf16 if ctx.bf16 else _b.tv2d_prox_fwd)(y, x, planes, H, W, L, int(sweeps), ws, wsb)
         ctx.dims = (planes, H, W, int(sweeps), wsb)
-        ctx.save_for_backward(ws, lam, *raw)
+        ctx.save_for_backward(ws, lam)
         return x
 
     @staticmethod
     def backward(ctx, g):
-        ws, lam, *raw = ctx.saved_tensors
+        ws, lam = ctx.saved_tensors
         planes, H, W, sweeps, wsb = ctx.dims
         g = _check_input(g, "tv prox 2d (gradient)", bf16_ok=ctx.bf16)
         if ctx.bf16 and g.dtype != torch.bfloat16:
@@ -143,18 +123,18 @@ class _Prox2d(torch.autograd.Function):
         # (the reverse sweep restarts from g and only reads the saved pass outputs; the two
         # correction tensors of the workspace are its scratch, so it may run again on the same graph)
         (_b.tv2d_prox_bwd_bf16 if ctx.bf16 else _b.tv2d_prox_bwd)(g, gy, gl, planes, H, W, L, sweeps, ws, wsb)
-        return gy, _lambda_grad(ctx, gl, *(raw or (None,))), None, None
+        return gy, (gl.reshape(ctx.lam_shape) if want_lam else None), None
 
 
 def tv_prox_1d(x: torch.Tensor, lam: torch.Tensor, axis: int = -1, lam_div: int = 1) -> torch.Tensor:
     """Differentiable batched 1D TV prox along `axis` (paper Eq. 1); see ``tv_lambda`` in
     ``include/tvprox.h`` for how `lam` and `lam_div` map rows to lambdas."""
-    return _Prox1d.apply(x, lam, axis, lam_div, False)
+    return _Prox1d.apply(x, lam, axis, lam_div)
 
 
 def tv_prox_2d(x: torch.Tensor, lam: torch.Tensor, sweeps: int = 4) -> torch.Tensor:
     """Differentiable 2D anisotropic TV prox of the trailing two axes (paper Eq. 2, Alg. 1)."""
-    return _Prox2d.apply(x, lam, sweeps, False)
+    return _Prox2d.apply(x, lam, sweeps)
 
 
 class TVLayer(torch.nn.Module):
@@ -185,14 +165,12 @@ class TVLayer(torch.nn.Module):
     def forward(self, x: torch.Tensor) -> torch.Tensor:
         if x.dim() not in (3, 4) or x.shape[-3] != self.num_channels:
             raise ValueError("expected [B, %d, H, W] or [%d, H, W]" % (self.num_channels, self.num_channels))
-        # (a subclass, or an instance, with lambdas of its own is asked for them)
-        soft = type(self).lambdas is TVLayer.lambdas and "lambdas" not in self.__dict__
-        lam = self.raw_lambda if soft else self.lambdas()
+        lam = self.lambdas()
         H, W = x.shape[-2], x.shape[-1]
         if self.mode == "2d":
-            y = _Prox2d.apply(x, lam, self.sweeps, soft)         # plane p = b * C + c uses lam[p % C]
+            y = tv_prox_2d(x, lam, self.sweeps)                  # plane p = b * C + c uses lam[p % C]
         elif self.mode == "rows":
-            y = _Prox1d.apply(x, lam, -1, H, soft)               # row id = (b * C + c) * H + h
+            y = tv_prox_1d(x, lam, axis=-1, lam_div=H)           # row id = (b * C + c) * H + h
         else:
-            y = _Prox1d.apply(x, lam, -2, W, soft)               # row id = (b * C + c) * W + w
+            y = tv_prox_1d(x, lam, axis=-2, lam_div=W)           # row id = (b * C + c) * W + w
         return 2.0 * x - y if self.sharpen else y

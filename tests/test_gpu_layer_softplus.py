@@ -1,5 +1,5 @@
-"""TVLayer takes the SoftPlus of its parameter into its Function: same bits as with the SoftPlus outside, for the gradient
-of a gradient too."""
+"""TVLayer's parameter and its SoftPlus: the gradient of a gradient, a parameter that is moved between the passes, and
+layers with lambdas of their own."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -32,6 +32,36 @@ def test_same_bits_as_outside(mode, shape, dtype, shared):
         out.append((x, gy, gr, second, frozen))
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("mode,shape", [("2d", (2, 3, 16, 16)), ("rows", (2, 3, 4, 32)), ("cols", (2, 3, 90, 7))])
+@pytest.mark.parametrize("frozen", [False, True])
+def test_parameter_moved_between_the_passes(mode, shape, frozen):
+    """The input's gradient does not need the parameter, which an optimizer or an average of weights may have moved by then."""
+    import torch
+
+    from paper_2204_03643_amd.layer import TVLayer
+    y = torch.randn(shape, device="cuda", requires_grad=True)
+    g = torch.randn(shape, device="cuda")
+    layer = TVLayer(3, mode=mode, sweeps=2).cuda().requires_grad_(not frozen)
+    want, = torch.autograd.grad(layer(y), [y], g)
+    x = layer(y)
+    with torch.no_grad():
+        layer.raw_lambda.add_(1)
+    got, = torch.autograd.grad(x, [y], g, retain_graph=True)
+    assert torch.equal(got, want)
+    if not frozen:
+        with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+            torch.autograd.grad(x, [y, layer.raw_lambda], g)
+
+
+def test_lambdas_of_the_class_replaced(monkeypatch):
+    import torch
+
+    from paper_2204_03643_amd.layer import TVLayer
+    y = torch.randn(1, 3, 16, 16, device="cuda")
+    monkeypatch.setattr(TVLayer, "lambdas", lambda self: torch.zeros(3, device="cuda"))
+    assert torch.equal(TVLayer(3).cuda()(y), y)
 
 
 def test_an_instance_with_lambdas_of_its_own():
