@@ -243,11 +243,12 @@ __global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
             double sum = 0.0;                    // (64 bits from here on)
 #pragma unroll 8
             for (int q = 0; q < T; ++q) sum += (double)terms[q * P + tid];
-            // neighbouring columns that share a slot leave as one term, in two floats
+            // neighbouring columns that share a slot leave as one term, in two floats (the second says nothing beside an infinity)
             for (uint32_t d = 0; d < p.part_lg; ++d) sum += __shfl_xor(sum, 1 << d);
             if (rvalid && (tid & ((1 << p.part_lg) - 1)) == 0) {
                 const float hi = (float)sum;
-                if (p.part_lg) *reinterpret_cast<float2 *>(p.partial + 2 * (size_t)(row >> p.part_lg)) = make_float2(hi, (float)(sum - (double)hi));
+                const float lo = isfinite(hi) ? (float)(sum - (double)hi) : 0.f;
+                if (p.part_lg) *reinterpret_cast<float2 *>(p.partial + 2 * (size_t)(row >> p.part_lg)) = make_float2(hi, lo);
                 else p.partial[row] = hi;
             }
         }

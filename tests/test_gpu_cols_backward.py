@@ -81,3 +81,34 @@ def test_one_bad_sample_stays_in_its_segment(n, bad):
         assert np.abs(got - want)[~hit].max() <= 73 * EPS * np.abs(g).max()
         if bad != -3e38:
             assert not np.isfinite(got[hit]).any()
+
+
+def _lambda_grads(x, g, count, div):
+    import torch
+
+    import paper_2204_03643_amd as tv
+    xt, gt = torch.from_numpy(x).cuda(), torch.from_numpy(g).cuda()
+    lam = torch.ones(count, device="cuda")
+    rows, L = tv.rows_along(x.shape, 1), tv.tv_lambda(lam.data_ptr(), count, div)
+    gy, gl = torch.empty_like(gt), torch.full((count,), float("nan"), device="cuda")
+    wsb = tv.tv1d_bwd_workspace_bytes(rows, L)
+    ws = torch.full((max(16, wsb),), 0xff, dtype=torch.uint8, device="cuda")
+    tv.tv1d_prox_bwd(gt, xt, gy, gl, rows, L, ws, wsb)
+    return gl.cpu().numpy()
+
+
+@pytest.mark.parametrize("n", [40, 100, 300, 1000])
+@pytest.mark.parametrize("bad", [float("inf"), -float("inf"), 3e38])
+def test_an_infinite_lambda_gradient(n, bad):
+    """A slot whose terms add up to an infinity has it as its gradient, whether one column or many share the slot."""
+    W = 64
+    x = np.zeros((1, n, W), np.float32)
+    x[0, n // 2:] = 1                               # one rise: the gradient is the sum of the lower halves' means less the upper ones'
+    g = np.ones(x.shape, np.float32)
+    if np.isinf(bad):
+        g[0, n // 4, 3] = bad
+    else:
+        g[0, :n // 2] = bad                         # (every column's term is a float, the sum of two is not)
+    want = np.float32(np.sign(bad) * np.inf)
+    assert _lambda_grads(x, g, 1, 1)[0] == want
+    assert np.array_equal(_lambda_grads(x, g, 4, 16), [want] + ([0] * 3 if np.isinf(bad) else [want] * 3))
