@@ -164,8 +164,7 @@ __global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
                 const float sign = (gmask >> i) & 1u ? (((upmask >> i) & 1u) ? 1.f : -1.f) : 0.f;
                 if (any) {
                     const double m = mean64(s, c);
-                    const float w = sign - sign_last;
-                    if (w != 0.f) gl = fma((double)w, m, gl);
+                    gl = fma((double)(sign - sign_last), m, gl);       // (also where the two cancel: an infinite mean, or NaN, shows)
                     g[i] = (float)m;
                 } else {
                     head_s = s;

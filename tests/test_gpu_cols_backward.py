@@ -112,3 +112,17 @@ def test_an_infinite_lambda_gradient(n, bad):
     want = np.float32(np.sign(bad) * np.inf)
     assert _lambda_grads(x, g, 1, 1)[0] == want
     assert np.array_equal(_lambda_grads(x, g, 4, 16), [want] + ([0] * 3 if np.isinf(bad) else [want] * 3))
+
+
+@pytest.mark.parametrize("n", [40, 100, 300, 1000])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_a_bad_segment_on_a_staircase_shows(n, bad):
+    """Between two rises a segment's mean enters once with either sign: an infinity or NaN there leaves NaN, wherever the segment
+    lies in its thread's chunk."""
+    W = n - 8
+    x = np.repeat((np.arange(n) // 2).astype(np.float32)[:, None], W, 1)[None]
+    g = np.ones(x.shape, np.float32)
+    at = np.arange(W)
+    g[0, at + 4, at] = bad
+    assert np.isnan(_lambda_grads(x, g, W, 1)).all()
+    assert np.isnan(_lambda_grads(x, g, 1, 1)).all()
