@@ -413,20 +413,33 @@ __device__ __forceinline__ uint2 pair_segment_code(const float (&xs)[C], int n, 
 }
 
 // The half of a pair's row mask (tv_small2d.hpp) that the lane leaves: the left lane the jumps, the right one the rises.
+// From the signs of differences, as in pair_segment_code, which say nothing next to an infinity or NaN: where a wave
+// has one, its masks come from the comparisons that readers of pass outputs make.  (From comparisons alone:
+// 1024 planes of 64 x 64, K = 4, forward, 131.7 -> 137.6 us.)
 template <int C, bool FULL>
 __device__ __forceinline__ uint2 pair_row_mask(const float (&xs)[C], int n, bool right)
 {
     uint32_t jump, rises;                       // local duals, as in pair_segment_code
-    {
-        const float d = xs[C - 1] - pair_other(xs[C - 1]);
-        rises = __float_as_uint(d) >> 31;
-        jump = __float_as_uint(0.0f - fabsf(d)) >> 31;
-    }
+    const float across = pair_other(xs[C - 1]);
+    float before = xs[C - 1] - across, check = 0.f;     // check: finite where every difference is, and not huge
+    rises = __float_as_uint(before) >> 31;
+    jump = __float_as_uint(0.0f - fabsf(before)) >> 31;
 #pragma unroll
     for (int k = C - 2; k >= 0; --k) {
         const float d = xs[k] - xs[k + 1];
         rises = __builtin_amdgcn_alignbit(rises, __float_as_uint(d), 31);
         jump = __builtin_amdgcn_alignbit(jump, __float_as_uint(0.0f - fabsf(d)), 31);
+        if (k % 2 == 0) check = fmaf(d, before, check);
+        before = d;
+    }
+    if (__any(!(fabsf(check) < INFINITY))) {
+        rises = across > xs[C - 1] ? 1u : 0u;
+        jump = across != xs[C - 1] ? 1u : 0u;
+#pragma unroll
+        for (int k = C - 2; k >= 0; --k) {
+            rises = rises << 1 | ((right ? !(xs[k] > xs[k + 1]) : xs[k + 1] > xs[k]) ? 1u : 0u);
+            jump = jump << 1 | (xs[k + 1] != xs[k] ? 1u : 0u);
+        }
     }
     // left: duals 0 .. C-1 as they are.  Right: its duals 0 .. C-2 are 2C-2 .. C of the row, which rises where the lane falls
     const uint32_t turned_jump = __builtin_bitreverse32(jump) >> (33 - C);

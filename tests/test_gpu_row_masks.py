@@ -83,3 +83,40 @@ def test_every_writer_with_every_reader(H, W, overrides):
         for a, b in zip((gy, gl), want[1:]):
             assert torch.isfinite(a).all()
             assert (a - b).abs().max() <= 2e-5 * (1 + b.abs().max()), (writer, keep, reader)
+
+
+@pytest.mark.parametrize("lam", [0.0, 0.3])
+@pytest.mark.parametrize("H,W", SIDES)
+def test_samples_that_are_no_numbers(H, W, lam, overrides):
+    """Infinities side by side, zeros of both signs and NaN: the masks say what comparisons of the pass outputs say."""
+    import torch
+
+    import paper_2204_03643_amd as tv
+    big, K = 1 << 40, 2
+    y, _, g = _case(H, W, 4)
+    y[0, 5, 3:9], y[1, 7:11, 20], y[2, ::2], y[2, ::2, 1::3] = np.inf, -np.inf, 0.0, -0.0
+    y[3, 5, 3], y[3, 9, 7:9], y[3, 20, 20] = np.nan, 3e38, np.inf
+    yt, lt, gt = (torch.from_numpy(a).cuda() for a in (y, np.full(4, lam, np.float32), g))
+    L = tv.tv_lambda(lt.data_ptr(), 4, 1)
+    wsb = tv.tv2d_workspace_bytes(4, H, W, K)
+    ws = torch.full((wsb,), 0xff, dtype=torch.uint8, device="cuda")
+
+    def run(writer, keep, reader):
+        group, pairs = {"pairs": (big, 0), "planes": (big, big)}[writer]
+        overrides(fused_keeps_passes=keep, plane_per_group64_planes_k2=group, plane_per_group64_full_planes_k2=pairs,
+                  pair_2d_planes=pairs, pair_2d_many_planes=pairs)
+        x, gy, gl = torch.empty_like(yt), torch.empty_like(yt), torch.empty_like(lt)
+        tv.tv2d_prox_fwd(yt, x, 4, H, W, L, K, ws, wsb)
+        overrides(fused_keeps_passes=1, plane_per_group64_bwd_planes=0 if reader == "pairs" else big,
+                  plane_per_group64_bwd_ragged_planes_k2=big if reader == "planes" else 0)
+        tv.tv2d_prox_bwd(gt, gy, gl, 4, H, W, L, K, ws, wsb)
+        return [t.cpu().numpy() for t in (x, gy, gl)]
+
+    for writer in ("pairs", "planes"):
+        for reader in ("planes", "passes"):
+            for a, b in zip(run(writer, 1, reader), run(writer, 0, reader)):
+                assert np.array_equal(a, b, equal_nan=True), (writer, reader)
+        for a, b in zip(run(writer, 0, "passes"), run(writer, 0, "pairs")):
+            same = np.isfinite(a)
+            assert np.array_equal(same, np.isfinite(b))
+            assert np.abs(a[same] - b[same]).max() <= 2e-5 * (1 + np.abs(a[same]).max()), writer
