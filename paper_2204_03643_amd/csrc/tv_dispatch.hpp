@@ -293,8 +293,13 @@ inline int64_t get(int which) { return table[which].value; }
 // 128 x 128 x 128, K = 4, 83 -> 94.)
 inline int64_t chunk_codes_lowest = table[kChunkCodesBytes].value;
 
+// Whether a line that decides which planes of 33-64 a side leave row masks has ever been moved: until then a reverse sweep
+// knows from the sizes whether its workspace can hold them.
+inline bool mask_lines_moved = false;
+
 inline void set(int which, int64_t value)
 {
+    if (which >= kPlanePerGroup64Planes && which <= kPair2dManyPlanes && value != table[which].value) mask_lines_moved = true;
     table[which].value = value;
     if (which == kChunkCodesBytes && value < chunk_codes_lowest) chunk_codes_lowest = value;
 }

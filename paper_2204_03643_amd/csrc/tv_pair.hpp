@@ -959,11 +959,15 @@ __global__ __launch_bounds__(64, C > 16 ? 3 : 4) void tv1d_fwd_pair_kernel(FwdPa
 // Reverse sweep of 1024 planes of 64 x 64, K = 4, a row per lane / two lanes: 69 / 48 us, 8192 planes, K = 2: 290 / 180;
 // 1024 planes of 40 x 40, K = 4, a plane per workgroup / two lanes: 56 / 31.
 // At most 2C / 5 samples short of 2C.
+// MASKS: the workspace may hold row masks.  QUADS: rows of a multiple of four samples, read in 16-byte pieces from pass outputs.
+// (A kernel for every case: with both ways of reading rows in one, 6000 planes of 32 x 40, K = 4, take 12 % longer,
+// 4200 of 60 x 60, K = 1, 18 %.)
 // ---------------------------------------------------------------------------------
-template <int C, bool FULL>
+template <int C, bool FULL, bool QUADS, bool MASKS>
 __global__ __launch_bounds__(128, 2) void tv2d_bwd_pair_kernel(Small2dBwdParams p)
 {
     static_assert(C > 16 && C <= 32 && C % 4 == 0, "planes of 33-64 samples a side");
+    static_assert(QUADS || !FULL, "2C is a multiple of four");
     using Tile = PairTile<C>;
     constexpr int HO = Tile::HALF, P = Tile::PITCH, S = 2 * C, NT = 4 * HO;
     __shared__ float A[2 * HO * P], B[2 * HO * P], rtab[S + 2], wave_term[2];
@@ -1010,7 +1014,7 @@ __global__ __launch_bounds__(128, 2) void tv2d_bwd_pair_kernel(Small2dBwdParams 
     // no branch a load).
     const int row_in = FULL ? idx : min(idx, H - 1), col_in = FULL ? idx : min(idx, W - 1);
     // Or, where the forward call left row masks, the row's mask.
-    const bool coded = p.tag && *p.tag == 1u;
+    const bool coded = MASKS && *p.tag == 1u;
     uint4 mask = make_uint4(0u, 0u, 0u, 0u);
     auto fetch = [&](int pass, float (&xv)[C]) {
         if (pass < 0) return;
@@ -1027,7 +1031,7 @@ __global__ __launch_bounds__(128, 2) void tv2d_bwd_pair_kernel(Small2dBwdParams 
         } else {
             const int c0 = right ? C : 0;
             const float *from = xs + row_in * W;
-            if (FULL || W % 4 == 0) {
+            if constexpr (QUADS) {
 #pragma unroll
                 for (int c = 0; c < C; c += 4) {
                     const float4 q = *reinterpret_cast<const float4 *>(from + (FULL ? c0 + c : min(c0 + c, W - 4)));

@@ -225,9 +225,9 @@ __device__ __forceinline__ float lanes_segment_means(float (&g)[C], uint32_t jm,
 }
 
 // T, C as in the forward kernel.  Planes of at most 32 x 32 read the segments of a pass from its
-// 8-byte codes, larger ones from their row masks (where p.tag says so) or its saved output.  p.partial gets one dL/dlam term per plane.
-// IO16: the upstream gradient and grad_y are bf16 in memory.
-template <int T, int C, bool IO16 = false>
+// 8-byte codes, larger ones from their row masks (MASKS, where p.tag says so) or its saved output.  p.partial gets one dL/dlam term per plane.
+// IO16: the upstream gradient and grad_y are bf16 in memory.  MASKS: the workspace may hold row masks.
+template <int T, int C, bool IO16 = false, bool MASKS = false>
 __global__ __launch_bounds__(T * T * C, C <= 4 ? 8 : 4) void tv2d_bwd_plane_kernel(Small2dBwdParams p)
 {
     constexpr int S = T * C, P = S + 1, NT = S * T, NW = NT / 64;
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(T * T * C, C <= 4 ? 8 : 4) void tv2d_bwd_plane_kern
 
     // Segments of pass `pass` for the thread's chunk of its row (row pass) or column (column
     // pass); fetched one pass ahead, so that the latency hides behind the pass before.
-    const bool coded = S > 32 && p.tag && *p.tag == 1u;
+    const bool coded = MASKS && *p.tag == 1u;
     auto fetch = [&](int pass, uint32_t &jm, uint32_t &up) {
         jm = 0u; up = 0u;
         if (pass < 0) return;

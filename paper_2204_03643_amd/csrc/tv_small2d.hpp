@@ -67,7 +67,7 @@ struct Small2dBwdParams {
     float       *partial;      // optional: one dL/dlam term per plane (all passes summed)
     int32_t      planes, H, W, sweeps;
     uint32_t     stream;       // tensors too large to stay in cache: non-temporal accesses
-    const uint32_t *tag;       // sides of 33-64: optional; holds 1 where the codes are row masks (below)
+    const uint32_t *tag;       // sides of 33-64, where the workspace may hold row masks (below): 1 if it does; null otherwise
 };                             // (IO16 kernels: g_up and gy point to bf16 bit patterns)
 
 // Row masks: what the reverse sweep reads of a pass on planes with both sides of 33-64 samples, 16 bytes a row where its output

@@ -312,14 +312,21 @@ int launch_bwd_pairs_2d(const tvk::Small2dBwdParams &q, hipStream_t stream)
 {
     const int longer = q.H > q.W ? q.H : q.W, shorter = q.H > q.W ? q.W : q.H;
     const dim3 grid((uint32_t)q.planes), block(128);
+#define TV_PAIR_ROWS(C, FULL, QUADS)                                                                                                    \
+    do {                                                                                                                                \
+        if (q.tag) hipLaunchKernelGGL((tvk::tv2d_bwd_pair_kernel<C, FULL, QUADS, true>), grid, block, 0, stream, q);                    \
+        else hipLaunchKernelGGL((tvk::tv2d_bwd_pair_kernel<C, FULL, QUADS, false>), grid, block, 0, stream, q);                         \
+        return launch_status();                                                                                                         \
+    } while (0)
 #define TV_PAIR(C)                                                                                                \
     if (longer <= 2 * C) {                                                                                        \
-        if (shorter == 2 * C) hipLaunchKernelGGL((tvk::tv2d_bwd_pair_kernel<C, true>), grid, block, 0, stream, q); \
-        else hipLaunchKernelGGL((tvk::tv2d_bwd_pair_kernel<C, false>), grid, block, 0, stream, q);                 \
-        return launch_status();                                                                                   \
+        if (shorter == 2 * C) TV_PAIR_ROWS(C, true, true);                                                        \
+        else if (q.W % 4 == 0) TV_PAIR_ROWS(C, false, true);                                                      \
+        else TV_PAIR_ROWS(C, false, false);                                                                       \
     }
     TV_PAIR(20) TV_PAIR(24) TV_PAIR(28) TV_PAIR(32)
 #undef TV_PAIR
+#undef TV_PAIR_ROWS
     return TV_ERR_UNSUPPORTED;
 }
 
@@ -1384,7 +1391,12 @@ static bool plane_per_group_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
     return planes <= (far ? most + 3 * (most / 5) : most);
 }
 
-// Whether a forward call on such planes leaves row masks.
+// Whether some forward call on such planes can have left row masks, and whether one now would.  (As with the chunk codes,
+// looking is a load that everything waits for and two ways behind a branch, a microsecond in reverse sweeps that never find masks.)
+static bool may_hold_row_masks_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
+{
+    return row_masks_2d(H, W) && (tvd::mask_lines_moved || plane_per_group_2d(planes, H, W, sweeps) || pairs_2d_fwd(planes, H, W, sweeps));
+}
 static bool leaves_row_masks_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
 {
     return row_masks_2d(H, W) && tvd::get(tvd::kFusedKeepsPasses) == 0 &&
@@ -1611,7 +1623,7 @@ int tv2d_prox_bwd(const float *g_up, float *grad_y, float *grad_lam, int64_t pla
     //   Abar = Pbar' + R^T(Bbar - Pbar'),    Ybar = Pbar = Abar.
     // Ybar and Pbar coincide from the second reverse step on, so two tensors carry the state.
     // (which of the two the workspace holds is found out on the device; what a forward call would leave now picks the mapping)
-    const bool masks = row_masks_2d(H, W), expect_masks = leaves_row_masks_2d(planes, H, W, sweeps);
+    const bool masks = may_hold_row_masks_2d(planes, H, W, sweeps), expect_masks = leaves_row_masks_2d(planes, H, W, sweeps);
     const uint2 *mask_codes = masks ? (const uint2 *)base : nullptr;
     const size_t mask_stride = row_mask_bytes_2d(planes, H, W) / sizeof(uint2);
     const uint32_t *mask_tag = masks ? row_mask_tag(base, planes, H, W, sweeps) : nullptr;
@@ -1635,6 +1647,7 @@ int tv2d_prox_bwd(const float *g_up, float *grad_y, float *grad_lam, int64_t pla
         q.stream = 0u;
         const dim3 grid((uint32_t)planes);
         if (cb) hipLaunchKernelGGL((tvk::tv2d_bwd_plane_kernel<16, 2>), grid, dim3(512), 0, stream, q);
+        else if (q.tag) hipLaunchKernelGGL((tvk::tv2d_bwd_plane_kernel<8, 8, false, true>), grid, dim3(512), 0, stream, q);
         else hipLaunchKernelGGL((tvk::tv2d_bwd_plane_kernel<8, 8>), grid, dim3(512), 0, stream, q);
         return launch_status() == TV_OK ? sum_planes() : TV_ERR_HIP;
     }
