@@ -126,3 +126,36 @@ def test_a_bad_segment_on_a_staircase_shows(n, bad):
     g[0, at + 4, at] = bad
     assert np.isnan(_lambda_grads(x, g, W, 1)).all()
     assert np.isnan(_lambda_grads(x, g, 1, 1)).all()
+
+
+@pytest.mark.parametrize("n", [33, 40, 44, 48, 50, 57, 60, 63, 64])
+def test_many_short_columns_with_and_without_a_lambda_gradient(n):
+    """More than 16 384 columns: the kernel that forms no dL/dlam has the bits of the one that does, and both are right where
+    the column's end cuts a thread's chunk."""
+    import torch
+
+    import paper_2204_03643_amd as tv
+    P, W = 410, 41
+    rng = np.random.default_rng(n)
+    x = _piecewise(rng, P, n, W)
+    g = rng.normal(size=x.shape).astype(np.float32)
+    want, wl = oracle.prox1d_bwd_batch(g, x, lam_count=P, axis=1, lam_div=W)
+    xt, gt = torch.from_numpy(x).cuda(), torch.from_numpy(g).cuda()
+    lam = torch.ones(P, device="cuda")
+    rows, L = tv.rows_along(x.shape, 1), tv.tv_lambda(lam.data_ptr(), P, W)
+    wsb = tv.tv1d_bwd_workspace_bytes(rows, L)
+    ws = torch.full((wsb,), 0xff, dtype=torch.uint8, device="cuda")
+    out = []
+    for gl in (torch.empty(P, device="cuda"), None):
+        room = torch.full((x.size + 64,), float("nan"), device="cuda")
+        gy = room[32:32 + x.size]
+        tv.tv1d_prox_bwd(gt, xt, gy, gl, rows, L, ws, wsb)
+        assert torch.isnan(room[:32]).all() and torch.isnan(room[32 + x.size:]).all()
+        out.append((gy.cpu().numpy().reshape(x.shape), gl))
+    assert np.array_equal(out[0][0], out[1][0])
+    # a mean is a float of a sum in 64 bits; a slot adds up in 64 bits a float from each of W x 4 threads, in each the terms that lie
+    # in its chunk and a mean at either end
+    assert np.abs(out[0][0] - want).max() <= 2 * EPS * np.abs(g).max()
+    terms = np.abs(np.diff(want, axis=1)) * (np.diff(x, axis=1) != 0)
+    bound = EPS * (terms.sum((1, 2)) + W * 4 * 2 * np.abs(want).max((1, 2)) + np.abs(wl))
+    assert (np.abs(out[0][1].cpu().numpy() - wl) <= 1.01 * bound).all()
