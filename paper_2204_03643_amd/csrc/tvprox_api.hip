@@ -1454,11 +1454,13 @@ int tv2d_prox_fwd(const float *y, float *x, int64_t planes, int64_t H, int64_t W
         q.y = y; q.x = x; q.saved = saved(0); q.saved_stride = tb / sizeof(float); q.keep_passes = tvd::get(tvd::kFusedKeepsPasses) != 0 ? 1u : 0u;
         q.codes = codes(0); q.code_stride = cb / sizeof(uint2); q.tag = nullptr;
         if (masks) { q.codes = mask_codes; q.code_stride = mask_stride; q.tag = mask_tag; }
+        if (masks && !mask_codes && zero_floats((float *)mask_tag, 1, stream) != TV_OK) return TV_ERR_HIP;     // (asked for by override only)
         q.lam = lam.lam; q.lam_count = lam.count;
         q.planes = (int32_t)planes; q.H = (int32_t)H; q.W = (int32_t)W; q.sweeps = sweeps;
         q.stream = 0u;
         const dim3 grid((uint32_t)planes);
         if (cb) hipLaunchKernelGGL((tvk::tv2d_fwd_plane_kernel<16, 2>), grid, dim3(512), 0, stream, q);
+        else if (q.codes) hipLaunchKernelGGL((tvk::tv2d_fwd_plane_kernel<8, 8, false, true>), grid, dim3(512), 0, stream, q);
         else hipLaunchKernelGGL((tvk::tv2d_fwd_plane_kernel<8, 8>), grid, dim3(512), 0, stream, q);
         return launch_status();
     }
