@@ -760,13 +760,18 @@ __global__ __launch_bounds__(T < 256 ? 256 : T) void reduce_lambda_kernel(
     const uint32_t slot = blockIdx.x * SLOTS + threadIdx.x / T, t = threadIdx.x % T;
     // rows of this slot: r = (q*count + slot)*div + i,  i < div,  q = 0, 1, ...
     // thread t visits the pairs (q, i) with q*div + i = t, t + T, t + 2T, ...
-    const uint32_t dq = T / div, di = T - dq * div;
+    // (with the two divisions that this takes only where div lies between 1 and T: they are a good part of a small call's sum)
+    uint32_t dq = T, di = 0, q = t, i0 = 0;
+    if (div >= T && div > 1) {
+        dq = div == T ? 1u : 0u; di = div == T ? 0u : T; q = 0; i0 = t;
+    } else if (div > 1) {
+        dq = T / div; di = T - dq * div; q = t / div; i0 = t - q * div;
+    }
     const uint64_t stride = (uint64_t)count * div, hop = dq * stride;
     double acc[LOADS] = {};
     partial += blockIdx.y * batch_stride;
     for (uint32_t b = blockIdx.y; b < batches; b += gridDim.y, partial += gridDim.y * batch_stride) {
-        const uint32_t q = t / div;
-        uint32_t i = t - q * div;
+        uint32_t i = i0;
         uint64_t g0 = q * stride + (uint64_t)slot * div;            // where the group of row i starts
         bool more = slot < count;
         while (more) {
