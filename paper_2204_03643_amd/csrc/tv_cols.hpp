@@ -162,39 +162,46 @@ __global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
         }
     }
     const uint32_t gmask = jmask & inrow;      // jumps that count for dL/dlam
-    jmask |= ~inrow;                           // (the end of the row ends a segment; samples past it are their own)
+    const uint32_t end = nv < C ? 1u << nv : 0u;       // the end of the row ends a segment (what lies past it counts for nothing)
+    const uint32_t jumps = gmask | end, lowest = jumps & (0u - jumps);
     if constexpr (HAS_SUB) {
 #pragma unroll
         for (int i = 0; i < C; ++i) g[i] -= sb[i];
     }
-#define TV_JUMP(i) ((jmask >> (i)) & 1u)
-    const uint32_t jumps = C == 32 ? jmask : jmask & ((1u << (C & 31)) - 1u);
+#define TV_JUMP(i) ((jumps >> (i)) & 1u)
     // Segments that lie inside the chunk are done at once.  Sums and means in 64 bits: dL/dlam sees only differences of
     // means, each once at either end of its segment, with the signs of the jumps there, and those of a slot cancel.
+    // A mean's weight is 2 or -2 where the row turns at the segment's end, and 0 where it goes on rising or falling (an infinite mean or NaN
+    // shows there too): the signs of all jumps of a chunk and of the jumps before them come from a few operations on its masks, a carry
+    // taking the sign of a jump to the next one.
+    const uint32_t up = upmask & gmask, up_before = ((up << 1) + ~jumps) & jumps;
+    const uint32_t turns = (up ^ up_before) & gmask, falls = turns & ~up;
     double gl = 0.0;
-    float sign_first = 0.f, sign_last = 0.f;
+    bool any = false;
     {
-        double s = 0.0, head_s = 0.0;
+        double s = 0.0, head_s = 0.0, m = 0.0;
         float c = 0.f;
-        bool any = false;
 #pragma unroll
         for (int i = 0; i < C; ++i) {
             s += (double)g[i]; c += 1.f;
             if (TV_JUMP(i)) {
-                const float sign = (gmask >> i) & 1u ? (((upmask >> i) & 1u) ? 1.f : -1.f) : 0.f;
                 if (any) {
-                    const double m = mean64(s, c);
-                    if (SUMS) gl = fma((double)(sign - sign_last), m, gl);       // (also where the two cancel: an infinite mean, or NaN, shows)
+                    m = mean64(s, c);
+                    if (SUMS) {
+                        constexpr int TWO = 30;                  // (the bit of a double's upper half that makes it 2)
+                        const uint32_t two = i <= TWO ? turns << (TWO - i & 31) : turns >> (i - TWO & 31);
+                        const uint32_t w = (two & 1u << TWO) | (falls << (31 - i) & 1u << 31);
+                        gl = fma(__builtin_bit_cast(double, (uint64_t)w << 32), m, gl);
+                    }
                     g[i] = (float)m;
                 } else {
                     head_s = s;
-                    sign_first = sign;
                 }
-                sign_last = sign;
                 any = true;
                 s = 0.0; c = 0.f;
             }
         }
+        if (SUMS && (end & ~lowest) != 0u) gl += (up_before & end) != 0u ? -m : m;       // the row's last segment has a sign at one end only
         const double tail_s = s;
         if (!any) head_s = s;
         const uint32_t head_n = any ? (uint32_t)__builtin_ctz(jumps | 0x80000000u) + 1u : (uint32_t)C;
@@ -227,10 +234,10 @@ __global__ __launch_bounds__(T *G) void tv1d_bwd_cols_kernel(BwdParams p)
     __syncthreads();
     {
         const double head_m = first[t * P + col], tail_m = last[t * P + col];
-        if (SUMS && sign_first != 0.f) gl = fma((double)sign_first, head_m, gl);
-        if (SUMS && sign_last != 0.f) gl = fma(-(double)sign_last, tail_m, gl);
+        if (SUMS && (lowest & gmask) != 0u) gl += (up & lowest) != 0u ? head_m : -head_m;
+        const uint32_t highest = 0x80000000u >> __builtin_clz(jumps | 1u);
+        if (SUMS && (highest & gmask) != 0u) gl += (up & highest) != 0u ? -tail_m : tail_m;
         const float head = (float)head_m;
-        const uint32_t lowest = jumps & (0u - jumps);
         float carry = (float)tail_m;
 #pragma unroll
         for (int i = C - 1; i >= 0; --i) {
