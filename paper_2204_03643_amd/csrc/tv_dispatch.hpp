@@ -134,14 +134,32 @@ inline Threshold table[kCount] = {
     //   K = 10: 36 x 36, 800 planes 194 252 288, 4096: 629 995 722;  47 x 47 237 283 340, 777 1111 1038;
     //      52 x 56 278 295 364, 1300: 441 424 491, 4096: 1003 1163 1127;  63 x 63 330 306 430, 504 441 620, 1150 1229 1666;
     //      64 x 64 274 310 400, 428 444 515, 995 1227 1406.
-    // (Where pass by pass is level at K = 2, its reverse sweep, which reads pass outputs, takes half as long again.)
     //   K = 1: 800 planes 40 x 40 27 43 35, 56 x 56 40 49 44, 64 x 64 46 54 50, 44 x 48 41 47 38, 60 x 60 60 52 46; 1300: 40 59 42,
     //      60 71 59, 67 74 64.
     {"plane_per_group64_full_planes_k2", 560, "... planes of 40 x 40, 48 x 48, 56 x 56 and 64 x 64, two sweeps; two lanes a row beyond"},
     {"plane_per_group64_full_planes_k3", 560, "... three or four sweeps"},
     {"plane_per_group64_full_planes_k5", 560, "... five sweeps or more"},
-    {"pair_2d_planes", 704, "2D planes of 33-56 a side that fill four fifths of 40, 48 or 56: two lanes a row beyond this many planes (sides beyond 48: not from 1025 to plane_per_group64_planes_k2; one sweep: squares of 40, 48, 56 and 64, up to 1024)"},
-    {"pair_2d_many_planes", 2048, "2D planes of 57-64 a side that fill four fifths of 64, no squares, two sweeps or more: two lanes a row beyond this many planes"},
+    {"pair_2d_planes", 704, "2D planes of 33-56 a side that fill four fifths of 40, 48 or 56: two lanes a row beyond this many planes (up to 1024 on sides beyond 48; beyond plane_per_group64_planes_k2 from two to ten sweeps on, by how much of its square a plane fills; one sweep: squares of 40, 48, 56 and 64, up to 1024)"},
+    // Beyond plane_per_group64_planes_k2, no squares, forward and forward + reverse sweep, ratio to the better way of the kernels that left
+    // pass outputs only (pass by pass beyond 1280 planes, as now with few sweeps):
+    //                     two lanes a row                                    pass by pass
+    //      K = 2:  1700 planes   3100        9000       1700        3100        9000
+    //      36 x 40  1.01 0.95  1.05 1.04  1.05 1.02   1.00 0.97  0.99 1.02  0.98 1.01
+    //      41 x 48  1.17 1.06  1.13 1.10  1.12 1.07   0.99 0.97  1.00 1.03  1.04 1.07
+    //      47 x 47  0.98 0.86  0.98 0.89  0.92 0.68   0.92 0.87  0.95 0.91  0.95 0.75
+    //      49 x 56  1.13 1.05  1.24 1.17  1.10 1.05   0.99 0.96  1.01 1.03  1.03 1.05
+    //      60 x 60  1.18 1.02  1.20 1.06  1.09 1.03   1.01 0.98  1.01 0.98  1.01 0.99
+    //      63 x 63  0.95 0.86  0.92 0.83  0.86 0.61   0.87 0.89  0.86 0.84  0.87 0.64
+    //      K = 3:  36 x 40 0.96 0.92, 0.98 0.98, 0.99 0.98;  41 x 48 1.07 1.01, 1.04 1.03, 1.03 1.01;  33 x 33 0.92 0.80, 0.98 0.85, 1.07 0.83
+    //              against 0.91 0.83, 0.91 0.85, 0.94 0.81;  53 x 55 0.91 0.84, 0.90 0.84, 0.85 0.59;  50 x 50 0.97 0.88, 1.02 0.95, 0.94 0.66
+    //      K = 4:  41 x 48 0.98 0.95, 0.98 0.99, 1.00 0.99;  50 x 50 0.91 0.84, 0.99 0.90, 0.92 0.63;  49 x 56 1.00 0.96, 1.13 1.08, 1.02 1.00;
+    //              60 x 60 1.02 0.92, 1.07 0.94, 0.98 0.92;  64 x 60 0.94 0.85, 1.00 0.90, 0.91 0.87;  60 x 64 1.08 0.91, 1.12 0.97, 1.03 0.95
+    //      K = 6:  52 x 56 0.94 0.92, 1.04 1.02;  49 x 56 0.95 0.93, 1.10 1.06;  60 x 60 0.97 0.86, 1.01 0.89;  62 x 64 1.05 0.88, 1.09 0.94
+    //      K = 10: 49 x 56 0.90 0.89, 1.05 1.03;  60 x 64 0.99 0.84, 1.05 0.89.
+    // A plane per workgroup, 1700 and 2600 planes (K = 2: 57 x 58 1.00 0.90, 1.05 0.97;  60 x 60 1.09 0.96, 1.16 1.03;  63 x 63 0.87 0.80, 0.91 0.85):
+    //      K = 3:  57 x 58 0.91 0.84, 0.96 0.88;  60 x 60 0.97 0.87, 1.09 0.94;  58 x 64 1.08 0.91, 1.16 0.94;
+    //      K = 4:  57 x 58 0.86 0.81, 0.92 0.84;  60 x 60 0.95 0.87, 1.05 0.92;  58 x 64 1.03 0.89, 1.11 0.92.
+    {"pair_2d_many_planes", 2560, "2D planes of 57-64 a side that fill four fifths of 64, no squares: a plane per workgroup up to this many planes (four fifths of it: three sweeps, and rows of 64 with four; plane_per_group64_planes_k2: two sweeps but for ragged rows), two lanes a row beyond (rows of 64 never, others from two to six sweeps on)"},
     // 2D reverse sweep of small batches with a plane per workgroup (tv_plane2d.hpp): both adjoint
     // state tensors of the plane in LDS, 16 x 2 or 8 x 8 threads x samples per row, the segment
     // sums across a row's threads by row shifts.  Against the row-per-lane one-launch kernel (a

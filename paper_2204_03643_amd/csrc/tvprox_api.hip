@@ -1338,8 +1338,35 @@ static bool pairs_2d_apply(int64_t H, int64_t W)
     return longer > 32 && longer <= 64 && 5 * shorter >= 4 * ((longer + 7) / 8 * 8);
 }
 
-// The forward call on these.  Time goes in rounds of 1024 planes (two waves a plane, four planes a CU), and what a
-// plane lacks of its square is worked on all the same, so an early second round is left to the other kernel where
+// The forward call on these, row masks and several sweeps, beyond plane_per_group64_planes_k2: from how many sweeps on it goes in one
+// launch, no squares.  Pass by pass costs two launches a sweep and a trip through memory for each, but works on the samples that are there,
+// and its row passes read rows of no multiple of four samples at half the rate.  The measurements are in tv_dispatch.hpp.
+static int one_launch_sweeps_2d(int64_t planes, int64_t H, int64_t W)
+{
+    const int64_t longer = H > W ? H : W, side = (longer + 7) / 8 * 8, group_most = tvd::get(tvd::kPlanePerGroup64PlanesK2);
+    if (W % 4 != 0) return 20 * H * W < 17 * side * side ? 4 : planes > 4 * group_most ? 2 : 3;
+    const bool full = 10 * H * W >= 9 * side * side;
+    if (longer <= 48) return full ? 3 : 4;
+    if (longer <= 56) return full ? 6 : 10;
+    return W == 64 ? 4097 : full ? 4 : 6;               // (rows of 64 fill the row pass' registers: never)
+}
+
+// ... with a plane per workgroup, up to this many planes.
+static int64_t plane_per_group64_most(int64_t H, int64_t W, int sweeps)
+{
+    if (sweeps == 1) return tvd::get(tvd::kPlanePerGroup64Planes);
+    const int64_t most = tvd::get(tvd::kPlanePerGroup64PlanesK2), many = tvd::get(tvd::kPair2dManyPlanes);
+    if (!pairs_2d_apply(H, W) || !row_masks_2d(H, W) || (H <= 56 && W <= 56)) return most;
+    // sides of 57-64, where two lanes a row pay for what a plane lacks of 64 x 64
+    int64_t farther = most;
+    if (W % 4 != 0) farther = sweeps >= (20 * H * W >= 17 * 64 * 64 ? 2 : 3) ? many : most;
+    else if (W == 64) farther = sweeps >= 4 ? many - many / 5 : most;
+    else if (sweeps >= 3) farther = sweeps >= 4 ? many : many - many / 5;
+    return farther > most ? farther : most;
+}
+
+// The forward call on planes that two lanes a row can take.  Time goes in rounds of 1024 planes (two waves a plane, four planes a CU), and what a
+// plane lacks of its square is worked on all the same, so an early second round is left to the other kernels where
 // that is much (measurements: tv_dispatch.hpp).  One sweep: squares in the first round.
 static bool pairs_2d_fwd(int64_t planes, int64_t H, int64_t W, int sweeps)
 {
@@ -1351,17 +1378,21 @@ static bool pairs_2d_fwd(int64_t planes, int64_t H, int64_t W, int sweeps)
         return planes > tvd::get(sweeps == 2 ? tvd::kPlanePerGroup64FullPlanesK2
                                              : (sweeps <= 4 ? tvd::kPlanePerGroup64FullPlanesK3 : tvd::kPlanePerGroup64FullPlanesK5));
     if (!row_masks_2d(H, W)) return beyond && planes <= group_most;         // (one side of 32: pass outputs, not masks)
-    if (longer <= 48) return beyond;
-    if (longer <= 56) return beyond && (planes <= 1024 || planes > group_most);
-    return planes > tvd::get(tvd::kPair2dManyPlanes);
+    if (longer <= 56) {
+        if (planes <= (longer <= 48 ? group_most : 1024)) return beyond;
+        return beyond && planes > group_most && sweeps >= one_launch_sweeps_2d(planes, H, W);
+    }
+    const int64_t many = tvd::get(tvd::kPair2dManyPlanes);
+    if (many == 0) return true;                                             // (moved there by override only)
+    return planes > many && planes > group_most && sweeps >= one_launch_sweeps_2d(planes, H, W);
 }
 
 // The reverse sweep of these, in one launch with two lanes a row, beyond the counts up to which a plane per workgroup is
 // faster; the measurements are in tv_dispatch.hpp.  masks: the forward call is one that leaves row masks; the
 // plane per workgroup then reads next to nothing, and what a plane lacks of its square or a late round of it lacks of
 // 1024 planes decides.  With pass outputs, planes that do not fill their square stay out, with one sweep or sides beyond 56,
-// where a second or third round is mostly empty, and with one sweep and ragged rows where they fill less than four
-// fifths of it.
+// where a second or third round is mostly empty, and with ragged rows where they fill less than four fifths of it (one sweep) or have sides
+// beyond 56 (several: 3100 planes of 57 x 58, K = 3, 1.6 times a plane per workgroup, 64 registers spilled).
 static bool pairs_2d_bwd(int64_t planes, int64_t H, int64_t W, int sweeps, bool masks)
 {
     if (!pairs_2d_apply(H, W)) return false;
@@ -1374,7 +1405,7 @@ static bool pairs_2d_bwd(int64_t planes, int64_t H, int64_t W, int sweeps, bool 
     }
     if (square) return planes > most;
     if (longer <= 56 && sweeps >= 2) return planes > most;
-    if (sweeps == 1 && W % 4 != 0 && 5 * H * W < 4 * side * side) return false;
+    if (W % 4 != 0 && (sweeps == 1 ? 5 * H * W < 4 * side * side : longer > 56)) return false;
     return planes > (longer <= 56 ? most : most + most / 2) && (planes <= 1024 || planes >= 3072);
 }
 
@@ -1390,10 +1421,7 @@ static bool plane_per_group_2d(int64_t planes, int64_t H, int64_t W, int sweeps)
         return small_side(H, W) == 32 && planes <= most + (oblong ? 3 * (most / 4) : sweeps == 1 ? 0 : most / 3);
     }
     if (H > 64 || W > 64 || pairs_2d_fwd(planes, H, W, sweeps)) return false;
-    const int64_t most = tvd::get(sweeps == 1 ? tvd::kPlanePerGroup64Planes : tvd::kPlanePerGroup64PlanesK2);
-    // (up to where two lanes a row take over from it: the others would pay a launch a pass)
-    const bool far = sweeps >= 2 && pairs_2d_apply(H, W) && row_masks_2d(H, W) && (H > 56 || W > 56);
-    return planes <= (far ? most + 3 * (most / 5) : most);
+    return planes <= plane_per_group64_most(H, W, sweeps);
 }
 
 // Whether some forward call on such planes can have left row masks, and whether one now would.  (As with the chunk codes,
