@@ -399,9 +399,15 @@ def dispatch_probe(dev) -> int:
         case(name, "at_threshold_%dx%d_k%d" % (H, W, K), lambda: two_d(n, H, W, K), 0, "a plane per workgroup", beyond)
         case(name, "beyond_%dx%d_k%d" % (H, W, K), lambda: two_d(n + n // 4, H, W, K), big, beyond, "a plane per workgroup")
     n = defaults["pair_2d_many_planes"]
-    for H, W, K in ((57, 58, 3), (60, 60, 2)):
+    for H, W, K in ((64, 60, 4), (63, 63, 3)):
         case("pair_2d_many_planes", "at_threshold_%dx%d_k%d" % (H, W, K), lambda: two_d(n, H, W, K), 0, "a plane per workgroup", "two lanes a row")
-        case("pair_2d_many_planes", "beyond_%dx%d_k%d" % (H, W, K), lambda: two_d(n + n // 4, H, W, K), big, "two lanes a row", "pass by pass")
+        case("pair_2d_many_planes", "beyond_%dx%d_k%d" % (H, W, K), lambda: two_d(n + n // 4, H, W, K), big, "two lanes a row",
+             "a plane per workgroup")
+    n = defaults["bwd_few_columns"]
+    for side in (64, 128, 256):
+        case("bwd_few_columns", "at_threshold_%d" % side, lambda: two_d(n // side, side, side, 1), 0, "twice the threads a column", "the others")
+        case("bwd_few_columns", "beyond_%d" % side, lambda: two_d(n // side + n // (4 * side), side, side, 1), big, "the threads of large calls",
+             "twice as many")
     for name, H, W, K, other in (("plane_per_group_bwd_planes", 32, 32, 4, "a row per lane"),
                                  ("plane_per_group64_bwd_planes", 64, 64, 4, "two lanes a row"),
                                  ("plane_per_group64_bwd_ragged_planes", 40, 46, 1, "pass by pass"),

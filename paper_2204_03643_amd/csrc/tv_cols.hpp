@@ -327,10 +327,7 @@ inline hipError_t launch_bwd_cols_t(BwdParams p, hipStream_t s)
 inline hipError_t launch_bwd_cols(const BwdParams &p, hipStream_t s)
 {
     const int n = p.L.n;
-    // Few columns: half the samples a thread and groups of 16, for shorter chains and more workgroups (3 planes of
-    // 166 x 200 6.0 -> 4.8 us, with sub 6.5 -> 5.1; 20 of 128 x 128 4.9 -> 4.1; 120 of 120 x 120, 14 400 columns, 7.4 -> 6.7;
-    // 40 of 256 x 256 8.1 -> 7.5).
-    if (p.L.n_rows <= 16384) {
+    if ((int64_t)p.L.n_rows <= tvd::get(tvd::kBwdFewColumns)) {
         if (n <= 64) return launch_bwd_cols_t<16, 4, 1, 16>(p, s);
         if (n <= 96) return launch_bwd_cols_t<16, 6, -2, 16>(p, s);
         if (n <= 128) return launch_bwd_cols_t<16, 8, 1, 16>(p, s);

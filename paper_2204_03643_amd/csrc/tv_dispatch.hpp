@@ -46,6 +46,7 @@ enum {
     kOneLambdaTriSide,
     kMlMinLength,
     kMlCoarsest,
+    kBwdFewColumns,
     kCount
 };
 
@@ -301,6 +302,10 @@ inline Threshold table[kCount] = {
     // 111 / 88 / 88, 99 / 81 / 81; 8192 (32M samples): 320 / 308 / 284, 331 / 314 / 290, 307 / 294 / 271;
     // 16 384 (32M): 398 / 385 / 356, 395 / 380 / 352, 389 / 376 / 351.
     {"ml_coarsest", 4096, "coarsest level of the multilevel start"},
+    // Backward along few columns of 33-256 samples: half the samples a thread and groups of 16 columns, for shorter chains and more
+    // workgroups (3 planes of 166 x 200 6.0 -> 4.8 us, with sub 6.5 -> 5.1; 20 of 128 x 128 4.9 -> 4.1; 120 of 120 x 120, 14 400
+    // columns, 7.4 -> 6.7; 40 of 256 x 256 8.1 -> 7.5).
+    {"bwd_few_columns", 16384, "backward along columns of 33-256 samples: twice the threads a column up to this many columns"},
 };
 
 inline int64_t get(int which) { return table[which].value; }

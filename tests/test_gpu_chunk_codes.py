@@ -33,6 +33,34 @@ def test_codes_and_kept_passes_give_the_same_bits(H, W, K, count):
     assert np.array_equal(kept["saved"][2 * K - 1], kept["x"], equal_nan=True)
 
 
+@pytest.mark.parametrize("H,W,K,count", [(65, 96, 1, 2), (96, 70, 2, 3), (97, 65, 2, 3), (128, 97, 3, 1), (129, 192, 2, 2), (192, 66, 1, 3), (256, 193, 1, 1)])
+def test_codes_read_by_the_columns_of_a_large_call(H, W, K, count):
+    """The same with the mappings that more than "bwd_few_columns" columns have, whose threads read a word or two each where
+    those of few columns read half a word or one; and the two mappings agree to rounding."""
+    import paper_2204_03643_amd as tv
+    rng = np.random.default_rng(H * 1000 + W)
+    y = (np.cumsum(rng.normal(scale=0.05, size=(3, H, W)), axis=-2) + rng.normal(scale=0.2, size=(3, H, W))).astype(np.float32)
+    g = rng.normal(size=y.shape).astype(np.float32)
+    lam = (10 ** rng.uniform(-2, 0, size=count)).astype(np.float32)
+    saved = {k: tv.tv_dispatch_threshold(k) for k in ("chunk_codes_bytes", "bwd_few_columns")}
+    try:
+        tv.tv_dispatch_override("chunk_codes_bytes", 0)
+        few = run_2d(y, lam, K, g, keep_passes=False)
+        tv.tv_dispatch_override("bwd_few_columns", 0)
+        lean = run_2d(y, lam, K, g, keep_passes=False)
+        kept = run_2d(y, lam, K, g, keep_passes=True)
+    finally:
+        for k, v in saved.items():
+            tv.tv_dispatch_override(k, v)
+    for k in ("x", "gy", "gl"):
+        assert np.array_equal(kept[k], lean[k]), k
+    # sums of 64 bits over other chunks: a mean may round the other way in each of the 2 K passes; and the floats that threads
+    # leave of dL/dlam, at most 16 a column of two means each, in each of the K column passes
+    largest = max(np.abs(g).max(), np.abs(few["gy"]).max())
+    assert np.abs(few["gy"] - lean["gy"]).max() <= 2 * K * 2.0 ** -23 * largest
+    assert np.abs(few["gl"] - lean["gl"]).max() <= 2.0 ** -23 * (K * 3 * W * 16 * 2 * largest + np.abs(few["gl"]).max())
+
+
 def test_reverse_sweep_twice_on_one_workspace():
     """The reverse sweep only reads the codes: a second one on the same workspace gives the same bits
     (63 lambdas: the reduction split over the most workgroups it has, beside the word that tells

@@ -1,4 +1,5 @@
-"""Backward along columns of 33-1024 samples, at the edges of the thread mappings, against the oracle."""
+"""Backward along columns of 33-1024 samples, at the edges of the thread mappings for few and for many columns, against the
+oracle."""
 import numpy as np
 import pytest
 
@@ -18,14 +19,33 @@ def _piecewise(rng, P, n, W):
     return np.take_along_axis(level, ids, axis=1)
 
 
+@pytest.fixture
+def columns(request):
+    """The mappings for few columns, and those for many (other ones up to 256 samples) on the same small calls."""
+    import paper_2204_03643_amd as tv
+    line = tv.tv_dispatch_threshold("bwd_few_columns")
+    if request.param == "many":
+        tv.tv_dispatch_override("bwd_few_columns", 0)
+    yield request.param
+    tv.tv_dispatch_override("bwd_few_columns", line)
+
+
+def _lengths(*ns):
+    return [(n, kind) for n in ns for kind in (("few", "many") if n <= 256 else ("few",))]
+
+
+# 3 x 37 columns: groups of columns that span planes, and a last one partly filled; 41 x 41: 53 groups of 32 or 106 of 16, runs of which
+# share an XCD, the last ones in launch order
+@pytest.mark.parametrize("P,W", [(3, 37), (41, 41)])
 @pytest.mark.parametrize("slots", ["one", "plane", "column"])
-@pytest.mark.parametrize("n", [33, 63, 64, 65, 96, 97, 128, 129, 192, 193, 256, 257, 384, 385, 512, 513, 768, 769, 1024])
-def test_columns(n, slots):
+@pytest.mark.parametrize("n,columns", _lengths(33, 63, 64, 65, 96, 97, 128, 129, 192, 193, 256, 257, 384, 385, 512, 513, 768, 769, 1024),
+                         indirect=["columns"])
+def test_columns(n, slots, P, W, columns):
     import torch
 
     import paper_2204_03643_amd as tv
 
-    P, W, dev = 3, 37, torch.device("cuda:0")      # (groups of columns that span planes, and a last one partly filled)
+    dev = torch.device("cuda:0")
     rng = np.random.default_rng(n)
     x = _piecewise(rng, P, n, W)
     g = rng.normal(size=x.shape).astype(np.float32)
@@ -41,23 +61,24 @@ def test_columns(n, slots):
     torch.cuda.synchronize()
     assert torch.isnan(room[:32]).all() and torch.isnan(room[32 + x.size:]).all()
     want, wl = oracle.prox1d_bwd_batch(g, x, lam_count=count, axis=1, lam_div=div)
-    # a mean: at most 2 x 32 additions inside a chunk, 7 across chunks and a reciprocal (2), each half an ulp of a sum
-    # of at most count * max|g|
-    mean_err = 73 * EPS * np.abs(g).max()
-    assert np.abs(gy.cpu().numpy().reshape(x.shape) - want).max() <= mean_err
-    # a slot: two means a jump, and at most 32 + 64 + 5 additions of what they leave
+    # sums and means in 64 bits: what shows is the rounding of the mean to a float
+    mean_err = 2.0 ** -40 * np.abs(g).max()
+    assert (np.abs(gy.cpu().numpy().reshape(x.shape) - want) <= EPS * np.abs(want) + mean_err).all()
+    # a slot: a float from every thread with a jump, in each the terms that lie in its chunk and a mean at either end; a float a
+    # column where columns do not leave in groups; and the slot's own
     jump = np.diff(x, axis=1) != 0
     terms = (np.abs(np.diff(want, axis=1)) * jump).sum(1).reshape(-1)
     jumps = jump.sum(1).reshape(-1)
+    largest = np.abs(want).max(1).reshape(-1)
     slot = (np.arange(P * W) // div) % count
     bound = np.zeros(count)
-    np.add.at(bound, slot, 2 * jumps * mean_err + 102 * EPS * terms)
-    assert (np.abs(gl.cpu().numpy() - wl) <= bound + EPS * np.abs(wl)).all()
+    np.add.at(bound, slot, EPS * (2 * terms + 2 * np.minimum(jumps, 64) * largest) + 2 * jumps * mean_err)
+    assert (np.abs(gl.cpu().numpy() - wl) <= 1.01 * bound + EPS * np.abs(wl)).all()
 
 
-@pytest.mark.parametrize("n", [40, 100, 300, 1000])
+@pytest.mark.parametrize("n,columns", _lengths(40, 100, 200, 300, 1000), indirect=["columns"])
 @pytest.mark.parametrize("bad", [float("nan"), float("inf"), -3e38])
-def test_one_bad_sample_stays_in_its_segment(n, bad):
+def test_one_bad_sample_stays_in_its_segment(n, bad, columns):
     import torch
 
     import paper_2204_03643_amd as tv
@@ -78,7 +99,7 @@ def test_one_bad_sample_stays_in_its_segment(n, bad):
         gy = torch.empty_like(ht)
         tv.tv1d_prox_bwd(ht, xt, gy, None, rows, L, None, 0)
         got = gy.cpu().numpy()
-        assert np.abs(got - want)[~hit].max() <= 73 * EPS * np.abs(g).max()
+        assert (np.abs(got - want) <= EPS * np.abs(want) + 2.0 ** -40 * np.abs(g).max())[~hit].all()
         if bad != -3e38:
             assert not np.isfinite(got[hit]).any()
 
@@ -97,9 +118,9 @@ def _lambda_grads(x, g, count, div):
     return gl.cpu().numpy()
 
 
-@pytest.mark.parametrize("n", [40, 100, 300, 1000])
+@pytest.mark.parametrize("n,columns", _lengths(40, 100, 200, 300, 1000), indirect=["columns"])
 @pytest.mark.parametrize("bad", [float("inf"), -float("inf"), 3e38])
-def test_an_infinite_lambda_gradient(n, bad):
+def test_an_infinite_lambda_gradient(n, bad, columns):
     """A slot whose terms add up to an infinity has it as its gradient, whether one column or many share the slot."""
     W = 64
     x = np.zeros((1, n, W), np.float32)
@@ -114,9 +135,9 @@ def test_an_infinite_lambda_gradient(n, bad):
     assert np.array_equal(_lambda_grads(x, g, 4, 16), [want] + ([0] * 3 if np.isinf(bad) else [want] * 3))
 
 
-@pytest.mark.parametrize("n", [40, 100, 300, 1000])
+@pytest.mark.parametrize("n,columns", _lengths(40, 100, 200, 300, 1000), indirect=["columns"])
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
-def test_a_bad_segment_on_a_staircase_shows(n, bad):
+def test_a_bad_segment_on_a_staircase_shows(n, bad, columns):
     """Between two rises a segment's mean enters once with either sign: an infinity or NaN there leaves NaN, wherever the segment
     lies in its thread's chunk."""
     W = n - 8

@@ -1,5 +1,5 @@
-"""Planes with both sides of 33-64 samples: the reverse sweep from row masks has the bits it has from pass outputs, whichever
-mappings wrote and read them, and finds out by itself which of the two a workspace holds."""
+"""Planes with both sides of 33-64 samples: the reverse sweep from row masks has the bits that the same mapping has from pass
+outputs, whichever mapping wrote them, and finds out by itself which of the two a workspace holds."""
 import itertools
 
 import numpy as np
@@ -78,10 +78,13 @@ def test_every_writer_with_every_reader(H, W, overrides):
         overrides(fused_keeps_passes=1, plane_per_group64_bwd_planes=0 if reader == "pairs" else big,
                   plane_per_group64_bwd_ragged_planes_k2=big if reader == "planes" else 0)
         tv.tv2d_prox_bwd(gt, gy, gl, 3, H, W, L, K, ws, wsb)
+        # masks or pass outputs: the same segments, and the same bits from one reader
+        for a, b in zip((x, gy, gl), first.setdefault((writer, reader), (x, gy, gl))):
+            assert torch.isfinite(a).all() and torch.equal(a, b), (writer, keep, reader)
+        # another reader rounds its means differently
         want = first.setdefault(writer, (x, gy, gl))
         assert torch.equal(x, want[0])
         for a, b in zip((gy, gl), want[1:]):
-            assert torch.isfinite(a).all()
             assert (a - b).abs().max() <= 2e-5 * (1 + b.abs().max()), (writer, keep, reader)
 
 
