@@ -404,7 +404,7 @@ def dispatch_probe(dev) -> int:
         case("pair_2d_many_planes", "beyond_%dx%d_k%d" % (H, W, K), lambda: two_d(n + n // 4, H, W, K), big, "two lanes a row",
              "a plane per workgroup")
     n = defaults["bwd_few_columns"]
-    for side in (64, 128, 256):
+    for side in (128, 256):
         case("bwd_few_columns", "at_threshold_%d" % side, lambda: two_d(n // side, side, side, 1), 0, "twice the threads a column", "the others")
         case("bwd_few_columns", "beyond_%d" % side, lambda: two_d(n // side + n // (4 * side), side, side, 1), big, "the threads of large calls",
              "twice as many")

@@ -123,7 +123,8 @@ int tv1d_prox_fwd_info(const float *y, float *x, int32_t *info, tv_rows rows, tv
  *           its dual, prolonged, is where the Newton iteration of the row itself starts.  The
  *           paper does not fix the starting point (Sec. 3.2); the minimiser is the same, and
  *           rows whose lambda is large against their sample-to-sample variation take 4 steps
- *           instead of 10-30.  Scratch: half of the input's size.  Without ws (and in tv1d_prox_fwd) the same start is taken
+ *           instead of 10-30.  Scratch: half of the input's size (a single
+ *           level, the default, uses the half of that which holds its duals).  Without ws (and in tv1d_prox_fwd) the same start is taken
  *           with the levels of a row kept in that row of x until the fine level overwrites it,
  *           whenever the rows are packed (no gap between them) and x does not overlap y; the
  *           results are bit-identical to those with ws.  A call in place (x == y) and rows

@@ -68,10 +68,10 @@ __device__ __forceinline__ double open_sum64(double v, int dist, int lane)
 // lane where a segment ends turn them into the two means that each chunk needs: that of the segment open at its
 // start and that of the one open at its end.
 // Bound by memory, and by the vector ALUs on columns of at most 64 samples: 24 planes of 512 x 512, backward with its
-// lambda sum, 26.7 -> 20.5 us (75 MB); 8M samples in planes of 33 / 64 / 100 / 200 / 481 / 900 a side
-// 124 / 69 / 65 / 44 / 44 / 47 -> 37 / 25 / 26 / 26 / 27 / 28.  (Before, every tensor crossed an LDS tile that turned columns into
+// lambda sum, 26.9 -> 19.1 us (75 MB); 8M samples in planes of 33 / 64 / 100 / 200 / 481 / 900 a side
+// 128 / 71 / 67 / 45 / 45 / 47 -> 35 / 25 / 26 / 25 / 26 / 27.  (Before, every tensor crossed an LDS tile that turned columns into
 // rows and back.)  Error against 64 bits, thirty calls: grad_y 6.3e-8 -> 2.5e-8, dL/dlam 3.1e-7 -> 4.0e-8; with
-// sums and means in 32 bits and dL/dlam in 64, 4.8e-8 and 2.4e-7, at 19.0 us: one lambda's gradient cancels, and was
+// sums and means in 32 bits and dL/dlam in 64, 4.8e-8 and 2.4e-7, at 19.0 us where 64 bits then took 20.5: one lambda's gradient cancels, and was
 // further off than before in one call of ten.
 // G: 32 columns, a line, where that leaves workgroups of at most 512 threads, 16 beyond (512 a side, with sub: 18.5 us, with 32
 // columns 21.6; 768, no sub, 64 threads of 12 samples 19.8, 32 threads of 24 and 32 columns 23.8).

@@ -303,8 +303,9 @@ inline Threshold table[kCount] = {
     // 16 384 (32M): 398 / 385 / 356, 395 / 380 / 352, 389 / 376 / 351.
     {"ml_coarsest", 4096, "coarsest level of the multilevel start"},
     // Backward along few columns of 33-256 samples: half the samples a thread and groups of 16 columns, for shorter chains and more
-    // workgroups (3 planes of 166 x 200 6.0 -> 4.8 us, with sub 6.5 -> 5.1; 20 of 128 x 128 4.9 -> 4.1; 120 of 120 x 120, 14 400
-    // columns, 7.4 -> 6.7; 40 of 256 x 256 8.1 -> 7.5).
+    // workgroups.  With dL/dlam, this / the mapping for more columns, us:
+    //    40 samples, 4096 columns 7.1 / 8.3, 16 384:  8.5 /  9.3, 32 768: 11.9 / 11.2;  128: 7.2 / 8.1, 10.2 / 10.3, 15.3 / 15.5;
+    //   160 samples, 4096 columns 8.7 / 9.0, 16 384: 12.4 / 11.5, 32 768: 21.8 / 18.5;  256: 8.2 / 9.5, 14.4 / 14.4, 23.1 / 22.2.
     {"bwd_few_columns", 16384, "backward along columns of 33-256 samples: twice the threads a column up to this many columns"},
 };
 

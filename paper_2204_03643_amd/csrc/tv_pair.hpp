@@ -506,8 +506,8 @@ __device__ __forceinline__ uint32_t pair_live(int cut, bool right)
 // between passes through one LDS tile, whose rows and columns both lie as PairTile has them.  As in
 // tv2d_fwd_small_kernel the tile also parks the solver's input, and the correction term that is not in
 // use lives in a lane-private LDS column.  Planes of at most 32 x 32 leave segment codes for the reverse
-// sweep, larger ones row masks (1024 planes of 64 x 64, K = 4, forward + reverse sweep 186 -> 177 us,
-// 2000 of 47 x 47, K = 3, 307 -> 265) or, where those are asked for, their pass outputs.
+// sweep, larger ones row masks (1024 planes of 64 x 64, K = 4, forward + reverse sweep 184 -> 173 us,
+// 2000 of 47 x 47, K = 3, 312 -> 260) or, where those are asked for, their pass outputs.
 // Registers: four waves a SIMD up to 32 x 32 (a fifth, at 96 registers, spills and is 10 % slower), two beyond,
 // where LDS holds no more (33 KB a plane).
 // ---------------------------------------------------------------------------------
@@ -955,7 +955,7 @@ __global__ __launch_bounds__(64, C > 16 ? 3 : 4) void tv1d_fwd_pair_kernel(FwdPa
 // waves and chains of 32.  Both adjoint state tensors of the plane lie in LDS as PairTile has them; of
 // a pass's output a lane reads its half row one pass ahead, rows in 16-byte pieces, columns in rows of 32
 // neighbouring columns, and keeps a jump and a direction bit a sample.
-// Row masks in place of pass outputs (p.tag): 1024 planes of 64 x 64, K = 4, 49.7 -> 43.4 us, 1000 of 50 x 50, K = 10, 97 -> 86.
+// Row masks in place of pass outputs (p.tag): 1024 planes of 64 x 64, K = 4, with the lambda sum 48 -> 38 us.
 // Reverse sweep of 1024 planes of 64 x 64, K = 4, a row per lane / two lanes: 69 / 48 us, 8192 planes, K = 2: 290 / 180;
 // 1024 planes of 40 x 40, K = 4, a plane per workgroup / two lanes: 56 / 31.
 // At most 2C / 5 samples short of 2C.

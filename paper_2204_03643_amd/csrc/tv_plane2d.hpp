@@ -24,7 +24,7 @@ namespace tvk {
 // T threads per row, C samples per thread: planes of at most S x S, S = T * C (16 x 2: up to
 // 32 x 32, with segment codes for the reverse sweep; 8 x 8: up to 64 x 64, with row masks where both sides are
 // longer than 32 and the passes are not asked for, pass outputs otherwise).  With masks, 256 planes of
-// 64 x 64, K = 4: forward 73 -> 68 us, reverse sweep 33 -> 20.  One plane per workgroup of S * T = 512 threads.
+// 64 x 64, K = 4: forward 73 -> 68 us, reverse sweep 33 -> 19.  One plane per workgroup of S * T = 512 threads.
 // (32 x 32 with 8 threads x 4 samples, 256 threads: 256 planes, K = 4, 52 us against 38 with
 // 16 x 2, whose chains are shorter; from 1500 planes on 8 x 4 is 5-10 % ahead, where the
 // row-per-lane kernels take over anyway.)

@@ -504,7 +504,8 @@ constexpr int kMlMaxLevels = 8;                // (where it starts and ends: tv_
 struct MlPlan {
     int levels;                       // coarse levels 1 .. levels (0 = the row itself)
     int64_t n[kMlMaxLevels + 1];
-    // scratch in a workspace: every level's rows packed, level after level (byte offsets)
+    // scratch in a workspace: every level's rows packed, level after level (byte offsets).  A single level that forms its averages
+    // itself, as it does with the default thresholds, does not touch its y; the room stays, since callers have stored the size.
     size_t y_off[kMlMaxLevels + 1], u_off[kMlMaxLevels + 1], flag_off, bytes;
     // scratch inside the output rows: all levels of a row within the row's own n floats (offsets
     // in floats from the start of the row, multiples of 4); row_floats = 0 if they do not fit
@@ -535,7 +536,8 @@ bool ml_plan(const tv_rows &r, int64_t n_rows, MlPlan *pl)
     return pl->levels > 0;
 }
 
-// out[row][j] = mean of in[row][kMlFactor j ...] (the samples that exist); one workgroup per row.
+// out[row][j] = mean of in[row][kMlFactor j ...] (the samples that exist); one workgroup per row.  For stacked levels and for
+// lengths below the default ml_min_length (both by override).
 // FIRST: `in` is the caller's tensor (rows by L), and the row's flag is decided here from the mean
 // absolute difference of neighbouring samples inside the groups; otherwise `in` holds n_in samples
 // per row, in_pitch floats apart, and rows with flag 0 are skipped.  out: out_pitch floats apart;
@@ -609,7 +611,7 @@ __global__ __launch_bounds__(256) void ml_average_kernel(const float *__restrict
 static_assert(tvk::kMlFactor == 4, "ml_average_kernel loads groups as float4");
 
 // The forward call on long rows with the multilevel start; p is the fine level, fully set up.
-// ws: the levels' scratch (MlPlan's workspace layout), or null: then every row's levels live in
+// ws: the levels' scratch (MlPlan's workspace layout, whose y a single level leaves alone), or null: then every row's levels live in
 // that row of the output p.x (MlPlan's in-row layout; packed rows, p.x apart from p.y), which the
 // fine level overwrites at its very end, after the one workgroup or wave that owns the row has
 // read the row's coarse dual at its start.
