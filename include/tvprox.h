@@ -262,7 +262,8 @@ int tv1d_prox_bwd_seg_bf16(const uint16_t *g_up, const uint64_t *seg, uint16_t *
  * after tv_dispatch_override("fused_keeps_passes", 1)), or codes in their place: where planes with both
  * sides of 33-64 samples run all their passes in one launch, and on sides of 65-768 samples from
  * "chunk_codes_bytes" of pass outputs on (the pass outputs instead after the
- * same override; the backward call finds out from the workspace).  x must not alias y.
+ * same override; the backward call finds out from the workspace, where with the
+ * thresholds as they are, or any that this process has overridden, it can be either).  x must not alias y.
  * From the second sweep on, the correction term a pass adds to its input is D^T u of the
  * same pass one sweep earlier (x = y - D^T u), and the pass starts its Newton iteration
  * from that dual.  Planes of at most 64 x 64 run all their passes in one launch where that is

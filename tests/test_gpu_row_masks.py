@@ -150,3 +150,31 @@ def test_one_launch_or_pass_by_pass(planes, H, W, K, masks):
     assert (x - x1).abs().max() <= 2e-5 * (1 + y.abs().max())
     # a jump of rounding size more or less moves gradients inside a segment: all but a few agree
     assert ((gy - gy1).abs() > 1e-4 * g.abs().max()).float().mean() < 1e-3
+
+
+def test_lines_restored_before_the_reverse_sweep(overrides):
+    """Masks from a forward call whose line was moved, and moved back by the time of the reverse sweep: it still looks for them."""
+    import torch
+
+    import paper_2204_03643_amd as tv
+    planes, H, W, K = 600, 40, 64, 1                # by default pass by pass, which leaves pass outputs
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    y, g = (torch.randn(planes, H, W, device="cuda", generator=gen) for _ in range(2))
+    lam = torch.tensor([0.3], device="cuda")
+    L = tv.tv_lambda(lam.data_ptr(), 1, 1)
+    wsb = tv.tv2d_workspace_bytes(planes, H, W, K)
+    default, out = tv.tv_dispatch_threshold("plane_per_group64_planes"), []
+    for line, masks in ((default, 0), (1 << 40, 1)):
+        ws = torch.full((wsb,), 0xff, dtype=torch.uint8, device="cuda")
+        x, gy, gl = torch.empty_like(y), torch.empty_like(y), torch.empty_like(lam)
+        overrides(plane_per_group64_planes=line)
+        tv.tv2d_prox_fwd(y, x, planes, H, W, L, K, ws, wsb)
+        overrides(plane_per_group64_planes=default)
+        assert int(ws[-16:-12].view(torch.int32)) == masks
+        if masks:
+            ws[planes * max(H, W) * 32:-64] = 0xff                  # (no pass outputs to read instead)
+        tv.tv2d_prox_bwd(g, gy, gl, planes, H, W, L, K, ws, wsb)
+        assert torch.isfinite(gy).all() and torch.isfinite(gl).all()
+        out.append((x, gy))
+    assert (out[0][0] - out[1][0]).abs().max() <= 2e-5 * (1 + y.abs().max())
+    assert ((out[0][1] - out[1][1]).abs() > 1e-4 * g.abs().max()).float().mean() < 1e-3
